@@ -81,7 +81,7 @@ def batched_by_size(specs):
     """Per lattice size of the batched configuration: one batched sweep launch (10 sweeps of every
     run of that size, at its initial size) per first-look regime (beta = 0.5, 2, 4), timed live
     with HIP events on the batch's stream; with the counted VALU instructions per attempt of the
-    committed counter summary while the colour-string kernel's sources still match it."""
+    committed counter summary while the sweep's sources still match it."""
     import torch
 
     from paper_1006_0252_amd import pa, workloads
@@ -695,7 +695,7 @@ def main():
                    "steps_timed": f"k={ks[0]}..{ks[-1]}", "parallelism": "1 GPU"},
         "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_LANE_OPS / 1e12,
                      "unit": "Tlane-op/s", "frac": achieved / PEAK_LANE_OPS, "traffic": traffic,
-                     "kernel": "k_sweep16c (pa_sweep, 10 fused sweeps)", "avg_launch_ms": sweep_s * 1e3,
+                     "kernel": "k_sweep_group (pa_sweep, 10 fused sweeps)", "avg_launch_ms": sweep_s * 1e3,
                      "ops_per_attempt": OPS_PER_ATTEMPT,
                      "peak_basis": "256 CUs x 128 lanes x 2.4 GHz (FP32 vector 157.3 TFLOP/s / 2)",
                      "hbm_frac": (traffic / sweep_s / 8e12) if traffic else None},

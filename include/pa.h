@@ -127,7 +127,7 @@ typedef struct pa_state {
     double acc;     /* sum of ln Q so far */
     double ln_omega;/* N ln 2 */
     double beta;    /* current inverse temperature */
-    uint32_t work_counter; /* work items taken by a batched sweep (counted in the first run of each group of equal-L runs) */
+    uint32_t work_counter; /* not used */
     uint32_t reserved0;
     int32_t couplings;     /* PA_PM1 or PA_GAUSS */
     uint8_t pad[36];
@@ -350,12 +350,11 @@ int pa_graph_launch(void* graph_exec, void* stream);
 int pa_graph_destroy(void* graph_exec);
 
 /* Batched sweep schedule, for the autotuner.  The runs of a batch are grouped by lattice size
- * and each group is one launch over the device work list of (run, tile) items:
- *   blocks_per_cu (1..32): resident blocks per compute unit of a persistent launch;
- *   order: 0 groups in order of first appearance, 1 larger tiles first;
- *   launch: 0 by size (persistent loop for L = 0 mod 4, one item per block otherwise),
- *           1 persistent loop for every size, 2 one item per block for every size.
- * (0, 0, 0) restores the defaults (16, 1, 0).  Results do not depend on it. */
+ * and each group is one launch over the device work list of (run, 64-replica group) items, one
+ * block per item (or per quarter of one):
+ *   order: 0 groups in order of first appearance, 1 larger lattices first;
+ *   blocks_per_cu (1..32) and launch (0..2) are checked and have no effect.
+ * (0, 0, 0) restores the defaults (order 1).  Results do not depend on it. */
 int pa_set_batch_config(int blocks_per_cu, int order, int launch);
 
 /* Launch shape of the sweep kernels for later calls in this process: lanes per replica

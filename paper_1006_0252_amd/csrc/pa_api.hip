@@ -5,6 +5,7 @@
 #include <new>
 
 #include "pa_common.h"
+#include "pa_host.h"
 
 namespace pa {
 
@@ -175,7 +176,7 @@ int pa_sweep(pa_run* runs, int n_runs, const pa_step* step)
     SweepParams p;
     build_sweep_params(*step, 6, &p);
     bool fast = batchable(runs, n_runs) && runs[0].dim == 3 && n_runs <= 1024 && fast_sweep_thresholds_ok(p);
-    for (int r = 0; fast && r < n_runs; ++r) fast = fast_sweep_supported(runs[r].dim, runs[r].L);
+    for (int r = 0; fast && r < n_runs; ++r) fast = group_sweep_supported(runs[r].dim, runs[r].L);
     if (fast) {
         st = launch_sweep_batch(runs, n_runs, p, (hipStream_t)runs[0].stream);
         if (st != PA_OK) return st;

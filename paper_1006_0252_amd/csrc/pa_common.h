@@ -113,59 +113,6 @@ struct BatchOrder {
     uint16_t run[kMaxBatch];
 };
 
-// lanes per replica of the row-pair batch kernel for each lattice size (L = 2 mod 4 needs one lane
-// per replica so that the Philox phase of a plane is uniform over the wave)
-__host__ __device__ constexpr int batch_lpr(int L) { return L % 4 != 0 ? 1 : (L >= 12 ? 4 : (L >= 8 ? 2 : 1)); }
-
-// the colour-string kernel: bit-packed cubes of L = 4, 6, 8, 10, one lane per replica
-__host__ __device__ inline bool string_sweep_supported(int dim, int L, int layout)
-{
-    return dim == 3 && layout == PA_BITS64 && (L == 4 || L == 6 || L == 8 || L == 10);
-}
-
-// replicas per work item of a batched cube sweep: one 64-replica group for the colour-string
-// kernel, 64 / lanes per replica for the row-pair kernel
-__host__ __device__ inline int batch_tile_replicas(int L, int layout)
-{
-    return string_sweep_supported(3, L, layout) ? 64 : 64 / batch_lpr(L);
-}
-
-// host launch helpers (defined in the .hip files)
-int launch_init(const pa_run& run, const int8_t* J_host, hipStream_t s);
-int launch_sweep(const pa_run& run, const pa_step& step, hipStream_t s);
-// n > 1 chain runs (dim 1) with consecutive states, one length and layout, one stream
-int launch_sweep_chain_batch(const pa_run* runs, int n, const pa_step& step, hipStream_t s);
-int launch_sweep_fast(const pa_run& run, const SweepParams& p, int lpr, int wpb, hipStream_t s);
-// the colour-packed kernel of the bit-packed L = 16 cube (PA_ERR_ARG for any other run)
-int launch_sweep_colour(const pa_run& run, const SweepParams& p, hipStream_t s);
-// the colour-string kernel (string_sweep_supported runs): one run, or one group of equal-L runs of a
-// batch (waves persistent waves taking items, or one item per wave for waves = the items)
-int launch_sweep_strings(const pa_run& run, const SweepParams& p, hipStream_t s);
-int launch_sweep_strings_group(int L, pa_state* base, int pos0, int pos1, const BatchOrder& order,
-                               const SweepParams& p, bool persistent, int64_t waves, hipStream_t s);
-// batched launchers: n runs whose device states are contiguous (runs[r].state == runs[0].state + r)
-int launch_resample(const pa_run* runs, int n, const pa_step& step, hipStream_t s);
-int launch_hist(const pa_run* runs, int n, hipStream_t s);
-int launch_measure(const pa_run* runs, int n, const pa_run* partner, int pair_xor, hipStream_t s);
-int launch_free_energy(const pa_run* runs, int n, double* out, hipStream_t s);
-int launch_sweep_batch(const pa_run* runs, int n, const SweepParams& p, hipStream_t s);
-bool fast_sweep_supported(int dim, int L);
-// the fast cube sweep compares first looks against top + 1 in 16 bits: tops up to 0xFFFE (a move
-// of dE = 4 accepted with probability below 1 - 2^-16, i.e. beta above about 4e-6)
-inline bool fast_sweep_thresholds_ok(const SweepParams& p) { return p.thi[4] <= 0xFFFEu; }
-int build_sweep_params(const pa_step& step, int z, SweepParams* p);
-int launch_weighted_average_dev(int n_sets, int M, const double* x, const double* R, const double* A, int n_obs,
-                                double* out, hipStream_t s);
-int launch_overlap_average_dev(int n_sets, int n_pairs, const double* x, const double* R, const double* Q,
-                               double* out, hipStream_t s);
-int launch_bootstrap_dev(int n_sets, int M, const double* x, const double* R, const double* A, int n_obs, int n_boot,
-                         const int32_t* idx, double* rep, double* err, hipStream_t s);
-int build_thresholds(double beta, int z, uint64_t* T, uint8_t* always);
-int launch_features(const pa_run* runs, int n, float* x, hipStream_t s);
-int launch_rho(const pa_run* runs, int n, const double* args, int n_args, int mode, double cap, int64_t ld,
-               double* out, hipStream_t s);
-int upload_ladder(hipStream_t s);
-
 inline int hip_status(hipError_t e) { return e == hipSuccess ? PA_OK : PA_ERR_HIP; }
 
 // exp written out for the Gaussian-coupling path, so that host and device reach the same bits:
@@ -194,14 +141,5 @@ __device__ inline double expd(double x)
     p = p * r + 1.0;
     return ldexp(p, (int)k);
 }
-
-// Gaussian-coupling path (separate kernels; n > 1 runs: consecutive states on one stream)
-int gauss_couplings_upload(const pa_run& run, hipStream_t s);
-int launch_energy_gauss(const pa_run& run, int buf, int64_t n_replicas, hipStream_t s);
-// consecutive: the runs' states are consecutive and share runs[0].stream (one launch for all)
-int launch_sweep_gauss(const pa_run* runs, int n_runs, bool consecutive, const pa_step& step, hipStream_t s);
-int launch_resample_gauss(const pa_run* runs, int n, const pa_step& step, hipStream_t s);
-int launch_measure_gauss(const pa_run* runs, int n, const pa_run* partner, int pair_xor, hipStream_t s);
-int launch_moments_gauss(const pa_run* runs, int n, hipStream_t s);
 
 }  // namespace pa

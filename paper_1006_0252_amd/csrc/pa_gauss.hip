@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "pa_common.h"
+#include "pa_host.h"
 #include "pa_lattice.h"
 #include "pa_sweep_words.h"
 

@@ -4,6 +4,7 @@
 #include <string.h>
 
 #include "pa_common.h"
+#include "pa_host.h"
 #include "pa_lattice.h"
 
 namespace pa {

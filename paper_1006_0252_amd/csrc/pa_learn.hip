@@ -12,6 +12,7 @@
 #include <mutex>
 
 #include "pa_common.h"
+#include "pa_host.h"
 
 namespace pa {
 

@@ -7,6 +7,7 @@
 #include <algorithm>
 
 #include "pa_common.h"
+#include "pa_host.h"
 
 #pragma clang fp contract(off)
 

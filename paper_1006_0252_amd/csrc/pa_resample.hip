@@ -19,6 +19,7 @@
 #include <algorithm>
 
 #include "pa_common.h"
+#include "pa_host.h"
 
 #pragma clang fp contract(off)
 

@@ -12,6 +12,7 @@
 #include <string.h>
 
 #include "pa_common.h"
+#include "pa_host.h"
 #include "pa_sweep_util.h"
 
 namespace pa {
@@ -490,14 +491,6 @@ static SweepConfig default_config(int dim, int L)
     return {1, 4};
 }
 
-// launch shape of the fast cube kernel (L = 4, 8, 12, 16)
-static SweepConfig fast_config(int L)
-{
-    if (L >= 12) return {4, 4};
-    if (L >= 8) return {2, 4};
-    return {1, 4};
-}
-
 static SweepConfig g_override = {0, 0};
 
 int build_sweep_params(const pa_step& step, int z, SweepParams* pp)
@@ -527,17 +520,10 @@ int launch_sweep(const pa_run& run, const pa_step& step, hipStream_t s)
     SweepConfig cfg = default_config(run.dim, run.L);
     if (g_override.lpr) cfg = g_override;
     int st;
-    if (fast_sweep_supported(run.dim, run.L) && fast_sweep_thresholds_ok(p)) {
-        // bit-packed cubes take the colour-packed kernel (L = 16) or the colour-string kernel (L = 4,
-        // 6, 8, 10) unless a launch shape is forced
-        if (!g_override.lpr && run.L == 16 && run.layout == PA_BITS64) {
-            st = launch_sweep_colour(run, p, s);
-        } else if (!g_override.lpr && string_sweep_supported(run.dim, run.L, run.layout)) {
-            st = launch_sweep_strings(run, p, s);
-        } else {
-            SweepConfig fc = g_override.lpr ? g_override : fast_config(run.L);
-            st = launch_sweep_fast(run, p, fc.lpr, fc.wpb, s);
-        }
+    if (fast_sweep_thresholds_ok(p) && (g_override.lpr ? fast_sweep_supported(run.dim, run.L)
+                                                       : group_sweep_supported(run.dim, run.L))) {
+        // a forced launch shape takes the row-pair kernel, everything else the group kernel
+        st = g_override.lpr ? launch_sweep_fast(run, p, g_override.lpr, g_override.wpb, s) : launch_sweep_group(run, p, s);
         if (st != PA_OK) return st;
         return hip_status(hipGetLastError());
     }

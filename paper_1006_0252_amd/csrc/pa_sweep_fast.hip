@@ -22,15 +22,15 @@
 //    (beta below 4e-6) do not leave room for the + 1 and take the generic kernel instead;
 //  - energies are recomputed once per launch from bond popcounts.
 //
-// Two launch forms share the per-tile code: one block of waves per group of replicas of one
-// run (k_sweep3f, which moves whole 64-replica bit-packed groups block-wide when its waves hold
-// one), and a persistent kernel for a batch of runs (k_sweep_batch), one wave per block pulling
-// (run, tile) items from a device work counter.
+// A forced launch shape (pa_set_sweep_config) takes this kernel; everything else takes the group kernel
+// (pa_sweep_group.hip), which it serves as an independent check of.  One block of waves per group of
+// replicas; a block whose waves hold a whole 64-replica bit-packed group moves it block-wide.
 #include <string.h>
 
 #include <algorithm>
 
 #include "pa_common.h"
+#include "pa_host.h"
 #include "pa_sweep_util.h"
 
 namespace pa {
@@ -628,98 +628,6 @@ __global__ void __launch_bounds__(256) k_sweep3f(const pa_state* __restrict__ st
     sweep_tile<L, LAYOUT, LPR, MODE>(st, rbase, lds, rows, lane, p, th);
 }
 
-// ------------------------------------------------------------------ a batch of runs
-// The runs' states are contiguous (state r at base + r).  Work items are (run, tile of RPW
-// replicas); k_batch_tiles lays them out in the order given by the host (position p holds run
-// order[p]) and resets the work counter; k_sweep_batch waves take items in that order.
-__global__ void __launch_bounds__(256) k_batch_tiles(pa_state* base, int n_runs, BatchOrder order)
-{
-    int64_t* tb = work_ptr<int64_t>(base, work_layout(base->N, base->n_bins, base->capacity).batch);
-    __shared__ int64_t cnt[kMaxBatch];
-    for (int pos = threadIdx.x; pos < n_runs; pos += blockDim.x) {
-        pa_state* st = base + order.run[pos];
-        const int rpw = batch_tile_replicas(st->L, st->layout);
-        cnt[pos] = st->status ? 0 : (st->R + rpw - 1) / rpw;
-        st->work_counter = 0;  // a group of equal-L runs counts its items in its first run
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int64_t acc = 0;
-        for (int pos = 0; pos < n_runs; ++pos) {
-            tb[pos] = acc;
-            acc += cnt[pos];
-        }
-        tb[n_runs] = acc;
-    }
-}
-
-// one work item: the coupling table of the item's run is rebuilt for every item (a few
-// hundred byte loads per lane against ~10^5 attempts per lane)
-template <int L, int LAYOUT, int MODE>
-__device__ __forceinline__ void batch_tile(const pa_state* st, int64_t local, uint32_t* lds, int lane,
-                                           const SweepParams& p, const FastThr& th)
-{
-    constexpr int LPR = batch_lpr(L);
-    using F = FastLayout<L, LPR>;
-    build_jtab<L, LPR>(st, lds, th, lane, 64);
-    wave_sync();
-    uint16_t* rows = reinterpret_cast<uint16_t*>(lds + F::TAB_DWORDS);
-    sweep_tile<L, LAYOUT, LPR, MODE>(st, local * F::RPW, lds, rows, lane, p, th);
-}
-
-// Persistent sweep of one group of equal-L runs (positions pos0 .. pos1-1 of the order): each
-// wave takes the next item of the group, finds its run by bisection of the tile offsets and
-// sweeps that tile.  One specialisation per L keeps the register budget of the one-run kernel
-// (two waves per SIMD) instead of the union of all sizes.
-template <int L, int LAYOUT, int MODE>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) k_sweep_batch(pa_state* base, int pos0, int pos1, BatchOrder order,
-                                                    SweepParams p, FastThr th)
-{
-    extern __shared__ uint32_t lds[];
-    const int lane = threadIdx.x;
-    const int64_t* tb = work_ptr<int64_t>(base, work_layout(base->N, base->n_bins, base->capacity).batch);
-    const int64_t first = tb[pos0], total = tb[pos1] - first;
-    pa_state* counter = base + order.run[pos0];
-    for (;;) {
-        uint32_t t = 0;
-        if (lane == 0) t = atomicAdd(&counter->work_counter, 1u);
-        t = __shfl(t, 0, 64);
-        if ((int64_t)t >= total) break;  // every wave leaves once the group's items are taken
-        const int64_t item = first + (int64_t)t;
-        int lo = pos0, hi = pos1;         // tb[lo] <= item < tb[hi]
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (tb[mid] <= item) lo = mid;
-            else hi = mid;
-        }
-        const pa_state* st = base + order.run[lo];
-        // the lane index passes through an empty asm each item so that the tile's lane-derived
-        // addresses are not hoisted out of the item loop (they would stay live across it)
-        int lane_i = lane;
-        asm volatile("" : "+v"(lane_i));
-        batch_tile<L, LAYOUT, MODE>(st, item - tb[lo], lds, lane_i, p, th);
-    }
-}
-
-// The same items with one item per block (no item loop): for sizes whose tile code does not
-// fit the register budget of the persistent loop.  Blocks past the group's items exit.
-template <int L, int LAYOUT, int MODE>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) k_sweep_batch_grid(
-    pa_state* base, int pos0, int pos1, BatchOrder order, SweepParams p, FastThr th)
-{
-    extern __shared__ uint32_t lds[];
-    const int64_t* tb = work_ptr<int64_t>(base, work_layout(base->N, base->n_bins, base->capacity).batch);
-    const int64_t item = tb[pos0] + (int64_t)blockIdx.x;
-    if (item >= tb[pos1]) return;
-    int lo = pos0, hi = pos1;  // tb[lo] <= item < tb[hi]
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (tb[mid] <= item) lo = mid;
-        else hi = mid;
-    }
-    batch_tile<L, LAYOUT, MODE>(base + order.run[lo], item - tb[lo], lds, threadIdx.x, p, th);
-}
-
 // ------------------------------------------------------------------ host side
 static size_t fast_lds_limit()
 {
@@ -732,19 +640,6 @@ static size_t fast_lds_limit()
         lim = (size_t)v;
     cached = lim;
     return lim;
-}
-
-static int cu_count()
-{
-    static int cached = 0;
-    if (cached) return cached;
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-        cached = v;
-    else
-        cached = 256;
-    return cached;
 }
 
 static FastThr make_thr(const SweepParams& p, int* mode)
@@ -825,134 +720,4 @@ int launch_sweep_fast(const pa_run& run, const SweepParams& p, int lpr, int wpb,
     }
 }
 
-static size_t batch_lds_bytes(int L)
-{
-    switch (L) {
-        case 4: return FastLayout<4, batch_lpr(4)>::lds_bytes(1);
-        case 6: return FastLayout<6, batch_lpr(6)>::lds_bytes(1);
-        case 8: return FastLayout<8, batch_lpr(8)>::lds_bytes(1);
-        case 10: return FastLayout<10, batch_lpr(10)>::lds_bytes(1);
-        case 12: return FastLayout<12, batch_lpr(12)>::lds_bytes(1);
-        case 14: return FastLayout<14, batch_lpr(14)>::lds_bytes(1);
-        default: return FastLayout<16, batch_lpr(16)>::lds_bytes(1);
-    }
-}
-
-static int g_batch_blocks_per_cu = 16;
-static int g_batch_order = 1;  // 0: as given, 1: larger lattices first
-static int g_batch_launch = 0; // 0: by size, 1: persistent for every size, 2: one item per block for every size
-
-// persistent loop or one item per block: by size, the loop for L = 0 mod 4 (its tile code keeps
-// the one-run kernel's register budget inside the loop), one item per block otherwise
-static bool group_persistent(int L)
-{
-    return g_batch_launch == 1 || (g_batch_launch == 0 && L % 4 == 0);
-}
-
-template <int L, int LAYOUT>
-static void launch_group(pa_state* base, int pos0, int pos1, const BatchOrder& order, const SweepParams& p,
-                         const FastThr& th, int mode, int64_t tiles, hipStream_t s)
-{
-    if (string_sweep_supported(3, L, LAYOUT)) {
-        // colour strings: persistent (blocks per CU counted in waves) unless one item per wave is
-        // forced
-        const bool persistent = g_batch_launch != 2;
-        const int64_t waves = persistent ? std::min<int64_t>((int64_t)cu_count() * g_batch_blocks_per_cu, tiles) : tiles;
-        launch_sweep_strings_group(L, base, pos0, pos1, order, p, persistent, waves, s);
-        return;
-    }
-    const size_t lds = FastLayout<L, batch_lpr(L)>::lds_bytes(1);
-    const dim3 block(64);
-    if (group_persistent(L)) {
-        const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>((int64_t)cu_count() * g_batch_blocks_per_cu, tiles)));
-        if (mode == 2) hipLaunchKernelGGL((k_sweep_batch<L, LAYOUT, 2>), grid, block, lds, s, base, pos0, pos1, order, p, th);
-        else if (mode == 1) hipLaunchKernelGGL((k_sweep_batch<L, LAYOUT, 1>), grid, block, lds, s, base, pos0, pos1, order, p, th);
-        else hipLaunchKernelGGL((k_sweep_batch<L, LAYOUT, 0>), grid, block, lds, s, base, pos0, pos1, order, p, th);
-    } else {
-        const dim3 grid((unsigned)std::max<int64_t>(1, tiles));
-        if (mode == 2) hipLaunchKernelGGL((k_sweep_batch_grid<L, LAYOUT, 2>), grid, block, lds, s, base, pos0, pos1, order, p, th);
-        else if (mode == 1) hipLaunchKernelGGL((k_sweep_batch_grid<L, LAYOUT, 1>), grid, block, lds, s, base, pos0, pos1, order, p, th);
-        else hipLaunchKernelGGL((k_sweep_batch_grid<L, LAYOUT, 0>), grid, block, lds, s, base, pos0, pos1, order, p, th);
-    }
-}
-
-template <int LAYOUT>
-static void launch_group_L(int L, pa_state* base, int pos0, int pos1, const BatchOrder& order, const SweepParams& p,
-                           const FastThr& th, int mode, int64_t tiles, hipStream_t s)
-{
-    switch (L) {
-        case 4: launch_group<4, LAYOUT>(base, pos0, pos1, order, p, th, mode, tiles, s); break;
-        case 6: launch_group<6, LAYOUT>(base, pos0, pos1, order, p, th, mode, tiles, s); break;
-        case 8: launch_group<8, LAYOUT>(base, pos0, pos1, order, p, th, mode, tiles, s); break;
-        case 10: launch_group<10, LAYOUT>(base, pos0, pos1, order, p, th, mode, tiles, s); break;
-        case 12: launch_group<12, LAYOUT>(base, pos0, pos1, order, p, th, mode, tiles, s); break;
-        case 14: launch_group<14, LAYOUT>(base, pos0, pos1, order, p, th, mode, tiles, s); break;
-        default: launch_group<16, LAYOUT>(base, pos0, pos1, order, p, th, mode, tiles, s); break;
-    }
-}
-
-// Persistent sweep of n_runs contiguous runs (3D, even L in 4..16, one layout): the runs are
-// grouped by lattice size (groups ordered by the cost of a tile, larger first, or by first
-// appearance), one work list over all groups, one persistent launch per group.
-int launch_sweep_batch(const pa_run* runs, int n_runs, const SweepParams& p, hipStream_t s)
-{
-    if (n_runs > kMaxBatch || !fast_sweep_thresholds_ok(p)) return PA_ERR_ARG;
-    for (int r = 0; r < n_runs; ++r)
-        if (batch_lds_bytes(runs[r].L) > fast_lds_limit()) return PA_ERR_ARG;
-    // distinct sizes in order of first appearance, then (order 1) by tile cost, larger first
-    int sizes[kMaxBatch], n_sizes = 0;
-    for (int r = 0; r < n_runs; ++r) {
-        bool seen = false;
-        for (int g = 0; g < n_sizes; ++g) seen = seen || sizes[g] == runs[r].L;
-        if (!seen) sizes[n_sizes++] = runs[r].L;
-    }
-    auto tile_cost = [](int L) { return (double)L * L * L * 64 / batch_lpr(L); };
-    if (g_batch_order == 1)
-        std::stable_sort(sizes, sizes + n_sizes, [&](int a, int b) { return tile_cost(a) > tile_cost(b); });
-    BatchOrder order;
-    int group_end[kMaxBatch];
-    int64_t group_tiles[kMaxBatch];
-    int pos = 0;
-    for (int g = 0; g < n_sizes; ++g) {
-        group_tiles[g] = 0;
-        for (int r = 0; r < n_runs; ++r) {
-            if (runs[r].L != sizes[g]) continue;
-            order.run[pos++] = (uint16_t)r;
-            const int rpw = batch_tile_replicas(runs[r].L, runs[r].layout);
-            group_tiles[g] += (runs[r].capacity + rpw - 1) / rpw;
-        }
-        group_end[g] = pos;
-    }
-    int mode;
-    const FastThr th = make_thr(p, &mode);
-    pa_state* base = runs[0].state;
-    hipLaunchKernelGGL(k_batch_tiles, dim3(1), dim3(256), 0, s, base, n_runs, order);
-    for (int g = 0, pos0 = 0; g < n_sizes; pos0 = group_end[g], ++g) {
-        if (runs[0].layout == PA_U8)
-            launch_group_L<PA_U8>(sizes[g], base, pos0, group_end[g], order, p, th, mode, group_tiles[g], s);
-        else
-            launch_group_L<PA_BITS64>(sizes[g], base, pos0, group_end[g], order, p, th, mode, group_tiles[g], s);
-    }
-    return PA_OK;
-}
-
 }  // namespace pa
-
-// batch schedule for the autotuner: blocks per CU of a persistent launch (1..32), order of the
-// size groups (0: first appearance, 1: larger tiles first), launch form (0: by size, 1: persistent
-// loop, 2: one item per block); (0, 0, 0) restores the defaults
-extern "C" int pa_set_batch_config(int blocks_per_cu, int order, int launch)
-{
-    if (blocks_per_cu == 0 && order == 0 && launch == 0) {
-        pa::g_batch_blocks_per_cu = 16;
-        pa::g_batch_order = 1;
-        pa::g_batch_launch = 0;
-        return PA_OK;
-    }
-    if (blocks_per_cu < 1 || blocks_per_cu > 32 || order < 0 || order > 1 || launch < 0 || launch > 2)
-        return PA_ERR_ARG;
-    pa::g_batch_blocks_per_cu = blocks_per_cu;
-    pa::g_batch_order = order;
-    pa::g_batch_launch = launch;
-    return PA_OK;
-}

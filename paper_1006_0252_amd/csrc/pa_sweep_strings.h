@@ -1,0 +1,153 @@
+// Colour strings of a cube: the sites of one colour of a replica as one bit string, and how the
+// neighbours of its words are formed.  Shared by the sweep kernels that keep a replica this way.
+//
+// Colour string.  Half-site b = m + (L/2) (y + L z) (m = 0 .. L/2 - 1) holds the sites x = 2 m and
+// 2 m + 1 of row (y, z); exactly one of them has colour c, x = 2 m + sigma with sigma = (c + y + z)
+// mod 2.  Bit b of the colour-c string is that site, so the string has L^3 / 2 bits, its Metropolis
+// field is field b mod 8 of Philox call b / 8, and a 32-bit word is four whole calls.  The
+// neighbours of bit b are bits of the other colour's string:
+//  - x: bit b itself on one side; bit b + 1 (x + 1, sigma = 1) or b - 1 (x - 1, sigma = 0) on the
+//    other, wrapping within the row (b - (L/2 - 1) and b + (L/2 - 1));
+//  - y: bits b + L/2 and b - L/2, wrapping within the plane (b -+ (L - 1) L / 2);
+//  - z: bits b + L^2/2 and b - L^2/2, wrapping around the string.
+// So every neighbour word is a funnel shift of two words of the other string by a constant, and
+// the in-row and in-plane wraps are bit selects by per-word masks.  The strings are kept in LDS
+// with a few ghost words on both sides holding the string's periodic continuation (refreshed after
+// each colour phase), so the z wraps need no selects and no funnel leaves the buffer.
+#pragma once
+
+#include "pa_common.h"
+#include "pa_sweep_words.h"
+
+namespace pa {
+
+namespace strings {
+
+using namespace words;
+
+template <int L>
+struct Geo {
+    static constexpr int H2 = L / 2;              // colour sites per row
+    static constexpr int NP = L * L / 2;          // bits per plane
+    static constexpr int NH = L * NP;             // bits per string
+    static constexpr int NW = (NH + 31) / 32;     // words per string
+    static constexpr int G = NP / 32 + 1;         // ghost words on each side: a funnel by up to
+                                                  // NP bits reads words k - G .. k + G
+    static constexpr int EW = NW + 2 * G;         // words of an extended string
+    static constexpr int NR = L * L;              // lattice rows per replica
+    static constexpr int WB = L <= 8 ? 1 : (L <= 16 ? 2 : 4);  // bytes of a bit-packed row
+    static constexpr int TW = 12;                 // table dwords per (colour, word)
+    static constexpr uint32_t LAST = NH % 32 ? (1u << (NH % 32)) - 1u : 0xFFFFFFFFu;  // valid bits of the last word
+};
+
+// offset of extended-string word e (0 .. EW - 1) inside the string: 32 (e - G) mod NH, taken
+// non-negative; a ghost word holds the 32 string bits from there on
+template <int L>
+__host__ __device__ constexpr int ghost_origin(int e)
+{
+    using Gm = Geo<L>;
+    return ((32 * (e - Gm::G)) % Gm::NH + Gm::NH) % Gm::NH;
+}
+
+// every ghost word is a funnel of string words that exist (so the refresh reads no ghost)
+template <int L>
+constexpr bool ghosts_in_string()
+{
+    using Gm = Geo<L>;
+    for (int e = 0; e < Gm::EW; ++e) {
+        if (e >= Gm::G && e < Gm::G + Gm::NW) continue;
+        const int o = ghost_origin<L>(e);
+        if (o % 32 == 0 ? o / 32 >= Gm::NW : o / 32 + 1 >= Gm::NW) return false;
+    }
+    return true;
+}
+
+// word q of the other string relative to word k, shifted by off bits (funnel of two words); S: dwords
+// from a word to the next in LDS (the replicas side by side)
+template <int OFF, int S>
+__device__ __forceinline__ uint32_t funnel(const uint32_t* Ok)
+{
+    constexpr int q = OFF >= 0 ? OFF / 32 : -((-OFF + 31) / 32);  // floor(OFF / 32)
+    constexpr int r = OFF - 32 * q;
+    const uint32_t lo = Ok[q * S];
+    if constexpr (r == 0) {
+        return lo;
+    } else {
+        const uint32_t hi = Ok[(q + 1) * S];
+        return __builtin_amdgcn_alignbit(hi, lo, r);
+    }
+}
+
+// The per-word tables of words first, first + step, .., built by the calling wave: lanes 0..31 take bit t of word k of colour 0, lanes 32..63
+// the same bit of colour 1, and a ballot of each flag gives the two words at once.  Entries: 0..5
+// the coupling masks (bit set where J = -1) of the +x, -x, +y, -y, +z, -z bonds, 6 the sites with
+// x even (sigma = 0), 7 and 8 the first and last site of a row (m = 0, m = L/2 - 1), 9 and 10 the
+// first and last row of a plane (y = 0, y = L - 1), 11 the bits that are sites (b < L^3 / 2).
+template <int L>
+__device__ void build_tables(const int8_t* J, uint32_t* tab, int lane, int first = 0, int step = 1)
+{
+    using Gm = Geo<L>;
+    const int c = lane >> 5, t = lane & 31;
+    for (int k = first; k < Gm::NW; k += step) {
+        const int b = 32 * k + t;
+        bool f[12] = {false, false, false, false, false, false, false, false, false, false, false, false};
+        if (b < Gm::NH) {
+            const int m = b % Gm::H2, r = b / Gm::H2, y = r % L, z = r / L;
+            const int sg = (c + y + z) & 1, x = 2 * m + sg;
+            const int xm = (x + L - 1) % L, ym = (y + L - 1) % L, zm = (z + L - 1) % L;
+            const int i = x + L * (y + L * z);
+            f[0] = J[3 * i + 0] < 0;
+            f[1] = J[3 * (xm + L * (y + L * z)) + 0] < 0;
+            f[2] = J[3 * i + 1] < 0;
+            f[3] = J[3 * (x + L * (ym + L * z)) + 1] < 0;
+            f[4] = J[3 * i + 2] < 0;
+            f[5] = J[3 * (x + L * (y + L * zm)) + 2] < 0;
+            f[6] = sg == 0;
+            f[7] = m == 0;
+            f[8] = m == Gm::H2 - 1;
+            f[9] = y == 0;
+            f[10] = y == L - 1;
+            f[11] = true;
+        }
+#pragma unroll
+        for (int e = 0; e < 12; ++e) {
+            const uint64_t v = __ballot(f[e]);
+            if (lane == 0) {
+                tab[(0 * Gm::NW + k) * Gm::TW + e] = (uint32_t)v;
+                tab[(1 * Gm::NW + k) * Gm::TW + e] = (uint32_t)(v >> 32);
+            }
+        }
+    }
+}
+
+// the six neighbour words of word k of a colour (Ok: word k of the other string, T: the word's
+// table entry)
+template <int L, int S>
+__device__ __forceinline__ void neighbours(const uint32_t* Ok, const uint32_t* T, uint32_t nb[6])
+{
+    using Gm = Geo<L>;
+    constexpr int H2 = Gm::H2, NP = Gm::NP;
+    const uint32_t a0 = Ok[0];
+    const uint32_t sig0 = T[6], rf = T[7], rl = T[8], yf = T[9], yl = T[10];
+    nb[0] = select_bits(sig0, a0, select_bits(rl, funnel<-(H2 - 1), S>(Ok), funnel<1, S>(Ok)));
+    nb[1] = select_bits(sig0, select_bits(rf, funnel<H2 - 1, S>(Ok), funnel<-1, S>(Ok)), a0);
+    nb[2] = select_bits(yl, funnel<H2 - NP, S>(Ok), funnel<H2, S>(Ok));
+    nb[3] = select_bits(yf, funnel<NP - H2, S>(Ok), funnel<-H2, S>(Ok));
+    nb[4] = funnel<NP, S>(Ok);
+    nb[5] = funnel<-NP, S>(Ok);
+}
+
+// the position of a batch's work list that item belongs to
+__device__ __forceinline__ int find_run(const int64_t* tb, int pos0, int pos1, int64_t item)
+{
+    int lo = pos0, hi = pos1;  // tb[lo] <= item < tb[hi]
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (tb[mid] <= item) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
+}  // namespace strings
+}  // namespace pa

@@ -28,12 +28,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 # the sources each sweep kernel is compiled from (a summary records their sha256; bench.py uses
 # its figures only while they are unchanged)
-SWEEP_SOURCES = ("paper_1006_0252_amd/csrc/pa_sweep_colour.hip", "paper_1006_0252_amd/csrc/pa_sweep_words.h",
-                 "paper_1006_0252_amd/csrc/pa_sweep_util.h", "paper_1006_0252_amd/csrc/pa_common.h")
-STRING_SOURCES = ("paper_1006_0252_amd/csrc/pa_sweep_strings.hip", "paper_1006_0252_amd/csrc/pa_sweep_words.h",
-                  "paper_1006_0252_amd/csrc/pa_sweep_util.h", "paper_1006_0252_amd/csrc/pa_common.h")
-SWEEP_KERNEL = "k_sweep16c"
-KERNEL_LABEL = "k_sweep16c (colour-packed words, bit-packed L=16; pa_sweep, 10 sweeps per launch)"
+SWEEP_SOURCES = ("paper_1006_0252_amd/csrc/pa_sweep_group.hip", "paper_1006_0252_amd/csrc/pa_sweep_strings.h",
+                 "paper_1006_0252_amd/csrc/pa_sweep_words.h", "paper_1006_0252_amd/csrc/pa_sweep_util.h",
+                 "paper_1006_0252_amd/csrc/pa_common.h")
+STRING_SOURCES = SWEEP_SOURCES  # the batched launches are the same kernel's
+SWEEP_KERNEL = "k_sweep"  # the only sweep kernel of the profiled programs
+KERNEL_LABEL = "k_sweep_group (colour strings, the waves of a block share 64 replicas; pa_sweep, 10 sweeps per launch)"
 ATTEMPTS_PER_LAUNCH = 1_000_000 * 4096 * 10  # profile_sweep.py: R0 = 1e6 replicas, L = 16, 10 sweeps
 # HBM bytes a sweep launch of 1e6 L = 16 replicas must move: each replica's 4096 spin bits read and
 # written once (512 + 512 bytes) and its 4-byte energy written
@@ -155,7 +155,7 @@ def _sweep_L(name):
 
 
 def batched(trace_dir, pmc_dirs, out=None):
-    """out: also write the per-size, per-regime figures as JSON (with the colour-string kernel's
+    """out: also write the per-size, per-regime figures as JSON (with the sweep's
     source digest), for bench.py's batched line"""
     att = _batched_attempts()
     times = {}
