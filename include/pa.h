@@ -28,8 +28,8 @@
  *     pa_state blocks are consecutive in device memory (state of run r at runs[0].state + r),
  *     share one stream and one layout, each kernel is launched once for all of them: the
  *     resampling and measurement kernels index runs by grid row, and the cube sweep (even L
- *     from 4 to 16) is one persistent launch whose waves take (run, tile of replicas) items
- *     from a device work list.  Otherwise the runs are processed one after the other.  The
+ *     from 4 to 20, and 24) is one launch per lattice size whose blocks take (run, 64-replica
+ *     group) items from a device work list.  Otherwise the runs are processed one after the other.  The
  *     results are the same either way (every draw is keyed by run seed and replica index).
  *
  * Physics conventions
@@ -189,7 +189,8 @@ typedef struct pa_info {
  * too small L (1D: L >= 4; 3D: L >= 2, L <= 32), capacity not a positive multiple of 64, a
  * coupling kind other than PA_PM1 / PA_GAUSS, or Gaussian couplings with a layout other than
  * PA_U8.  Couplings take 1 byte per bond (PA_PM1) or 8 (PA_GAUSS), energies 4 or 8 bytes per
- * replica; with PA_GAUSS the work buffer also holds the sweep's threshold tables (640 N bytes:
+ * replica; with PA_GAUSS the work buffer also holds the sweep's threshold tables (640 N bytes, N
+ * rounded up to 16:
  * 16-bit first-look entries and 64-bit thresholds per site and neighbour pattern, rewritten by
  * every pa_sweep), so buffers must be sized with the run's coupling kind. */
 int pa_buffer_sizes(int dim, int L, int layout, int couplings, int64_t capacity, int n_records, pa_sizes* out);
@@ -219,9 +220,10 @@ int pa_init_couplings(pa_run* runs, int n_runs, const int8_t* const* J_host);
  * order j = 0, 1, ... (eq. Q), ln Q = -dbeta E_lo + ln S - ln R~,
  * copies of j ~ Poisson((R_target w_j) / S) by the ladder of pa_resample.  FP64 products and
  * sums are never fused.  In calls with n_runs > 1, Gaussian runs whose pa_state blocks are
- * consecutive and share a stream take one launch per kernel, others one after the other;
+ * consecutive and share a stream (and, for the sweep, one size) take one launch per kernel, others one
+ * after the other;
  * pa_resampled_fraction / pa_rho_steps reject them.  pa_sweep tabulates, per call, the top 16
- * bits of T64 for every site and neighbour pattern (cubes of side 4 and 8, chains of 16k <= 1024
+ * bits of T64 for every site and neighbour pattern (cubes of side 4 to 16, chains of up to 4096
  * sites; other shapes compute dE per attempt): the accepted moves are the same. */
 
 /* theta = step->n_sweeps Metropolis sweeps of every replica at beta = step->beta_to
@@ -236,7 +238,7 @@ int pa_init_couplings(pa_run* runs, int n_runs, const int8_t* const* J_host);
  * t = step->t0 + s is the global sweep index, r the replica's index in the population.
  * Energies are updated with the spins.  Sizes: chains of any length; cubes of even side up
  * to 20, and 24 and 32 (other sides: PA_ERR_ARG, nothing launched); Gaussian couplings: any
- * size the buffers allow (tabled kernels for cube sides 4 and 8 and chains of 16k <= 1024 sites,
+ * size the buffers allow (tabled kernels for cube sides 4 to 16 and chains of up to 4096 sites,
  * one thread per replica otherwise). */
 int pa_sweep(pa_run* runs, int n_runs, const pa_step* step);
 

@@ -12,7 +12,8 @@
 #include "pa_common.h"
 #include "pa_host.h"
 #include "pa_lattice.h"
-#include "pa_sweep_words.h"
+#include "pa_sweep_strings.h"
+#include "pa_sweep_util.h"
 
 #pragma clang fp contract(off)
 
@@ -159,33 +160,42 @@ __global__ void __launch_bounds__(64) k_sweep_gauss(const pa_state* __restrict__
 }
 
 // ------------------------------------------------------------------ tabled sweep
-// The same sweeps with lane = replica and a wave of 64 replicas.  Each lane keeps its spins as
-// 16-site segments in LDS (bit j of segment m is site 16m + j), so the neighbour bits of a whole
-// segment come from a few shifts of at most five segment words.
+// The same sweeps with lane = replica: 64 replicas side by side in LDS, each as its two colour
+// strings (pa_sweep_strings.h; on the chain bit b of the colour-c string is site 2 b + c), and a word
+// of 32 sites of a colour at a time.
 //
 // dE of an attempt depends only on the site and on the pattern b of the bits s_j xor s_i of
 // its neighbours in field order: flipping every spin negates each term of h exactly, hence h,
 // and leaves dE unchanged.  Per call, k_gauss_table tabulates for every site and pattern
 // T64 = floor(p 2^64) with p = expd(-(beta dE)) computed as in k_sweep_gauss (s_i = 0, s_j = bit
 // of b), or all ones where the flip is always accepted (dE <= 0 or p >= 1; a p below 1 gives at
-// most 2^64 - 2^11), and its top T16 = T64 >> 48.  An attempt compares its 16-bit draw u with T16:
-// u < T16 accepts, u > T16 rejects, and u == T16 (rare) compares the 64-bit draw with T64, as
-// k_sweep_gauss does (always accepting where T64 is all ones).  The outcome of every attempt is
-// therefore the same as there.
+// most 2^64 - 2^11), and the bound min(T16, 0xFFFE) + 1 of its top T16 = T64 >> 48.  An attempt
+// compares its 16-bit draw u with the bound: bound - u saturated is 2 or more where u < T16 (accept), 1
+// where u = T16 (a tie: the 64-bit draw against T64 decides, as in k_sweep_gauss) and 0 where u > T16
+// (reject).  With T16 = 0xFFFF the bound is one too low: u = 0xFFFE comes out as a tie and u = 0xFFFF as a
+// rejection, so both are looked at again with T64 (a running maximum of the draws finds the
+// latter).  The outcome of every attempt is therefore the same as there.
 //
-// Table layout (after the work layout): u16 [colour c][segment m][pattern b][k], k = 0..7 the
-// sites of colour c in segment m in ascending order.  Site i of colour c has h = i >> 1 = 8m + k
-// (rows have even length, so exactly one of 2h, 2h + 1 has colour c).  The lanes of a wave work on
-// the same segment at the same time, so lane b loads the 16-byte row [c][m][b]: one coalesced 1 KB
-// load per segment whose address does not depend on the spins, issued a step ahead.  Each
-// attempt then takes its entry from lane b = its pattern with ds_bpermute, a lane-to-lane read at
-// the latency of LDS, instead of a gather from the cache at the latency of memory.  The u64 table of
-// T64 follows in the same order.
-
-constexpr int kGaussWaves = 4;
+// Table layout (after the work layout): u16 [colour c][call m][pattern b][k], k = 0..7 the sites of
+// half-index 8 m + k, the eight sites whose draws are the fields of Philox call m.  The lanes of a wave
+// work on the same word at the same time, so lane b loads the 16-byte row [c][m][b] of each of the
+// word's four calls: coalesced 1 KB loads whose addresses do not depend on the spins, issued a word
+// ahead.  Each attempt then takes its entry from lane b = its pattern with ds_bpermute, a lane-to-lane
+// read at the latency of LDS, instead of a gather from the cache at the latency of memory.
+// ds_bpermute reads only bits 2..7 of its address, and an 8 x 8 bit transpose of the six neighbour
+// words puts the patterns of sites k, 8 + k, 16 + k, 24 + k into bits 2..7 of the four bytes of one
+// word, so an address is one shift.  The u64 table of T64 follows in the same order.
+//
+// Bound by the vector ALU and the latency of a wave's own chain: 11.3 VALU and 1.27 LDS instructions per
+// attempt at side 8, of which Philox 4.7; the 94 registers leave five waves per SIMD.  126 runs of side
+// 8, R = 2000, 100 sweeps: 4.27 ms, 3.0e12 attempts/s; with one wave per group (as the kernel before, on
+// 16-site segments of both colours: 13.9 VALU) 5.23 ms, and a second round of blocks as soon as some
+// runs have more than 32 groups (R = 2060: 4.50 ms against 6.62 ms).  50 runs: 4.12 -> 2.11 ms.  The
+// sides other than 4 and 8 took one thread per replica: side 6, 8 runs, 20 sweeps 40 ms -> 0.10 ms.
+// Chain of 256 sites, 200 runs of 1000, 50 sweeps 1.13 -> 0.91 ms; 64 sites 0.31 -> 0.25 ms.
 
 // h of site i for neighbour pattern b (bit a: neighbour a in field order has s_j != s_i); LC: the
-// cube side as a constant (its divisions become shifts), 0 for L at run time
+// cube side as a constant (its divisions become shifts or multiplications), 0 for L at run time
 template <int NB, int LC = 0>
 __device__ double gauss_field_pattern(const double* __restrict__ J, int i, int b, int L_rt, int N)
 {
@@ -221,11 +231,14 @@ __device__ __forceinline__ uint16_t* gauss_table(const pa_state* st)
     return reinterpret_cast<uint16_t*>(st->work + work_layout(st->N, st->n_bins, st->capacity).total);
 }
 
+// calls per colour (the last one may have fewer than eight sites: its entries past them are zero)
+__host__ __device__ inline int gauss_calls(int N) { return (N / 2 + 7) / 8; }
+
 // the u64 table of full thresholds, after the NB-pattern u16 table (8-byte aligned)
 template <int NB>
 __device__ __forceinline__ uint64_t* gauss_table64(const pa_state* st)
 {
-    return reinterpret_cast<uint64_t*>(gauss_table(st) + ((size_t)st->N << NB));
+    return reinterpret_cast<uint64_t*>(gauss_table(st) + ((size_t)(16 * gauss_calls(st->N)) << NB));
 }
 
 // grid (entries / 256, runs): entry e = (c, m, b, k) of run blockIdx.y; LC as in gauss_field_pattern
@@ -236,487 +249,521 @@ __global__ void __launch_bounds__(256) k_gauss_table(pa_state* __restrict__ stat
     if (st->status) return;
     const int N = st->N, L = LC ? LC : st->L;
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (N << NB)) return;
-    const int half = (N / 2) << NB;
+    const int half = (8 * gauss_calls(N)) << NB;
+    if (e >= 2 * half) return;
     const int c = e >= half, rem = e - c * half;
     const int b = (rem >> 3) & ((1 << NB) - 1), hh = 8 * (rem >> (NB + 3)) + (rem & 7);
-    const int i0 = 2 * hh;
-    const int col0 = NB == 2 ? 0 : ((i0 % L) + (i0 / L) % L + i0 / (L * L)) & 1;
-    const int i = i0 + (col0 != c);
     uint64_t T64 = 0;
-    const bool always = gauss_threshold(gauss_field_pattern<NB, LC>(reinterpret_cast<const double*>(st->J), i, b, L, N),
-                                        beta, &T64);
-    if (always) T64 = ~0ull;
-    gauss_table(st)[e] = (uint16_t)(T64 >> 48);
+    uint32_t bound = 0;
+    if (hh < N / 2) {
+        const int i0 = 2 * hh;
+        const int col0 = NB == 2 ? 0 : ((i0 % L) + (i0 / L) % L + i0 / (L * L)) & 1;
+        const int i = i0 + (col0 != c);
+        const double h = gauss_field_pattern<NB, LC>(reinterpret_cast<const double*>(st->J), i, b, L, N);
+        if (gauss_threshold(h, beta, &T64)) T64 = ~0ull;
+        const uint32_t T16 = (uint32_t)(T64 >> 48);
+        bound = (T16 < 0xFFFEu ? T16 : 0xFFFEu) + 1u;
+    }
+    gauss_table(st)[e] = (uint16_t)bound;
     gauss_table64<NB>(st)[e] = T64;
-}
-
-__device__ __forceinline__ uint32_t bytes_to_bits4(uint32_t w)  // bytes b0..b3 in {0,1} -> b0 | b1<<1 | ...
-{
-    return (w * 0x10204080u) >> 28;
-}
-
-__device__ __forceinline__ uint32_t bits4_to_bytes(uint32_t n)  // inverse of bytes_to_bits4
-{
-    return (n * 0x00204081u) & 0x01010101u;
-}
-
-// A lane's segments in LDS: segments 2p and 2p + 1 are the low and high halves of the lane's
-// 32-bit word of pair p, and the words of a wave's 64 lanes lie side by side ([pair][lane]), so a
-// pair is one ds_read_b32 without bank conflicts.  seg points at the lane's word of pair 0.
-__device__ __forceinline__ uint16_t& seg_at(uint16_t* seg, int m)
-{
-    return seg[(m >> 1) * 128 + (m & 1)];
-}
-
-__device__ __forceinline__ uint32_t pair_at(const uint16_t* seg, int p)
-{
-    return *reinterpret_cast<const uint32_t*>(seg + p * 128);
-}
-
-__device__ __forceinline__ void pair_store(uint16_t* seg, int p, uint32_t w)
-{
-    *reinterpret_cast<uint32_t*>(seg + p * 128) = w;
-}
-
-// the colour parity of segment m's first site (chain: 0; cube: (q * rows per segment + z) & 1 of
-// its segment q in z plane z)
-template <int NB, int L>
-__device__ __forceinline__ int gauss_segment_parity(int m)
-{
-    if constexpr (NB == 2) {
-        return 0;
-    } else {
-        constexpr int SP = L * L / 16, NR = 16 / L;
-        const int z = m / SP, q = m - z * SP;
-        return (q * NR + z) & 1;
-    }
-}
-
-// the neighbour words of segment m in field order, each xor the segment itself
-template <int NB, int L>
-__device__ __forceinline__ void gauss_segment_words(uint16_t* __restrict__ seg, int m, int nseg, uint32_t D,
-                                                    uint32_t X[NB], int* par)
-{
-    if constexpr (NB == 2) {
-        const uint32_t Sn = seg_at(seg, m + 1 == nseg ? 0 : m + 1);
-        const uint32_t Sp = seg_at(seg, m == 0 ? nseg - 1 : m - 1);
-        X[0] = (((D >> 1) | (Sn << 15)) & 0xFFFFu) ^ D;
-        X[1] = (((D << 1) | (Sp >> 15)) & 0xFFFFu) ^ D;
-        *par = 0;
-    } else {
-        constexpr int SP = L * L / 16;  // segments per z plane
-        constexpr int NR = 16 / L;      // rows per segment
-        constexpr uint32_t Mhi = L == 4 ? 0x8888u : 0x8080u;  // x = L - 1
-        constexpr uint32_t Mlo = L == 4 ? 0x1111u : 0x0101u;  // x = 0
-        const int z = m / SP, q = m - z * SP;
-        const uint32_t Sn = seg_at(seg, z * SP + (q + 1 == SP ? 0 : q + 1));
-        const uint32_t Sp = seg_at(seg, z * SP + (q == 0 ? SP - 1 : q - 1));
-        const uint32_t Sz = seg_at(seg, (z + 1 == L ? 0 : z + 1) * SP + q);
-        const uint32_t Szm = seg_at(seg, (z == 0 ? L - 1 : z - 1) * SP + q);
-        X[0] = (((D >> 1) & ~Mhi) | ((D << (L - 1)) & Mhi)) ^ D;
-        X[1] = (((D >> L) | (Sn << (16 - L))) & 0xFFFFu) ^ D;
-        X[2] = Sz ^ D;
-        X[3] = (((D << 1) & ~Mlo & 0xFFFFu) | ((D >> (L - 1)) & Mlo)) ^ D;
-        X[4] = (((D << L) | (Sp >> (16 - L))) & 0xFFFFu) ^ D;
-        X[5] = Szm ^ D;
-        *par = gauss_segment_parity<NB, L>(m);
-    }
-}
-
-// Cube side 8: the neighbour words of pair p (four x rows of one z plane, segments 2p and 2p + 1 in
-// the low and high halves), each xor the pair itself, formed on whole 32-bit words.  The plane's
-// other pair So holds the rows on both y sides.
-__device__ __forceinline__ void gauss_pair_words8(const uint16_t* __restrict__ seg, int p, uint32_t D2, uint32_t So,
-                                                  uint32_t X[6])
-{
-    const int z = p >> 1, h = p & 1;  // two pairs per plane
-    const uint32_t Sz = pair_at(seg, 2 * (z == 7 ? 0 : z + 1) + h);
-    const uint32_t Szm = pair_at(seg, 2 * (z == 0 ? 7 : z - 1) + h);
-    constexpr uint32_t Mhi = 0x80808080u, Mlo = 0x01010101u;  // x = 7, x = 0 in each row byte
-    X[0] = (((D2 >> 1) & ~Mhi) | ((D2 << 7) & Mhi)) ^ D2;
-    X[1] = ((D2 >> 8) | (So << 24)) ^ D2;
-    X[2] = Sz ^ D2;
-    X[3] = (((D2 << 1) & ~Mlo) | ((D2 >> 7) & Mlo)) ^ D2;
-    X[4] = ((D2 << 8) | (So >> 24)) ^ D2;
-    X[5] = Szm ^ D2;
-}
-
-// Chains of an even number of segments: the neighbour words of pair p (sites 32 p .. 32 p + 31),
-// each xor the pair itself, formed on whole 32-bit words (npair pairs, periodic)
-__device__ __forceinline__ void gauss_pair_words_chain(const uint16_t* __restrict__ seg, int p, int npair, uint32_t D2,
-                                                       uint32_t X[2])
-{
-    const uint32_t Sn = pair_at(seg, p + 1 == npair ? 0 : p + 1);
-    const uint32_t Sp = pair_at(seg, p == 0 ? npair - 1 : p - 1);
-    X[0] = ((D2 >> 1) | (Sn << 31)) ^ D2;
-    X[1] = ((D2 << 1) | (Sp >> 31)) ^ D2;
-}
-
-// the k-th site (k = 0..7, ascending) of colour parity SEL inside a segment (chain: j & 1; cube:
-// (x + y) & 1 of the site inside the segment)
-template <int NB, int L, int SEL>
-__host__ __device__ constexpr int seg_site(int k)
-{
-    int c = 0;
-    for (int j = 0; j < 16; ++j) {
-        const int cj = NB == 2 ? (j & 1) : (((j % L) + (j / L)) & 1);
-        if (cj == SEL) {
-            if (c == k) return j;
-            ++c;
-        }
-    }
-    return -1;
-}
-
-// ds_bpermute takes the source lane from bits 2..7 of its byte address and ignores the others.
-// Shifted by a + 2, bit a of site j's pattern lies at bit j + a + 2, so acc >> j is a valid address
-// for site j as long as no other site of acc has a bit in j + 2 .. j + NB + 1.  (For NB = 2, bits
-// 4..7 may hold other sites' bits: lanes that agree mod 4 hold the same table row.)  The 8 sites of
-// a segment are split greedily into chains of sites at least NB apart, and one and-or chain per
-// chain builds its acc.  Evaluated at compile time.
-template <int NB, int L, int SEL>
-struct SegPlan {
-    int site[8], chain[8], n_chains;
-    uint32_t mask[8][NB];  // [chain][a]: the bits of the chain's sites taken from X[a] << (a + 2)
-    constexpr SegPlan() : site{}, chain{}, n_chains(0), mask{}
-    {
-        int last[8] = {};
-        for (int k = 0; k < 8; ++k) {
-            site[k] = seg_site<NB, L, SEL>(k);
-            int c = 0;
-            while (c < n_chains && site[k] - last[c] < NB) ++c;
-            if (c == n_chains) ++n_chains;
-            last[c] = site[k];
-            chain[k] = c;
-            for (int a = 0; a < NB; ++a) mask[c][a] |= 4u << (site[k] + a);
-        }
-    }
-};
-
-// sites 2w and 2w + 1 share one packed compare: they lie in one row, two apart, and 2w below 14
-template <int NB, int L, int SEL>
-__host__ __device__ constexpr bool seg_pairs_ok()
-{
-    for (int w = 0; w < 4; ++w)
-        if (seg_site<NB, L, SEL>(2 * w + 1) != seg_site<NB, L, SEL>(2 * w) + 2 || seg_site<NB, L, SEL>(2 * w) > 13)
-            return false;
-    return true;
 }
 
 typedef uint32_t gu32x4 __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(1))) gu32x4* grow_ptr;  // table rows, global memory
 
-// v_pk_min_u16, written out: as an expression the optimiser may split it into compares per half
-__device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b)
-{
-    uint32_t r;
-    asm("v_pk_min_u16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
-// (v & m) | (w & ~m) in one v_bfi_b32 with the mask in a scalar register (as an expression, the
-// optimiser keeps the unused bits exact, which costs an and and an or per term)
-__device__ __forceinline__ uint32_t bfi_sgpr(uint32_t m, uint32_t v, uint32_t w)
-{
-    uint32_t r;
-    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "s"(m), "v"(v), "v"(w));
-    return r;
-}
-
-// a - b per 16-bit half, saturated at zero (v_pk_sub_u16 with clamp)
-__device__ __forceinline__ uint32_t pk_sub_sat_u16(uint32_t a, uint32_t b)
-{
-    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, a),
-                                                                      __builtin_bit_cast(u16x2, b)));
-}
-
-// The table entries of the 8 sites of colour parity SEL in a segment, as lane reads of the rows:
-// raw[2w] holds site 2w's entry in its low half, raw[2w + 1] site 2w + 1's in its high half (word w
-// of a row holds the entries of sites 2w and 2w + 1 for the row's pattern).  The reads stay in
-// flight until gauss_segment_decide uses them.
-template <int NB, int L, int SEL, int HALF = 0>
-__device__ __forceinline__ void gauss_segment_fetch(const uint32_t X[NB], const gu32x4& row, uint32_t raw[8])
-{
-    static_assert(seg_pairs_ok<NB, L, SEL>(), "segment sites do not pair");
-    // the lane addresses: site j's pattern in bits 2.. of acc >> j (the segment in bits 16 * HALF ..
-    // of the neighbour words; shifting right by 14 - a puts bit 16 + j at j + a + 2, and the low
-    // half's bits below a + 2, which no chain takes)
-    constexpr SegPlan<NB, L, SEL> plan{};
-    constexpr int NC = plan.n_chains;
-    uint32_t P[NB], acc[NC];
-#pragma unroll
-    for (int a = 0; a < NB; ++a) P[a] = HALF ? X[a] >> (14 - a) : X[a] << (a + 2);
-    // only the chain's fields matter (the lane read ignores the other bits), so each neighbour word
-    // is merged in with one bit-field insert of its field bits
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        acc[c] = P[0];
-#pragma unroll
-        for (int a = 1; a < NB; ++a) acc[c] = bfi_sgpr(plan.mask[c][a], P[a], acc[c]);
-    }
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-        raw[k] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(acc[plan.chain[k]] >> plan.site[k]), (int)row[k >> 1]);
-}
-
-// The attempts of the 8 sites of colour parity SEL in a segment.  Site k's draw is field k of the
-// segment's Philox call (half k & 1 of word k >> 1), the same half as its table entry, so one
-// packed compare takes sites 2w and 2w + 1.  u < T16 accepts; returns the flips (site bits), and
-// *tied is set where some site has u == T16 (those are neither flipped here nor final).
-template <int NB, int L, int SEL>
-__device__ __forceinline__ uint32_t gauss_segment_decide(const uint32_t raw[8], const uint4v& v, bool* tied)
-{
-    const uint32_t vw[4] = {v.x, v.y, v.z, v.w};
-    uint32_t G = 0, tmin = 0xFFFFFFFFu;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        const uint32_t thi = __builtin_amdgcn_perm(raw[2 * w + 1], raw[2 * w], 0x07060100u);  // low, high half
-        tmin = pk_min_u16(tmin, vw[w] ^ thi);  // a zero half: u == T16
-        // 1 in each half where u < T16: site 2w's bit at its site, site 2w + 1's 16 above that
-        G |= pk_min_u16(pk_sub_sat_u16(thi, vw[w]), 0x00010001u) << seg_site<NB, L, SEL>(2 * w);
-    }
-    *tied = (tmin & 0xFFFFu) == 0 || (tmin >> 16) == 0;
-    // site 2w + 1 lies two above site 2w (and every site 2w below 14): the high bits move down 14
-    return (G & 0xFFFFu) | (G >> 14);
-}
-
-// the sites of colour parity SEL in a segment with u == T16
-template <int NB, int L, int SEL>
-__device__ __forceinline__ uint32_t gauss_segment_ties(const uint32_t raw[8], const uint4v& v)
-{
-    const uint32_t vw[4] = {v.x, v.y, v.z, v.w};
-    uint32_t tie = 0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        const uint32_t x = vw[w] ^ __builtin_amdgcn_perm(raw[2 * w + 1], raw[2 * w], 0x07060100u);
-        tie |= (uint32_t)((x & 0xFFFFu) == 0) << seg_site<NB, L, SEL>(2 * w);
-        tie |= (uint32_t)((x >> 16) == 0) << seg_site<NB, L, SEL>(2 * w + 1);
-    }
-    return tie;
-}
-
-struct GaussWords { uint32_t w[6]; };
-
-// The exact decisions of one lane's tied sites of segment m (site bits ties; X the segment's
-// neighbour words, T64m its rows of the u64 table): the 64-bit draw U = (u << 48) | 48 bits of the
-// tie stream against T64 (Sec. II).
+// Lane addresses of the 32 sites' table entries from the neighbour words X (each xor the own word, in
+// field order): the pattern of site 8 i + k in bits 2 .. NB + 1 of what site_address gives for it
+// (other bits arbitrary; on the chain, bits 4..7 too: lanes that agree mod 4 hold the same row).
 template <int NB>
-__device__ __forceinline__ uint32_t gauss_resolve_ties(const uint64_t* __restrict__ T64m, GaussWords X, uint4v v,
-                                                       uint32_t ties, int m, uint32_t rr, uint32_t ctr2, uint32_t k0,
-                                                       uint32_t k1)
+struct Patterns {
+    uint32_t P[NB == 6 ? 8 : 2];
+    __device__ __forceinline__ void make(const uint32_t (&X)[NB])
+    {
+        using words::select_bits;
+        if constexpr (NB == 6) {
+            // rows 2..7 of the transpose are the neighbour words, rows 0 and 1 arbitrary
+            constexpr uint32_t M4 = 0x0F0F0F0Fu, M2 = 0x33333333u, M1 = 0x55555555u;
+            uint32_t A[8];
+            A[0] = X[2] << 4;
+            A[1] = X[3] << 4;
+            A[2] = select_bits(M4, X[0], X[4] << 4);
+            A[3] = select_bits(M4, X[1], X[5] << 4);
+            A[4] = X[2];
+            A[5] = X[3];
+            A[6] = select_bits(M4, X[0] >> 4, X[4]);
+            A[7] = select_bits(M4, X[1] >> 4, X[5]);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                if (r & 2) continue;
+                const uint32_t lo = A[r], hi = A[r + 2];
+                A[r] = select_bits(M2, lo, hi << 2);
+                A[r + 2] = select_bits(M2, lo >> 2, hi);
+            }
+#pragma unroll
+            for (int r = 0; r < 8; r += 2) {
+                P[r] = select_bits(M1, A[r], A[r + 1] << 1);
+                P[r + 1] = select_bits(M1, A[r] >> 1, A[r + 1]);
+            }
+        } else {
+            // even sites j at bits j, j + 1 of P[0], odd ones at bits j - 1, j of P[1]
+            P[0] = select_bits(0x55555555u, X[0], X[1] << 1);
+            P[1] = select_bits(0xAAAAAAAAu, X[1], X[0] >> 1);
+        }
+    }
+    __device__ __forceinline__ uint32_t address(int i, int k) const  // constants after unrolling
+    {
+        if constexpr (NB == 6) {
+            return P[k] >> (8 * i);
+        } else {
+            const int s = 8 * i + (k & ~1);
+            return s >= 2 ? P[k & 1] >> (s - 2) : P[k & 1] << (2 - s);
+        }
+    }
+};
+
+// v_pk_max_u16, written out as first_look's minimum is
+__device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b)
 {
+    uint32_t r;
+    asm("v_pk_max_u16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+struct GaussX { uint32_t w[6]; };
+
+// The attempts of a word that the bounds leave open, decided exactly: ties (bits with u = bound - 1)
+// and, where top is set, the sites with u = 0xFFFF (their calls are drawn again).  T64w: the word's rows
+// of the u64 table; sites is the mask of the word's sites, odd that of the sites 2 h + 1.  Returns the
+// accepted ones.
+template <int NB>
+static __device__ __noinline__ uint32_t gauss_resolve(const uint64_t* __restrict__ T64w, GaussX X, uint32_t ties, bool top,
+                                                      uint32_t sites, uint32_t odd, uint32_t k, uint32_t rr, uint32_t ctr2,
+                                                      uint32_t k0, uint32_t k1)
+{
+    if (top) {
+        for (int i = 0; i < 4; ++i) {
+            const uint4v v = philox10(4 * k + i, rr, ctr2, kTagMet, k0, k1);
+            for (int f = 0; f < 8; ++f) ties |= (uint32_t)(field16(v, f) == 0xFFFFu) << (8 * i + f);
+        }
+    }
+    ties &= sites;
     uint32_t F = 0;
     while (ties) {
         const int j = __builtin_ctz(ties);
         ties &= ties - 1;
         int b = 0;
         for (int a = 0; a < NB; ++a) b |= (int)((X.w[a] >> j) & 1u) << a;
-        const int k = j >> 1;  // site j is the k-th of its colour in the segment
-        const uint64_t T = T64m[(b << 3) + k];
-        const uint32_t u = (word_of(v, k >> 1) >> (16 * (k & 1))) & 0xFFFFu;
-        const uint4v w = philox10((uint32_t)(16 * m + j), rr, ctr2, kTagTie, k0, k1);
-        const uint64_t U = ((uint64_t)u << 48) | (uint64_t)w.x | ((uint64_t)(w.y & 0xFFFFu) << 32);
-        F |= (uint32_t)(T == ~0ull || U < T) << j;
+        const uint64_t T = T64w[((((j >> 3) << NB) + b) << 3) + (j & 7)];
+        const uint32_t T16 = (uint32_t)(T >> 48);
+        const uint32_t u = (field16(philox10(4 * k + (j >> 3), rr, ctr2, kTagMet, k0, k1), j & 7));
+        bool accept = T == ~0ull || u < T16;
+        if (!accept && u == T16) accept = tie_accept(u, T, 2u * (32u * k + j) + ((odd >> j) & 1u), rr, ctr2, k0, k1);
+        F |= (uint32_t)accept << j;
     }
     return F;
 }
 
-
-// The rare first-look ties of segment m, decided exactly before it is written: the neighbour words
-// are formed again (segment m's own word has not changed) and the tied lanes compare their 64-bit
-// draws with the u64 table.
-template <int NB, int L, int SEL>
-__device__ __forceinline__ uint32_t gauss_segment_tie_flips(uint16_t* __restrict__ seg, int m, int nseg, uint32_t D,
-                                                            const uint32_t raw[8], const uint4v& v,
-                                                            const uint64_t* __restrict__ T64c, uint32_t rr,
-                                                            uint32_t ctr2, uint32_t k0, uint32_t k1)
+// The attempts of word w of a colour (bits `sites` of it): X the neighbour words xor w in field order,
+// rows the table rows of the word's calls in this lane, T64w the word's rows of the u64 table.  Returns
+// the new word.  CALLS: the calls with sites (0: nbytes of them, known at run time).
+template <int NB, int CALLS, int NR>
+__device__ __forceinline__ uint32_t gauss_word(uint32_t w, const uint32_t (&X)[NB], const gu32x4 (&rows)[NR], uint32_t sites,
+                                               uint32_t odd, int nbytes, const uint64_t* __restrict__ T64w, uint32_t k,
+                                               const words::Lane& c)
 {
-    const uint32_t ties = gauss_segment_ties<NB, L, SEL>(raw, v);
-    if (!ties) return 0;
-    uint32_t X[NB];
-    int par;
-    gauss_segment_words<NB, L>(seg, m, nseg, D, X, &par);
-    GaussWords xw = {};
+    using words::select_bits;
+    Patterns<NB> pt;
+    pt.make(X);
+    uint32_t raw[4][8];
 #pragma unroll
-    for (int a = 0; a < NB; ++a) xw.w[a] = X[a];
-    return gauss_resolve_ties<NB>(T64c + ((size_t)m << (NB + 3)), xw, v, ties, m, rr, ctr2, k0, k1);
-}
-
-// The attempts of segments m0 .. m0 + G - 1, all of colour parity SEL (rows: their table rows):
-// the lane reads of every segment's entries, then their draws while those are in flight, then the
-// decisions.  G is the number of consecutive segments of one colour parity taken per step: cube
-// side 8, the four of a z plane (two pairs); chains of an even number of segments, a pair;
-// otherwise one (side 4 alternates the parity from segment to segment).
-template <int NB, int L, int SEL, int G>
-__device__ __forceinline__ void gauss_group_step(uint16_t* __restrict__ seg, int m0, int nseg, const gu32x4 (&rows)[G],
-                                                 const uint64_t* __restrict__ T64c, uint32_t rr, uint32_t ctr2,
-                                                 uint32_t k0, uint32_t k1)
-{
-    uint32_t D[G], raw[G][8];
-    if constexpr (G == 4) {
-        // a z plane: its two pairs, each the other's neighbour in y; the neighbour words once per
-        // pair for both halves
-        const uint32_t A = pair_at(seg, m0 >> 1), B = pair_at(seg, (m0 >> 1) + 1);
-        uint32_t X[6];
-        gauss_pair_words8(seg, m0 >> 1, A, B, X);
-        gauss_segment_fetch<NB, L, SEL, 0>(X, rows[0], raw[0]);
-        gauss_segment_fetch<NB, L, SEL, 1>(X, rows[1], raw[1]);
-        gauss_pair_words8(seg, (m0 >> 1) + 1, B, A, X);
-        gauss_segment_fetch<NB, L, SEL, 0>(X, rows[2], raw[2]);
-        gauss_segment_fetch<NB, L, SEL, 1>(X, rows[3], raw[3]);
-        D[0] = A & 0xFFFFu;
-        D[1] = A >> 16;
-        D[2] = B & 0xFFFFu;
-        D[3] = B >> 16;
-    } else if constexpr (G == 2) {
-        static_assert(NB == 2, "pairs of one parity: chains");
-        const uint32_t A = pair_at(seg, m0 >> 1);
-        uint32_t X[2];
-        gauss_pair_words_chain(seg, m0 >> 1, nseg >> 1, A, X);
-        gauss_segment_fetch<NB, L, SEL, 0>(X, rows[0], raw[0]);
-        gauss_segment_fetch<NB, L, SEL, 1>(X, rows[1], raw[1]);
-        D[0] = A & 0xFFFFu;
-        D[1] = A >> 16;
-    } else {
-        D[0] = seg_at(seg, m0);
-        uint32_t X[NB];
-        int par;
-        gauss_segment_words<NB, L>(seg, m0, nseg, D[0], X, &par);
-        gauss_segment_fetch<NB, L, SEL>(X, rows[0], raw[0]);
-    }
-    uint4v v[G];
+    for (int i = 0; i < 4; ++i) {
+        if (CALLS ? i >= CALLS : i >= nbytes) break;
 #pragma unroll
-    for (int g = 0; g < G; ++g) v[g] = words::philox10_lane((uint32_t)(m0 + g), rr, ctr2, kTagMet, k0, k1);
-    uint32_t F[G];
+        for (int t = 0; t < 8; ++t)
+            raw[i][t] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)pt.address(i, t), (int)rows[i][t >> 1]);
+    }
+    // outcomes and their places as in words::decide_word
+    uint32_t ra = 0, rb = 0, umax = 0;
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        bool tied;
-        F[g] = gauss_segment_decide<NB, L, SEL>(raw[g], v[g], &tied);
-        if (__ballot(tied)) F[g] |= gauss_segment_tie_flips<NB, L, SEL>(seg, m0 + g, nseg, D[g], raw[g], v[g], T64c, rr, ctr2, k0, k1);
-    }
-    if constexpr (G >= 2) pair_store(seg, m0 >> 1, (D[0] | (D[1] << 16)) ^ (F[0] | (F[1] << 16)));
-    if constexpr (G == 4) pair_store(seg, (m0 >> 1) + 1, (D[2] | (D[3] << 16)) ^ (F[2] | (F[3] << 16)));
-    if constexpr (G == 1) seg_at(seg, m0) = (uint16_t)(D[0] ^ F[0]);
-}
-
-// 1-D grid of blocks of kGaussWaves independent waves; block -> (run, group of kGaussWaves tiles):
-// with 8 or more runs, the runs are split into 8 contiguous ranges and the blocks of range x are
-// those with id = x mod 8 (blocks go round-robin to the 8 XCDs, so a run's table stays in one
-// L2); LDS per wave: pairs of segments [N / 32 rounded up][64].  Every lane of a wave takes part in the lane reads of
-// the table (lanes past R compute on zero spins and store nothing), so no branch may split a wave
-// around them.
-template <int NB, int L, int G>
-__global__ void __launch_bounds__(kGaussWaves * 64) k_sweep_gauss_tab(pa_state* __restrict__ states, int n_runs,
-                                                                      int groups, int64_t t0, int ns)
-{
-    int run, group;
-    if (n_runs >= 8) {
-        const int per_xcd = (n_runs + 7) / 8;
-        const int k = blockIdx.x >> 3;
-        run = (int)(blockIdx.x & 7) * per_xcd + k / groups;
-        group = k % groups;
-    } else {
-        run = blockIdx.x / groups;
-        group = blockIdx.x % groups;
-    }
-    if (run >= n_runs) return;
-    const pa_state* st = states + run;
-    if (st->status) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t tile = (int64_t)group * kGaussWaves + wave;
-    const int64_t R = st->R;
-    if (tile * 64 >= R) return;
-    extern __shared__ uint16_t lds16[];
-    const int N = st->N;
-    const int nseg = N >> 4;
-    const double* __restrict__ J = reinterpret_cast<const double*>(st->J);
-    const uint16_t* __restrict__ Tab = gauss_table(st);
-    const uint64_t* __restrict__ Tab64 = gauss_table64<NB>(st);
-    const int npair = (nseg + 1) >> 1;
-    uint16_t* seg = lds16 + wave * npair * 128 + 2 * lane;
-    const uint32_t k0 = (uint32_t)st->seed, k1 = (uint32_t)(st->seed >> 32);
-    const int64_t r = tile * 64 + lane;
-    const bool valid = r < R;
-    uint8_t* row = (uint8_t*)st->spins[st->cur] + r * st->row_stride;
-#pragma unroll 1
-    for (int m = 0; m < nseg; ++m) {
-        uint32_t w = 0;
-        if (valid) {
-            const uint4 q = *reinterpret_cast<const uint4*>(row + 16 * m);
-            w = bytes_to_bits4(q.x) | (bytes_to_bits4(q.y) << 4) | (bytes_to_bits4(q.z) << 8) | (bytes_to_bits4(q.w) << 12);
+    for (int i = 0; i < 4; ++i) {
+        if (CALLS ? i >= CALLS : i >= nbytes) break;
+        const uint4v v = words::philox10_lane(4 * k + i, c.rr, c.ctr2, kTagMet, c.k0, c.k1);
+        const uint32_t vw[4] = {v.x, v.y, v.z, v.w};
+        uint32_t e[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            // site 2 t's entry is the low half of its word, site 2 t + 1's the high half
+            const uint32_t bound = __builtin_amdgcn_perm(raw[i][2 * t + 1], raw[i][2 * t], 0x07060100u);
+            e[t] = words::first_look(bound, vw[t]);
+            umax = (i | t) == 0 ? vw[t] : pk_max_u16(umax, vw[t]);
         }
-        seg_at(seg, m) = (uint16_t)w;
+        const int o = 8 * (i & 1);
+        uint32_t r = i < 2 ? ra : rb;
+        r = (i & 1) ? words::lshl_or(e[0], o, r) : e[0];
+        r = words::lshl_or(e[1], o + 2, r);
+        r = words::lshl_or(e[2], o + 4, r);
+        r = words::lshl_or(e[3], o + 6, r);
+        if (i < 2) ra = r;
+        else rb = r;
     }
-    const uint32_t rr = (uint32_t)r;
-    const int prow = lane & ((1 << NB) - 1);  // the pattern whose table entries this lane holds
+    uint32_t acc = select_bits(0x0000FFFFu, select_bits(0x5555u, ra >> 1, ra >> 16), select_bits(0x55550000u, rb << 15, rb));
+    const bool top = (umax | 0xFFFFu) == 0xFFFFFFFFu || (umax & 0xFFFFu) == 0xFFFFu;
+    if (((ra | rb) & 0x55555555u) != 0 || top) {
+        const uint32_t ties = select_bits(0x0000FFFFu, select_bits(0x5555u, ra, ra >> 15),
+                                          select_bits(0x55550000u, rb << 16, rb << 1));
+        if ((ties & sites) || top) {
+            GaussX gx = {};
+#pragma unroll
+            for (int a = 0; a < NB; ++a) gx.w[a] = X[a];
+            acc |= gauss_resolve<NB>(T64w, gx, ties, top, sites, odd, k, c.rr, c.ctr2, c.k0, c.k1);
+        }
+    }
+    return w ^ (acc & sites);
+}
+
+// A block takes four waves: 4 / NWV groups of 64 replicas, the words of each split by NWV waves.  1-D
+// grid; block -> (run, block of the run): with 8 or more runs, the (run, block) items are split into 8
+// contiguous ranges and the blocks of range x are those with id = x mod 8 (blocks go round-robin to the
+// 8 XCDs, so a run's table stays in one L2, or in two where a run straddles ranges).  Every lane of a
+// wave takes part in the lane reads of the table (lanes past R compute and store nothing), so no
+// branch may split a wave around them.
+constexpr int kGaussWaves = 4;
+
+__device__ __forceinline__ bool gauss_place(int n_runs, int blocks, int* run, int* block)
+{
+    const int items = n_runs * blocks;
+    const int item = n_runs >= 8 ? (int)(blockIdx.x & 7) * ((items + 7) / 8) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+    const int end = n_runs >= 8 ? min(items, (int)((blockIdx.x & 7) + 1) * ((items + 7) / 8)) : items;
+    if (item >= end) return false;
+    *run = item / blocks;
+    *block = item % blocks;
+    return true;
+}
+
+template <int NWV>
+__device__ __forceinline__ void gauss_sync()
+{
+    if constexpr (NWV == 1) wave_sync();
+    else __syncthreads();
+}
+
+template <int L, int NWV>
+struct GaussCubeSmem {
+    static constexpr int GPB = kGaussWaves / NWV;
+    uint32_t E[GPB][2 * strings::Geo<L>::EW * 64];                       // the extended strings, [word][replica]
+    uint32_t tab[2 * strings::Geo<L>::NW * strings::Geo<L>::TW];         // geometry masks
+};
+
+template <int L, int NWV>
+__global__ void __launch_bounds__(kGaussWaves * 64) k_sweep_gauss_cube(pa_state* __restrict__ states, int n_runs,
+                                                                       int blocks, int64_t t0, int ns)
+{
+    using Gm = strings::Geo<L>;
+    constexpr int G = Gm::G, EW = Gm::EW, NW = Gm::NW, TW = Gm::TW, GPB = kGaussWaves / NWV;
+    constexpr bool WHOLE = Gm::NH % 32 == 0;
+    constexpr int M = (Gm::NH + 7) / 8;  // calls per colour
+    __shared__ GaussCubeSmem<L, NWV> sm;
+    int run, block;
+    if (!gauss_place(n_runs, blocks, &run, &block)) return;
+    const pa_state* st = states + run;
+    const int64_t R = st->R;
+    if (st->status || (int64_t)block * GPB * 64 >= R) return;
+    const int lane = threadIdx.x & 63, w4 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    strings::build_tables<L, false>(nullptr, sm.tab, lane, w4, kGaussWaves);
+    __syncthreads();
+    const int gi = w4 / NWV, wave = w4 % NWV;
+    const int64_t r = ((int64_t)block * GPB + gi) * 64 + lane;
+    if (r - lane >= R) return;  // (NWV = 1: no barrier of the block follows)
+    const bool valid = r < R;
+    uint32_t* E0 = sm.E[gi] + lane;
+    uint32_t* E1 = E0 + EW * 64;
+    uint8_t* row = (uint8_t*)st->spins[st->cur] + r * Gm::STRIDE;
+    auto put = [&](uint32_t* S, int k, uint32_t v) {
+        S[(G + k) * 64] = v;
+        if constexpr (WHOLE) {
+            if (k < G) S[(G + NW + k) * 64] = v;
+            if (k >= NW - G) S[(k - (NW - G)) * 64] = v;
+        }
+    };
+#pragma unroll 1
+    for (int k = wave; k < NW; k += NWV) {
+        uint32_t ev, od;
+        strings::load_word_u8(row, Gm::STRIDE, k, &ev, &od);
+        const uint32_t sig0 = sm.tab[k * TW + 6], in = sm.tab[k * TW + 11];  // colour 0: x even, sites
+        put(E0, k, words::select_bits(sig0, ev, od) & in);
+        put(E1, k, words::select_bits(sig0, od, ev) & in);
+    }
+    gauss_sync<NWV>();
+    if constexpr (!WHOLE) {
+        strings::refresh_ghosts<L, 64>(E0, wave, NWV);
+        strings::refresh_ghosts<L, 64>(E1, wave, NWV);
+        gauss_sync<NWV>();
+    }
+
+    const uint16_t* __restrict__ Tab = gauss_table(st);
+    const uint64_t* __restrict__ Tab64 = gauss_table64<6>(st);
+    words::Lane c;
+    c.rr = (uint32_t)r;
+    c.k0 = (uint32_t)st->seed;
+    c.k1 = (uint32_t)(st->seed >> 32);
+    // this lane's rows of the calls of word k of a colour (calls past the last one: the last one's)
+    auto load_rows = [&](int col, int k, gu32x4 (&rows)[4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int m = WHOLE || 4 * k + i < M ? 4 * k + i : M - 1;
+            rows[i] = ((grow_ptr)Tab)[((col * M + m) << 6) + lane];
+        }
+    };
+    gu32x4 rows[4];
+    if (wave < NW) load_rows(0, wave, rows);
     for (int64_t t = t0; t < t0 + ns; ++t) {
         for (int col = 0; col < 2; ++col) {
-            const uint32_t ctr2 = (uint32_t)(2 * t + col);
-            // this lane's row of segment m is T[m << NB]
-            const grow_ptr T = (grow_ptr)(Tab + (col ? ((N / 2) << NB) : 0)) + prow;
-            // groups of G segments of one colour parity: their table rows (loaded a group ahead),
-            // the lane reads of their entries, their draws while those are in flight, then the
-            // decisions
-            const uint64_t* __restrict__ T64c = Tab64 + (col ? ((N / 2) << NB) : 0);
-            gu32x4 rows[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) rows[g] = T[g << NB];
+            c.ctr2 = (uint32_t)(2 * t + col);
+            uint32_t* W = col ? E1 : E0;
+            const uint32_t* O = col ? E0 : E1;
 #pragma unroll 1
-            for (int m0 = 0; m0 < nseg; m0 += G) {
-                const int n0 = m0 + G < nseg ? m0 + G : m0;
-                gu32x4 next[G];
+            for (int k = wave; k < NW; k += NWV) {
+                // the rows of the wave's next word (of the other colour after its last one)
+                gu32x4 next[4];
+                const bool last = k + NWV >= NW;
+                load_rows(last ? col ^ 1 : col, last ? wave : k + NWV, next);
+                const uint32_t* T = sm.tab + (col * NW + k) * TW;
+                const uint32_t w = W[(G + k) * 64];
+                uint32_t nb[6];
+                strings::neighbours<L, 64>(O + (G + k) * 64, T, nb);  // +x, -x, +y, -y, +z, -z
+                const uint32_t X[6] = {w ^ nb[0], w ^ nb[2], w ^ nb[4], w ^ nb[1], w ^ nb[3], w ^ nb[5]};
+                const uint32_t sites = WHOLE ? 0xFFFFFFFFu : T[11];
+                put(W, k, gauss_word<6, 4>(w, X, rows, sites, ~T[6], 4, Tab64 + ((size_t)(col * M + 4 * k) << 9), k, c));
 #pragma unroll
-                for (int g = 0; g < G; ++g) next[g] = T[(n0 + g) << NB];
-                if ((gauss_segment_parity<NB, L>(m0) ^ col) == 0)
-                    gauss_group_step<NB, L, 0, G>(seg, m0, nseg, rows, T64c, rr, ctr2, k0, k1);
-                else
-                    gauss_group_step<NB, L, 1, G>(seg, m0, nseg, rows, T64c, rr, ctr2, k0, k1);
-#pragma unroll
-                for (int g = 0; g < G; ++g) rows[g] = next[g];
+                for (int i = 0; i < 4; ++i) rows[i] = next[i];
+            }
+            gauss_sync<NWV>();
+            if constexpr (!WHOLE) {
+                strings::refresh_ghosts<L, 64>(W, wave, NWV);
+                gauss_sync<NWV>();
             }
         }
     }
-    // write back; E in bond order (site i, then axis +x, +y, +z; chain: bond i -- i+1)
+
+    // spins back, and (the group's first wave) E in bond order: site i, then axis +x, +y, +z
+#pragma unroll 1
+    for (int k = wave; k < NW; k += NWV) {
+        const uint32_t sig0 = sm.tab[k * TW + 6], in = sm.tab[k * TW + 11];
+        const uint32_t a = E0[(G + k) * 64], b = E1[(G + k) * 64];
+        if (valid)
+            strings::store_word_u8(row, Gm::STRIDE, k, words::select_bits(sig0, a, b) & in, words::select_bits(sig0, b, a) & in);
+    }
+    if (wave != 0) return;
+    const double* __restrict__ J = reinterpret_cast<const double*>(st->J);
+    constexpr uint32_t LM = (1u << L) - 1u;
     double E = 0.0;
 #pragma unroll 1
-    for (int m = 0; m < nseg; ++m) {
-        const uint32_t D = seg_at(seg, m);
-        uint32_t X[NB];
-        int par;
-        gauss_segment_words<NB, L>(seg, m, nseg, D, X, &par);
-        const double* Jm = J + (NB == 2 ? 16 * m : 48 * m);
-        // unrolled by 4 only: unrolled fully, the couplings of a whole segment would be held in VGPRs
-#pragma unroll 4
-        for (int j = 0; j < 16; ++j) {
-            if constexpr (NB == 2) {
-                E = E + (((X[0] >> j) & 1u) ? -Jm[j] : Jm[j]);
-            } else {
-#pragma unroll
-                for (int a = 0; a < 3; ++a) E = E + (((X[a] >> j) & 1u) ? -Jm[3 * j + a] : Jm[3 * j + a]);
+    for (int z = 0; z < L; ++z) {
+        uint32_t own = strings::string_row<L, 64>(0, z, E0 + G * 64, E1 + G * 64);
+        const uint32_t first = own;
+#pragma unroll 1
+        for (int y = 0; y < L; ++y) {
+            const uint32_t yp = y + 1 < L ? strings::string_row<L, 64>(y + 1, z, E0 + G * 64, E1 + G * 64) : first;
+            const uint32_t zp = strings::string_row<L, 64>(y, z + 1 < L ? z + 1 : 0, E0 + G * 64, E1 + G * 64);
+            const uint32_t bx = own ^ (((own >> 1) | (own << (L - 1))) & LM), by = own ^ yp, bz = own ^ zp;
+            const double* Jr = J + 3 * L * (y + L * z);
+            // unrolled by 2 only: unrolled fully, the couplings of a whole row would be held in VGPRs
+#pragma unroll 2
+            for (int x = 0; x < L; ++x) {
+                E = E + (((bx >> x) & 1u) ? -Jr[3 * x] : Jr[3 * x]);
+                E = E + (((by >> x) & 1u) ? -Jr[3 * x + 1] : Jr[3 * x + 1]);
+                E = E + (((bz >> x) & 1u) ? -Jr[3 * x + 2] : Jr[3 * x + 2]);
             }
-        }
-        if (valid) {
-            uint4 q;
-            q.x = bits4_to_bytes(D & 15u);
-            q.y = bits4_to_bytes((D >> 4) & 15u);
-            q.z = bits4_to_bytes((D >> 8) & 15u);
-            q.w = bits4_to_bytes((D >> 12) & 15u);
-            *reinterpret_cast<uint4*>(row + 16 * m) = q;
+            own = yp;
         }
     }
     if (valid) reinterpret_cast<double*>(st->energy[st->cur])[r] = E;
 }
 
-// the tabled kernels cover cubes of side 4 and 8 and chains of N = 16 k <= 1024 sites
-static bool gauss_tab_shape(int dim, int L, int* NB)
+// Chains: the two strings of a 64-replica group in dynamic LDS ([colour][word][64]), its words split by
+// the block's waves.  No ghost words: the bits of a word past its ends come from the words on both
+// sides, periodically.
+// WHOLE: N is a multiple of 64, every word has 32 sites.
+template <bool WHOLE>
+__global__ void __launch_bounds__(kGaussWaves * 64) k_sweep_gauss_chain(pa_state* __restrict__ states, int n_runs,
+                                                                        int blocks, int64_t t0, int ns)
 {
-    if (dim == 3 && (L == 4 || L == 8)) *NB = 6;
-    else if (dim == 1 && L % 16 == 0 && L <= 1024) *NB = 2;
-    else return false;
-    return true;
+    constexpr int NWV = kGaussWaves;
+    extern __shared__ uint32_t lds[];
+    int run, block;
+    if (!gauss_place(n_runs, blocks, &run, &block)) return;
+    const pa_state* st = states + run;
+    const int64_t R = st->R;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r = (int64_t)block * 64 + lane;
+    if (st->status || r - lane >= R) return;  // the same for the whole block
+    const bool valid = r < R;
+    const int N = st->N, NH = N >> 1, NW = (NH + 31) >> 5, M = gauss_calls(N);
+    const int end = (NH - 1) & 31;  // bit of the string's last site in its last word
+    const uint32_t last_sites = 0xFFFFFFFFu >> (31 - end);
+    const int last_bytes = (end >> 3) + 1;
+    uint32_t* E0 = lds + lane;
+    uint32_t* E1 = E0 + NW * 64;
+    const int stride = st->row_stride;
+    uint8_t* row = (uint8_t*)st->spins[st->cur] + r * stride;
+#pragma unroll 1
+    for (int k = wave; k < NW; k += NWV) {
+        uint32_t ev, od;
+        strings::load_word_u8(row, stride, k, &ev, &od);
+        const uint32_t in = k + 1 == NW ? last_sites : 0xFFFFFFFFu;
+        E0[k * 64] = ev & in;
+        E1[k * 64] = od & in;
+    }
+    gauss_sync<NWV>();
+    // the string's word k shifted by one site: bit b holds bit b + 1 or b - 1, periodically
+    auto up = [&](const uint32_t* S, int k, uint32_t a) {
+        return k + 1 < NW ? __builtin_amdgcn_alignbit(S[(k + 1) * 64], a, 1) : (a >> 1) | (S[0] << end);
+    };
+    auto down = [&](const uint32_t* S, int k, uint32_t a) {
+        return k > 0 ? __builtin_amdgcn_alignbit(a, S[(k - 1) * 64], 31) : (a << 1) | (S[(NW - 1) * 64] >> end);
+    };
+    const uint16_t* __restrict__ Tab = gauss_table(st);
+    const uint64_t* __restrict__ Tab64 = gauss_table64<2>(st);
+    words::Lane c;
+    c.rr = (uint32_t)r;
+    c.k0 = (uint32_t)st->seed;
+    c.k1 = (uint32_t)(st->seed >> 32);
+    auto load_rows = [&](int col, int k, gu32x4 (&rows)[4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int m = WHOLE || 4 * k + i < M ? 4 * k + i : M - 1;
+            rows[i] = ((grow_ptr)Tab)[((col * M + m) << 2) + (lane & 3)];
+        }
+    };
+    gu32x4 rows[4];
+    if (wave < NW) load_rows(0, wave, rows);
+    for (int64_t t = t0; t < t0 + ns; ++t) {
+        for (int col = 0; col < 2; ++col) {
+            c.ctr2 = (uint32_t)(2 * t + col);
+            uint32_t* W = col ? E1 : E0;
+            const uint32_t* O = col ? E0 : E1;
+#pragma unroll 1
+            for (int k = wave; k < NW; k += NWV) {
+                gu32x4 next[4];
+                const bool last = k + NWV >= NW;
+                load_rows(last ? col ^ 1 : col, last ? wave : k + NWV, next);
+                const uint32_t w = W[k * 64], a = O[k * 64];
+                // neighbours +1 and -1 of site 2 b + col
+                const uint32_t X[2] = {w ^ (col ? up(O, k, a) : a), w ^ (col ? a : down(O, k, a))};
+                const uint64_t* T64w = Tab64 + ((size_t)(col * M + 4 * k) << 5);
+                const uint32_t odd = col ? 0xFFFFFFFFu : 0u;
+                const bool full = WHOLE || k + 1 < NW;
+                W[k * 64] = gauss_word<2, WHOLE ? 4 : 0>(w, X, rows, full ? 0xFFFFFFFFu : last_sites, odd, full ? 4 : last_bytes,
+                                                 T64w, k, c);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) rows[i] = next[i];
+            }
+            gauss_sync<NWV>();
+        }
+    }
+#pragma unroll 1
+    for (int k = wave; k < NW; k += NWV)
+        if (valid) strings::store_word_u8(row, stride, k, E0[k * 64], E1[k * 64]);
+    if (wave != 0) return;
+    // E in bond order: bond i joins sites i and i + 1
+    const double* __restrict__ J = reinterpret_cast<const double*>(st->J);
+    double E = 0.0;
+#pragma unroll 1
+    for (int k = 0; k < NW; ++k) {
+        const uint32_t a = E0[k * 64], b = E1[k * 64];
+        const uint32_t d0 = a ^ b, d1 = b ^ up(E0, k, a);
+        const int n = k + 1 == NW ? end + 1 : 32;
+        const double* Jk = J + 64 * k;
+#pragma unroll 4
+        for (int j = 0; j < n; ++j) {
+            E = E + (((d0 >> j) & 1u) ? -Jk[2 * j] : Jk[2 * j]);
+            E = E + (((d1 >> j) & 1u) ? -Jk[2 * j + 1] : Jk[2 * j + 1]);
+        }
+    }
+    if (valid) reinterpret_cast<double*>(st->energy[st->cur])[r] = E;
 }
+
+// Chains of up to 128 sites: a replica's two strings are one or two registers each, and so are the rows
+// of all their calls (CALLS per colour), so a sweep touches no memory; four groups of one wave per block.
+template <int CALLS>
+__global__ void __launch_bounds__(kGaussWaves * 64) k_sweep_gauss_short(pa_state* __restrict__ states, int n_runs,
+                                                                        int blocks, int64_t t0, int ns)
+{
+    constexpr int NW = (CALLS + 3) / 4, LAST = CALLS - 4 * (NW - 1);  // words, calls of the last one
+    int run, block;
+    if (!gauss_place(n_runs, blocks, &run, &block)) return;
+    const pa_state* st = states + run;
+    const int64_t R = st->R;
+    const int lane = threadIdx.x & 63, w4 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r = ((int64_t)block * kGaussWaves + w4) * 64 + lane;
+    if (st->status || r - lane >= R) return;
+    const int end = (st->N / 2 - 1) & 31;  // the last site's bit in the last word
+    const uint32_t sites = 0xFFFFFFFFu >> (31 - end);
+    const int stride = st->row_stride;
+    uint8_t* row = (uint8_t*)st->spins[st->cur] + r * stride;
+    uint32_t s[2][NW];
+#pragma unroll
+    for (int k = 0; k < NW; ++k) strings::load_word_u8(row, stride, k, &s[0][k], &s[1][k]);
+    s[0][NW - 1] &= sites;
+    s[1][NW - 1] &= sites;
+    // a string's word k shifted by one site, periodically (bits past the last site arbitrary)
+    auto up = [&](const uint32_t (&v)[NW], int k) {
+        return k + 1 < NW ? __builtin_amdgcn_alignbit(v[NW - 1], v[k], 1) : (v[k] >> 1) | (v[0] << end);
+    };
+    auto down = [&](const uint32_t (&v)[NW], int k) {
+        return k > 0 ? __builtin_amdgcn_alignbit(v[k], v[0], 31) : (v[0] << 1) | (v[NW - 1] >> end);
+    };
+    const uint16_t* __restrict__ Tab = gauss_table(st);
+    const uint64_t* __restrict__ Tab64 = gauss_table64<2>(st);
+    gu32x4 rows[2][CALLS];
+#pragma unroll
+    for (int i = 0; i < 2 * CALLS; ++i) rows[i / CALLS][i % CALLS] = ((grow_ptr)Tab)[(i << 2) + (lane & 3)];
+    words::Lane c;
+    c.rr = (uint32_t)r;
+    c.k0 = (uint32_t)st->seed;
+    c.k1 = (uint32_t)(st->seed >> 32);
+    for (int64_t t = t0; t < t0 + ns; ++t) {
+#pragma unroll
+        for (int col = 0; col < 2; ++col) {
+            c.ctr2 = (uint32_t)(2 * t + col);
+#pragma unroll
+            for (int k = 0; k < NW; ++k) {
+                // site 2 b: neighbours 2 b + 1 and 2 b - 1; site 2 b + 1: 2 b + 2 and 2 b
+                const uint32_t w = s[col][k], a = s[col ^ 1][k];
+                const uint32_t X[2] = {w ^ (col ? up(s[0], k) : a), w ^ (col ? a : down(s[1], k))};
+                const uint64_t* T64w = Tab64 + ((size_t)(col * CALLS + 4 * k) << 5);
+                const uint32_t odd = col ? 0xFFFFFFFFu : 0u;
+                if (k + 1 < NW) {
+                    const gu32x4 (&rw)[4] = *reinterpret_cast<const gu32x4 (*)[4]>(&rows[col][0]);
+                    s[col][k] = gauss_word<2, 4>(w, X, rw, 0xFFFFFFFFu, odd, 4, T64w, (uint32_t)k, c);
+                } else {
+                    const gu32x4 (&rw)[LAST] = *reinterpret_cast<const gu32x4 (*)[LAST]>(&rows[col][4 * (NW - 1)]);
+                    s[col][k] = gauss_word<2, LAST>(w, X, rw, sites, odd, LAST, T64w, (uint32_t)k, c);
+                }
+            }
+        }
+    }
+    if (r < R)
+#pragma unroll
+        for (int k = 0; k < NW; ++k) strings::store_word_u8(row, stride, k, s[0][k], s[1][k]);
+    // E in bond order: bond i joins sites i and i + 1
+    const double* __restrict__ J = reinterpret_cast<const double*>(st->J);
+    double E = 0.0;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+        const uint32_t d0 = s[0][k] ^ s[1][k], d1 = s[1][k] ^ up(s[0], k);
+        const int n = k + 1 < NW ? 32 : end + 1;
+#pragma unroll 4
+        for (int j = 0; j < n; ++j) {
+            E = E + (((d0 >> j) & 1u) ? -J[64 * k + 2 * j] : J[64 * k + 2 * j]);
+            E = E + (((d1 >> j) & 1u) ? -J[64 * k + 2 * j + 1] : J[64 * k + 2 * j + 1]);
+        }
+    }
+    if (r < R) reinterpret_cast<double*>(st->energy[st->cur])[r] = E;
+}
+
+// the tabled kernels cover cubes of even side 4 to 16 and chains of up to 4096 sites
+static bool gauss_tab_shape(int dim, int L) { return dim == 3 ? L >= 4 && L <= 16 : L <= 4096; }
 
 // energy mean, variance, skewness of the population (one block; any summation order: these are
 // compared to 1e-12, not bit for bit)
@@ -765,57 +812,93 @@ int launch_energy_gauss(const pa_run& run, int buf, int64_t n, hipStream_t s)
     return hip_status(hipGetLastError());
 }
 
+// n runs of one shape with consecutive states from base on stream s; cap the largest capacity
+struct GaussLaunch {
+    pa_state* base;
+    int n;
+    int64_t cap;
+    hipStream_t s;
+};
+
+template <int NWV, class K>
+static int launch_gauss_sweep(K kernel, size_t lds, const GaussLaunch& a, const pa_step& step)
+{
+    const int64_t per_block = 64 * (kGaussWaves / NWV);
+    const int64_t blocks = (a.cap + per_block - 1) / per_block;
+    const int64_t grid = a.n >= 8 ? (a.n * blocks + 7) / 8 * 8 : a.n * blocks;
+    if (grid > INT32_MAX) return PA_ERR_ARG;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kGaussWaves * 64), lds, a.s, a.base, a.n, (int)blocks, step.t0,
+                       step.n_sweeps);
+    return hip_status(hipGetLastError());
+}
+
+template <int NB, int LC>
+static void launch_gauss_table(int N, const GaussLaunch& a, double beta)
+{
+    const unsigned blocks = (unsigned)((((16 * gauss_calls(N)) << NB) + 255) / 256);
+    hipLaunchKernelGGL((k_gauss_table<NB, LC>), dim3(blocks, (unsigned)a.n), dim3(256), 0, a.s, a.base, beta);
+}
+
+template <int L>
+static int launch_gauss_cube(const GaussLaunch& a, const pa_step& step)
+{
+    launch_gauss_table<6, L>(L * L * L, a, step.beta_to);
+    constexpr int NWV = L == 4 ? 1 : 4;  // (side 4: one word per colour)
+    return launch_gauss_sweep<NWV>(k_sweep_gauss_cube<L, NWV>, 0, a, step);
+}
+
+static int launch_gauss_chain(int N, const GaussLaunch& a, const pa_step& step)
+{
+    launch_gauss_table<2, 0>(N, a, step.beta_to);
+    switch (gauss_calls(N)) {
+        case 1: return launch_gauss_sweep<1>(k_sweep_gauss_short<1>, 0, a, step);
+        case 2: return launch_gauss_sweep<1>(k_sweep_gauss_short<2>, 0, a, step);
+        case 3: return launch_gauss_sweep<1>(k_sweep_gauss_short<3>, 0, a, step);
+        case 4: return launch_gauss_sweep<1>(k_sweep_gauss_short<4>, 0, a, step);
+        case 5: return launch_gauss_sweep<1>(k_sweep_gauss_short<5>, 0, a, step);
+        case 6: return launch_gauss_sweep<1>(k_sweep_gauss_short<6>, 0, a, step);
+        case 7: return launch_gauss_sweep<1>(k_sweep_gauss_short<7>, 0, a, step);
+        case 8: return launch_gauss_sweep<1>(k_sweep_gauss_short<8>, 0, a, step);
+        default: break;
+    }
+    const size_t lds = (size_t)2 * ((N / 2 + 31) / 32) * 64 * 4;
+    return N % 64 == 0 ? launch_gauss_sweep<kGaussWaves>(k_sweep_gauss_chain<true>, lds, a, step)
+                       : launch_gauss_sweep<kGaussWaves>(k_sweep_gauss_chain<false>, lds, a, step);
+}
+
 int launch_sweep_gauss(const pa_run* runs, int n_runs, bool consecutive, const pa_step& step, hipStream_t s)
 {
-    int NB = 0;
-    bool tab = gauss_tab_shape(runs[0].dim, runs[0].L, &NB);
-    for (int r = 0; r < n_runs; ++r)
-        tab = tab && runs[r].dim == runs[0].dim && runs[r].L == runs[0].L && ((uintptr_t)runs[r].spins[0] & 15) == 0 &&
-              ((uintptr_t)runs[r].spins[1] & 15) == 0;
-    if (!tab) {
+    const int dim = runs[0].dim, L = runs[0].L;
+    bool same = true;
+    for (int r = 1; r < n_runs; ++r) same = same && runs[r].dim == dim && runs[r].L == L;
+    if (n_runs > 1 && !(consecutive && same)) {
         for (int r = 0; r < n_runs; ++r) {
-            hipLaunchKernelGGL(k_sweep_gauss, dim3((unsigned)((runs[r].capacity + 63) / 64)), dim3(64), 0,
-                               (hipStream_t)runs[r].stream, (const pa_state*)runs[r].state, step.beta_to, step.t0,
-                               step.n_sweeps);
+            const int st = launch_sweep_gauss(&runs[r], 1, true, step, (hipStream_t)runs[r].stream);
+            if (st != PA_OK) return st;
+        }
+        return PA_OK;
+    }
+    if (!gauss_tab_shape(dim, L)) {
+        for (int r = 0; r < n_runs; ++r) {
+            hipLaunchKernelGGL(k_sweep_gauss, dim3((unsigned)((runs[r].capacity + 63) / 64)), dim3(64), 0, s,
+                               (const pa_state*)runs[r].state, step.beta_to, step.t0, step.n_sweeps);
             const int st = hip_status(hipGetLastError());
             if (st != PA_OK) return st;
         }
         return PA_OK;
     }
-    const int dim = runs[0].dim, L = runs[0].L;
-    const int N = dim == 1 ? L : L * L * L;
-    const size_t lds = (size_t)kGaussWaves * ((N / 16 + 1) / 2) * 64 * 4;
-    auto go = [&](pa_state* base, int n, int64_t capacity, hipStream_t str) {
-        const dim3 tgrid((unsigned)(((N << NB) + 255) / 256), (unsigned)n);
-        if (NB == 2) hipLaunchKernelGGL((k_gauss_table<2, 0>), tgrid, dim3(256), 0, str, base, step.beta_to);
-        else if (L == 4) hipLaunchKernelGGL((k_gauss_table<6, 4>), tgrid, dim3(256), 0, str, base, step.beta_to);
-        else hipLaunchKernelGGL((k_gauss_table<6, 8>), tgrid, dim3(256), 0, str, base, step.beta_to);
-        int st = hip_status(hipGetLastError());
-        if (st != PA_OK) return st;
-        const int groups = (int)((capacity / 64 + kGaussWaves - 1) / kGaussWaves);
-        const int64_t blocks = n >= 8 ? (int64_t)8 * ((n + 7) / 8) * groups : (int64_t)n * groups;
-        if (blocks > INT32_MAX) return PA_ERR_ARG;
-        const dim3 grid((unsigned)blocks), block(kGaussWaves * 64);
-        if (dim == 1 && (N / 16) % 2 == 0)
-            hipLaunchKernelGGL((k_sweep_gauss_tab<2, 0, 2>), grid, block, lds, str, base, n, groups, step.t0, step.n_sweeps);
-        else if (dim == 1)
-            hipLaunchKernelGGL((k_sweep_gauss_tab<2, 0, 1>), grid, block, lds, str, base, n, groups, step.t0, step.n_sweeps);
-        else if (L == 4)
-            hipLaunchKernelGGL((k_sweep_gauss_tab<6, 4, 1>), grid, block, lds, str, base, n, groups, step.t0, step.n_sweeps);
-        else
-            hipLaunchKernelGGL((k_sweep_gauss_tab<6, 8, 4>), grid, block, lds, str, base, n, groups, step.t0, step.n_sweeps);
-        return hip_status(hipGetLastError());
-    };
-    if (consecutive) {
-        int64_t cap = 0;
-        for (int r = 0; r < n_runs; ++r) cap = runs[r].capacity > cap ? runs[r].capacity : cap;
-        return go(runs[0].state, n_runs, cap, s);  // s is the runs' common stream
+    GaussLaunch a = {runs[0].state, n_runs, 0, s};
+    for (int r = 0; r < n_runs; ++r) a.cap = runs[r].capacity > a.cap ? runs[r].capacity : a.cap;
+    if (dim == 1) return launch_gauss_chain(L, a, step);
+    switch (L) {
+        case 4: return launch_gauss_cube<4>(a, step);
+        case 6: return launch_gauss_cube<6>(a, step);
+        case 8: return launch_gauss_cube<8>(a, step);
+        case 10: return launch_gauss_cube<10>(a, step);
+        case 12: return launch_gauss_cube<12>(a, step);
+        case 14: return launch_gauss_cube<14>(a, step);
+        default: return launch_gauss_cube<16>(a, step);
     }
-    for (int r = 0; r < n_runs; ++r) {
-        const int st = go(runs[r].state, 1, runs[r].capacity, (hipStream_t)runs[r].stream);
-        if (st != PA_OK) return st;
-    }
-    return PA_OK;
 }
 
 int launch_moments_gauss(const pa_run* runs, int n, hipStream_t s)

@@ -79,63 +79,8 @@ struct BlockSmem {
     uint2 tt[256];  // first-look bounds
 };
 
-// even and odd bits of a row word of up to 32 bits, as 16-bit numbers
-__device__ __forceinline__ uint32_t split_row(uint32_t v, uint32_t* odd)
-{
-    uint32_t o;
-    const uint32_t e = split_colours(v, &o);
-    *odd = (o | (o >> 8)) & 0xFFFFu;
-    return (e | (e >> 8)) & 0xFFFFu;
-}
-
-__device__ __forceinline__ uint32_t merge_row(uint32_t e, uint32_t o)
-{
-    return merge_colours((e | (e << 8)) & 0x00FF00FFu, (o | (o << 8)) & 0x00FF00FFu);
-}
-
-// Sites 2 h (ev) and 2 h + 1 (od) of the 32 half-sites h of word k, from the byte rows: 64 bytes of
-// the replica's row as 16-byte pieces (the row is padded to 16 bytes; pieces past it are zero)
-template <int L>
-__device__ __forceinline__ void load_word_u8(const uint8_t* row, int k, uint32_t* ev, uint32_t* od)
-{
-    constexpr int STRIDE = (L * L * L + 15) / 16 * 16;
-    uint32_t e = 0, o = 0;
-    uint4 q[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        q[i] = 64 * k + 16 * i < STRIDE ? *reinterpret_cast<const uint4*>(row + 64 * k + 16 * i) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t d[4] = {q[i].x, q[i].y, q[i].z, q[i].w};
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {  // eight sites: even ones in bytes 0, 2 of two dwords
-            e |= pack4(__builtin_amdgcn_perm(d[2 * t + 1], d[2 * t], 0x06040200u)) << (8 * i + 4 * t);
-            o |= pack4(__builtin_amdgcn_perm(d[2 * t + 1], d[2 * t], 0x07050301u)) << (8 * i + 4 * t);
-        }
-    }
-    *ev = e;
-    *od = o;
-}
-
-template <int L>
-__device__ __forceinline__ void store_word_u8(uint8_t* row, int k, uint32_t ev, uint32_t od)
-{
-    constexpr int STRIDE = (L * L * L + 15) / 16 * 16;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (64 * k + 16 * i >= STRIDE) break;
-        uint32_t d[4];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const uint32_t e = unpack4(ev >> (8 * i + 4 * t)), o = unpack4(od >> (8 * i + 4 * t));
-            d[2 * t] = __builtin_amdgcn_perm(o, e, 0x05010400u);
-            d[2 * t + 1] = __builtin_amdgcn_perm(o, e, 0x07030602u);
-        }
-        *reinterpret_cast<uint4*>(row + 64 * k + 16 * i) = make_uint4(d[0], d[1], d[2], d[3]);
-    }
-}
-
-// the same from the bit-packed rows of the group (base: the lane's word of row 0): half-sites 32 k ..
+// Sites 2 h (ev) and 2 h + 1 (od) of the 32 half-sites h of word k from the bit-packed rows of the
+// group (base: the lane's word of row 0): half-sites 32 k ..
 // lie in the rows 32 k / (L/2) ..
 template <int L>
 __device__ __forceinline__ void load_word_bits(const uint8_t* base, int k, uint32_t* ev, uint32_t* od)
@@ -175,42 +120,11 @@ template <int L, int S>
 __device__ __forceinline__ void store_row_bits(uint8_t* base, int r, const uint32_t* E0, const uint32_t* E1)
 {
     using Gm = Geo<L>;
-    constexpr int H2 = Gm::H2;
-    constexpr uint32_t HM = (1u << H2) - 1u;
-    const int y = r % L, z = r / L, b0 = H2 * r, k = b0 >> 5, sh = b0 & 31;
-    // the word after the string's last one is a ghost word, so k + 1 exists
-    const uint32_t c0 = __builtin_amdgcn_alignbit(E0[(k + 1) * S], E0[k * S], sh) & HM;
-    const uint32_t c1 = __builtin_amdgcn_alignbit(E1[(k + 1) * S], E1[k * S], sh) & HM;
-    const bool odd = (y + z) & 1;  // colour 0 takes x = 2 m + (y + z) mod 2
-    const uint32_t v = merge_row(odd ? c1 : c0, odd ? c0 : c1);
+    const uint32_t v = string_row<L, S>(r % L, r / L, E0, E1);
     uint8_t* a = base + (int64_t)r * 64 * Gm::WB;
     if (Gm::WB == 1) *a = (uint8_t)v;
     else if (Gm::WB == 2) *(uint16_t*)a = (uint16_t)v;
     else *(uint32_t*)a = v;
-}
-
-// The ghost words (and the unused bits of a partial last word) of a string whose length is not a
-// whole number of words (S at the replica's column, Q dwords from word to word), ghost i taken by unit
-// i mod units.  Unit 0 fills the last word before it forms the one ghost word that reads it; no other
-// ghost reads a word that another unit writes, as all come from words of the string.
-template <int L, int Q>
-__device__ __forceinline__ void refresh_ghosts(uint32_t* S, int unit, int units)
-{
-    using Gm = Geo<L>;
-    static_assert(ghosts_in_string<L>(), "ghost words must come from string words");
-    constexpr int G = Gm::G, NW = Gm::NW, last = G + NW - 1;
-    if (unit == 0) {
-        S[last * Q] = select_bits(Gm::LAST, S[last * Q], S[G * Q] << (Gm::NH % 32));
-        constexpr int o = ghost_origin<L>(G - 1), q = G + o / 32;
-        S[(G - 1) * Q] = __builtin_amdgcn_alignbit(S[(q + 1) * Q], S[q * Q], o % 32);
-    }
-    for (int i = unit; i < 2 * G - 1; i += units) {
-        // ghosts 0 .. G - 2 before the string, then those after it
-        const int e = i < G - 1 ? i : NW + i + 1;
-        const int o = i < G - 1 ? Gm::NH - 32 * (G - e) : 32 * (e - G) - Gm::NH;
-        const uint32_t* a = S + (G + (o >> 5)) * Q;
-        S[e * Q] = __builtin_amdgcn_alignbit(a[Q], a[0], o & 31);
-    }
 }
 
 // N_S sweeps of the Q replicas from r0 on of one run by the group's waves
@@ -235,7 +149,7 @@ __device__ __forceinline__ void sweep_shared(const pa_state* st, int64_t r0, int
     const int64_t R = st->R, r = r0 + q;
     const bool valid = r < R;
     uint8_t* rows = (uint8_t*)st->spins[st->cur] +
-                    (LAYOUT == PA_U8 ? r * ((L * L * L + 15) / 16 * 16) : ((r >> 6) * Gm::NR * 64 + (r & 63)) * Gm::WB);
+                    (LAYOUT == PA_U8 ? r * Gm::STRIDE : ((r >> 6) * Gm::NR * 64 + (r & 63)) * Gm::WB);
     // a word and, where ghost words are copies of whole words, its ghost copies
     auto put = [&](uint32_t* S, int k, uint32_t v) {
         S[(G + k) * Q] = v;
@@ -248,7 +162,7 @@ __device__ __forceinline__ void sweep_shared(const pa_state* st, int64_t r0, int
 #pragma unroll 1
     for (int k = unit; k < NW; k += UNITS) {
         uint32_t ev, od;
-        if constexpr (LAYOUT == PA_U8) load_word_u8<L>(rows, k, &ev, &od);
+        if constexpr (LAYOUT == PA_U8) load_word_u8(rows, Gm::STRIDE, k, &ev, &od);
         else load_word_bits<L>(rows, k, &ev, &od);
         const uint32_t sig0 = sm.tab[k * TW + 6], in = sm.tab[k * TW + 11];  // colour 0: x even, sites
         put(E0, k, select_bits(sig0, ev, od) & in);
@@ -323,7 +237,7 @@ __device__ __forceinline__ void sweep_shared(const pa_state* st, int64_t r0, int
         for (int k = unit; k < NW; k += UNITS) {
             const uint32_t sig0 = sm.tab[k * TW + 6], in = sm.tab[k * TW + 11];
             const uint32_t a = E0[(G + k) * Q], b = E1[(G + k) * Q];
-            if (valid) store_word_u8<L>(rows, k, select_bits(sig0, a, b) & in, select_bits(sig0, b, a) & in);
+            if (valid) store_word_u8(rows, Gm::STRIDE, k, select_bits(sig0, a, b) & in, select_bits(sig0, b, a) & in);
         }
     } else {
 #pragma unroll 1

@@ -36,6 +36,7 @@ struct Geo {
     static constexpr int EW = NW + 2 * G;         // words of an extended string
     static constexpr int NR = L * L;              // lattice rows per replica
     static constexpr int WB = L <= 8 ? 1 : (L <= 16 ? 2 : 4);  // bytes of a bit-packed row
+    static constexpr int STRIDE = (L * L * L + 15) / 16 * 16;  // bytes of a byte row
     static constexpr int TW = 12;                 // table dwords per (colour, word)
     static constexpr uint32_t LAST = NH % 32 ? (1u << (NH % 32)) - 1u : 0xFFFFFFFFu;  // valid bits of the last word
 };
@@ -78,12 +79,14 @@ __device__ __forceinline__ uint32_t funnel(const uint32_t* Ok)
     }
 }
 
-// The per-word tables of words first, first + step, .., built by the calling wave: lanes 0..31 take bit t of word k of colour 0, lanes 32..63
-// the same bit of colour 1, and a ballot of each flag gives the two words at once.  Entries: 0..5
+// The per-word tables of words first, first + step, .., built by the calling wave: lanes 0..31 take
+// bit t of word k of colour 0, lanes 32..63 the same bit of colour 1, and a ballot of each flag gives
+// the two words at once.  Entries: 0..5
 // the coupling masks (bit set where J = -1) of the +x, -x, +y, -y, +z, -z bonds, 6 the sites with
 // x even (sigma = 0), 7 and 8 the first and last site of a row (m = 0, m = L/2 - 1), 9 and 10 the
-// first and last row of a plane (y = 0, y = L - 1), 11 the bits that are sites (b < L^3 / 2).
-template <int L>
+// first and last row of a plane (y = 0, y = L - 1), 11 the bits that are sites (b < L^3 / 2).  Without
+// COUPLINGS (J unused) 0..5 are zero.
+template <int L, bool COUPLINGS = true>
 __device__ void build_tables(const int8_t* J, uint32_t* tab, int lane, int first = 0, int step = 1)
 {
     using Gm = Geo<L>;
@@ -96,12 +99,14 @@ __device__ void build_tables(const int8_t* J, uint32_t* tab, int lane, int first
             const int sg = (c + y + z) & 1, x = 2 * m + sg;
             const int xm = (x + L - 1) % L, ym = (y + L - 1) % L, zm = (z + L - 1) % L;
             const int i = x + L * (y + L * z);
-            f[0] = J[3 * i + 0] < 0;
-            f[1] = J[3 * (xm + L * (y + L * z)) + 0] < 0;
-            f[2] = J[3 * i + 1] < 0;
-            f[3] = J[3 * (x + L * (ym + L * z)) + 1] < 0;
-            f[4] = J[3 * i + 2] < 0;
-            f[5] = J[3 * (x + L * (y + L * zm)) + 2] < 0;
+            if (COUPLINGS) {
+                f[0] = J[3 * i + 0] < 0;
+                f[1] = J[3 * (xm + L * (y + L * z)) + 0] < 0;
+                f[2] = J[3 * i + 1] < 0;
+                f[3] = J[3 * (x + L * (ym + L * z)) + 1] < 0;
+                f[4] = J[3 * i + 2] < 0;
+                f[5] = J[3 * (x + L * (y + L * zm)) + 2] < 0;
+            }
             f[6] = sg == 0;
             f[7] = m == 0;
             f[8] = m == Gm::H2 - 1;
@@ -135,6 +140,97 @@ __device__ __forceinline__ void neighbours(const uint32_t* Ok, const uint32_t* T
     nb[3] = select_bits(yf, funnel<NP - H2, S>(Ok), funnel<-H2, S>(Ok));
     nb[4] = funnel<NP, S>(Ok);
     nb[5] = funnel<-NP, S>(Ok);
+}
+
+// Sites 2 h (ev) and 2 h + 1 (od) of the 32 half-sites h of word k, from the byte rows: 64 bytes of
+// the replica's row as 16-byte pieces (the row has stride bytes, a multiple of 16; pieces past it are
+// zero)
+__device__ __forceinline__ void load_word_u8(const uint8_t* row, int stride, int k, uint32_t* ev, uint32_t* od)
+{
+    uint32_t e = 0, o = 0;
+    uint4 q[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        q[i] = 64 * k + 16 * i < stride ? *reinterpret_cast<const uint4*>(row + 64 * k + 16 * i) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t d[4] = {q[i].x, q[i].y, q[i].z, q[i].w};
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {  // eight sites: even ones in bytes 0, 2 of two dwords
+            e |= pack4(__builtin_amdgcn_perm(d[2 * t + 1], d[2 * t], 0x06040200u)) << (8 * i + 4 * t);
+            o |= pack4(__builtin_amdgcn_perm(d[2 * t + 1], d[2 * t], 0x07050301u)) << (8 * i + 4 * t);
+        }
+    }
+    *ev = e;
+    *od = o;
+}
+
+__device__ __forceinline__ void store_word_u8(uint8_t* row, int stride, int k, uint32_t ev, uint32_t od)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (64 * k + 16 * i >= stride) break;
+        uint32_t d[4];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const uint32_t e = unpack4(ev >> (8 * i + 4 * t)), o = unpack4(od >> (8 * i + 4 * t));
+            d[2 * t] = __builtin_amdgcn_perm(o, e, 0x05010400u);
+            d[2 * t + 1] = __builtin_amdgcn_perm(o, e, 0x07030602u);
+        }
+        *reinterpret_cast<uint4*>(row + 64 * k + 16 * i) = make_uint4(d[0], d[1], d[2], d[3]);
+    }
+}
+
+// The ghost words (and the unused bits of a partial last word) of a string whose length is not a
+// whole number of words (S at the replica's column, Q dwords from word to word), ghost i taken by unit
+// i mod units.  Unit 0 fills the last word before it forms the one ghost word that reads it; no other
+// ghost reads a word that another unit writes, as all come from words of the string.
+template <int L, int Q>
+__device__ __forceinline__ void refresh_ghosts(uint32_t* S, int unit, int units)
+{
+    using Gm = Geo<L>;
+    static_assert(ghosts_in_string<L>(), "ghost words must come from string words");
+    constexpr int G = Gm::G, NW = Gm::NW, last = G + NW - 1;
+    if (unit == 0) {
+        S[last * Q] = select_bits(Gm::LAST, S[last * Q], S[G * Q] << (Gm::NH % 32));
+        constexpr int o = ghost_origin<L>(G - 1), q = G + o / 32;
+        S[(G - 1) * Q] = __builtin_amdgcn_alignbit(S[(q + 1) * Q], S[q * Q], o % 32);
+    }
+    for (int i = unit; i < 2 * G - 1; i += units) {
+        // ghosts 0 .. G - 2 before the string, then those after it
+        const int e = i < G - 1 ? i : NW + i + 1;
+        const int o = i < G - 1 ? Gm::NH - 32 * (G - e) : 32 * (e - G) - Gm::NH;
+        const uint32_t* a = S + (G + (o >> 5)) * Q;
+        S[e * Q] = __builtin_amdgcn_alignbit(a[Q], a[0], o & 31);
+    }
+}
+
+// even and odd bits of a row word of up to 32 bits, as 16-bit numbers
+__device__ __forceinline__ uint32_t split_row(uint32_t v, uint32_t* odd)
+{
+    uint32_t o;
+    const uint32_t e = split_colours(v, &o);
+    *odd = (o | (o >> 8)) & 0xFFFFu;
+    return (e | (e >> 8)) & 0xFFFFu;
+}
+
+__device__ __forceinline__ uint32_t merge_row(uint32_t e, uint32_t o)
+{
+    return merge_colours((e | (e << 8)) & 0x00FF00FFu, (o | (o << 8)) & 0x00FF00FFu);
+}
+
+// lattice row (y, z) of a replica (bit x: the site) from its strings (E0, E1 at word 0 of the string; S
+// dwords from word to word); the word after a string's last one is a ghost word, so it exists
+template <int L, int S>
+__device__ __forceinline__ uint32_t string_row(int y, int z, const uint32_t* E0, const uint32_t* E1)
+{
+    constexpr int H2 = Geo<L>::H2;
+    constexpr uint32_t HM = (1u << H2) - 1u;
+    const int b0 = H2 * (y + L * z), k = b0 >> 5, sh = b0 & 31;
+    const uint32_t c0 = __builtin_amdgcn_alignbit(E0[(k + 1) * S], E0[k * S], sh) & HM;
+    const uint32_t c1 = __builtin_amdgcn_alignbit(E1[(k + 1) * S], E1[k * S], sh) & HM;
+    const bool odd = (y + z) & 1;  // colour 0 takes x = 2 m + (y + z) mod 2
+    return merge_row(odd ? c1 : c0, odd ? c0 : c1);
 }
 
 // the position of a batch's work list that item belongs to
