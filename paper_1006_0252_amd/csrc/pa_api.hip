@@ -153,11 +153,11 @@ int pa_init_couplings(pa_run* runs, int n_runs, const int8_t* const* J_host)
         int st = check_run(runs[r]);
         if (st != PA_OK) return st;
     }
+    int st = upload_ladder((hipStream_t)runs[0].stream);
+    if (st != PA_OK) return st;
+    if (consecutive_runs(runs, n_runs) && n_runs <= 65535) return launch_init(runs, n_runs, J_host, (hipStream_t)runs[0].stream);
     for (int r = 0; r < n_runs; ++r) {
-        hipStream_t s = (hipStream_t)runs[r].stream;
-        int st = upload_ladder(s);
-        if (st != PA_OK) return st;
-        st = launch_init(runs[r], J_host ? J_host[r] : nullptr, s);
+        st = launch_init(&runs[r], 1, J_host ? J_host + r : nullptr, (hipStream_t)runs[r].stream);
         if (st != PA_OK) return st;
     }
     return PA_OK;

@@ -39,23 +39,65 @@ static void philox_host(uint32_t c[4], uint32_t k0, uint32_t k1)
 
 // J_b = sqrt(-2 ln u1) cos(2 pi u2) from Philox(ctr (b, 0, 0, 6), key disorder seed): u1 from
 // the top 27 + 26 bits of words 0, 1 (plus one, so u1 > 0), u2 from words 2, 3
-int gauss_couplings_upload(const pa_run& run, hipStream_t s)
+static void couplings_host(uint64_t seed, std::vector<double>& J)
 {
-    const int64_t B = run.dim == 1 ? run.L : 3 * (int64_t)run.L * run.L * run.L;
-    std::vector<double> J((size_t)B);
-    const uint32_t k0 = (uint32_t)run.disorder_seed, k1 = (uint32_t)(run.disorder_seed >> 32);
-    for (int64_t b = 0; b < B; ++b) {
+    const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+    for (size_t b = 0; b < J.size(); ++b) {
         uint32_t w[4] = {(uint32_t)b, 0u, 0u, 6u};
         philox_host(w, k0, k1);
         const uint64_t m1 = ((uint64_t)(w[0] >> 5) << 26) | (uint64_t)(w[1] >> 6);
         const uint64_t m2 = ((uint64_t)(w[2] >> 5) << 26) | (uint64_t)(w[3] >> 6);
         const double u1 = ldexp((double)(m1 + 1), -53);
         const double u2 = ldexp((double)m2, -53);
-        J[(size_t)b] = sqrt(-2.0 * log(u1)) * cos(6.283185307179586 * u2);
+        J[b] = sqrt(-2.0 * log(u1)) * cos(6.283185307179586 * u2);
     }
-    // synchronous: the host vector is released on return
-    if (hipMemcpyAsync(run.J, J.data(), (size_t)B * 8, hipMemcpyHostToDevice, s) != hipSuccess) return PA_ERR_HIP;
-    return hip_status(hipStreamSynchronize(s));
+}
+
+// the couplings of run blockIdx.y from those of run src.run[blockIdx.y] (the same realization)
+__global__ void __launch_bounds__(256) k_copy_couplings(pa_state* base, BatchOrder src)
+{
+    const pa_state* st = base + blockIdx.y;
+    const int from = src.run[blockIdx.y];
+    if (from == (int)blockIdx.y) return;
+    const double* a = reinterpret_cast<const double*>(base[from].J);
+    double* b = reinterpret_cast<double*>(st->J);
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < st->n_bonds; i += gridDim.x * blockDim.x) b[i] = a[i];
+}
+
+// Couplings of n runs with consecutive states, the states already written on s.  Up to kMaxBatch runs at
+// a time, a realization that several of them share is drawn and uploaded once (for its first run) and
+// copied on the device for the others.
+int gauss_couplings_upload(const pa_run* runs, int n, hipStream_t s)
+{
+    for (int r0 = 0; r0 < n; r0 += kMaxBatch) {
+        const int m = n - r0 < kMaxBatch ? n - r0 : kMaxBatch;
+        const pa_run* q = runs + r0;
+        BatchOrder src;
+        std::vector<std::vector<double>> J;
+        J.reserve((size_t)m);
+        int64_t most = 0;
+        bool copies = false;
+        for (int r = 0; r < m; ++r) {
+            int from = 0;
+            while (from < r && !(src.run[from] == from && q[from].L == q[r].L && q[from].disorder_seed == q[r].disorder_seed)) ++from;
+            src.run[r] = (uint16_t)from;
+            const int64_t B = q[r].dim == 1 ? q[r].L : 3 * (int64_t)q[r].L * q[r].L * q[r].L;
+            most = B > most ? B : most;
+            if (from != r) {
+                copies = true;
+                continue;
+            }
+            J.emplace_back((size_t)B);
+            couplings_host(q[r].disorder_seed, J.back());
+            if (hipMemcpyAsync(q[r].J, J.back().data(), (size_t)B * 8, hipMemcpyHostToDevice, s) != hipSuccess) return PA_ERR_HIP;
+        }
+        if (copies)
+            hipLaunchKernelGGL(k_copy_couplings, dim3((unsigned)((most + 255) / 256), (unsigned)m), dim3(256), 0, s,
+                               runs[r0].state, src);
+        // the host vectors are released on return
+        if (hipStreamSynchronize(s) != hipSuccess) return PA_ERR_HIP;
+    }
+    return PA_OK;
 }
 
 // ------------------------------------------------------------------ device helpers
@@ -87,13 +129,14 @@ __device__ double energy_gauss(const pa_state* st, const uint8_t* s)
     return E;
 }
 
-// thread per replica
-__global__ void __launch_bounds__(64) k_energy_gauss(const pa_state* __restrict__ st, int buf, int64_t n)
+// thread per replica of the current population
+__global__ void __launch_bounds__(64) k_energy_gauss(const pa_state* __restrict__ base)
 {
+    const pa_state* st = base + blockIdx.y;
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    const uint8_t* s = (const uint8_t*)st->spins[buf] + r * st->row_stride;
-    reinterpret_cast<double*>(st->energy[buf])[r] = energy_gauss(st, s);
+    if (r >= st->R) return;
+    const uint8_t* s = (const uint8_t*)st->spins[st->cur] + r * st->row_stride;
+    reinterpret_cast<double*>(st->energy[st->cur])[r] = energy_gauss(st, s);
 }
 
 // N_S checkerboard sweeps of one replica per thread; the draws are those of the +-1 path
@@ -805,13 +848,6 @@ __global__ void __launch_bounds__(256) k_moments_gauss(pa_state* base)
 }
 
 // ------------------------------------------------------------------ launchers
-int launch_energy_gauss(const pa_run& run, int buf, int64_t n, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_energy_gauss, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, s, (const pa_state*)run.state,
-                       buf, n);
-    return hip_status(hipGetLastError());
-}
-
 // n runs of one shape with consecutive states from base on stream s; cap the largest capacity
 struct GaussLaunch {
     pa_state* base;
@@ -842,14 +878,14 @@ static void launch_gauss_table(int N, const GaussLaunch& a, double beta)
 template <int L>
 static int launch_gauss_cube(const GaussLaunch& a, const pa_step& step)
 {
-    launch_gauss_table<6, L>(L * L * L, a, step.beta_to);
+    if (step.n_sweeps > 0) launch_gauss_table<6, L>(L * L * L, a, step.beta_to);
     constexpr int NWV = L == 4 ? 1 : 4;  // (side 4: one word per colour)
     return launch_gauss_sweep<NWV>(k_sweep_gauss_cube<L, NWV>, 0, a, step);
 }
 
 static int launch_gauss_chain(int N, const GaussLaunch& a, const pa_step& step)
 {
-    launch_gauss_table<2, 0>(N, a, step.beta_to);
+    if (step.n_sweeps > 0) launch_gauss_table<2, 0>(N, a, step.beta_to);
     switch (gauss_calls(N)) {
         case 1: return launch_gauss_sweep<1>(k_sweep_gauss_short<1>, 0, a, step);
         case 2: return launch_gauss_sweep<1>(k_sweep_gauss_short<2>, 0, a, step);
@@ -899,6 +935,26 @@ int launch_sweep_gauss(const pa_run* runs, int n_runs, bool consecutive, const p
         case 14: return launch_gauss_cube<14>(a, step);
         default: return launch_gauss_cube<16>(a, step);
     }
+}
+
+// energies of the current populations of n runs with consecutive states: the tabled kernels with no
+// sweeps, which hold 64 replicas' spins in LDS (one thread per replica over byte rows took 156 us for
+// 2000 replicas of side 8, whatever the number of runs), one thread per replica past their shapes
+int launch_energy_gauss(const pa_run* runs, int n, hipStream_t s)
+{
+    bool tab = true;
+    int64_t cap = 0;
+    for (int r = 0; r < n; ++r) {
+        tab = tab && gauss_tab_shape(runs[r].dim, runs[r].L) && runs[r].L == runs[0].L;
+        cap = runs[r].capacity > cap ? runs[r].capacity : cap;
+    }
+    if (tab) {
+        pa_step none = {};
+        return launch_sweep_gauss(runs, n, true, none, s);
+    }
+    hipLaunchKernelGGL(k_energy_gauss, dim3((unsigned)((cap + 63) / 64), (unsigned)n), dim3(64), 0, s,
+                       (const pa_state*)runs[0].state);
+    return hip_status(hipGetLastError());
 }
 
 int launch_moments_gauss(const pa_run* runs, int n, hipStream_t s)

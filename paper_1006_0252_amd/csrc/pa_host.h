@@ -6,7 +6,9 @@
 namespace pa {
 
 // host launch helpers (defined in the .hip files)
-int launch_init(const pa_run& run, const int8_t* J_host, hipStream_t s);
+// initialise n runs with consecutive states on one stream, of one dim, layout and coupling kind (any sizes)
+int launch_init(const pa_run* runs, int n, const int8_t* const* J_host, hipStream_t s);
+int launch_init_group(int L, int layout, pa_state* base, const BatchOrder& order, int n, int64_t cap, hipStream_t s);
 int launch_sweep(const pa_run& run, const pa_step& step, hipStream_t s);
 // n > 1 chain runs (dim 1) with consecutive states, one length and layout, one stream
 int launch_sweep_chain_batch(const pa_run* runs, int n, const pa_step& step, hipStream_t s);
@@ -41,8 +43,8 @@ int launch_rho(const pa_run* runs, int n, const double* args, int n_args, int mo
 int upload_ladder(hipStream_t s);
 
 // Gaussian-coupling path (separate kernels; n > 1 runs: consecutive states on one stream)
-int gauss_couplings_upload(const pa_run& run, hipStream_t s);
-int launch_energy_gauss(const pa_run& run, int buf, int64_t n_replicas, hipStream_t s);
+int gauss_couplings_upload(const pa_run* runs, int n, hipStream_t s);
+int launch_energy_gauss(const pa_run* runs, int n, hipStream_t s);
 // consecutive: the runs' states are consecutive and share runs[0].stream (one launch for all)
 int launch_sweep_gauss(const pa_run* runs, int n_runs, bool consecutive, const pa_step& step, hipStream_t s);
 int launch_resample_gauss(const pa_run* runs, int n, const pa_step& step, hipStream_t s);

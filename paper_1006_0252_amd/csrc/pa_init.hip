@@ -1,7 +1,10 @@
 // Run initialisation (Sec. II: R0 replicas at beta = 0, each uniform over the 2^N
 // microstates; couplings +-1 from the disorder seed; energies E = + sum J s s).
 #include <math.h>
+#include <stddef.h>
 #include <string.h>
+
+#include <algorithm>
 
 #include "pa_common.h"
 #include "pa_host.h"
@@ -9,22 +12,40 @@
 
 namespace pa {
 
-__global__ void k_write_state(pa_state* st, pa_state init) { *st = init; }
+// All kernels here take runs with consecutive states (grid.y = run), so a batch is initialised by a few
+// launches: one per kernel and run took 5 to 10 us each, the runs one after the other (256 runs of the
+// mixed batch: 26 ms of 128; 200 rings: 5 ms of a 10 ms pass).
+
+// the host's states by value, as many as fit a kernel's arguments
+constexpr int kStatesPerLaunch = 12;
+struct StateChunk {
+    pa_state s[kStatesPerLaunch];
+};
+
+__global__ void __launch_bounds__(64) k_write_states(pa_state* base, StateChunk c)
+{
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(&c.s[blockIdx.x]);
+    reinterpret_cast<uint32_t*>(base + blockIdx.x)[threadIdx.x] = src[threadIdx.x];
+}
 
 // J_b = -1 iff bit (b mod 128) of Philox(ctr (b/128, 0, 0, 5), key disorder seed) is set
-__global__ void k_couplings(int8_t* J, int n_bonds, uint32_t k0, uint32_t k1)
+__global__ void __launch_bounds__(256) k_couplings(const pa_state* __restrict__ base)
 {
+    const pa_state* st = base + blockIdx.y;
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= n_bonds) return;
-    const uint4v v = philox10((uint32_t)(b >> 7), 0u, 0u, kTagCoupling, k0, k1);
+    if (b >= st->n_bonds) return;
+    const uint4v v = philox10((uint32_t)(b >> 7), 0u, 0u, kTagCoupling, (uint32_t)st->disorder_seed,
+                              (uint32_t)(st->disorder_seed >> 32));
     const uint32_t bit = (word_of(v, (b & 127) >> 5) >> (b & 31)) & 1u;
-    J[b] = bit ? (int8_t)-1 : (int8_t)1;
+    st->J[b] = bit ? (int8_t)-1 : (int8_t)1;
 }
 
 // u8: thread per (replica, 16 consecutive sites); spin i of replica r is bit (i mod 128)
 // of Philox(ctr (i/128, r, 0, 1), key seed)
-__global__ void k_init_u8(const pa_state* __restrict__ st, uint32_t k0, uint32_t k1)
+__global__ void __launch_bounds__(256) k_init_u8(const pa_state* __restrict__ base)
 {
+    const pa_state* st = base + blockIdx.y;
+    const uint32_t k0 = (uint32_t)st->seed, k1 = (uint32_t)(st->seed >> 32);
     const int N = st->N, stride = st->row_stride;
     const int per_row = stride / 16;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -57,8 +78,10 @@ __device__ inline uint32_t load_row(const pa_state* st, int buf, int64_t r, int 
     return ((const uint32_t*)base)[idx];
 }
 
-__global__ void __launch_bounds__(256) k_init_bits64(const pa_state* __restrict__ st, uint32_t k0, uint32_t k1)
+__global__ void __launch_bounds__(256) k_init_bits64(const pa_state* __restrict__ states)
 {
+    const pa_state* st = states + blockIdx.y;
+    const uint32_t k0 = (uint32_t)st->seed, k1 = (uint32_t)(st->seed >> 32);
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= st->capacity) return;
     const bool valid = r < st->R0;
@@ -94,8 +117,9 @@ __global__ void __launch_bounds__(256) k_init_bits64(const pa_state* __restrict_
 }
 
 // u8 energies: one wave per replica, lanes over sites, each site owns its + bonds
-__global__ void __launch_bounds__(256) k_energy_u8(const pa_state* __restrict__ st, int buf)
+__global__ void __launch_bounds__(256) k_energy_u8(const pa_state* __restrict__ base, int buf)
 {
+    const pa_state* st = base + blockIdx.y;
     const int N = st->N, L = st->L, dim = st->dim, stride = st->row_stride;
     const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -120,8 +144,9 @@ __global__ void __launch_bounds__(256) k_energy_u8(const pa_state* __restrict__ 
 }
 
 // bit-packed energies: thread per replica, E = n_bonds - 2 * (bonds with J s s = -1)
-__global__ void __launch_bounds__(256) k_energy_bits64(const pa_state* __restrict__ st, int buf)
+__global__ void __launch_bounds__(256) k_energy_bits64(const pa_state* __restrict__ base, int buf)
 {
+    const pa_state* st = base + blockIdx.y;
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int L = st->L;
     const int NR = n_rows_of(st);
@@ -170,31 +195,29 @@ __global__ void __launch_bounds__(256) k_energy_bits64(const pa_state* __restric
 
 // record[0] and the energy base E_base = -n_bonds + ((E_0 + n_bonds) mod 4): every energy
 // of a +-1 realisation has the residue of E_0 mod 4 (each flip changes E by 4c - 2z)
-__global__ void k_init_finish(pa_state* st)
+__global__ void __launch_bounds__(256) k_init_finish(pa_state* base)
 {
+    pa_state* st = base + blockIdx.y;
+    // record[0] is the first 16 doubles
+    const int64_t n = (int64_t)st->n_records * (int)(sizeof(pa_record) / sizeof(double));
+    double* d = reinterpret_cast<double*>(st->record);
+    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
+        double v = 0.0;
+        if (i == offsetof(pa_record, minus_betaF) / sizeof(double)) v = st->ln_omega;
+        if (i == offsetof(pa_record, R) / sizeof(double)) v = (double)st->R;
+        d[i] = v;
+    }
+    if (threadIdx.x != 0) return;
     const int B = st->n_bonds;
     if (st->couplings != PA_GAUSS) {
         const int E0 = st->energy[0][0];
         st->E_base = -B + (((E0 + B) % 4) + 4) % 4;
     }
-    for (int k = 0; k < st->n_records; ++k) {
-        pa_record* rec = st->record + k;
-        double* d = reinterpret_cast<double*>(rec);
-        for (int j = 0; j < (int)(sizeof(pa_record) / sizeof(double)); ++j) d[j] = 0.0;
-    }
-    pa_record* r0 = st->record;
-    r0->beta = 0.0;
-    r0->lnQ = 0.0;
-    r0->minus_betaF = st->ln_omega;
-    r0->R = (double)st->R;
     st->initialised = 1;
 }
 
-int launch_init(const pa_run& run, const int8_t* J_host, hipStream_t s)
+static pa_state host_state(const pa_run& run, const pa_sizes& sz)
 {
-    pa_sizes sz;
-    int rc = pa_buffer_sizes(run.dim, run.L, run.layout, run.couplings, run.capacity, run.n_records, &sz);
-    if (rc != PA_OK) return rc;
     pa_state h;
     memset(&h, 0, sizeof(h));
     h.dim = run.dim;
@@ -221,50 +244,95 @@ int launch_init(const pa_run& run, const int8_t* J_host, hipStream_t s)
     h.n_records = run.n_records;
     h.R = run.R0;
     h.R_new = run.R0;
-    h.cur = 0;
-    h.status = 0;
-    h.k = 0;
-    h.acc = 0.0;
     h.ln_omega = (double)sz.N * log(2.0);
-    h.beta = 0.0;
-    h.initialised = 0;
     h.couplings = run.couplings;
-    hipLaunchKernelGGL(k_write_state, dim3(1), dim3(1), 0, s, run.state, h);
+    return h;
+}
 
-    const uint32_t s0 = (uint32_t)run.seed, s1 = (uint32_t)(run.seed >> 32);
-    if (run.couplings == PA_GAUSS) {
+int launch_init(const pa_run* runs, int n, const int8_t* const* J_host, hipStream_t s)
+{
+    pa_state* base = runs[0].state;
+    const bool gauss = runs[0].couplings == PA_GAUSS;
+    const int layout = runs[0].layout;
+    // one launch covers the largest run of the call
+    int64_t cap = 0, R0 = 0, bonds = 0, stride = 0;
+    bool all_given = J_host != nullptr;
+    for (int r = 0; r < n; ++r) {
+        pa_sizes sz;
+        const int rc = pa_buffer_sizes(runs[r].dim, runs[r].L, layout, runs[r].couplings, runs[r].capacity, runs[r].n_records, &sz);
+        if (rc != PA_OK) return rc;
+        cap = std::max(cap, runs[r].capacity);
+        R0 = std::max(R0, runs[r].R0);
+        bonds = std::max(bonds, sz.n_bonds);
+        stride = std::max(stride, sz.row_stride);
+        const int8_t* J = J_host ? J_host[r] : nullptr;
+        all_given = all_given && J;
+        if (J) {
+            if (gauss) return PA_ERR_ARG;
+            for (int64_t b = 0; b < sz.n_bonds; ++b)
+                if (J[b] != 1 && J[b] != -1) return PA_ERR_ARG;
+        }
+    }
+    for (int r0 = 0; r0 < n; r0 += kStatesPerLaunch) {
+        StateChunk c;
+        const int m = std::min(kStatesPerLaunch, n - r0);
+        memset(&c, 0, sizeof(c));
+        for (int i = 0; i < m; ++i) {
+            pa_sizes sz;
+            const pa_run& run = runs[r0 + i];
+            pa_buffer_sizes(run.dim, run.L, layout, run.couplings, run.capacity, run.n_records, &sz);
+            c.s[i] = host_state(run, sz);
+        }
+        hipLaunchKernelGGL(k_write_states, dim3((unsigned)m), dim3(64), 0, s, base + r0, c);
+    }
+    const unsigned ny = (unsigned)n;
+    const dim3 g_u8((unsigned)((R0 * (stride / 16) + 255) / 256), ny);
+    if (gauss) {
         // couplings from the host (libm), then spins as for +-1 couplings and FP64 energies
-        if (J_host) return PA_ERR_ARG;
-        rc = gauss_couplings_upload(run, s);
+        int rc = gauss_couplings_upload(runs, n, s);
         if (rc != PA_OK) return rc;
-        const int64_t threads = run.R0 * (sz.row_stride / 16);
-        hipLaunchKernelGGL(k_init_u8, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, run.state, s0, s1);
-        rc = launch_energy_gauss(run, 0, run.R0, s);
+        hipLaunchKernelGGL(k_init_u8, g_u8, dim3(256), 0, s, base);
+        rc = launch_energy_gauss(runs, n, s);
         if (rc != PA_OK) return rc;
-        hipLaunchKernelGGL(k_init_finish, dim3(1), dim3(1), 0, s, run.state);
+        hipLaunchKernelGGL(k_init_finish, dim3(1, ny), dim3(256), 0, s, base);
         return hip_status(hipGetLastError());
     }
-
-    const int B = (int)sz.n_bonds;
-    if (J_host) {
-        for (int b = 0; b < B; ++b)
-            if (J_host[b] != 1 && J_host[b] != -1) return PA_ERR_ARG;
-        if (hipMemcpyAsync(run.J, J_host, (size_t)B, hipMemcpyHostToDevice, s) != hipSuccess) return PA_ERR_HIP;
-    } else {
-        hipLaunchKernelGGL(k_couplings, dim3((B + 255) / 256), dim3(256), 0, s, run.J, B,
-                           (uint32_t)run.disorder_seed, (uint32_t)(run.disorder_seed >> 32));
+    if (!all_given) hipLaunchKernelGGL(k_couplings, dim3((unsigned)((bonds + 255) / 256), ny), dim3(256), 0, s, base);
+    for (int r = 0; J_host && r < n; ++r) {
+        if (!J_host[r]) continue;
+        const int64_t B = runs[r].dim == 1 ? runs[r].L : 3 * (int64_t)runs[r].L * runs[r].L * runs[r].L;
+        if (hipMemcpyAsync(runs[r].J, J_host[r], (size_t)B, hipMemcpyHostToDevice, s) != hipSuccess) return PA_ERR_HIP;
     }
-    const uint32_t k0 = (uint32_t)run.seed, k1 = (uint32_t)(run.seed >> 32);
-    if (run.layout == PA_U8) {
-        const int64_t threads = run.R0 * (sz.row_stride / 16);
-        hipLaunchKernelGGL(k_init_u8, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, run.state, k0, k1);
-        hipLaunchKernelGGL(k_energy_u8, dim3((unsigned)((run.R0 + 3) / 4)), dim3(256), 0, s, run.state, 0);
+    // cubes the group kernel takes: spins and energies in one pass, one launch per side; when the call
+    // holds any other run, every run draws its spins and then sums its energies from them
+    bool group = n <= kMaxBatch;
+    for (int r = 0; r < n; ++r) group = group && group_sweep_supported(runs[r].dim, runs[r].L);
+    if (group) {
+        bool done[33] = {};
+        for (int r = 0; r < n; ++r) {
+            const int L = runs[r].L;
+            if (done[L]) continue;
+            done[L] = true;
+            BatchOrder order;
+            int m = 0;
+            int64_t capL = 0;
+            for (int q = r; q < n; ++q) {
+                if (runs[q].L != L) continue;
+                order.run[m++] = (uint16_t)q;
+                capL = std::max(capL, runs[q].capacity);
+            }
+            const int rc = launch_init_group(L, layout, base, order, m, capL, s);
+            if (rc != PA_OK) return rc;
+        }
+    } else if (layout == PA_U8) {
+        hipLaunchKernelGGL(k_init_u8, g_u8, dim3(256), 0, s, base);
+        hipLaunchKernelGGL(k_energy_u8, dim3((unsigned)((R0 + 3) / 4), ny), dim3(256), 0, s, base, 0);
     } else {
-        const unsigned blocks = (unsigned)((run.capacity + 255) / 256);
-        hipLaunchKernelGGL(k_init_bits64, dim3(blocks), dim3(256), 0, s, run.state, k0, k1);
-        hipLaunchKernelGGL(k_energy_bits64, dim3(blocks), dim3(256), 0, s, run.state, 0);
+        const dim3 g((unsigned)((cap + 255) / 256), ny);
+        hipLaunchKernelGGL(k_init_bits64, g, dim3(256), 0, s, base);
+        hipLaunchKernelGGL(k_energy_bits64, g, dim3(256), 0, s, base, 0);
     }
-    hipLaunchKernelGGL(k_init_finish, dim3(1), dim3(1), 0, s, run.state);
+    hipLaunchKernelGGL(k_init_finish, dim3(1, ny), dim3(256), 0, s, base);
     return hip_status(hipGetLastError());
 }
 

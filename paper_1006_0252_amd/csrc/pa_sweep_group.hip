@@ -127,8 +127,23 @@ __device__ __forceinline__ void store_row_bits(uint8_t* base, int r, const uint3
     else *(uint32_t*)a = v;
 }
 
-// N_S sweeps of the Q replicas from r0 on of one run by the group's waves
-template <int L, int MODE, int LAYOUT, int LPR>
+// the initial spins of word k's sites 2 h (ev) and 2 h + 1 (od): 64 consecutive bits of the replica's
+// stream, half of a call
+__device__ __forceinline__ void init_word(int k, uint32_t r, bool valid, uint32_t k0, uint32_t k1, uint32_t* ev,
+                                          uint32_t* od)
+{
+    const uint4v v = philox10((uint32_t)(k >> 1), r, 0u, kTagInit, k0, k1);
+    const uint32_t lo = valid ? ((k & 1) ? v.z : v.x) : 0u, hi = valid ? ((k & 1) ? v.w : v.y) : 0u;
+    uint32_t o_lo, o_hi;
+    const uint32_t e_lo = split_row(lo, &o_lo), e_hi = split_row(hi, &o_hi);
+    *ev = e_lo | (e_hi << 16);
+    *od = o_lo | (o_hi << 16);
+}
+
+// N_S sweeps of the Q replicas from r0 on of one run by the group's waves.  INIT: no sweeps; the spins
+// are the run's initial draws instead of loads (spin i of replica r is bit i mod 128 of Philox(ctr
+// (i / 128, r, 0, 1), key seed); zero past R), and in the bit-packed layout the whole group is stored.
+template <int L, int MODE, int LAYOUT, int LPR, bool INIT = false>
 __device__ __forceinline__ void sweep_shared(const pa_state* st, int64_t r0, int wave, GroupSmem<L, LPR>& sm,
                                              const uint2* tt, const SweepParams& p, const Thr& th)
 {
@@ -142,6 +157,18 @@ __device__ __forceinline__ void sweep_shared(const pa_state* st, int64_t r0, int
         if constexpr (NWV == 1) wave_sync();
         else __syncthreads();
     };
+    if constexpr (INIT && LAYOUT == PA_BITS64) {
+        if (r0 >= st->R) {  // the same for the whole group
+            uint8_t* a = (uint8_t*)st->spins[0] + ((r0 >> 6) * Gm::NR * 64 + (r0 & 63) + q) * Gm::WB;
+            for (int i = unit; i < Gm::NR; i += UNITS) {
+                uint8_t* w = a + (int64_t)i * 64 * Gm::WB;
+                if (Gm::WB == 1) *w = 0;
+                else if (Gm::WB == 2) *(uint16_t*)w = 0;
+                else *(uint32_t*)w = 0;
+            }
+            return;
+        }
+    }
     if (wave == 0 && lane < Q) sm.neg[lane] = 0;
     build_tables<L>(st->J, sm.tab, lane, wave, NWV);
     uint32_t* E0 = sm.E + q;
@@ -162,7 +189,8 @@ __device__ __forceinline__ void sweep_shared(const pa_state* st, int64_t r0, int
 #pragma unroll 1
     for (int k = unit; k < NW; k += UNITS) {
         uint32_t ev, od;
-        if constexpr (LAYOUT == PA_U8) load_word_u8(rows, Gm::STRIDE, k, &ev, &od);
+        if constexpr (INIT) init_word(k, (uint32_t)r, valid, (uint32_t)st->seed, (uint32_t)(st->seed >> 32), &ev, &od);
+        else if constexpr (LAYOUT == PA_U8) load_word_u8(rows, Gm::STRIDE, k, &ev, &od);
         else load_word_bits<L>(rows, k, &ev, &od);
         const uint32_t sig0 = sm.tab[k * TW + 6], in = sm.tab[k * TW + 11];  // colour 0: x even, sites
         put(E0, k, select_bits(sig0, ev, od) & in);
@@ -179,7 +207,7 @@ __device__ __forceinline__ void sweep_shared(const pa_state* st, int64_t r0, int
     c.rr = (uint32_t)r;
     c.k0 = (uint32_t)st->seed;
     c.k1 = (uint32_t)(st->seed >> 32);
-    for (int s = 0; s < p.n_sweeps; ++s) {
+    for (int s = 0; s < (INIT ? 0 : p.n_sweeps); ++s) {
         for (int col = 0; col < 2; ++col) {
             c.ctr2 = (uint32_t)(2 * (p.t0 + s) + col);
             uint32_t* W = col ? E1 : E0;
@@ -242,7 +270,7 @@ __device__ __forceinline__ void sweep_shared(const pa_state* st, int64_t r0, int
     } else {
 #pragma unroll 1
         for (int i = unit; i < Gm::NR; i += UNITS)
-            if (valid) store_row_bits<L, Q>(rows, i, E0 + G * Q, E1 + G * Q);
+            if (valid || INIT) store_row_bits<L, Q>(rows, i, E0 + G * Q, E1 + G * Q);
     }
     sync();
     if (wave == 0 && lane < Q && valid) st->energy[st->cur][r] = st->n_bonds - 2 * (int)sm.neg[lane];
@@ -302,6 +330,32 @@ __global__ void __launch_bounds__(threads_of(L, LPR)) k_sweep_group_batch(pa_sta
     sweep_shared<L, MODE, LAYOUT, LPR>(st, r0, wave, sm.g[gi], sm.tt, p, th);
 }
 
+// Initial population and energies of runs of one side (grid.y: position in order), written once: drawing
+// the rows and then reading them back per bond took 1.3 ms at L = 16, 10^6 replicas, this 0.4 ms.
+template <int L, int LAYOUT>
+__global__ void __launch_bounds__(threads_of(L, always_split(L) ? 4 : 1)) k_init_group(pa_state* base, BatchOrder order)
+{
+    constexpr int LPR = always_split(L) ? 4 : 1;
+    __shared__ BlockSmem<L, LPR> sm;
+    const pa_state* st = base + order.run[blockIdx.y];
+    int gi, wave;
+    place<L, LPR>(&gi, &wave);
+    const int64_t r0 = ((int64_t)blockIdx.x * groups_of(L, LPR) + gi) * (64 / LPR);
+    // (a wave that leaves alone is a whole group and meets no barrier)
+    if (r0 >= (LAYOUT == PA_U8 ? st->R : st->capacity)) return;
+    sweep_shared<L, 2, LAYOUT, LPR, true>(st, r0, wave, sm.g[gi], sm.tt, SweepParams{}, Thr{});
+}
+
+template <int L>
+static void launch_init(pa_state* base, const BatchOrder& order, int n, int64_t cap, int layout, hipStream_t s)
+{
+    constexpr int LPR = always_split(L) ? 4 : 1;
+    const int64_t per_block = 64 / LPR * groups_of(L, LPR);
+    const dim3 g((unsigned)((cap + per_block - 1) / per_block), (unsigned)n), b(threads_of(L, LPR));
+    if (layout == PA_U8) hipLaunchKernelGGL((k_init_group<L, PA_U8>), g, b, 0, s, base, order);
+    else hipLaunchKernelGGL((k_init_group<L, PA_BITS64>), g, b, 0, s, base, order);
+}
+
 struct Launch {
     const pa_run* run;   // one run, or
     pa_state* base;      // the states of a batch with positions pos0 .. pos1 - 1 of order
@@ -357,6 +411,19 @@ static int dispatch(int L, int layout, const Launch& a, const SweepParams& p, hi
 }
 
 }  // namespace group
+
+// initial spins and energies of the n runs order.run[0 ..] of side L (cap: their largest capacity)
+int launch_init_group(int L, int layout, pa_state* base, const BatchOrder& order, int n, int64_t cap, hipStream_t s)
+{
+#define PA_INIT_L(LL) \
+    case LL: group::launch_init<LL>(base, order, n, cap, layout, s); return PA_OK;
+    switch (L) {
+        PA_INIT_L(4) PA_INIT_L(6) PA_INIT_L(8) PA_INIT_L(10) PA_INIT_L(12) PA_INIT_L(14) PA_INIT_L(16) PA_INIT_L(18)
+        PA_INIT_L(20) PA_INIT_L(24)
+        default: return PA_ERR_ARG;
+    }
+#undef PA_INIT_L
+}
 
 int launch_sweep_group(const pa_run& run, const SweepParams& p, hipStream_t s)
 {

@@ -66,3 +66,26 @@ def test_batch_of_every_form(layout):
         solo.sweep(step)
         assert np.array_equal(b.energies(), solo.energies())
         assert np.array_equal(b.population()[0], solo.population()[0])
+
+
+@pytest.mark.parametrize("layout", ["u8", "bits64"])
+@pytest.mark.parametrize("shapes", [[(3, 4, 70), (3, 18, 20), (3, 4, 1), (3, 20, 17)], [(3, 2, 70), (3, 6, 65)],
+                                    [(1, 40, 70), (1, 64, 3)]])
+def test_batch_initial_populations(shapes, layout):
+    """couplings, spins, energies and records of a batch initialised at once: sides of the group kernel,
+    a call that holds another side, and chains; one run's couplings given"""
+    print(f"[case] batch init {shapes} {layout}", flush=True)
+    specs = [dict(dim=d, L=L, R0=R0, seed=50 + i, disorder_seed=i) for i, (d, L, R0) in enumerate(shapes)]
+    batch = pa.Batch(specs, 3, layout=layout, device=DEV)
+    J_given = 1 - 2 * (np.arange(batch.runs[1].n_bonds) % 3 == 0).astype(np.int8)
+    for given in (False, True):
+        J_list = [np.ascontiguousarray(o.couplings(sp["dim"], sp["L"], sp["disorder_seed"]), np.int8) for sp in specs]
+        J_list[1] = J_given if given else J_list[1]
+        batch.init(J_list if given else None)
+        for sp, J, run in zip(specs, J_list, batch.runs):
+            assert np.array_equal(run.couplings(), J)
+            s, E = run.population()
+            s_o, E_o = o.init_replicas(sp["dim"], sp["L"], J, sp["seed"], 0, sp["R0"])
+            assert np.array_equal(s, s_o) and np.array_equal(E, E_o)
+            rec = run.records()
+            assert rec[0, 4] == sp["R0"] and rec[0, 2] == run.N * np.log(2.0) and not rec[1:].any()
