@@ -12,6 +12,7 @@ int launch_init_group(int L, int layout, pa_state* base, const BatchOrder& order
 int launch_sweep(const pa_run& run, const pa_step& step, hipStream_t s);
 // n > 1 chain runs (dim 1) with consecutive states, one length and layout, one stream
 int launch_sweep_chain_batch(const pa_run* runs, int n, const pa_step& step, hipStream_t s);
+bool launch_sweep_chain(int N, int layout, const pa_state* base, int n, int64_t cap, const SweepParams& p, hipStream_t s);
 int launch_sweep_fast(const pa_run& run, const SweepParams& p, int lpr, int wpb, hipStream_t s);
 // the group kernel (cube sides 4 to 20 and 24, both layouts): one run, or a group of equal-L runs of a
 // batch (items, groups: 64-replica groups of the runs' capacities and of their target sizes)

@@ -528,6 +528,8 @@ int launch_sweep(const pa_run& run, const pa_step& step, hipStream_t s)
         return hip_status(hipGetLastError());
     }
     if (run.dim == 1) {
+        if (!g_override.lpr && launch_sweep_chain(run.L, run.layout, run.state, 1, run.capacity, p, s))
+            return hip_status(hipGetLastError());
         const int NR = (run.L + 31) / 32;
         if (cfg.lpr > NR) cfg.lpr = 1;
         if (cfg.lpr > 2) cfg.lpr = 2;
@@ -567,6 +569,8 @@ int launch_sweep_chain_batch(const pa_run* runs, int n, const pa_step& step, hip
     if (cfg.lpr > 2) cfg.lpr = 2;
     int64_t cap = 0;
     for (int r = 0; r < n; ++r) cap = runs[r].capacity > cap ? runs[r].capacity : cap;
+    if (!g_override.lpr && launch_sweep_chain(runs[0].L, runs[0].layout, runs[0].state, n, cap, p, s))
+        return hip_status(hipGetLastError());
     const int st = launch1(runs[0], p, cfg, zero, s, n, cap);
     if (st != PA_OK) return st;
     return hip_status(hipGetLastError());

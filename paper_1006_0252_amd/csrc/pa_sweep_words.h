@@ -251,7 +251,8 @@ static __device__ __noinline__ uint32_t resolve_zero_bytes(uint32_t bytes, uint3
 
 // The Metropolis decision for the 32 sites of word w with bond classes c0, c1, c2 (c2 set: a
 // candidate, c >= 4; clear: flips outright); returns the new word.  MODE 0: bounds from the
-// 256-entry table tt; MODE 2: every top zero.  UNIFORM_CALLS: call0 is the same over the wave
+// 256-entry table tt; MODE 1: one bound, that of c = 4, for every candidate (chains); MODE 2: every top
+// zero.  UNIFORM_CALLS: call0 is the same over the wave
 // (philox10_lane keeps the uniform rounds on the scalar unit).  ws_fn() gives the word's WordSites
 // (only the rare tie paths need them).  NBYTES < 4: only bytes 0 .. NBYTES - 1 hold sites (the last
 // word of a string); the other bytes' calls are not drawn and their bits come out as non-candidates
@@ -295,6 +296,7 @@ __device__ __forceinline__ uint32_t decide_word(uint32_t w, uint32_t c0, uint32_
         // c1 in the high one
         const uint32_t cl = select_bits(0x0F0F0F0Fu, c0, c1 << 4);
         const uint32_t ch = select_bits(0x0F0F0F0Fu, c0 >> 4, c1);
+        const uint32_t one = (th.thi4 + 1u) * 0x00010001u;
         // outcomes: byte i's Philox word j (sites 2 j, 2 j + 1) at 2 j + 8 (i & 1) and 16 higher,
         // bytes 0, 1 in ra and bytes 2, 3 in rb
         uint32_t ra = 0, rb = 0;
@@ -303,7 +305,8 @@ __device__ __forceinline__ uint32_t decide_word(uint32_t w, uint32_t c0, uint32_
             const uint4v v = UNIFORM_CALLS ? philox10_lane(call0 + call_step * i, c.rr, c.ctr2, kTagMet, c.k0, c.k1)
                                            : philox10(call0 + call_step * i, c.rr, c.ctr2, kTagMet, c.k0, c.k1);
             uint2 bl, bh;
-            if (i == 0) { bl = tab_entry<0>(tt, cl); bh = tab_entry<0>(tt, ch); }
+            if (MODE == 1) { bl = bh = make_uint2(one, one); }
+            else if (i == 0) { bl = tab_entry<0>(tt, cl); bh = tab_entry<0>(tt, ch); }
             else if (i == 1) { bl = tab_entry<1>(tt, cl); bh = tab_entry<1>(tt, ch); }
             else if (i == 2) { bl = tab_entry<2>(tt, cl); bh = tab_entry<2>(tt, ch); }
             else { bl = tab_entry<3>(tt, cl); bh = tab_entry<3>(tt, ch); }
