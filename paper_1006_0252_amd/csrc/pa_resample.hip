@@ -519,20 +519,13 @@ __device__ inline void gather_rows(const pa_state* st, int64_t j, int64_t rn, in
 
 // commit an accepted step: swap the buffers, accumulate ln Q (eq. sumQ) and write record[k]; a step
 // refused by a sticky flag leaves state and records as they were
-__global__ void k_finish(pa_state* base, ResampleParams p)
+__device__ inline void commit_step(pa_state* st, const ResampleParams& p, double lnQ, double S, double E_lo)
 {
-    pa_state* st = base + blockIdx.y;
-    if (st->status) return;
-    const WorkLayout wl = work_layout(st->N, st->n_bins, st->capacity);
-    const int64_t* misc = work_ptr<int64_t>(st, wl.misc);
-    const double lnQ = *reinterpret_cast<const double*>(&misc[kMiscLnQ]);
-    const double E_lo = st->couplings == PA_GAUSS ? *reinterpret_cast<const double*>(&misc[kMiscEmin])
-                                                  : (double)misc[kMiscEmin];
     pa_record* rec = st->record + p.k;
     rec->beta = p.beta_to;
     rec->lnQ = lnQ;
     rec->minus_betaF = st->ln_omega + (st->acc + lnQ);
-    rec->S = *reinterpret_cast<const double*>(&misc[kMiscS]);
+    rec->S = S;
     rec->R = (double)st->R_new;
     rec->E_lo = E_lo;
     st->acc = st->acc + lnQ;
@@ -540,6 +533,16 @@ __global__ void k_finish(pa_state* base, ResampleParams p)
     st->R = st->R_new;
     st->k = p.k;
     st->beta = p.beta_to;
+}
+
+__global__ void k_finish(pa_state* base, ResampleParams p)
+{
+    pa_state* st = base + blockIdx.y;
+    if (st->status) return;
+    const int64_t* misc = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).misc);
+    const double E_lo = st->couplings == PA_GAUSS ? *reinterpret_cast<const double*>(&misc[kMiscEmin])
+                                                  : (double)misc[kMiscEmin];
+    commit_step(st, p, *reinterpret_cast<const double*>(&misc[kMiscLnQ]), *reinterpret_cast<const double*>(&misc[kMiscS]), E_lo);
 }
 
 // Launch shapes cover the largest run of the call; grid.y indexes the runs, whose states
@@ -653,6 +656,240 @@ __global__ void __launch_bounds__(kStageThreads) k_gather_bits_staged(pa_state* 
     else gather_staged<uint32_t>(st, stage);
 }
 
+static void launch_gather(const pa_run* runs, int n, hipStream_t s)
+{
+    const BatchShape b = batch_shape(runs, n);
+    pa_state* base = runs[0].state;
+    if (runs[0].layout == PA_U8) {
+        const int64_t threads = b.cap_max * (b.stride_max / 16);
+        hipLaunchKernelGGL(k_gather_u8, dim3((unsigned)((threads + 255) / 256), n), dim3(256), 0, s, base);
+    } else {
+        const unsigned blocks = (unsigned)((b.cap_max + kStageThreads - 1) / kStageThreads);
+        hipLaunchKernelGGL(k_gather_bits_staged, dim3(blocks, n), dim3(kStageThreads), 0, s, base);
+    }
+}
+
+// ------------------------------------------------------------------ small populations
+// +-1 runs of up to kSmallCap replicas and kSmallBins energy bins (every run of the call): a block per run does the whole resampling with the population's energies, weights, copy
+// numbers and offsets in registers and LDS.  The chain of kernels above is bound by its launches there:
+// ten of 3 to 5 us each for a few us of work (1000 rings of 64 sites: 36 us a step, this 13 us; the 200 runs
+// of that ensemble 50 us, this 17 us).  Same histogram, sums in the same order, same draws.
+// GATHER: the block also moves the rows and commits the step (byte rows of up to kSmallRows bytes per
+// run); otherwise it leaves the source map and the step's ln Q and S for the gather kernel and k_finish.
+constexpr int kSmallCap = 4096, kSmallBins = 8192, kSmallThreads = 1024, kSmallPer = kSmallCap / kSmallThreads;
+constexpr int64_t kSmallRows = 192 << 10;
+
+// the parts of mean copy number lam: Poisson(64) blocks q, ladder level m and thinning threshold keep;
+// false (no copies) unless lam > 0
+__device__ inline bool poisson_parts(double lam, int* m, int64_t* q, uint64_t* keep)
+{
+    if (!(lam > 0.0)) return false;
+    double rem = lam;
+    *q = 0;
+    if (lam > 64.0) {
+        *q = (int64_t)ceil(lam / 64.0) - 1;
+        rem = lam - 64.0 * (double)*q;
+    }
+    *m = ladder_level(rem);
+    *keep = (uint64_t)floor(ldexp(rem, 32 - *m));
+    return true;
+}
+
+template <typename T, class F>
+__device__ __forceinline__ T block_reduce(T x, T* red, F f)
+{
+    for (int o = 32; o > 0; o >>= 1) x = f(x, __shfl_xor(x, o, 64));
+    __syncthreads();  // red may be in use
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+    __syncthreads();
+    T v = red[0];
+    for (int w = 1; w < kSmallThreads / 64; ++w) v = f(v, red[w]);
+    return v;
+}
+
+template <bool GATHER>
+__global__ void __launch_bounds__(kSmallThreads) k_resample_small(pa_state* base, ResampleParams p)
+{
+    pa_state* st = base + blockIdx.x;
+    if (st->status) return;
+    extern __shared__ double dyn[];  // products of a chunk of bins, then the histogram
+    __shared__ int32_t off[kSmallCap + 1];
+    __shared__ uint16_t src_of[kSmallCap];
+    __shared__ int64_t red[kSmallThreads / 64];
+    __shared__ double S_sh;
+    const int tid = threadIdx.x;
+    const int R = (int)st->R;
+    const int cur = st->cur;
+    const double dbeta = p.beta_to - p.beta_from;
+    const double Rt = p.R_target > 0.0 ? p.R_target : (double)st->R0;
+    const WorkLayout wl = work_layout(st->N, st->n_bins, st->capacity);
+    int64_t* misc = work_ptr<int64_t>(st, wl.misc);
+
+    // E_lo, the weights and S in its fixed order
+    double wt[kSmallPer];
+    double* prod = dyn;
+    uint32_t* hist = reinterpret_cast<uint32_t*>(dyn + kSmallThreads);
+    const int32_t* E = st->energy[cur];
+    const int nb = st->n_bins, Eb = st->E_base;
+    int e[kSmallPer], lo = INT32_MAX, hi = INT32_MIN;
+    for (int b = tid; b < nb; b += kSmallThreads) hist[b] = 0;
+#pragma unroll
+    for (int i = 0; i < kSmallPer; ++i) {
+        const int j = tid + i * kSmallThreads;
+        e[i] = j < R ? E[j] : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSmallPer; ++i) {
+        if (tid + i * kSmallThreads >= R) break;
+        atomicAdd(&hist[(e[i] - Eb) >> 2], 1u);
+        lo = min(lo, e[i]);
+        hi = max(hi, e[i]);
+    }
+    int* redi = reinterpret_cast<int*>(red);
+    lo = block_reduce(lo, redi, [](int a, int b) { return min(a, b); });
+    hi = block_reduce(hi, redi, [](int a, int b) { return max(a, b); });
+    const double E_lo = (double)lo;
+    const int ilo = R > 0 ? (lo - Eb) >> 2 : 0, n = R > 0 ? ((hi - Eb) >> 2) - ilo + 1 : 0;
+    double sum = 0.0;  // energies ascending (thread 0)
+    for (int b0 = 0; b0 < n; b0 += kSmallThreads) {
+        if (b0 + tid < n) prod[tid] = (double)hist[ilo + b0 + tid] * p.w[b0 + tid];
+        __syncthreads();
+        if (tid == 0) {
+            const int cnt = min(kSmallThreads, n - b0);
+            for (int t = 0; t < cnt; ++t) sum = sum + prod[t];
+        }
+        __syncthreads();
+    }
+    if (tid == 0) S_sh = sum;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSmallPer; ++i) wt[i] = tid + i * kSmallThreads < R ? p.w[(e[i] - lo) >> 2] : 0.0;
+    if (tid == 0 && isfinite(sum) && sum > 0.0) {
+        st->E_lo = lo;
+        st->E_hi = hi;
+    }
+    const double S = S_sh;
+    if (!isfinite(S) || !(S > 0.0)) {  // the same for the whole block
+        if (tid == 0) st->status |= PA_FLAG_NONFINITE;
+        return;
+    }
+
+    // copy numbers and their exclusive scan, 1024 replicas at a time in order
+    const CopyDraws cd0 = {0u, (uint32_t)p.k, (uint32_t)st->seed, (uint32_t)(st->seed >> 32)};
+    int64_t carry = 0;
+#pragma unroll
+    for (int i = 0; i < kSmallPer; ++i) {
+        if (i * kSmallThreads >= R) break;
+        const int j = tid + i * kSmallThreads;
+        const bool live = j < R;
+        int m = kLadderMin;
+        int64_t q = 0;
+        uint64_t keep = 0;
+        const bool drawn = live && poisson_parts((Rt * wt[i]) / S, &m, &q, &keep);
+        CopyDraws cd = cd0;
+        cd.j = (uint32_t)j;
+        const bool heavy = drawn && (q > 0 || m >= kCopiesHeavyM);
+        int64_t n = drawn && !heavy ? copies_light(cd, m, keep) : 0;
+        n = copies_heavy_by_wave(heavy, n, cd, m, q, keep);
+        const int32_t c = (int32_t)min(n, (int64_t)INT32_MAX);
+        if (live) st->counts[j] = c;
+        int64_t x = live ? c : 0;  // inclusive wave scan
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t y = __shfl_up(x, o, 64);
+            if ((tid & 63) >= o) x += y;
+        }
+        __syncthreads();
+        if ((tid & 63) == 63) red[tid >> 6] = x;
+        __syncthreads();
+        int64_t pre = carry, all = 0;
+        for (int w = 0; w < kSmallThreads / 64; ++w) {
+            if (w < (tid >> 6)) pre += red[w];
+            all += red[w];
+        }
+        const int64_t o = pre + x - (live ? c : 0);
+        if (live) off[j] = (int32_t)min(o, (int64_t)INT32_MAX);
+        carry += all;
+    }
+    if (tid == 0) {
+        st->R_new = carry;
+        if (carry > st->capacity) st->status |= PA_FLAG_CAPACITY;
+        else if (carry == 0) st->status |= PA_FLAG_EXTINCT;
+    }
+    if (carry > st->capacity || carry == 0) return;  // the same for the whole block
+    const int R_new = (int)carry;
+    if (tid == 0) off[R] = R_new;
+    __syncthreads();
+    for (int j = tid; j <= R; j += kSmallThreads) st->offsets[j] = off[j];
+
+    // the source of each new replica: the largest j with off[j] <= d
+    int32_t* src = work_ptr<int32_t>(st, wl.src);
+    for (int d = tid; d < R_new; d += kSmallThreads) {
+        int lo = 0, hi = R;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (off[mid] <= d) lo = mid;
+            else hi = mid;
+        }
+        if (GATHER) src_of[d] = (uint16_t)lo;
+        else src[d] = lo;
+    }
+    const double lnQ = -dbeta * E_lo + log(S) - log((double)R);
+    if constexpr (!GATHER) {
+        if (tid == 0) {
+            misc[kMiscEmin] = lo;
+            *reinterpret_cast<double*>(&misc[kMiscLnQ]) = lnQ;
+            *reinterpret_cast<double*>(&misc[kMiscS]) = S;
+        }
+        return;
+    } else {
+        __syncthreads();
+        const int per_row = st->row_stride / 16, pieces = R_new * per_row;
+        const uint4* A = reinterpret_cast<const uint4*>(st->spins[cur]);
+        uint4* B = reinterpret_cast<uint4*>(st->spins[cur ^ 1]);
+        constexpr int U = 4;  // loads in flight per thread
+        for (int t0 = tid; t0 < pieces; t0 += U * kSmallThreads) {
+            uint4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int t = t0 + u * kSmallThreads, rn = t / per_row;
+                if (t < pieces) v[u] = A[src_of[rn] * per_row + (t - rn * per_row)];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (t0 + u * kSmallThreads < pieces) B[t0 + u * kSmallThreads] = v[u];
+        }
+        for (int d = tid; d < R_new; d += kSmallThreads) st->energy[cur ^ 1][d] = st->energy[cur][src_of[d]];
+        __syncthreads();  // every thread has read the state
+        if (tid == 0) commit_step(st, p, lnQ, S, E_lo);
+    }
+}
+
+// launches the resampling of small populations; false when a run of the call is not small
+static bool launch_resample_small(const pa_run* runs, int n, const ResampleParams& p, hipStream_t s)
+{
+    int64_t cap = 0, bins = 0, rows = 0;
+    for (int r = 0; r < n; ++r) {
+        pa_sizes sz;
+        pa_buffer_sizes(runs[r].dim, runs[r].L, runs[r].layout, runs[r].couplings, runs[r].capacity, runs[r].n_records, &sz);
+        cap = std::max(cap, runs[r].capacity);
+        bins = std::max(bins, sz.n_bins);
+        rows = std::max(rows, runs[r].capacity * sz.row_stride);
+    }
+    if (cap > kSmallCap || bins > kSmallBins) return false;
+    pa_state* base = runs[0].state;
+    const bool gather = runs[0].layout == PA_U8 && rows <= kSmallRows;
+    const size_t lds = kSmallThreads * 8 + (size_t)bins * 4;
+    const dim3 g((unsigned)n), b(kSmallThreads);
+    if (gather) hipLaunchKernelGGL(k_resample_small<true>, g, b, lds, s, base, p);
+    else hipLaunchKernelGGL(k_resample_small<false>, g, b, lds, s, base, p);
+    if (!gather) {
+        launch_gather(runs, n, s);
+        hipLaunchKernelGGL(k_finish, dim3(1, (unsigned)n), dim3(1), 0, s, base, p);
+    }
+    return true;
+}
+
 int launch_resample(const pa_run* runs, int n, const pa_step& step, hipStream_t s)
 {
     const BatchShape b = batch_shape(runs, n);
@@ -662,6 +899,7 @@ int launch_resample(const pa_run* runs, int n, const pa_step& step, hipStream_t 
     p.R_target = step.R_target;
     p.w = step.weights;
     p.k = step.k;
+    if (launch_resample_small(runs, n, p, s)) return hip_status(hipGetLastError());
     pa_state* base = runs[0].state;
     const unsigned cap_blocks = (unsigned)((b.cap_max + 255) / 256);
     const unsigned n_scan = (unsigned)((b.cap_max + kScanTile - 1) / kScanTile);
@@ -672,13 +910,7 @@ int launch_resample(const pa_run* runs, int n, const pa_step& step, hipStream_t 
     hipLaunchKernelGGL(k_scan_top, dim3(1, n), dim3(256), 0, s, base);
     hipLaunchKernelGGL(k_scan_down, dim3(n_scan, n), dim3(256), 0, s, base);
     hipLaunchKernelGGL(k_src, dim3(cap_blocks, n), dim3(256), 0, s, base);
-    if (runs[0].layout == PA_U8) {
-        const int64_t threads = b.cap_max * (b.stride_max / 16);
-        hipLaunchKernelGGL(k_gather_u8, dim3((unsigned)((threads + 255) / 256), n), dim3(256), 0, s, base);
-    } else {
-        const unsigned blocks = (unsigned)((b.cap_max + kStageThreads - 1) / kStageThreads);
-        hipLaunchKernelGGL(k_gather_bits_staged, dim3(blocks, n), dim3(kStageThreads), 0, s, base);
-    }
+    launch_gather(runs, n, s);
     hipLaunchKernelGGL(k_finish, dim3(1, n), dim3(1), 0, s, base, p);
     return hip_status(hipGetLastError());
 }
@@ -727,9 +959,7 @@ __global__ void __launch_bounds__(256) k_gauss_weights(pa_state* base, double db
 
 // a block per run: S in replica order, ln Q (the step's record is written by k_finish).  The block
 // loads the weights a chunk at a time into LDS with coalesced loads, and one thread adds them in
-// order from there: the chain of dependent FP64 additions is then the cost (R = 2000: 22 us; from
-// global memory, one thread with eight loads ahead waited out the load latency every eight
-// additions: 50 us)
+// order from there, 16 LDS loads ahead of the chain of dependent FP64 additions
 constexpr int kNormChunk = 4096;
 
 __global__ void __launch_bounds__(256) k_gauss_normalise(pa_state* base, ResampleParams p)
@@ -746,8 +976,17 @@ __global__ void __launch_bounds__(256) k_gauss_normalise(pa_state* base, Resampl
         const int n = (int)(R - j0 < kNormChunk ? R - j0 : kNormChunk);
         for (int i = threadIdx.x; i < n; i += blockDim.x) chunk[i] = w[j0 + i];
         __syncthreads();
-        if (threadIdx.x == 0)
-            for (int i = 0; i < n; ++i) S = S + chunk[i];
+        if (threadIdx.x == 0) {
+            int i = 0;
+            for (; i + 16 <= n; i += 16) {
+                double c[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) c[u] = chunk[i + u];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) S = S + c[u];
+            }
+            for (; i < n; ++i) S = S + chunk[i];
+        }
         __syncthreads();
     }
     if (threadIdx.x != 0) return;
@@ -778,17 +1017,8 @@ __global__ void __launch_bounds__(256) k_gauss_copies(pa_state* base, ResamplePa
     int m = kLadderMin;
     int64_t q = 0;
     uint64_t keep = 0;
-    if (lam > 0.0) {
-        double rem = lam;
-        if (lam > 64.0) {
-            q = (int64_t)ceil(lam / 64.0) - 1;
-            rem = lam - 64.0 * (double)q;
-        }
-        m = ladder_level(rem);
-        keep = (uint64_t)floor(ldexp(rem, 32 - m));
-    }
+    const bool drawn = poisson_parts(lam, &m, &q, &keep);
     const CopyDraws cd = {(uint32_t)j, (uint32_t)p.k, (uint32_t)st->seed, (uint32_t)(st->seed >> 32)};
-    const bool drawn = lam > 0.0;
     const bool heavy = drawn && (q > 0 || m >= kCopiesHeavyM);
     int64_t n = drawn && !heavy ? copies_light(cd, m, keep) : 0;
     n = copies_heavy_by_wave(heavy, n, cd, m, q, keep);
@@ -805,12 +1035,8 @@ int launch_resample_gauss(const pa_run* runs, int n, const pa_step& step, hipStr
     p.w = nullptr;
     p.k = step.k;
     pa_state* base = runs[0].state;
-    int64_t cap = 0, stride = 0;
-    for (int r = 0; r < n; ++r) {
-        const int64_t N = runs[r].dim == 1 ? runs[r].L : (int64_t)runs[r].L * runs[r].L * runs[r].L;
-        cap = std::max<int64_t>(cap, runs[r].capacity);
-        stride = std::max<int64_t>(stride, (N + 15) / 16 * 16);
-    }
+    int64_t cap = 0;
+    for (int r = 0; r < n; ++r) cap = std::max<int64_t>(cap, runs[r].capacity);
     const unsigned cap_blocks = (unsigned)((cap + 255) / 256);
     const unsigned n_scan = (unsigned)((cap + kScanTile - 1) / kScanTile);
     const unsigned ny = (unsigned)n;
@@ -822,8 +1048,7 @@ int launch_resample_gauss(const pa_run* runs, int n, const pa_step& step, hipStr
     hipLaunchKernelGGL(k_scan_top, dim3(1, ny), dim3(256), 0, s, base);
     hipLaunchKernelGGL(k_scan_down, dim3(n_scan, ny), dim3(256), 0, s, base);
     hipLaunchKernelGGL(k_src, dim3(cap_blocks, ny), dim3(256), 0, s, base);
-    const int64_t threads = cap * (stride / 16);  // one per 16 bytes of a row
-    hipLaunchKernelGGL(k_gather_u8, dim3((unsigned)((threads + 255) / 256), ny), dim3(256), 0, s, base);
+    launch_gather(runs, n, s);
     hipLaunchKernelGGL(k_finish, dim3(1, ny), dim3(1), 0, s, base, p);
     return hip_status(hipGetLastError());
 }
