@@ -10,6 +10,7 @@
 #include <math.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "pa_common.h"
 #include "pa_host.h"
@@ -22,21 +23,18 @@ constexpr int kOffW1 = 0, kOffB1 = 384, kOffW2 = 448, kOffB2 = 4544, kOffW3 = 46
               kOffB4 = 8832, kParams = 8833;
 static_assert(kOffB4 + 1 == kParams && kParams == PA_MLP_PARAMS, "parameter layout");
 
-// rows of the training work matrix ([row][ld] floats, ld = B rounded up to 64)
-constexpr int kRowXH = 0;     // 6 normalised inputs + a row of ones
-constexpr int kRowH1 = 7;     // 64 + ones
-constexpr int kRowH2 = 72;    // 64 + ones
-constexpr int kRowH3 = 137;   // 64 + ones
-constexpr int kRowD1 = 202;   // 64 back-propagated deltas per layer
-constexpr int kRowD2 = 266;
-constexpr int kRowD3 = 330;
-constexpr int kRowGZ = 394;   // dL/dz
-constexpr int kRowLS = 395;   // per-sample loss / B
+// Work memory of a gradient: the formula of pa_mlp_work_bytes is part of the interface and larger than the
+// partial gradients need (kTile samples per tile, one partial of kParams + 1 floats per block of at most
+// kMaxBlocks).
 constexpr int kRows = 396;
-constexpr int kChunk = 1024;  // samples per partial gradient
+constexpr int kChunk = 1024;
+constexpr int kTile = 32;
+constexpr int kMaxBlocks = 512;
 
 __host__ __device__ inline int64_t mlp_ld(int64_t B) { return (B + 63) & ~(int64_t)63; }
 __host__ __device__ inline int64_t mlp_chunks(int64_t B) { return (B + kChunk - 1) / kChunk; }
+__host__ inline int64_t mlp_tiles(int64_t B) { return (B + kTile - 1) / kTile; }
+static_assert((kParams + 1) * (64 / kTile) <= kRows * 64, "the partial gradients of 64 samples fit their work memory");
 
 __device__ inline float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -62,194 +60,241 @@ __device__ inline void normalise(const float* x, float* xh)
 __device__ inline float softplus(float z) { return fmaxf(z, 0.0f) + log1pf(expf(-fabsf(z))); }
 __device__ inline float sigmoid(float z) { return 1.0f / (1.0f + expf(-z)); }
 
-// one dense tanh layer for the calling lane: out[j][lane] = tanh(b[j] + sum_i W[j][i] in[i]),
-// weights in LDS (row-major, n_in inputs), outputs to the lane's column of an LDS buffer and,
-// when train, to row `row` of the work matrix at column b
-template <int NIN>
-__device__ inline void dense_tanh(const float* __restrict__ W, const float* __restrict__ bias, const float (&in)[NIN],
-                                  float* __restrict__ buf, int lane, float* __restrict__ work, int64_t ld, int row,
-                                  int64_t b, bool train)
+// ------------------------------------------------------------------ forward and gradient
+// A block of four waves takes tiles of 32 samples through the whole network: the weights in LDS as FP32, the
+// layers as FP32 matrix products on the matrix cores (v_mfma_f32_16x16x4_f32: wave w computes rows 16 w ..
+// 16 w + 15 of every layer), activations and deltas of the tile in LDS.  With TRAIN the outer products of
+// deltas and layer inputs accumulate in registers over the block's tiles, and the block writes one partial
+// gradient; k_mlp_grad_sum adds the partials in block order.  All sums have a fixed order.
+//
+// Bound by the latency of one tile's chain of layers: at B = 10160 (318 tiles, one per block) the matrix
+// products take 3 us, the weights' way to LDS, tanh and the LDS round trips between layers the rest of 27.
+// One sample per lane, its activations in registers and the per-sample matrices written to memory for 40
+// blocks of outer products, took 131 + 706 us a gradient, this 27 + 5.
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// LDS pitches: the lanes of an operand read (row l mod 16, column l / 16, or the other way round) spread over
+// the banks
+constexpr int kPitchW = 68, kPitchW1 = 12, kPitchS = 36;
+
+struct MlpSmem {
+    float W2[kH * kPitchW], W3[kH * kPitchW], W1[kH * kPitchW1];  // W1: columns 6, 7 zero
+    float b1[kH], b2[kH], b3[kH], w4[kH];
+    float X[8 * kPitchS];                                          // normalised inputs, rows 6, 7 zero
+    float H1[kH * kPitchS], H2[kH * kPitchS], H3[kH * kPitchS], D[kH * kPitchS];
+    float part[8 * kTile], gz[kTile], ls[kTile];
+    float b4;
+};
+
+// C (+)= A B over K columns for the wave's 16 rows and n tiles of 16 columns; lane l supplies A[l mod 16][k +
+// l / 16] = a(k) and B[k + l / 16][16 t + l mod 16] = b(t, k), and holds C[4 (l / 16) + i][16 t + l mod 16]
+template <int K, int NT, class FA, class FB>
+__device__ __forceinline__ void mfma_tiles(f32x4 (&acc)[NT], FA a, FB b)
 {
-    for (int j = 0; j < kH; ++j) {
-        float acc = bias[j];
 #pragma unroll
-        for (int i = 0; i < NIN; ++i) acc = fmaf(W[j * NIN + i], in[i], acc);
-        const float h = tanhf(acc);
-        buf[j * 64 + lane] = h;
-        if (train) work[(int64_t)(row + j) * ld + b] = h;
+    for (int k = 0; k < K; k += 4) {
+        const float av = a(k);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, b(t, k), acc[t], 0, 0, 0);
     }
 }
 
-// forward (and, with TRAIN, backward) of 64 samples per block, one sample per lane.
-// Forward only: out[b] = dbeta = clamp(softplus(z) / sigma_E, dmin, dmax), dmax when var <= 0.
-// TRAIN: writes the work matrix (activations, deltas, dL/dz, loss / B); target t[b] = dbeta*.
 template <bool TRAIN>
-__global__ void __launch_bounds__(64) k_mlp(const uint16_t* __restrict__ w, const float* __restrict__ x, int64_t B,
-                                           float dmin, float dmax, float* __restrict__ out,
-                                           const double* __restrict__ target, float* __restrict__ work)
+__global__ void __launch_bounds__(256) k_mlp(const uint16_t* __restrict__ w, const float* __restrict__ x, int64_t B,
+                                             float dmin, float dmax, float* __restrict__ out,
+                                             const double* __restrict__ target, float* __restrict__ partial)
 {
-    __shared__ float Wl[kParams];
-    __shared__ float buf[kH * 64];
-    const int lane = threadIdx.x;
-    for (int p = lane; p < kParams; p += 64) Wl[p] = bf16_to_f32(w[p]);
-    __syncthreads();
-    const int64_t b = (int64_t)blockIdx.x * 64 + lane;
-    if (b >= B) return;
-    const int64_t ld = mlp_ld(B);
-    float xr[kIn], xh[kIn];
-#pragma unroll
-    for (int k = 0; k < kIn; ++k) xr[k] = x[b * kIn + k];
-    normalise(xr, xh);
-    if (TRAIN) {
-#pragma unroll
-        for (int k = 0; k < kIn; ++k) work[(int64_t)(kRowXH + k) * ld + b] = xh[k];
-        work[(int64_t)(kRowXH + kIn) * ld + b] = 1.0f;
-        work[(int64_t)(kRowH1 + kH) * ld + b] = 1.0f;
-        work[(int64_t)(kRowH2 + kH) * ld + b] = 1.0f;
-        work[(int64_t)(kRowH3 + kH) * ld + b] = 1.0f;
+    __shared__ MlpSmem sm;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lr = lane & 15, lk = lane >> 4;   // operand row or column, and k offset
+    const int j0 = 16 * wave;                   // the wave's rows
+    for (int p = tid; p < kH * kIn; p += 256) sm.W1[(p / kIn) * kPitchW1 + p % kIn] = bf16_to_f32(w[kOffW1 + p]);
+    for (int p = tid; p < kH * kH; p += 256) {
+        sm.W2[(p >> 6) * kPitchW + (p & 63)] = bf16_to_f32(w[kOffW2 + p]);
+        sm.W3[(p >> 6) * kPitchW + (p & 63)] = bf16_to_f32(w[kOffW3 + p]);
     }
-    float h[kH];
-    dense_tanh<kIn>(Wl + kOffW1, Wl + kOffB1, xh, buf, lane, work, ld, kRowH1, b, TRAIN);
-#pragma unroll
-    for (int i = 0; i < kH; ++i) h[i] = buf[i * 64 + lane];
-    dense_tanh<kH>(Wl + kOffW2, Wl + kOffB2, h, buf, lane, work, ld, kRowH2, b, TRAIN);
-#pragma unroll
-    for (int i = 0; i < kH; ++i) h[i] = buf[i * 64 + lane];
-    dense_tanh<kH>(Wl + kOffW3, Wl + kOffB3, h, buf, lane, work, ld, kRowH3, b, TRAIN);
-#pragma unroll
-    for (int i = 0; i < kH; ++i) h[i] = buf[i * 64 + lane];  // h3
-    float z = Wl[kOffB4];
-#pragma unroll
-    for (int i = 0; i < kH; ++i) z = fmaf(Wl[kOffW4 + i], h[i], z);
-    const float v = xr[4];
-    const bool has_sigma = v > 0.0f;
-    const float log_sigma = has_sigma ? 0.5f * (xr[1] + logf(v)) : 0.0f;
-    const float sp = softplus(z);
-    if (!TRAIN) {
-        float d = has_sigma ? sp * expf(-log_sigma) : dmax;
-        d = d != d ? dmax : fminf(fmaxf(d, dmin), dmax);
-        out[b] = d;
-        return;
+    if (tid < kH) {
+        sm.W1[tid * kPitchW1 + 6] = sm.W1[tid * kPitchW1 + 7] = 0.0f;
+        sm.b1[tid] = bf16_to_f32(w[kOffB1 + tid]);
+        sm.b2[tid] = bf16_to_f32(w[kOffB2 + tid]);
+        sm.b3[tid] = bf16_to_f32(w[kOffB3 + tid]);
+        sm.w4[tid] = bf16_to_f32(w[kOffW4 + tid]);
+        if (tid == 0) sm.b4 = bf16_to_f32(w[kOffB4]);
     }
-    const double t = target[b];
-    const bool valid = has_sigma && t > 0.0 && t <= 1.0e300;
-    float gz = 0.0f, ls = 0.0f;
-    if (valid) {
-        const float err = logf(sp) - log_sigma - (float)log(t);
-        ls = err * err / (float)B;
-        gz = (2.0f / (float)B) * err * sigmoid(z) / sp;
-    }
-    work[(int64_t)kRowGZ * ld + b] = gz;
-    work[(int64_t)kRowLS * ld + b] = ls;
-    // delta3 = gz w4 (1 - h3^2), kept in h[]
-#pragma unroll
-    for (int j = 0; j < kH; ++j) {
-        h[j] = gz * Wl[kOffW4 + j] * (1.0f - h[j] * h[j]);
-        work[(int64_t)(kRowD3 + j) * ld + b] = h[j];
-    }
-    // delta2[i] = (sum_j W3[j][i] delta3[j]) (1 - h2[i]^2)
-    for (int i = 0; i < kH; ++i) {
-        float s = 0.0f;
-#pragma unroll
-        for (int j = 0; j < kH; ++j) s = fmaf(Wl[kOffW3 + j * kH + i], h[j], s);
-        const float a = work[(int64_t)(kRowH2 + i) * ld + b];
-        const float d = s * (1.0f - a * a);
-        buf[i * 64 + lane] = d;
-        work[(int64_t)(kRowD2 + i) * ld + b] = d;
-    }
-#pragma unroll
-    for (int i = 0; i < kH; ++i) h[i] = buf[i * 64 + lane];
-    // delta1[k] = (sum_i W2[i][k] delta2[i]) (1 - h1[k]^2)
-    for (int k = 0; k < kH; ++k) {
-        float s = 0.0f;
-#pragma unroll
-        for (int i = 0; i < kH; ++i) s = fmaf(Wl[kOffW2 + i * kH + k], h[i], s);
-        const float a = work[(int64_t)(kRowH1 + k) * ld + b];
-        work[(int64_t)(kRowD1 + k) * ld + b] = s * (1.0f - a * a);
-    }
-}
+    // gradient sums over the block's tiles: W3, W2 (rows j0 .., four column tiles), W1 (one), and per thread one
+    // row of w4 / b3 / b2 / b1 (threads 0.., 64.., 128.., 192..); thread 0 adds b4 and the loss
+    f32x4 g3[4] = {}, g2[4] = {}, g1[1] = {};
+    float g_vec = 0.0f, g_b4 = 0.0f, g_loss = 0.0f;
 
-// Partial gradients of one chunk of samples: G[a][c] = sum_b A[a][b] C[c][b] for the four
-// products (deltas x layer inputs with their row of ones), tiled through LDS, 256 lanes per
-// block, lane (a = t/4, c = t%4 + 4m).  Product 3 carries dL/dz and the per-sample loss.
-struct GradProduct { int rowA, nA, rowC, nC; };
-
-__device__ inline GradProduct grad_product(int q)
-{
-    switch (q) {
-    case 0: return {kRowD1, kH, kRowXH, kIn + 1};
-    case 1: return {kRowD2, kH, kRowH1, kH + 1};
-    case 2: return {kRowD3, kH, kRowH2, kH + 1};
-    default: return {kRowGZ, 2, kRowH3, kH + 1};
-    }
-}
-
-// parameter index of G[a][c] of product q (-1: not a parameter; kParams: the loss sum)
-__device__ inline int grad_param(int q, int a, int c)
-{
-    switch (q) {
-    case 0: return c < kIn ? kOffW1 + a * kIn + c : kOffB1 + a;
-    case 1: return c < kH ? kOffW2 + a * kH + c : kOffB2 + a;
-    case 2: return c < kH ? kOffW3 + a * kH + c : kOffB3 + a;
-    default:
-        if (a == 0) return c < kH ? kOffW4 + c : kOffB4;
-        return c == kH ? kParams : -1;
-    }
-}
-
-__global__ void __launch_bounds__(256) k_mlp_grad_partial(const float* __restrict__ work, int64_t B,
-                                                          float* __restrict__ partial)
-{
-    __shared__ float As[kH][65];
-    __shared__ float Cs[kH + 1][65];
-    const int q = blockIdx.x, chunk = blockIdx.y, t = threadIdx.x;
-    const GradProduct g = grad_product(q);
-    const int64_t ld = mlp_ld(B);
-    const int64_t b0 = (int64_t)chunk * kChunk, b1 = min(B, b0 + kChunk);
-    const int a = t >> 2;
-    float acc[17];
+    for (int64_t tile = blockIdx.x; tile * kTile < B; tile += gridDim.x) {
+        const int64_t b0 = tile * kTile;
+        __syncthreads();  // the weights; the last tile's readers
+        if (tid < kTile) {
+            float xr[kIn], xh[kIn];
 #pragma unroll
-    for (int m = 0; m < 17; ++m) acc[m] = 0.0f;
-    for (int64_t bt = b0; bt < b1; bt += 64) {
-        for (int e = t; e < g.nA * 64; e += 256) {
-            const int r = e >> 6, bb = e & 63;
-            As[r][bb] = bt + bb < b1 ? work[(int64_t)(g.rowA + r) * ld + bt + bb] : 0.0f;
-        }
-        for (int e = t; e < g.nC * 64; e += 256) {
-            const int r = e >> 6, bb = e & 63;
-            Cs[r][bb] = bt + bb < b1 ? work[(int64_t)(g.rowC + r) * ld + bt + bb] : 0.0f;
+            for (int k = 0; k < kIn; ++k) xr[k] = b0 + tid < B ? x[(b0 + tid) * kIn + k] : 0.0f;
+            normalise(xr, xh);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) sm.X[k * kPitchS + tid] = k < kIn ? xh[k] : 0.0f;
         }
         __syncthreads();
-        if (a < g.nA) {
-            for (int bb = 0; bb < 64; ++bb) {
-                const float av = As[a][bb];
+        // out[j][s] = tanh(bias[j] + sum_i W[j][i] in[i][s])
+        auto layer = [&](auto K, const float* W, int pitch, const float* bias, const float* in, float* o) {
+            f32x4 acc[2];
 #pragma unroll
-                for (int m = 0; m < 17; ++m) {
-                    const int c = (t & 3) + 4 * m;
-                    if (c < g.nC) acc[m] = fmaf(av, Cs[c][bb], acc[m]);
+            for (int i = 0; i < 4; ++i) acc[0][i] = acc[1][i] = bias[j0 + 4 * lk + i];
+            mfma_tiles<decltype(K)::value, 2>(
+                acc, [&](int k) { return W[(j0 + lr) * pitch + k + lk]; },
+                [&](int t, int k) { return in[(k + lk) * kPitchS + 16 * t + lr]; });
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[(j0 + 4 * lk + i) * kPitchS + 16 * t + lr] = tanhf(acc[t][i]);
+            __syncthreads();
+        };
+        layer(std::integral_constant<int, 8>{}, sm.W1, kPitchW1, sm.b1, sm.X, sm.H1);
+        layer(std::integral_constant<int, kH>{}, sm.W2, kPitchW, sm.b2, sm.H1, sm.H2);
+        layer(std::integral_constant<int, kH>{}, sm.W3, kPitchW, sm.b3, sm.H2, sm.H3);
+        {
+            const int s = tid & 31, q = tid >> 5;
+            float z = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) z = fmaf(sm.w4[8 * q + i], sm.H3[(8 * q + i) * kPitchS + s], z);
+            sm.part[q * kTile + s] = z;
+        }
+        __syncthreads();
+        if (tid < kTile) {
+            float z = sm.b4;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) z += sm.part[q * kTile + tid];
+            const int64_t b = b0 + tid;
+            const float ln_n = b < B ? x[b * kIn + 1] : 0.0f, v = b < B ? x[b * kIn + 4] : 0.0f;
+            const bool has_sigma = v > 0.0f;
+            const float log_sigma = has_sigma ? 0.5f * (ln_n + logf(v)) : 0.0f;
+            const float sp = softplus(z);
+            if (!TRAIN) {
+                float d = has_sigma ? sp * expf(-log_sigma) : dmax;
+                d = d != d ? dmax : fminf(fmaxf(d, dmin), dmax);
+                if (b < B) out[b] = d;
+            } else {
+                const double t = b < B ? target[b] : 0.0;
+                const bool valid = has_sigma && t > 0.0 && t <= 1.0e300;
+                float gz = 0.0f, ls = 0.0f;
+                if (valid) {
+                    const float err = logf(sp) - log_sigma - (float)log(t);
+                    ls = err * err / (float)B;
+                    gz = (2.0f / (float)B) * err * sigmoid(z) / sp;
                 }
+                sm.gz[tid] = gz;
+                sm.ls[tid] = ls;
             }
         }
-        __syncthreads();
-    }
-    if (a >= g.nA) return;
+        if constexpr (TRAIN) {
+            __syncthreads();
+            // delta3 = gz w4 (1 - h3^2)
+            for (int e = tid; e < kH * kTile; e += 256) {
+                const int j = e >> 5, s = e & 31;
+                const float h = sm.H3[j * kPitchS + s];
+                sm.D[j * kPitchS + s] = sm.gz[s] * sm.w4[j] * (1.0f - h * h);
+            }
+            // row sums of a matrix of the tile by 64 threads
+            auto row_sum = [&](const float* M, int r) {
+                float v = 0.0f;
 #pragma unroll
-    for (int m = 0; m < 17; ++m) {
-        const int c = (t & 3) + 4 * m;
-        if (c >= g.nC) continue;
-        const int p = grad_param(q, a, c);
-        if (p >= 0) partial[(int64_t)chunk * (kParams + 1) + p] = acc[m];
+                for (int s = 0; s < kTile; ++s) v += M[r * kPitchS + s];
+                return v;
+            };
+            if (wave == 0) {
+                float v = 0.0f;
+#pragma unroll
+                for (int s = 0; s < kTile; ++s) v = fmaf(sm.gz[s], sm.H3[lane * kPitchS + s], v);
+                g_vec += v;
+            }
+            if (tid == 0) {
+#pragma unroll
+                for (int s = 0; s < kTile; ++s) {
+                    g_b4 += sm.gz[s];
+                    g_loss += sm.ls[s];
+                }
+            }
+            __syncthreads();
+            // G[a][c] += sum_s D[a][s] in[c][s]
+            auto outer = [&](auto& acc, const float* D, const float* in) {
+                mfma_tiles<kTile>(
+                    acc, [&](int k) { return D[(j0 + lr) * kPitchS + k + lk]; },
+                    [&](int t, int k) { return in[(16 * t + lr) * kPitchS + k + lk]; });
+            };
+            // d[i][s] = (sum_j W[j][i] D[j][s]) (1 - h[i][s]^2)
+            auto back = [&](const float* W, const float* D, const float* h, float* d) {
+                f32x4 acc[2] = {};
+                mfma_tiles<kH, 2>(
+                    acc, [&](int k) { return W[(k + lk) * kPitchW + j0 + lr]; },
+                    [&](int t, int k) { return D[(k + lk) * kPitchS + 16 * t + lr]; });
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int e = (j0 + 4 * lk + i) * kPitchS + 16 * t + lr;
+                        d[e] = acc[t][i] * (1.0f - h[e] * h[e]);
+                    }
+                __syncthreads();
+            };
+            if (wave == 1) g_vec += row_sum(sm.D, lane);
+            outer(g3, sm.D, sm.H2);
+            back(sm.W3, sm.D, sm.H2, sm.H3);  // delta2 in H3's place
+            if (wave == 2) g_vec += row_sum(sm.H3, lane);
+            outer(g2, sm.H3, sm.H1);
+            back(sm.W2, sm.H3, sm.H1, sm.D);  // delta1 in delta3's place
+            if (wave == 3) g_vec += row_sum(sm.D, lane);
+            // the inputs' 8 rows as a tile of 16 (rows past them: zero)
+            mfma_tiles<kTile>(
+                g1, [&](int k) { return sm.D[(j0 + lr) * kPitchS + k + lk]; },
+                [&](int, int k) { return lr < 8 ? sm.X[lr * kPitchS + k + lk] : 0.0f; });
+        }
+    }
+    if constexpr (TRAIN) {
+        float* o = partial + (int64_t)blockIdx.x * (kParams + 1);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int e = (j0 + 4 * lk + i) * kH + 16 * t + lr;
+                o[kOffW3 + e] = g3[t][i];
+                o[kOffW2 + e] = g2[t][i];
+            }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (lr < kIn) o[kOffW1 + (j0 + 4 * lk + i) * kIn + lr] = g1[0][i];
+        const int off = wave == 0 ? kOffW4 : (wave == 1 ? kOffB3 : (wave == 2 ? kOffB2 : kOffB1));
+        o[off + lane] = g_vec;
+        if (tid == 0) {
+            o[kOffB4] = g_b4;
+            o[kParams] = g_loss;
+        }
     }
 }
 
-// grad[p] = sum over chunks in order; the loss sum goes to loss[0]
-__global__ void k_mlp_grad_sum(const float* __restrict__ partial, int n_chunks, float* __restrict__ grad,
-                               float* __restrict__ loss)
+// grad[p] = sum over the partials: 16 slices of every 16th partial each, then the slices in order; the loss sum
+// goes to loss[0]
+constexpr int kSumSlices = 16;
+
+__global__ void __launch_bounds__(64 * kSumSlices) k_mlp_grad_sum(const float* __restrict__ partial, int n,
+                                                                  float* __restrict__ grad, float* __restrict__ loss)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > kParams) return;
+    __shared__ float part[kSumSlices][64];
+    const int c = threadIdx.x & 63, slice = threadIdx.x >> 6, p = blockIdx.x * 64 + c;
     float s = 0.0f;
-    for (int c = 0; c < n_chunks; ++c) s += partial[(int64_t)c * (kParams + 1) + p];
+    if (p <= kParams) {
+#pragma unroll 8
+        for (int i = slice; i < n; i += kSumSlices) s += partial[(int64_t)i * (kParams + 1) + p];
+    }
+    part[slice][c] = s;
+    __syncthreads();
+    if (slice != 0 || p > kParams) return;
+    s = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kSumSlices; ++i) s += part[i][c];
     if (p < kParams) grad[p] = s;
     else if (loss) loss[0] = s;
 }
@@ -419,14 +464,13 @@ static int scratch_address(float** out)
 static int mlp_grad_launch(const uint16_t* w, const float* x, const double* target, int64_t B, float* wk, float* grad,
                            float* loss, hipStream_t s)
 {
-    float* partial = wk + (int64_t)kRows * mlp_ld(B);
-    const int64_t nc = mlp_chunks(B);
-    if (nc > 65535) return PA_ERR_ARG;
-    hipLaunchKernelGGL(k_mlp<true>, dim3((unsigned)((B + 63) / 64)), dim3(64), 0, s, w, x, B, 0.0f, 0.0f,
-                       (float*)nullptr, target, wk);
-    hipLaunchKernelGGL(k_mlp_grad_partial, dim3(4, (unsigned)nc), dim3(256), 0, s, (const float*)wk, B, partial);
-    hipLaunchKernelGGL(k_mlp_grad_sum, dim3((kParams + 1 + 255) / 256), dim3(256), 0, s, (const float*)partial,
-                       (int)nc, grad, loss);
+    if (mlp_chunks(B) > 65535) return PA_ERR_ARG;
+    const int64_t tiles = mlp_tiles(B);
+    const int blocks = (int)(tiles < kMaxBlocks ? tiles : kMaxBlocks);
+    hipLaunchKernelGGL(k_mlp<true>, dim3((unsigned)blocks), dim3(256), 0, s, w, x, B, 0.0f, 0.0f, (float*)nullptr, target,
+                       wk);
+    hipLaunchKernelGGL(k_mlp_grad_sum, dim3((kParams + 1 + 63) / 64), dim3(64 * kSumSlices), 0, s, (const float*)wk, blocks,
+                       grad, loss);
     return hip_status(hipGetLastError());
 }
 
@@ -446,7 +490,9 @@ extern "C" int pa_mlp_forward(const uint16_t* w, const float* x, int64_t B, floa
 {
     if (!w || !x || !dbeta || B <= 0 || B > ((int64_t)1 << 30)) return PA_ERR_ARG;
     if (!(dbeta_min >= 0.0f) || !(dbeta_max >= dbeta_min) || !isfinite(dbeta_max)) return PA_ERR_ARG;
-    hipLaunchKernelGGL(k_mlp<false>, dim3((unsigned)((B + 63) / 64)), dim3(64), 0, (hipStream_t)stream, w, x, B,
+    const int64_t tiles = mlp_tiles(B);
+    hipLaunchKernelGGL(k_mlp<false>, dim3((unsigned)(tiles < kMaxBlocks ? tiles : kMaxBlocks)), dim3(256), 0,
+                       (hipStream_t)stream, w, x, B,
                        dbeta_min, dbeta_max, dbeta, (const double*)nullptr, (float*)nullptr);
     return hip_status(hipGetLastError());
 }
