@@ -21,8 +21,8 @@ constexpr int kLadderMax = 6;
 constexpr int kLadderLevels = kLadderMax - kLadderMin + 1;
 constexpr int kLadderCap = 256;  // entries per level (the largest level, 2^6, needs < 200)
 
-// scan tile: replicas per block of the device-wide exclusive scan
-constexpr int kScanTile = 1024;
+// scan tile: replicas per block of the copy numbers and of their device-wide exclusive scan
+constexpr int kScanTile = 256;
 
 struct uint4v { uint32_t x, y, z, w; };
 

@@ -7,9 +7,10 @@
 //   normalise S = sum_E h(E) w(E - E_lo) in ascending E (FP64, one thread, fixed order),
 //             ln Q, and per bin the mean copy number lambda = R_target w / S split into
 //             Poisson(64) blocks q, ladder level m and thinning threshold
-//   copies    Poisson(lambda) per replica from its Philox stream (integer compares only)
-//   scan      exclusive scan of the copy numbers -> offsets, R~', capacity/extinction flags
-//   src       source replica of every new replica (binary search of the offsets)
+//   copies    Poisson(lambda) per replica from its Philox stream (integer compares only), and the sum
+//             of each tile of kScanTile replicas
+//   offsets   exclusive scan of the copy numbers -> offsets, R~', capacity/extinction flags; source
+//             replica of every new replica
 //   gather    copy spins and energies into the other buffer
 //   finish    swap buffers, R~ = R~', accumulate ln Q, record
 // Every kernel is a no-op once the run's sticky status is set.
@@ -318,13 +319,26 @@ __device__ inline int64_t copies_heavy_by_wave(bool heavy, int64_t n, const Copy
     return n;
 }
 
-__global__ void __launch_bounds__(256) k_copies(pa_state* base, int32_t k)
+// sum of the block's copy numbers into its tile's slot (every thread of the block calls this)
+__device__ inline void tile_sum(const pa_state* st, int64_t c)
+{
+    __shared__ int64_t part[kScanTile / 64];
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    int64_t s = 0;
+    for (int w = 0; w < kScanTile / 64; ++w) s += part[w];
+    work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).scan)[blockIdx.x] = s;
+}
+
+__global__ void __launch_bounds__(kScanTile) k_copies(pa_state* base, int32_t k)
 {
     pa_state* st = base + blockIdx.y;
     if (st->status) return;
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t R = st->R;
-    if (j - (int64_t)(threadIdx.x & 63) >= R) return;  // the whole wave past R
+    if ((int64_t)blockIdx.x * kScanTile >= R) return;  // the whole block past R
     const WorkLayout wl = work_layout(st->N, st->n_bins, st->capacity);
     const int64_t* bin_q = work_ptr<int64_t>(st, wl.bin_q);
     const uint64_t* bin_keep = work_ptr<uint64_t>(st, wl.bin_keep);
@@ -346,120 +360,80 @@ __global__ void __launch_bounds__(256) k_copies(pa_state* base, int32_t k)
     const bool heavy = drawn && (q > 0 || m >= kCopiesHeavyM);
     int64_t n = drawn && !heavy ? copies_light(cd, m, keep) : 0;
     n = copies_heavy_by_wave(heavy, n, cd, m, q, keep);
-    if (live) st->counts[j] = (int32_t)min(n, (int64_t)INT32_MAX);
+    const int32_t c = (int32_t)min(n, (int64_t)INT32_MAX);
+    if (live) st->counts[j] = c;
+    tile_sum(st, live ? c : 0);
 }
 
-// block sums of the copy numbers over tiles of kScanTile replicas
-__global__ void __launch_bounds__(256) k_scan_reduce(pa_state* base)
+// Offsets and sources, a block per tile of kScanTile consecutive sources.  The block adds the sums of the
+// tiles before it (and all of them, for R~' and the capacity and extinction checks, which every block
+// makes alike and block 0 records), scans its own copy numbers into offsets[j] (offsets[R] = R~'), and its
+// new replicas offsets[j0] .. offsets[j0 + 256] - 1 each find their source in the block's offsets in LDS
+// (largest j with offsets[j] <= r', 8 LDS steps) and are written in order.  Per new replica over the whole
+// array, the same search took ~20 dependent global loads; per source, the writes of uneven copy numbers
+// were scattered and slower still.  As separate launches (sums, their scan, offsets, sources) 27 us at
+// 10^6 replicas and four launches of 4 us at 5 10^4; this 12 and 5.
+__global__ void __launch_bounds__(kScanTile) k_offsets(pa_state* base)
 {
     pa_state* st = base + blockIdx.y;
     if (st->status) return;
-    if ((int64_t)blockIdx.x * kScanTile >= st->capacity) return;  // grid sized for the largest run
-    __shared__ int64_t part[4];
     const int64_t R = st->R;
-    const int64_t tile0 = (int64_t)blockIdx.x * kScanTile;
-    int64_t acc = 0;
-    for (int t = threadIdx.x; t < kScanTile; t += blockDim.x)
-        if (tile0 + t < R) acc += st->counts[tile0 + t];
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int64_t* scan = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).scan);
-        scan[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+    const int64_t j0 = (int64_t)blockIdx.x * kScanTile;
+    if (j0 >= R) return;
+    __shared__ int64_t red[2][kScanTile / 64];
+    __shared__ int64_t off[kScanTile + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const WorkLayout wl = work_layout(st->N, st->n_bins, st->capacity);
+    const int64_t* sums = work_ptr<int64_t>(st, wl.scan);
+    const int tiles = (int)((R + kScanTile - 1) / kScanTile), mine = (int)blockIdx.x;
+    int64_t before = 0, total = 0;
+#pragma unroll 4
+    for (int i = tid; i < tiles; i += kScanTile) {
+        const int64_t v = sums[i];
+        total += v;
+        before += i < mine ? v : 0;
     }
-}
-
-// exclusive scan of the block sums (one block), total R~', capacity and extinction checks
-__global__ void __launch_bounds__(256) k_scan_top(pa_state* base)
-{
-    pa_state* st = base + blockIdx.y;
-    const int n_blocks = (int)((st->capacity + kScanTile - 1) / kScanTile);
-    if (st->status) return;
-    __shared__ int64_t carry_sh;
-    __shared__ int64_t wsum[4];
-    int64_t* scan = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).scan);
-    if (threadIdx.x == 0) carry_sh = 0;
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int i0 = 0; i0 < n_blocks; i0 += 256) {
-        const int i = i0 + threadIdx.x;
-        const int64_t v = i < n_blocks ? scan[i] : 0;
-        int64_t x = v;  // inclusive wave scan
-        for (int off = 1; off < 64; off <<= 1) {
-            const int64_t y = __shfl_up(x, off, 64);
-            if (lane >= off) x += y;
-        }
-        if (lane == 63) wsum[wv] = x;
-        __syncthreads();
-        int64_t pre = carry_sh;
-        for (int w = 0; w < wv; ++w) pre += wsum[w];
-        if (i < n_blocks) scan[i] = pre + x - v;
-        __syncthreads();
-        if (threadIdx.x == 255) carry_sh = pre + x;
-        __syncthreads();
+    for (int o = 32; o > 0; o >>= 1) {
+        total += __shfl_xor(total, o, 64);
+        before += __shfl_xor(before, o, 64);
     }
-    if (threadIdx.x == 0) {
-        const int64_t total = carry_sh;
+    if (lane == 0) {
+        red[0][wv] = total;
+        red[1][wv] = before;
+    }
+    __syncthreads();
+    total = before = 0;
+    for (int w = 0; w < kScanTile / 64; ++w) {
+        total += red[0][w];
+        before += red[1][w];
+    }
+    const bool over = total > st->capacity;
+    if (mine == 0 && tid == 0) {
         st->R_new = total;
-        if (total > st->capacity) st->status |= PA_FLAG_CAPACITY;
+        if (over) st->status |= PA_FLAG_CAPACITY;
         else if (total == 0) st->status |= PA_FLAG_EXTINCT;
     }
-}
-
-// offsets[j] = scan[tile] + exclusive scan inside the tile; offsets[R] = R~'
-__global__ void __launch_bounds__(256) k_scan_down(pa_state* base)
-{
-    pa_state* st = base + blockIdx.y;
-    if (st->status) return;
-    __shared__ int64_t wsum[4];
-    __shared__ int64_t carry_sh;
-    const int64_t R = st->R;
-    const int64_t tile0 = (int64_t)blockIdx.x * kScanTile;
-    if (tile0 >= R) return;
-    const int64_t* scan = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).scan);
-    if (threadIdx.x == 0) carry_sh = scan[blockIdx.x];
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int t0 = 0; t0 < kScanTile; t0 += 256) {
-        const int64_t j = tile0 + t0 + threadIdx.x;
-        const int64_t v = j < R ? st->counts[j] : 0;
-        int64_t x = v;
-        for (int off = 1; off < 64; off <<= 1) {
-            const int64_t y = __shfl_up(x, off, 64);
-            if (lane >= off) x += y;
-        }
-        if (lane == 63) wsum[wv] = x;
-        __syncthreads();
-        int64_t pre = carry_sh;
-        for (int w = 0; w < wv; ++w) pre += wsum[w];
-        if (j < R) st->offsets[j] = pre + x - v;
-        __syncthreads();
-        if (threadIdx.x == 255) carry_sh = pre + x;
-        __syncthreads();
+    if (over || total == 0) return;  // the same for every block
+    const int64_t j = j0 + tid;
+    const int64_t v = j < R ? st->counts[j] : 0;
+    int64_t x = v;  // inclusive wave scan
+    for (int o = 1; o < 64; o <<= 1) {
+        const int64_t y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
     }
-    if (tile0 + kScanTile >= R && threadIdx.x == 0) st->offsets[R] = st->R_new;
-}
-
-// source replica of each new replica, a block per 256 consecutive sources: their offsets go to LDS,
-// and the block's new replicas offsets[j0] .. offsets[j0 + 256] - 1 each find their source there
-// (largest j with offsets[j] <= r', 8 LDS steps) and are written in order.  Per new replica over
-// the whole array, the same search took ~20 dependent global loads; per source, the writes of
-// uneven copy numbers were scattered and slower still.
-__global__ void __launch_bounds__(256) k_src(pa_state* base)
-{
-    pa_state* st = base + blockIdx.y;
-    if (st->status) return;
-    const int64_t R = st->R;
-    const int64_t j0 = (int64_t)blockIdx.x * 256;
-    if (j0 >= R) return;
-    const int n = (int)(R - j0 < 256 ? R - j0 : 256);
-    __shared__ int64_t off[257];
-    for (int i = threadIdx.x; i <= n; i += 256) off[i] = st->offsets[j0 + i];  // offsets[R] = R~'
+    __syncthreads();  // red has been read
+    if (lane == 63) red[0][wv] = x;
     __syncthreads();
-    const int64_t A = off[0], B = off[n];
-    int32_t* src = work_ptr<int32_t>(st, work_layout(st->N, st->n_bins, st->capacity).src);
-    for (int64_t d = A + threadIdx.x; d < B; d += 256) {
+    int64_t pre = before;
+    for (int w = 0; w < wv; ++w) pre += red[0][w];
+    off[tid] = pre + x - v;
+    if (tid == kScanTile - 1) off[kScanTile] = pre + x;
+    if (j < R) st->offsets[j] = pre + x - v;
+    if (j == R - 1) st->offsets[R] = total;
+    __syncthreads();
+    const int n = (int)(R - j0 < kScanTile ? R - j0 : kScanTile);
+    int32_t* src = work_ptr<int32_t>(st, wl.src);
+    for (int64_t d = before + tid; d < off[n]; d += kScanTile) {
         int lo = 0, hi = n;  // off[lo] <= d < off[hi]
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
@@ -901,15 +875,11 @@ int launch_resample(const pa_run* runs, int n, const pa_step& step, hipStream_t 
     p.k = step.k;
     if (launch_resample_small(runs, n, p, s)) return hip_status(hipGetLastError());
     pa_state* base = runs[0].state;
-    const unsigned cap_blocks = (unsigned)((b.cap_max + 255) / 256);
-    const unsigned n_scan = (unsigned)((b.cap_max + kScanTile - 1) / kScanTile);
+    const unsigned tiles = (unsigned)((b.cap_max + kScanTile - 1) / kScanTile);
     launch_hist(runs, n, s);
     hipLaunchKernelGGL(k_normalise, dim3(1, n), dim3(256), 0, s, base, p);
-    hipLaunchKernelGGL(k_copies, dim3(cap_blocks, n), dim3(256), 0, s, base, (int32_t)step.k);
-    hipLaunchKernelGGL(k_scan_reduce, dim3(n_scan, n), dim3(256), 0, s, base);
-    hipLaunchKernelGGL(k_scan_top, dim3(1, n), dim3(256), 0, s, base);
-    hipLaunchKernelGGL(k_scan_down, dim3(n_scan, n), dim3(256), 0, s, base);
-    hipLaunchKernelGGL(k_src, dim3(cap_blocks, n), dim3(256), 0, s, base);
+    hipLaunchKernelGGL(k_copies, dim3(tiles, n), dim3(kScanTile), 0, s, base, (int32_t)step.k);
+    hipLaunchKernelGGL(k_offsets, dim3(tiles, n), dim3(kScanTile), 0, s, base);
     launch_gather(runs, n, s);
     hipLaunchKernelGGL(k_finish, dim3(1, n), dim3(1), 0, s, base, p);
     return hip_status(hipGetLastError());
@@ -1001,13 +971,13 @@ __global__ void __launch_bounds__(256) k_gauss_normalise(pa_state* base, Resampl
 }
 
 // copy numbers from the replica weights, drawn as in k_copies
-__global__ void __launch_bounds__(256) k_gauss_copies(pa_state* base, ResampleParams p)
+__global__ void __launch_bounds__(kScanTile) k_gauss_copies(pa_state* base, ResampleParams p)
 {
     pa_state* st = base + blockIdx.y;
     if (st->status) return;
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t R = st->R;
-    if (j - (int64_t)(threadIdx.x & 63) >= R) return;  // the whole wave past R
+    if ((int64_t)blockIdx.x * kScanTile >= R) return;  // the whole block past R
     const int64_t* misc = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).misc);
     const double S = *reinterpret_cast<const double*>(&misc[kMiscGaussS]);
     const double* w = reinterpret_cast<const double*>(st->energy[st->cur ^ 1]);
@@ -1022,7 +992,9 @@ __global__ void __launch_bounds__(256) k_gauss_copies(pa_state* base, ResamplePa
     const bool heavy = drawn && (q > 0 || m >= kCopiesHeavyM);
     int64_t n = drawn && !heavy ? copies_light(cd, m, keep) : 0;
     n = copies_heavy_by_wave(heavy, n, cd, m, q, keep);
-    if (live) st->counts[j] = (int32_t)min(n, (int64_t)INT32_MAX);
+    const int32_t c = (int32_t)min(n, (int64_t)INT32_MAX);
+    if (live) st->counts[j] = c;
+    tile_sum(st, live ? c : 0);
 }
 
 // runs: n runs with consecutive states on one stream (grid.y = run), or a single run
@@ -1038,16 +1010,13 @@ int launch_resample_gauss(const pa_run* runs, int n, const pa_step& step, hipStr
     int64_t cap = 0;
     for (int r = 0; r < n; ++r) cap = std::max<int64_t>(cap, runs[r].capacity);
     const unsigned cap_blocks = (unsigned)((cap + 255) / 256);
-    const unsigned n_scan = (unsigned)((cap + kScanTile - 1) / kScanTile);
+    const unsigned tiles = (unsigned)((cap + kScanTile - 1) / kScanTile);
     const unsigned ny = (unsigned)n;
     hipLaunchKernelGGL(k_gauss_min, dim3(1, ny), dim3(256), 0, s, base);
     hipLaunchKernelGGL(k_gauss_weights, dim3(cap_blocks, ny), dim3(256), 0, s, base, step.beta_to - step.beta_from);
     hipLaunchKernelGGL(k_gauss_normalise, dim3(1, ny), dim3(256), 0, s, base, p);
-    hipLaunchKernelGGL(k_gauss_copies, dim3(cap_blocks, ny), dim3(256), 0, s, base, p);
-    hipLaunchKernelGGL(k_scan_reduce, dim3(n_scan, ny), dim3(256), 0, s, base);
-    hipLaunchKernelGGL(k_scan_top, dim3(1, ny), dim3(256), 0, s, base);
-    hipLaunchKernelGGL(k_scan_down, dim3(n_scan, ny), dim3(256), 0, s, base);
-    hipLaunchKernelGGL(k_src, dim3(cap_blocks, ny), dim3(256), 0, s, base);
+    hipLaunchKernelGGL(k_gauss_copies, dim3(tiles, ny), dim3(kScanTile), 0, s, base, p);
+    hipLaunchKernelGGL(k_offsets, dim3(tiles, ny), dim3(kScanTile), 0, s, base);
     launch_gather(runs, n, s);
     hipLaunchKernelGGL(k_finish, dim3(1, ny), dim3(1), 0, s, base, p);
     return hip_status(hipGetLastError());
