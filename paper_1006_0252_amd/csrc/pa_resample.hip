@@ -372,7 +372,7 @@ __global__ void __launch_bounds__(kScanTile) k_copies(pa_state* base, int32_t k)
 // (largest j with offsets[j] <= r', 8 LDS steps) and are written in order.  Per new replica over the whole
 // array, the same search took ~20 dependent global loads; per source, the writes of uneven copy numbers
 // were scattered and slower still.  As separate launches (sums, their scan, offsets, sources) 27 us at
-// 10^6 replicas and four launches of 4 us at 5 10^4; this 12 and 5.
+// 10^6 replicas and four launches of 4 us at 5 10^4; this 18 and 5.
 __global__ void __launch_bounds__(kScanTile) k_offsets(pa_state* base)
 {
     pa_state* st = base + blockIdx.y;
@@ -468,28 +468,27 @@ __global__ void __launch_bounds__(256) k_gather_u8(pa_state* base)
     }
 }
 
-// bit-packed gather of one replica: loop over rows; a row word of replica j sits at
+// bit-packed gather of rows row0 .. row1 - 1 of one replica; a row word of replica j sits at
 // (j/64 * n_rows + rho) * 64 + j mod 64 (row words of 1, 2 or 4 bytes by lattice size)
 // (16 loads in flight per lane: one dependent load-store pair per row leaves the copy latency-
 // bound, a few hundred bytes in flight per wave against the microseconds of HBM latency)
 template <typename Wt>
-__device__ inline void gather_rows(const pa_state* st, int64_t j, int64_t rn, int n_rows)
+__device__ inline void gather_rows(const pa_state* st, int64_t j, int64_t rn, int n_rows, int row0, int row1)
 {
     constexpr int U = 16;
     const int cur = st->cur;
     const Wt* a = (const Wt*)st->spins[cur] + ((j >> 6) * n_rows) * 64 + (j & 63);
     Wt* b = (Wt*)st->spins[cur ^ 1] + ((rn >> 6) * n_rows) * 64 + (rn & 63);
-    int rho = 0;
-    for (; rho + U <= n_rows; rho += U) {
+    int rho = row0;
+    for (; rho + U <= row1; rho += U) {
         Wt v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) v[u] = a[(int64_t)(rho + u) * 64];
 #pragma unroll
         for (int u = 0; u < U; ++u) b[(int64_t)(rho + u) * 64] = v[u];
     }
-    for (; rho < n_rows; ++rho) b[(int64_t)rho * 64] = a[(int64_t)rho * 64];
+    for (; rho < row1; ++rho) b[(int64_t)rho * 64] = a[(int64_t)rho * 64];
 }
-
 
 // commit an accepted step: swap the buffers, accumulate ln Q (eq. sumQ) and write record[k]; a step
 // refused by a sticky flag leaves state and records as they were
@@ -522,7 +521,7 @@ __global__ void k_finish(pa_state* base, ResampleParams p)
 // Launch shapes cover the largest run of the call; grid.y indexes the runs, whose states
 // are contiguous (state r at runs[0].state + r).  A single run is n = 1.
 struct BatchShape {
-    int64_t cap_max = 0, bins_max = 0, stride_max = 0;
+    int64_t cap_max = 0, stride_max = 0, rows_max = 0;
 };
 
 static BatchShape batch_shape(const pa_run* runs, int n)
@@ -532,8 +531,8 @@ static BatchShape batch_shape(const pa_run* runs, int n)
         pa_sizes sz;
         pa_buffer_sizes(runs[r].dim, runs[r].L, runs[r].layout, runs[r].couplings, runs[r].capacity, runs[r].n_records, &sz);
         b.cap_max = std::max(b.cap_max, runs[r].capacity);
-        b.bins_max = std::max(b.bins_max, sz.n_bins);
         b.stride_max = std::max(b.stride_max, sz.row_stride);
+        b.rows_max = std::max<int64_t>(b.rows_max, runs[r].dim == 1 ? (runs[r].L + 31) / 32 : runs[r].L * runs[r].L);
     }
     return b;
 }
@@ -568,12 +567,16 @@ int launch_hist(const pa_run* runs, int n, hipStream_t s)
 // destination group that needs it (a group's sources straddle two source groups about a third of
 // the time).  A block whose sources span more than kStageGroups groups (large copy numbers next to
 // long runs of zeros) gathers per replica with gather_rows.
+// A replica's rows are split over the blocks of grid.z, whole passes each, up to kGatherBlocks blocks in
+// all: 2 10^4 replicas of L = 20 are 40 blocks of destinations, whose 400 rows in turn took 93 us (64 MB
+// moved), split 14; 10^6 of L = 16 have blocks enough and take 205 us (1.02 GB) either way.
+constexpr int kGatherBlocks = 2048;
 constexpr int kStageThreads = 512;  // destination replicas per block (eight bit-packed groups)
 constexpr int kStageGroups = 16;
 constexpr int kStageRows = 8;
 
 template <typename Wt>
-__device__ __forceinline__ void gather_staged(pa_state* st, uint4* stage)
+__device__ __forceinline__ void gather_staged(pa_state* st, int rows_per, uint4* stage)
 {
     constexpr int LPL = 64 * (int)sizeof(Wt) / 16;  // 16-byte pieces of a 64-replica row
     const int64_t R_new = st->R_new;
@@ -585,12 +588,15 @@ __device__ __forceinline__ void gather_staged(pa_state* st, uint4* stage)
     const bool valid = rn < R_new;
     const int64_t j = valid ? src[rn] : 0;
     const int n_rows = st->dim == 1 ? (st->N + 31) / 32 : st->L * st->L;
+    const int row0 = (int)blockIdx.z * rows_per, row1 = min(row0 + rows_per, n_rows);
+    if (row0 >= row1) return;  // a small lattice of a batch
+    const bool first = row0 == 0;  // moves the energies
     const int64_t g_lo = src[d0] >> 6, g_hi = src[d1] >> 6;  // the same for every thread
     const int cur = st->cur;
     if (g_hi - g_lo + 1 > kStageGroups) {
         if (valid) {
-            gather_rows<Wt>(st, j, rn, n_rows);
-            st->energy[cur ^ 1][rn] = st->energy[cur][j];
+            gather_rows<Wt>(st, j, rn, n_rows, row0, row1);
+            if (first) st->energy[cur ^ 1][rn] = st->energy[cur][j];
         }
         return;
     }
@@ -600,8 +606,8 @@ __device__ __forceinline__ void gather_staged(pa_state* st, uint4* stage)
     const Wt* S = reinterpret_cast<const Wt*>(stage);
     const int64_t jl = j - g_lo * 64;  // the source's place among the staged groups' replicas
     const int jg = (int)(jl >> 6), jo = (int)(jl & 63);
-    for (int r0 = 0; r0 < n_rows; r0 += kStageRows) {
-        const int nr = n_rows - r0 < kStageRows ? n_rows - r0 : kStageRows;
+    for (int r0 = row0; r0 < row1; r0 += kStageRows) {
+        const int nr = row1 - r0 < kStageRows ? row1 - r0 : kStageRows;
         // staged piece e: group e / (nr LPL), row r0 + (e / LPL) mod nr, piece e mod LPL
         for (int e = threadIdx.x; e < nsrc * nr * LPL; e += kStageThreads) {
             const int line = e / LPL, part = e - line * LPL;
@@ -614,20 +620,20 @@ __device__ __forceinline__ void gather_staged(pa_state* st, uint4* stage)
         }
         __syncthreads();
     }
-    if (valid) st->energy[cur ^ 1][rn] = st->energy[cur][j];
+    if (valid && first) st->energy[cur ^ 1][rn] = st->energy[cur][j];
 }
 
-// one block of kStageThreads destinations of run blockIdx.y; the row word's width is the run's (a
+// one block of kStageThreads destinations of run blockIdx.y and a slice of its rows; the row word's width is the run's (a
 // batch may mix lattice sizes), the staging buffer sized for the widest
-__global__ void __launch_bounds__(kStageThreads) k_gather_bits_staged(pa_state* base)
+__global__ void __launch_bounds__(kStageThreads, 8) k_gather_bits_staged(pa_state* base, int rows_per)
 {
     __shared__ uint4 stage[kStageGroups * kStageRows * 16];
     pa_state* st = base + blockIdx.y;
     if (st->status) return;
     const int WB = st->dim == 1 ? 4 : (st->L <= 8 ? 1 : (st->L <= 16 ? 2 : 4));
-    if (WB == 1) gather_staged<uint8_t>(st, stage);
-    else if (WB == 2) gather_staged<uint16_t>(st, stage);
-    else gather_staged<uint32_t>(st, stage);
+    if (WB == 1) gather_staged<uint8_t>(st, rows_per, stage);
+    else if (WB == 2) gather_staged<uint16_t>(st, rows_per, stage);
+    else gather_staged<uint32_t>(st, rows_per, stage);
 }
 
 static void launch_gather(const pa_run* runs, int n, hipStream_t s)
@@ -638,8 +644,12 @@ static void launch_gather(const pa_run* runs, int n, hipStream_t s)
         const int64_t threads = b.cap_max * (b.stride_max / 16);
         hipLaunchKernelGGL(k_gather_u8, dim3((unsigned)((threads + 255) / 256), n), dim3(256), 0, s, base);
     } else {
-        const unsigned blocks = (unsigned)((b.cap_max + kStageThreads - 1) / kStageThreads);
-        hipLaunchKernelGGL(k_gather_bits_staged, dim3(blocks, n), dim3(kStageThreads), 0, s, base);
+        const int64_t blocks = (b.cap_max + kStageThreads - 1) / kStageThreads;
+        const int64_t passes = (b.rows_max + kStageRows - 1) / kStageRows;
+        const int64_t slices = std::max<int64_t>(1, std::min(passes, kGatherBlocks / (blocks * n)));
+        const int64_t per = (passes + slices - 1) / slices;  // passes of a slice
+        const dim3 grid((unsigned)blocks, n, (unsigned)((passes + per - 1) / per));
+        hipLaunchKernelGGL(k_gather_bits_staged, grid, dim3(kStageThreads), 0, s, base, (int)per * kStageRows);
     }
 }
 
