@@ -9,8 +9,10 @@
 // with one bound).  Lane = replica, so the words' call indices are the same over a wave.
 //
 // Bound by the vector ALU where the population fills the chip (6.9 instructions per attempt, Philox 4.7)
-// and by a wave's own chain of instructions where it does not.  The generic kernel takes a site at a
-// time and moves byte rows a byte at a time: N = 64, 5 sweeps, 1000 replicas 29 us, 200 runs of them 80.
+// and by a wave's own chain of instructions where it does not (hence the second pair of kernels, with a
+// lane per call).  The generic kernel takes a site at a
+// time and moves byte rows a byte at a time: N = 64, 5 sweeps, 1000 replicas 29 us (here
+// 5 us), 200 runs of them 80 (here 24).
 #include "pa_common.h"
 #include "pa_host.h"
 #include "pa_sweep_strings.h"
@@ -215,10 +217,233 @@ __global__ void __launch_bounds__(64 * kWaves) k_sweep_chain(const pa_state* __r
     if (wave == 0 && valid) st->energy[st->cur][r] = N - 2 * neg_sum[lane];
 }
 
+// 16 consecutive sites (byte i of word k's two strings) of a replica's rows
+template <int LAYOUT>
+__device__ __forceinline__ void load_piece(const uint8_t* rows, int stride, int n_rows, int k, int i, uint32_t* ev, uint32_t* od)
+{
+    *ev = *od = 0;
+    if constexpr (LAYOUT == PA_U8) {
+        if (64 * k + 16 * i >= stride) return;
+        const uint4 q = *reinterpret_cast<const uint4*>(rows + 64 * k + 16 * i);
+        *ev = pack4(__builtin_amdgcn_perm(q.y, q.x, 0x06040200u)) | (pack4(__builtin_amdgcn_perm(q.w, q.z, 0x06040200u)) << 4);
+        *od = pack4(__builtin_amdgcn_perm(q.y, q.x, 0x07050301u)) | (pack4(__builtin_amdgcn_perm(q.w, q.z, 0x07050301u)) << 4);
+    } else {
+        const int row = 2 * k + (i >> 1);
+        if (row >= n_rows) return;
+        *ev = split_row(reinterpret_cast<const uint32_t*>(rows)[64 * row] >> (16 * (i & 1)) & 0xFFFFu, od);
+    }
+}
+
+// the same sites back from the whole words (bit-packed: one store per row, by its first piece)
+template <int LAYOUT>
+__device__ __forceinline__ void store_piece(uint8_t* rows, int stride, int n_rows, int k, int i, uint32_t ev, uint32_t od)
+{
+    if constexpr (LAYOUT == PA_U8) {
+        if (64 * k + 16 * i >= stride) return;
+        const uint32_t e0 = unpack4(ev >> (8 * i)), o0 = unpack4(od >> (8 * i));
+        const uint32_t e1 = unpack4(ev >> (8 * i + 4)), o1 = unpack4(od >> (8 * i + 4));
+        *reinterpret_cast<uint4*>(rows + 64 * k + 16 * i) =
+            make_uint4(__builtin_amdgcn_perm(o0, e0, 0x05010400u), __builtin_amdgcn_perm(o0, e0, 0x07030602u),
+                       __builtin_amdgcn_perm(o1, e1, 0x05010400u), __builtin_amdgcn_perm(o1, e1, 0x07030602u));
+    } else {
+        const int row = 2 * k + (i >> 1);
+        if ((i & 1) || row >= n_rows) return;
+        reinterpret_cast<uint32_t*>(rows)[64 * row] = merge_row((ev >> (8 * i)) & 0xFFFFu, (od >> (8 * i)) & 0xFFFFu);
+    }
+}
+
+// byte i of one colour's updated word k: one call
+template <int MODE>
+__device__ __forceinline__ uint32_t update_byte(uint32_t w, uint32_t cand, int k, int i, int col, const Lane& c, const Thr& th)
+{
+    const uint32_t call = (uint32_t)(4 * k + i);
+    const uint32_t nb = decide_word<MODE, false, 1>((w >> (8 * i)) & 0xFFu, 0u, 0u, (cand >> (8 * i)) & 0xFFu, call, 1u, nullptr,
+                                                    c, th, [&]() { return WordSites{call, 1u, 16u * call, 16u, col ? 0xFFFFFFFFu : 0u}; });
+    return nb & 0xFFu;
+}
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
+}
+
+// A lane per call instead of one per replica, where the population has too few groups to fill the chip.
+// Up to 128 sites: four or eight neighbouring lanes hold the replica's words, each decides its byte, and
+// the lanes put the word together among themselves.  NW: words per colour; a block of kWaves waves takes
+// 256 / (4 NW) replicas.
+template <int NW, int MODE, int LAYOUT>
+__global__ void __launch_bounds__(64 * kWaves) k_sweep_chain_short_split(const pa_state* __restrict__ base, SweepParams p, Thr th)
+{
+    constexpr int LPR = 4 * NW;
+    const pa_state* __restrict__ st = base + blockIdx.y;
+    const int64_t R = st->R, r = ((int64_t)blockIdx.x * (64 * kWaves) + threadIdx.x) / LPR;
+    if (st->status || ((int64_t)blockIdx.x * (64 * kWaves) + (threadIdx.x & ~63u)) / LPR >= R) return;  // the whole wave
+    const int N = st->N, n_rows = (N + 31) / 32, stride = st->row_stride;
+    const int l = threadIdx.x % LPR, k = l >> 2, i = l & 3;  // this lane's word and byte
+    const int end = (N / 2 - 1) & 31;  // the last site's bit in the last word
+    const bool last = k + 1 == NW;
+    const uint32_t sites = last ? 0xFFFFFFFFu >> (31 - end) : 0xFFFFFFFFu;
+    uint8_t* rows = replica_rows<LAYOUT>(st, r < R ? r : R - 1, n_rows);
+    // the two colours' words: this lane's, and the replica's other one (the same where there is one)
+    uint32_t own[2], oth[2], j[3];
+    auto whole = [&](uint32_t byte) {  // the word of the quad's bytes
+        uint32_t x = byte << (8 * i);
+        x |= dpp<0xB1>(x);
+        x |= dpp<0x4E>(x);
+        return x;
+    };
+    auto other = [&](uint32_t v) { return NW == 1 ? v : dpp<0x141>(v); };
+    load_piece<LAYOUT>(rows, stride, n_rows, k, i, &own[0], &own[1]);
+#pragma unroll
+    for (int col = 0; col < 2; ++col) {
+        own[col] = whole(own[col]) & sites;
+        oth[col] = other(own[col]);
+    }
+    {
+        uint32_t m[NW][3];
+#pragma unroll
+        for (int q = 0; q < NW; ++q) bond_masks(st->J, N, q, threadIdx.x & 63, m[q]);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) j[d] = last ? m[NW - 1][d] : m[0][d];
+    }
+    // the other word's bit that comes in at the top (up) and at the bottom (down) of a shifted word
+    const int top = last ? end : 31, bottom = k > 0 ? 31 : end;
+    Lane c;
+    c.rr = (uint32_t)r;
+    c.k0 = (uint32_t)st->seed;
+    c.k1 = (uint32_t)(st->seed >> 32);
+    for (int t = 0; t < p.n_sweeps; ++t) {
+#pragma unroll
+        for (int col = 0; col < 2; ++col) {
+            c.ctr2 = (uint32_t)(2 * (p.t0 + t) + col);
+            const uint32_t w = own[col], a = own[col ^ 1], o = oth[col ^ 1];
+            const uint32_t b0 = xor3(w, a, j[0]);
+            const uint32_t b1 = col ? xor3(w, (a >> 1) | (o << top), j[1]) : xor3(w, (a << 1) | (o >> bottom), j[2]);
+            own[col] = select_bits(sites, whole(update_byte<MODE>(w, b0 & b1 & sites, k, i, col, c, th)), w);
+            oth[col] = other(own[col]);
+        }
+    }
+    int neg = __popc(xor3(own[0], own[1], j[0]) & sites) +
+              __popc(xor3(own[1], (own[0] >> 1) | (oth[0] << top), j[1]) & sites);
+    neg += NW == 1 ? 0 : (int)dpp<0x141>((uint32_t)neg);
+    if (r >= R) return;
+    store_piece<LAYOUT>(rows, stride, n_rows, k, i, own[0], own[1]);
+    if (l == 0) st->energy[st->cur][r] = N - 2 * neg;
+}
+
+// Longer chains: Q replicas per block, their words in LDS ([colour][word][replica]), each byte of a colour
+// taken by one thread.  Q = 16 where 16 calls are all of a colour (up to 256 sites), else 4 (N = 1024, 1000
+// replicas, five sweeps: 16 replicas a block 22.4 us, 8 15.9, 4 11.7).
+template <int Q, int MODE, int LAYOUT>
+__global__ void __launch_bounds__(64 * kWaves) k_sweep_chain_split(const pa_state* __restrict__ base, SweepParams p, Thr th)
+{
+    constexpr int UNITS = 64 * kWaves / Q;
+    extern __shared__ uint32_t lds[];
+    const pa_state* __restrict__ st = base + blockIdx.y;
+    const int q = threadIdx.x % Q, unit = threadIdx.x / Q;
+    const int64_t R = st->R, r0 = (int64_t)blockIdx.x * Q, r = r0 + q;
+    if (st->status || r0 >= R) return;  // the same for the whole block
+    const int N = st->N, n_rows = (N + 31) / 32, stride = st->row_stride, NW = (N / 2 + 31) / 32;
+    const int calls = (N / 2 + 7) / 8, end = (N / 2 - 1) & 31;
+    const uint32_t last_sites = 0xFFFFFFFFu >> (31 - end);
+    uint32_t* S0 = lds + q;
+    uint32_t* S1 = S0 + NW * Q;
+    uint32_t* masks = lds + 2 * NW * Q;
+    int* neg_sum = reinterpret_cast<int*>(masks + 4 * NW);
+    if (threadIdx.x < Q) neg_sum[threadIdx.x] = 0;
+    uint8_t* rows = replica_rows<LAYOUT>(st, r < R ? r : R - 1, n_rows);
+    for (int b = unit; b < 4 * NW; b += UNITS) {  // bytes past the last site are zero
+        const int k = b >> 2, i = b & 3;
+        const uint32_t in = ((k + 1 < NW ? 0xFFFFFFFFu : last_sites) >> (8 * i)) & 0xFFu;
+        uint32_t ev, od;
+        load_piece<LAYOUT>(rows, stride, n_rows, k, i, &ev, &od);
+        reinterpret_cast<uint8_t*>(S0 + k * Q)[i] = (uint8_t)(ev & in);
+        reinterpret_cast<uint8_t*>(S1 + k * Q)[i] = (uint8_t)(od & in);
+    }
+    for (int k = threadIdx.x >> 6; k < NW; k += kWaves) {
+        const int lane = threadIdx.x & 63;
+        uint32_t j[3];
+        bond_masks(st->J, N, k, lane, j);
+        if (lane < 3) masks[4 * k + lane] = lane == 0 ? j[0] : (lane == 1 ? j[1] : j[2]);
+    }
+    __syncthreads();
+    auto up = [&](const uint32_t* S, int k, uint32_t a) {
+        return k + 1 < NW ? __builtin_amdgcn_alignbit(S[(k + 1) * Q], a, 1) : (a >> 1) | (S[0] << end);
+    };
+    auto down = [&](const uint32_t* S, int k, uint32_t a) {
+        return k > 0 ? __builtin_amdgcn_alignbit(a, S[(k - 1) * Q], 31) : (a << 1) | (S[(NW - 1) * Q] >> end);
+    };
+    Lane c;
+    c.rr = (uint32_t)r;
+    c.k0 = (uint32_t)st->seed;
+    c.k1 = (uint32_t)(st->seed >> 32);
+    for (int t = 0; t < p.n_sweeps; ++t) {
+#pragma unroll
+        for (int col = 0; col < 2; ++col) {
+            c.ctr2 = (uint32_t)(2 * (p.t0 + t) + col);
+            uint32_t* W = col ? S1 : S0;
+            const uint32_t* O = col ? S0 : S1;
+            // a thread writes only its byte of a word, and the byte's other readers in this phase use
+            // their own bytes of it alone
+#pragma unroll 1
+            for (int b = unit; b < calls; b += UNITS) {
+                const int k = b >> 2, i = b & 3;
+                const uint32_t w = W[k * Q], a = O[k * Q];
+                const uint32_t* j = masks + 4 * k;
+                const uint32_t b0 = xor3(w, a, j[0]);
+                const uint32_t b1 = col ? xor3(w, up(O, k, a), j[1]) : xor3(w, down(O, k, a), j[2]);
+                const uint32_t sites = k + 1 < NW ? 0xFFFFFFFFu : last_sites;
+                const uint32_t x = update_byte<MODE>(w, b0 & b1 & sites, k, i, col, c, th);
+                reinterpret_cast<uint8_t*>(W + k * Q)[i] = (uint8_t)select_bits(sites >> (8 * i), x, w >> (8 * i));
+            }
+            __syncthreads();
+        }
+    }
+    int neg = 0;
+    for (int b = unit; b < 4 * NW; b += UNITS) {
+        const int k = b >> 2, i = b & 3;
+        const uint32_t a = S0[k * Q], d = S1[k * Q];
+        if (i == 0) {
+            const uint32_t in = k + 1 < NW ? 0xFFFFFFFFu : last_sites;
+            neg += __popc(xor3(a, d, masks[4 * k]) & in) + __popc(xor3(d, up(S0, k, a), masks[4 * k + 1]) & in);
+        }
+        if (r < R) store_piece<LAYOUT>(rows, stride, n_rows, k, i, a, d);
+    }
+    if (neg) atomicAdd(&neg_sum[q], neg);
+    __syncthreads();
+    if (threadIdx.x < Q && r < R) st->energy[st->cur][r] = N - 2 * neg_sum[q];
+}
+
+// Where the population (its capacity, in groups of 64, over the runs of the call) is too small for a lane
+// per replica to fill the chip, a lane per call (five sweeps at beta 0.5, capacities 1.5 times 1000 replicas
+// a run, lane per replica and per call).  Chains of up to 128 sites, more than one call: N = 64, 1 run 10.4
+// and 7.4 us, 32 runs (800 groups) 11.6 and 10.0, 64 runs (1600) 15.3 and 12.9, 100 runs 15.9 and 16.6; N = 128,
+// 1 run 16.1 and 7.8, 64 runs 25.4 and 18.6; N = 16 has one call and gains nothing (7.1 and 7.4).  Longer
+// ones: N = 200, 1 run 14.2 and 10.3, 8 runs (200 groups) 15.0 and 13.0, 16 runs 17.5 and 17.6; N = 1024, 1 run 39
+// and 11.7, 8 runs 40.8 and 25.2.
+constexpr int64_t kSplitShort = 1536, kSplitLong = 256;
+
 template <int MODE, int LAYOUT>
 static void launch(int N, const pa_state* base, int n, int64_t cap, const SweepParams& p, const Thr& th, hipStream_t s)
 {
     const int calls = (N / 2 + 7) / 8;
+    const int NW = (N / 2 + 31) / 32;
+    const int64_t groups = n * (cap / 64);
+    if (NW <= 2 && calls > 1 && groups <= kSplitShort) {
+        const dim3 b(64 * kWaves), g((unsigned)((cap * 4 * NW + b.x - 1) / b.x), (unsigned)n);
+        if (NW == 1) hipLaunchKernelGGL((k_sweep_chain_short_split<1, MODE, LAYOUT>), g, b, 0, s, base, p, th);
+        else hipLaunchKernelGGL((k_sweep_chain_short_split<2, MODE, LAYOUT>), g, b, 0, s, base, p, th);
+        return;
+    }
+    if (NW > 2 && groups <= kSplitLong) {
+        const int Q = calls <= 16 ? 16 : 4;
+        const size_t lds = ((size_t)2 * NW * Q + 4 * NW + Q) * 4;
+        const dim3 b(64 * kWaves), g((unsigned)(cap / Q), (unsigned)n);
+        if (Q == 16) hipLaunchKernelGGL((k_sweep_chain_split<16, MODE, LAYOUT>), g, b, lds, s, base, p, th);
+        else hipLaunchKernelGGL((k_sweep_chain_split<4, MODE, LAYOUT>), g, b, lds, s, base, p, th);
+        return;
+    }
     const dim3 b(64 * kWaves), g((unsigned)((cap / 64 + kWaves - 1) / kWaves), (unsigned)n);
     switch (calls) {
         case 1: hipLaunchKernelGGL((k_sweep_chain_short<1, MODE, LAYOUT>), g, b, 0, s, base, p, th); return;
@@ -231,7 +456,6 @@ static void launch(int N, const pa_state* base, int n, int64_t cap, const SweepP
         case 8: hipLaunchKernelGGL((k_sweep_chain_short<8, MODE, LAYOUT>), g, b, 0, s, base, p, th); return;
         default: break;
     }
-    const int NW = (N / 2 + 31) / 32;
     const size_t lds = ((size_t)2 * NW * 64 + 4 * NW + 64) * 4;
     hipLaunchKernelGGL((k_sweep_chain<MODE, LAYOUT>), dim3((unsigned)(cap / 64), (unsigned)n), b, lds, s, base, p, th);
 }
