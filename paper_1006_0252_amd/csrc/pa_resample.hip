@@ -164,6 +164,23 @@ struct ResampleParams {
     int32_t k;
 };
 
+// S plus x[0 .. n - 1] in order by one thread, 16 LDS loads ahead of the chain of dependent additions
+__device__ inline double add_in_order(double S, const double* x, int n)
+{
+    int i = 0;
+    for (; i + 16 <= n; i += 16) {
+        double c[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) c[u] = x[i + u];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) S = S + c[u];
+    }
+    for (; i < n; ++i) S = S + x[i];
+    return S;
+}
+
+constexpr int kNoCopies = 1000;  // the level of a bin of zero weight: no draws, copy number 0
+
 // smallest m in [kLadderMin, kLadderMax] with 2^m >= x (0 < x <= 64)
 __device__ inline int ladder_level(double x)
 {
@@ -197,8 +214,7 @@ __global__ void __launch_bounds__(256) k_normalise(pa_state* base, ResampleParam
         const int cnt = min(1024, n - b0);
         for (int t = threadIdx.x; t < cnt; t += blockDim.x) prod[t] = (double)hist[ilo + b0 + t] * p.w[b0 + t];
         __syncthreads();
-        if (threadIdx.x == 0)
-            for (int t = 0; t < cnt; ++t) S = S + prod[t];
+        if (threadIdx.x == 0) S = add_in_order(S, prod, cnt);
         __syncthreads();
     }
     if (threadIdx.x == 0) S_sh = S;
@@ -224,7 +240,7 @@ __global__ void __launch_bounds__(256) k_normalise(pa_state* base, ResampleParam
         const int b = ilo + t;
         if (!(lam > 0.0)) {
             bin_q[b] = 0;
-            bin_m[b] = 1000;  // no draws: copy number 0
+            bin_m[b] = kNoCopies;
             bin_keep[b] = 0;
             continue;
         }
@@ -241,19 +257,35 @@ __global__ void __launch_bounds__(256) k_normalise(pa_state* base, ResampleParam
     }
 }
 
-// the smallest n with u < C[n] (C non-decreasing, its last entries 2^32 > u).  Small means walk
-// the table from 0 (a few steps); from 2^3 on, a branch-free binary search: n counts the entries
-// <= u, eight dependent loads instead of about 2^m (a Poisson(64) block took ~64)
-__device__ inline int64_t invert_ladder(int m, uint32_t u)
+// Poisson(2^m) by inversion: the smallest n with u < C[n] (C non-decreasing, its last entries 2^32 > u).
+// The first 16 entries of the levels below 2^3, less one so that they fit 32 bits, are kept in LDS: eight
+// at a time in two loads, counting the entries below u; a walk through the table waits out a load per
+// step.  From 2^3 on, a branch-free binary search: n counts the entries <= u.
+constexpr int kLowLevels = 3 - kLadderMin, kLowEntries = 16;
+
+__device__ inline void load_low(uint32_t* low)
+{
+    for (int i = threadIdx.x; i < kLowLevels * kLowEntries; i += blockDim.x)
+        low[i] = (uint32_t)(g_ladder[i / kLowEntries][i % kLowEntries] - 1);
+}
+
+__device__ inline int invert_ladder(int m, uint32_t u, const uint32_t* low)
 {
     const uint64_t* C = g_ladder[m - kLadderMin];
+    int n = 0;
     if (m < 3) {
-        int64_t n = 0;
-        while (!((uint64_t)u < C[n])) ++n;
+        const uint4* L = reinterpret_cast<const uint4*>(low + (m - kLadderMin) * kLowEntries);
+#pragma unroll
+        for (int i = 0; i < kLowEntries / 8; ++i) {
+            if (n < 8 * i) break;
+            const uint4 a = L[2 * i], b = L[2 * i + 1];
+            n += (u > a.x) + (u > a.y) + (u > a.z) + (u > a.w) + (u > b.x) + (u > b.y) + (u > b.z) + (u > b.w);
+        }
+        if (n == kLowEntries)
+            while (!((uint64_t)u < C[n])) ++n;
         return n;
     }
     static_assert(kLadderCap == 256, "binary search over 256 entries");
-    int n = 0;
 #pragma unroll
     for (int step = 128; step > 0; step >>= 1)
         if (C[n + step - 1] <= (uint64_t)u) n += step;
@@ -263,56 +295,53 @@ __device__ inline int64_t invert_ladder(int m, uint32_t u)
 // Copy numbers: replica j's Poisson(lambda_j) count at step k is the sum of q Poisson(64) blocks and
 // a Poisson(2^m) count K thinned by K draws against keep = rem 2^(32 - m).  Draw d (blocks d = 0 ..
 // q - 1, K at d = q, the thinning draws at d = q + 1 ..) is word d mod 4 of Philox(d / 4, j, k, 4).
-// Light lanes (no blocks, 2^m < 16) draw in turn; the wave takes each heavy lane's draws
-// together, spread over its 64 lanes (the draws are counter-based, so any lane can make any of
-// them, and the count is an integer sum), instead of waiting for one lane to make them one by one.
-constexpr int kCopiesHeavyM = 4;
+// Every lane finds its own K, and thins it itself up to kOwnDraws draws (most in the call that gave K);
+// the wave takes the other lanes' draws together, a call per lane (the draws are counter-based, so any lane
+// can make any of them, and the count is an integer sum).
+// Walking the table in global memory draw by draw, with the wave on each lane of mean 8 and more in turn:
+// 5 10^4 replicas of L = 8 at beta 0 14 us, 2 10^4 of L = 20 at beta 3 28 us, 10^6 of L = 16 31 us; this 9, 6.5, 22.
+constexpr int kOwnDraws = 27;
 
 struct CopyDraws {
     uint32_t j, k, k0, k1;
-    __device__ uint32_t at(uint32_t d) const
-    {
-        return word_of(philox10(d >> 2, j, k, kTagPoisson, k0, k1), (int)(d & 3));
-    }
+    __device__ uint4v call(uint32_t c) const { return philox10(c, j, k, kTagPoisson, k0, k1); }
 };
 
-__device__ inline int64_t copies_light(const CopyDraws& cd, int m, uint64_t keep)
+// every lane of the wave calls this (lanes without a replica or copies with drawn = false); v0: call 0, made
+// while the loads that lead to lambda are in flight
+__device__ inline int64_t draw_copies(bool drawn, const CopyDraws& mine, uint4v v0, int m, int64_t q, uint64_t keep,
+                                      const uint32_t* low)
 {
-    uint32_t d = 0;
-    uint4v v = {0, 0, 0, 0};
-    auto draw = [&]() -> uint32_t {
-        if ((d & 3) == 0) v = philox10(d >> 2, cd.j, cd.k, kTagPoisson, cd.k0, cd.k1);
-        const uint32_t u = word_of(v, d & 3);
-        ++d;
-        return u;
-    };
-    const int64_t K = invert_ladder(m, draw());
     int64_t n = 0;
-    for (int64_t e = 0; e < K; ++e)
-        if ((uint64_t)draw() < keep) ++n;
-    return n;
-}
-
-// every lane of the wave calls this (lanes without a replica with heavy = false); returns the
-// count of a heavy lane's replica, n unchanged elsewhere
-__device__ inline int64_t copies_heavy_by_wave(bool heavy, int64_t n, const CopyDraws& mine, int m, int64_t q,
-                                               uint64_t keep)
-{
-    const int lane = (int)(threadIdx.x & 63);
-    uint64_t todo = __ballot(heavy);
+    int K = 0;
+    if (drawn) {
+        uint4v v = q < 4 ? v0 : mine.call((uint32_t)q >> 2);
+        K = invert_ladder(m, word_of(v, (int)(q & 3)), low);
+        if (q == 0 && K <= kOwnDraws) {
+            n = (K > 0 && v.y < keep) + (K > 1 && v.z < keep) + (K > 2 && v.w < keep);
+            for (int d = 4; d <= K; d += 4) {
+                v = mine.call((uint32_t)d >> 2);
+                n += (v.x < keep) + (d + 1 <= K && v.y < keep) + (d + 2 <= K && v.z < keep) + (d + 3 <= K && v.w < keep);
+            }
+        }
+    }
+    uint64_t todo = __ballot(drawn && (q > 0 || K > kOwnDraws));
     while (todo) {
-        const int h = __builtin_ctzll(todo);
+        const int lane = (int)(threadIdx.x & 63), h = __builtin_ctzll(todo);
         todo &= todo - 1;
         CopyDraws cd = mine;
         cd.j = (uint32_t)__shfl((int)mine.j, h, 64);
-        const int mh = __shfl(m, h, 64);
         const int64_t qh = __shfl(q, h, 64);
         const uint64_t keeph = (uint64_t)__shfl((int64_t)keep, h, 64);
+        const int64_t d0 = qh + 1, d1 = qh + __shfl(K, h, 64);  // the thinning draws
         int64_t part = 0;
-        for (int64_t blk = lane; blk < qh; blk += 64) part += invert_ladder(kLadderMax, cd.at((uint32_t)blk));
-        const int64_t K = invert_ladder(mh, cd.at((uint32_t)qh));
-        for (int64_t e = lane; e < K; e += 64)
-            if ((uint64_t)cd.at((uint32_t)(qh + 1 + e)) < keeph) ++part;
+        for (int64_t blk = lane; blk < qh; blk += 64)
+            part += invert_ladder(kLadderMax, word_of(cd.call((uint32_t)blk >> 2), (int)(blk & 3)), low);
+        for (int64_t c = (d0 >> 2) + lane; 4 * c <= d1; c += 64) {
+            const uint4v v = cd.call((uint32_t)c);
+#pragma unroll
+            for (int w = 0; w < 4; ++w) part += 4 * c + w >= d0 && 4 * c + w <= d1 && word_of(v, w) < keeph;
+        }
         for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
         if (lane == h) n = part;
     }
@@ -339,27 +368,28 @@ __global__ void __launch_bounds__(kScanTile) k_copies(pa_state* base, int32_t k)
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t R = st->R;
     if ((int64_t)blockIdx.x * kScanTile >= R) return;  // the whole block past R
+    __shared__ __attribute__((aligned(16))) uint32_t low[kLowLevels * kLowEntries];
+    load_low(low);
     const WorkLayout wl = work_layout(st->N, st->n_bins, st->capacity);
     const int64_t* bin_q = work_ptr<int64_t>(st, wl.bin_q);
     const uint64_t* bin_keep = work_ptr<uint64_t>(st, wl.bin_keep);
     const int32_t* bin_m = work_ptr<int32_t>(st, wl.bin_m);
     const bool live = j < R;
-    int m = 1000;  // bins of zero weight carry m = 1000: no copies
+    const CopyDraws cd = {(uint32_t)j, (uint32_t)k, (uint32_t)st->seed, (uint32_t)(st->seed >> 32)};
+    const uint4v v0 = cd.call(0);
+    int m = kNoCopies;
     int64_t q = 0;
     uint64_t keep = 0;
     if (live) {
         const int b = (st->energy[st->cur][j] - st->E_base) >> 2;
         m = bin_m[b];
-        if (m != 1000) {
+        if (m != kNoCopies) {
             q = bin_q[b];
             keep = bin_keep[b];
         }
     }
-    const CopyDraws cd = {(uint32_t)j, (uint32_t)k, (uint32_t)st->seed, (uint32_t)(st->seed >> 32)};
-    const bool drawn = live && m != 1000;
-    const bool heavy = drawn && (q > 0 || m >= kCopiesHeavyM);
-    int64_t n = drawn && !heavy ? copies_light(cd, m, keep) : 0;
-    n = copies_heavy_by_wave(heavy, n, cd, m, q, keep);
+    __syncthreads();
+    const int64_t n = draw_copies(live && m != kNoCopies, cd, v0, m, q, keep, low);
     const int32_t c = (int32_t)min(n, (int64_t)INT32_MAX);
     if (live) st->counts[j] = c;
     tile_sum(st, live ? c : 0);
@@ -654,14 +684,20 @@ static void launch_gather(const pa_run* runs, int n, hipStream_t s)
 }
 
 // ------------------------------------------------------------------ small populations
-// +-1 runs of up to kSmallCap replicas and kSmallBins energy bins (every run of the call): a block per run does the whole resampling with the population's energies, weights, copy
-// numbers and offsets in registers and LDS.  The chain of kernels above is bound by its launches there:
-// ten of 3 to 5 us each for a few us of work (1000 rings of 64 sites: 36 us a step, this 13 us; the 200 runs
-// of that ensemble 50 us, this 17 us).  Same histogram, sums in the same order, same draws.
+// +-1 runs of up to kSmallCap replicas and kSmallBins energy bins (every run of the call): a block per run
+// does the whole resampling with the population's energies, weights, copy numbers and offsets in
+// registers and LDS.  The chain of kernels above is bound by its launches there: ten of 3 to 5 us each for
+// a few us of work (1000 rings of 64 sites: 36 us a step, this 9 us; the 200 runs of that ensemble 50 us,
+// this 12 us).  Same histogram, sums in the same order, same draws.
+// Bound by its own chain of latencies, so everything it reads is asked for at once: the state's fields
+// (one by one where they are used, 14 us), energies, weights, rows; the replicas' first draws are made
+// meanwhile.
 // GATHER: the block also moves the rows and commits the step (byte rows of up to kSmallRows bytes per
 // run); otherwise it leaves the source map and the step's ln Q and S for the gather kernel and k_finish.
 constexpr int kSmallCap = 4096, kSmallBins = 8192, kSmallThreads = 1024, kSmallPer = kSmallCap / kSmallThreads;
 constexpr int64_t kSmallRows = 192 << 10;
+constexpr int kStagePieces = 4096;  // 16-byte pieces of rows kept in LDS (64 KB)
+constexpr int kCommit = kSmallThreads - 1;  // the thread of the step's one-thread work, in the wave with the fewest replicas
 
 // the parts of mean copy number lam: Poisson(64) blocks q, ladder level m and thinning threshold keep;
 // false (no copies) unless lam > 0
@@ -679,49 +715,88 @@ __device__ inline bool poisson_parts(double lam, int* m, int64_t* q, uint64_t* k
     return true;
 }
 
-template <typename T, class F>
-__device__ __forceinline__ T block_reduce(T x, T* red, F f)
+// x combined over the wave's lanes up to each lane (DPP): a lane without a source combines with none
+template <int CTRL, int ROWS, class F>
+__device__ __forceinline__ int dpp_step(int x, int none, F f)
 {
-    for (int o = 32; o > 0; o >>= 1) x = f(x, __shfl_xor(x, o, 64));
-    __syncthreads();  // red may be in use
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
-    __syncthreads();
-    T v = red[0];
-    for (int w = 1; w < kSmallThreads / 64; ++w) v = f(v, red[w]);
-    return v;
+    return f(x, __builtin_amdgcn_update_dpp(none, x, CTRL, ROWS, 0xF, false));
 }
+
+template <class F>
+__device__ __forceinline__ int wave_scan(int x, int none, F f)
+{
+    x = dpp_step<0x111, 0xF>(x, none, f);  // row_shr 1, 2, 4, 8, then the rows before
+    x = dpp_step<0x112, 0xF>(x, none, f);
+    x = dpp_step<0x114, 0xF>(x, none, f);
+    x = dpp_step<0x118, 0xF>(x, none, f);
+    x = dpp_step<0x142, 0xA>(x, none, f);
+    return dpp_step<0x143, 0xC>(x, none, f);
+}
+
+// pointers known to be global: loads and stores through the state's pointers are flat ones, which the
+// scalar loads after them wait for
+template <typename T>
+using glob = T __attribute__((address_space(1)))*;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 template <bool GATHER>
 __global__ void __launch_bounds__(kSmallThreads) k_resample_small(pa_state* base, ResampleParams p)
 {
+    constexpr int kBig = 1 << 24;  // sums of 64 numbers below it fit 31 bits; larger ones overflow the run
+    static_assert(kSmallCap < kBig && kSmallPer * (kSmallThreads / 64) == 64, "a lane per wave's total");
     pa_state* st = base + blockIdx.x;
     if (st->status) return;
-    extern __shared__ double dyn[];  // products of a chunk of bins, then the histogram
-    __shared__ int32_t off[kSmallCap + 1];
+    extern __shared__ double dyn[];  // products of a chunk of bins, the first weights, then the histogram
+    __shared__ __attribute__((aligned(16))) uint32_t low[kLowLevels * kLowEntries];
     __shared__ uint16_t src_of[kSmallCap];
-    __shared__ int64_t red[kSmallThreads / 64];
+    __shared__ u32x4 stage[GATHER ? kStagePieces : 1];  // the first rows, asked for at the start
+    __shared__ int64_t totals[64];  // copies of replicas 64 i ..
+    __shared__ int lohi[2];
     __shared__ double S_sh;
-    const int tid = threadIdx.x;
-    const int R = (int)st->R;
-    const int cur = st->cur;
-    const double dbeta = p.beta_to - p.beta_from;
-    const double Rt = p.R_target > 0.0 ? p.R_target : (double)st->R0;
-    const WorkLayout wl = work_layout(st->N, st->n_bins, st->capacity);
-    int64_t* misc = work_ptr<int64_t>(st, wl.misc);
-
-    // E_lo, the weights and S in its fixed order
-    double wt[kSmallPer];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // the state's fields, all read at once
+    int cur = st->cur, nb = st->n_bins, Eb = st->E_base, stride = st->row_stride, R = (int)st->R;
+    int64_t capacity = st->capacity, R0 = st->R0;
+    uint64_t seed = st->seed;
+    int32_t *E0 = st->energy[0], *E1 = st->energy[1], *counts = st->counts;
+    int64_t* offsets = st->offsets;
+    void *s0 = st->spins[0], *s1 = st->spins[1];
+    asm volatile("" : "+s"(cur), "+s"(nb), "+s"(Eb), "+s"(stride), "+s"(R), "+s"(capacity), "+s"(R0), "+s"(seed), "+s"(E0),
+                 "+s"(E1), "+s"(counts), "+s"(offsets), "+s"(s0), "+s"(s1));
+    const double Rt = p.R_target > 0.0 ? p.R_target : (double)R0;
+    const CopyDraws cd0 = {0u, (uint32_t)p.k, (uint32_t)seed, (uint32_t)(seed >> 32)};
+    const glob<int32_t> E = (glob<int32_t>)(cur ? E1 : E0), E_new = (glob<int32_t>)(cur ? E0 : E1);
+    const int per_row = stride / 16;
     double* prod = dyn;
-    uint32_t* hist = reinterpret_cast<uint32_t*>(dyn + kSmallThreads);
-    const int32_t* E = st->energy[cur];
-    const int nb = st->n_bins, Eb = st->E_base;
+    double* w_sh = dyn + kSmallThreads;
+    uint32_t* hist = reinterpret_cast<uint32_t*>(dyn + 2 * kSmallThreads);
+
+    // the energies' histogram and range; everything that the kernel reads is asked for here
     int e[kSmallPer], lo = INT32_MAX, hi = INT32_MIN;
-    for (int b = tid; b < nb; b += kSmallThreads) hist[b] = 0;
+#pragma unroll
+    for (int i = 0; i < kSmallPer; ++i) e[i] = tid + i * kSmallThreads < R ? E[tid + i * kSmallThreads] : 0;
+    const double w_mine = tid < nb ? p.w[tid] : 0.0;
+    uint4v v0[kSmallPer];  // the replicas' first draws
 #pragma unroll
     for (int i = 0; i < kSmallPer; ++i) {
-        const int j = tid + i * kSmallThreads;
-        e[i] = j < R ? E[j] : 0;
+        CopyDraws cd = cd0;
+        cd.j = (uint32_t)(tid + i * kSmallThreads);
+        if (i * kSmallThreads < R) v0[i] = cd.call(0);
     }
+    const glob<u32x4> A = (glob<u32x4>)(cur ? s1 : s0), B = (glob<u32x4>)(cur ? s0 : s1);
+    const int staged = GATHER ? min(R * per_row, kStagePieces) : 0;
+    u32x4 rows[kStagePieces / kSmallThreads];
+#pragma unroll
+    for (int u = 0; u < kStagePieces / kSmallThreads; ++u)
+        if (tid + u * kSmallThreads < staged) rows[u] = A[tid + u * kSmallThreads];
+    const double lnR = tid == kCommit ? log((double)R) : 0.0;
+    load_low(low);
+    for (int b = tid; b < nb; b += kSmallThreads) hist[b] = 0;
+    if (tid == 0) {
+        lohi[0] = INT32_MAX;
+        lohi[1] = INT32_MIN;
+    }
+    w_sh[tid] = w_mine;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kSmallPer; ++i) {
@@ -730,122 +805,160 @@ __global__ void __launch_bounds__(kSmallThreads) k_resample_small(pa_state* base
         lo = min(lo, e[i]);
         hi = max(hi, e[i]);
     }
-    int* redi = reinterpret_cast<int*>(red);
-    lo = block_reduce(lo, redi, [](int a, int b) { return min(a, b); });
-    hi = block_reduce(hi, redi, [](int a, int b) { return max(a, b); });
-    const double E_lo = (double)lo;
+    lo = wave_scan(lo, INT32_MAX, [](int a, int b) { return min(a, b); });
+    hi = wave_scan(hi, INT32_MIN, [](int a, int b) { return max(a, b); });
+    if (lane == 63 && lo <= hi) {
+        atomicMin(&lohi[0], lo);
+        atomicMax(&lohi[1], hi);
+    }
+    __syncthreads();
+    lo = lohi[0];
+    hi = lohi[1];
     const int ilo = R > 0 ? (lo - Eb) >> 2 : 0, n = R > 0 ? ((hi - Eb) >> 2) - ilo + 1 : 0;
-    double sum = 0.0;  // energies ascending (thread 0)
+
+    // S, energies ascending (thread 0)
+    double sum = 0.0;
     for (int b0 = 0; b0 < n; b0 += kSmallThreads) {
-        if (b0 + tid < n) prod[tid] = (double)hist[ilo + b0 + tid] * p.w[b0 + tid];
+        if (b0 > 0) __syncthreads();  // the last chunk has been added
+        if (b0 + tid < n) prod[tid] = (double)hist[ilo + b0 + tid] * (b0 == 0 ? w_mine : p.w[b0 + tid]);
         __syncthreads();
-        if (tid == 0) {
-            const int cnt = min(kSmallThreads, n - b0);
-            for (int t = 0; t < cnt; ++t) sum = sum + prod[t];
-        }
-        __syncthreads();
+        if (tid == 0) sum = add_in_order(sum, prod, min(kSmallThreads, n - b0));
     }
     if (tid == 0) S_sh = sum;
     __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kSmallPer; ++i) wt[i] = tid + i * kSmallThreads < R ? p.w[(e[i] - lo) >> 2] : 0.0;
-    if (tid == 0 && isfinite(sum) && sum > 0.0) {
-        st->E_lo = lo;
-        st->E_hi = hi;
-    }
     const double S = S_sh;
     if (!isfinite(S) || !(S > 0.0)) {  // the same for the whole block
         if (tid == 0) st->status |= PA_FLAG_NONFINITE;
         return;
     }
+    if (tid == 0) {
+        st->E_lo = lo;
+        st->E_hi = hi;
+    }
 
-    // copy numbers and their exclusive scan, 1024 replicas at a time in order
-    const CopyDraws cd0 = {0u, (uint32_t)p.k, (uint32_t)st->seed, (uint32_t)(st->seed >> 32)};
-    int64_t carry = 0;
+#pragma unroll
+    for (int u = 0; u < kStagePieces / kSmallThreads; ++u)
+        if (tid + u * kSmallThreads < staged) stage[tid + u * kSmallThreads] = rows[u];
+
+    // copy numbers c and, o, their exclusive sum within the wave
+    int c[kSmallPer], o[kSmallPer];
+#pragma unroll
+    for (int i = 0; i < kSmallPer; ++i) {
+        c[i] = o[i] = 0;
+        if (i * kSmallThreads >= R) {
+            if (lane == 0) totals[i * (kSmallThreads / 64) + wave] = 0;
+            continue;
+        }
+        const int j = tid + i * kSmallThreads, b = (e[i] - lo) >> 2;
+        int m = kLadderMin;
+        int64_t q = 0;
+        uint64_t keep = 0;
+        const double w = j < R ? (b < kSmallThreads ? w_sh[b] : p.w[b]) : 0.0;
+        const bool drawn = poisson_parts((Rt * w) / S, &m, &q, &keep);
+        CopyDraws cd = cd0;
+        cd.j = (uint32_t)j;
+        c[i] = (int32_t)min(draw_copies(drawn, cd, v0[i], m, q, keep, low), (int64_t)INT32_MAX);
+        if (j < R) ((glob<int32_t>)counts)[j] = c[i];
+        int64_t total;
+        if (__ballot(c[i] >= kBig)) {
+            total = c[i];
+            for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
+        } else {
+            const int x = wave_scan(c[i], 0, [](int a, int b) { return a + b; });
+            o[i] = x - c[i];
+            total = x;  // lane 63's is the wave's
+        }
+        if (lane == 63) totals[i * (kSmallThreads / 64) + wave] = total;
+    }
+    __syncthreads();
+    int64_t R_all = totals[lane];
+    int before = (int)R_all;
+    if (__ballot(R_all >= kBig)) {
+        for (int off = 32; off > 0; off >>= 1) R_all += __shfl_xor(R_all, off, 64);
+    } else {
+        before = wave_scan(before, 0, [](int a, int b) { return a + b; });
+        R_all = __builtin_amdgcn_readlane(before, 63);
+        before -= (int)totals[lane];
+    }
+    const bool over = R_all > capacity;
+    if (tid == 0) {
+        st->R_new = R_all;
+        if (over) st->status |= PA_FLAG_CAPACITY;
+        else if (R_all == 0) st->status |= PA_FLAG_EXTINCT;
+    }
+    if (over || R_all == 0) return;  // the same for the whole block
+    const int R_new = (int)R_all;
+
+    // offsets, and each replica's place in the new population: its lane writes up to kOwnCopies copies, the
+    // wave the rest of a replica with more
+    constexpr int kOwnCopies = 8;
+    const glob<int64_t> off_out = (glob<int64_t>)offsets;
+    const WorkLayout wl = work_layout(st->N, nb, capacity);
+    const glob<int32_t> src = (glob<int32_t>)work_ptr<int32_t>(st, wl.src);
+    if (tid == 0) off_out[R] = R_new;
 #pragma unroll
     for (int i = 0; i < kSmallPer; ++i) {
         if (i * kSmallThreads >= R) break;
         const int j = tid + i * kSmallThreads;
-        const bool live = j < R;
-        int m = kLadderMin;
-        int64_t q = 0;
-        uint64_t keep = 0;
-        const bool drawn = live && poisson_parts((Rt * wt[i]) / S, &m, &q, &keep);
-        CopyDraws cd = cd0;
-        cd.j = (uint32_t)j;
-        const bool heavy = drawn && (q > 0 || m >= kCopiesHeavyM);
-        int64_t n = drawn && !heavy ? copies_light(cd, m, keep) : 0;
-        n = copies_heavy_by_wave(heavy, n, cd, m, q, keep);
-        const int32_t c = (int32_t)min(n, (int64_t)INT32_MAX);
-        if (live) st->counts[j] = c;
-        int64_t x = live ? c : 0;  // inclusive wave scan
-        for (int o = 1; o < 64; o <<= 1) {
-            const int64_t y = __shfl_up(x, o, 64);
-            if ((tid & 63) >= o) x += y;
+        const int first = o[i] + __builtin_amdgcn_readlane(before, i * (kSmallThreads / 64) + wave);
+        if (j < R) off_out[j] = first;
+        auto put = [&](int d, int from, int energy) {
+            if constexpr (GATHER) {
+                src_of[d] = (uint16_t)from;
+                E_new[d] = energy;
+            } else {
+                src[d] = from;
+            }
+        };
+        for (int t = 0; t < min(c[i], kOwnCopies); ++t) put(first + t, j, e[i]);
+        uint64_t todo = __ballot(c[i] > kOwnCopies);
+        while (todo) {
+            const int h = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            const int ch = __builtin_amdgcn_readlane(c[i], h), fh = __builtin_amdgcn_readlane(first, h);
+            const int eh = __builtin_amdgcn_readlane(e[i], h);
+            for (int t = kOwnCopies + lane; t < ch; t += 64) put(fh + t, j - lane + h, eh);
         }
-        __syncthreads();
-        if ((tid & 63) == 63) red[tid >> 6] = x;
-        __syncthreads();
-        int64_t pre = carry, all = 0;
-        for (int w = 0; w < kSmallThreads / 64; ++w) {
-            if (w < (tid >> 6)) pre += red[w];
-            all += red[w];
-        }
-        const int64_t o = pre + x - (live ? c : 0);
-        if (live) off[j] = (int32_t)min(o, (int64_t)INT32_MAX);
-        carry += all;
     }
-    if (tid == 0) {
-        st->R_new = carry;
-        if (carry > st->capacity) st->status |= PA_FLAG_CAPACITY;
-        else if (carry == 0) st->status |= PA_FLAG_EXTINCT;
-    }
-    if (carry > st->capacity || carry == 0) return;  // the same for the whole block
-    const int R_new = (int)carry;
-    if (tid == 0) off[R] = R_new;
-    __syncthreads();
-    for (int j = tid; j <= R; j += kSmallThreads) st->offsets[j] = off[j];
-
-    // the source of each new replica: the largest j with off[j] <= d
-    int32_t* src = work_ptr<int32_t>(st, wl.src);
-    for (int d = tid; d < R_new; d += kSmallThreads) {
-        int lo = 0, hi = R;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (off[mid] <= d) lo = mid;
-            else hi = mid;
-        }
-        if (GATHER) src_of[d] = (uint16_t)lo;
-        else src[d] = lo;
-    }
-    const double lnQ = -dbeta * E_lo + log(S) - log((double)R);
+    const double E_lo = (double)lo;
+    double lnQ = 0.0;
+    auto set_lnQ = [&] {  // one thread's work (kept there: else every thread takes the logarithm)
+        double x = S;
+        asm volatile("" : "+v"(x));
+        lnQ = -(p.beta_to - p.beta_from) * E_lo + log(x) - lnR;
+    };
     if constexpr (!GATHER) {
-        if (tid == 0) {
+        if (tid == kCommit) {
+            set_lnQ();
+            int64_t* misc = work_ptr<int64_t>(st, wl.misc);
             misc[kMiscEmin] = lo;
             *reinterpret_cast<double*>(&misc[kMiscLnQ]) = lnQ;
             *reinterpret_cast<double*>(&misc[kMiscS]) = S;
         }
-        return;
     } else {
+        const int pieces = R_new * per_row;
+        // t / per_row: exact, as (t + 0.5) / per_row is at least 0.5 / per_row from a whole number, against an error
+        // of t / per_row 2^-22, and t < 12288
+        const float inv = 1.0f / (float)per_row;
         __syncthreads();
-        const int per_row = st->row_stride / 16, pieces = R_new * per_row;
-        const uint4* A = reinterpret_cast<const uint4*>(st->spins[cur]);
-        uint4* B = reinterpret_cast<uint4*>(st->spins[cur ^ 1]);
         constexpr int U = 4;  // loads in flight per thread
-        for (int t0 = tid; t0 < pieces; t0 += U * kSmallThreads) {
-            uint4 v[U];
+        for (int t0 = tid; t0 - tid < pieces; t0 += U * kSmallThreads) {
+            u32x4 v[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int t = t0 + u * kSmallThreads, rn = t / per_row;
-                if (t < pieces) v[u] = A[src_of[rn] * per_row + (t - rn * per_row)];
+                const int t = t0 + u * kSmallThreads, rn = (int)(((float)t + 0.5f) * inv);
+                if (t >= pieces) continue;
+                const int from = src_of[rn] * per_row + (t - rn * per_row);
+                if (from < kStagePieces) v[u] = stage[from];
+                else v[u] = A[from];
             }
+            if (t0 == kCommit) set_lnQ();  // while the loads are in flight
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (t0 + u * kSmallThreads < pieces) B[t0 + u * kSmallThreads] = v[u];
         }
-        for (int d = tid; d < R_new; d += kSmallThreads) st->energy[cur ^ 1][d] = st->energy[cur][src_of[d]];
         __syncthreads();  // every thread has read the state
-        if (tid == 0) commit_step(st, p, lnQ, S, E_lo);
+        if (tid == kCommit) commit_step(st, p, lnQ, S, E_lo);
     }
 }
 
@@ -863,7 +976,7 @@ static bool launch_resample_small(const pa_run* runs, int n, const ResampleParam
     if (cap > kSmallCap || bins > kSmallBins) return false;
     pa_state* base = runs[0].state;
     const bool gather = runs[0].layout == PA_U8 && rows <= kSmallRows;
-    const size_t lds = kSmallThreads * 8 + (size_t)bins * 4;
+    const size_t lds = kSmallThreads * 16 + (size_t)bins * 4;
     const dim3 g((unsigned)n), b(kSmallThreads);
     if (gather) hipLaunchKernelGGL(k_resample_small<true>, g, b, lds, s, base, p);
     else hipLaunchKernelGGL(k_resample_small<false>, g, b, lds, s, base, p);
@@ -938,8 +1051,7 @@ __global__ void __launch_bounds__(256) k_gauss_weights(pa_state* base, double db
 }
 
 // a block per run: S in replica order, ln Q (the step's record is written by k_finish).  The block
-// loads the weights a chunk at a time into LDS with coalesced loads, and one thread adds them in
-// order from there, 16 LDS loads ahead of the chain of dependent FP64 additions
+// loads the weights a chunk at a time into LDS with coalesced loads, and one thread adds them in order
 constexpr int kNormChunk = 4096;
 
 __global__ void __launch_bounds__(256) k_gauss_normalise(pa_state* base, ResampleParams p)
@@ -956,17 +1068,7 @@ __global__ void __launch_bounds__(256) k_gauss_normalise(pa_state* base, Resampl
         const int n = (int)(R - j0 < kNormChunk ? R - j0 : kNormChunk);
         for (int i = threadIdx.x; i < n; i += blockDim.x) chunk[i] = w[j0 + i];
         __syncthreads();
-        if (threadIdx.x == 0) {
-            int i = 0;
-            for (; i + 16 <= n; i += 16) {
-                double c[16];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) c[u] = chunk[i + u];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) S = S + c[u];
-            }
-            for (; i < n; ++i) S = S + chunk[i];
-        }
+        if (threadIdx.x == 0) S = add_in_order(S, chunk, n);
         __syncthreads();
     }
     if (threadIdx.x != 0) return;
@@ -988,6 +1090,8 @@ __global__ void __launch_bounds__(kScanTile) k_gauss_copies(pa_state* base, Resa
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t R = st->R;
     if ((int64_t)blockIdx.x * kScanTile >= R) return;  // the whole block past R
+    __shared__ __attribute__((aligned(16))) uint32_t low[kLowLevels * kLowEntries];
+    load_low(low);
     const int64_t* misc = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).misc);
     const double S = *reinterpret_cast<const double*>(&misc[kMiscGaussS]);
     const double* w = reinterpret_cast<const double*>(st->energy[st->cur ^ 1]);
@@ -999,9 +1103,9 @@ __global__ void __launch_bounds__(kScanTile) k_gauss_copies(pa_state* base, Resa
     uint64_t keep = 0;
     const bool drawn = poisson_parts(lam, &m, &q, &keep);
     const CopyDraws cd = {(uint32_t)j, (uint32_t)p.k, (uint32_t)st->seed, (uint32_t)(st->seed >> 32)};
-    const bool heavy = drawn && (q > 0 || m >= kCopiesHeavyM);
-    int64_t n = drawn && !heavy ? copies_light(cd, m, keep) : 0;
-    n = copies_heavy_by_wave(heavy, n, cd, m, q, keep);
+    const uint4v v0 = cd.call(0);
+    __syncthreads();
+    const int64_t n = draw_copies(drawn, cd, v0, m, q, keep, low);
     const int32_t c = (int32_t)min(n, (int64_t)INT32_MAX);
     if (live) st->counts[j] = c;
     tile_sum(st, live ? c : 0);
