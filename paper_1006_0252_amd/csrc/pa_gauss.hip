@@ -231,11 +231,11 @@ __global__ void __launch_bounds__(64) k_sweep_gauss(const pa_state* __restrict__
 //
 // Bound by the vector ALU and the latency of a wave's own chain: 11.3 VALU and 1.27 LDS instructions per
 // attempt at side 8, of which Philox 4.7; the 94 registers leave five waves per SIMD.  126 runs of side
-// 8, R = 2000, 100 sweeps: 4.27 ms, 3.0e12 attempts/s; with one wave per group (as the kernel before, on
+// 8, R = 2000, 100 sweeps: 4.11 ms, 3.1e12 attempts/s; with one wave per group (as the kernel before, on
 // 16-site segments of both colours: 13.9 VALU) 5.23 ms, and a second round of blocks as soon as some
-// runs have more than 32 groups (R = 2060: 4.50 ms against 6.62 ms).  50 runs: 4.12 -> 2.11 ms.  The
-// sides other than 4 and 8 took one thread per replica: side 6, 8 runs, 20 sweeps 40 ms -> 0.10 ms.
-// Chain of 256 sites, 200 runs of 1000, 50 sweeps 1.13 -> 0.91 ms; 64 sites 0.31 -> 0.25 ms.
+// runs have more than 32 groups (R = 2060: 4.30 ms against 6.62 ms).  50 runs: 4.12 -> 2.08 ms.  The
+// sides other than 4 and 8 took one thread per replica: side 6, 8 runs, 20 sweeps 40 ms -> 0.09 ms.
+// Chain of 256 sites, 200 runs of 1000, 50 sweeps 1.13 -> 0.87 ms; 64 sites 0.31 -> 0.24 ms.
 
 // h of site i for neighbour pattern b (bit a: neighbour a in field order has s_j != s_i); LC: the
 // cube side as a constant (its divisions become shifts or multiplications), 0 for L at run time
@@ -372,39 +372,136 @@ __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b)
     return r;
 }
 
+// A cube's energy in bond order.  A bond's term is +-J, added as fma(+-1, J, E): the product is exact, so
+// the sum rounds once, as E + (+-J).  The wave holds a lattice row's couplings, one per lane, and reads each
+// from its lane as a scalar.  Loaded as scalars two sites at a time, they had the wave wait most of the time:
+// a call of one sweep of 2000 replicas took, side 6 36 us, 8 61 us, 10 107 us; so 27, 45 and 71.
+__device__ __forceinline__ double lane_of(double x, int lane)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// E plus J, or less J where bit x of d is set.  sign and one: 2^31 and the high half of 1.0, kept in
+// registers by the caller (as literals they cost the and and the or an instruction each)
+struct SignWords {
+    uint32_t sign = 0x80000000u, one = 0x3FF00000u;
+    __device__ __forceinline__ SignWords() { asm volatile("" : "+v"(sign), "+v"(one)); }
+};
+
+__device__ __forceinline__ double bond_sign(uint32_t d, int x, const SignWords& k)
+{
+    return __builtin_bit_cast(double, (uint64_t)words::select_bits(k.sign, d << (31 - x), k.one) << 32);
+}
+
+// E of a cube from its strings (E0, E1 at word 0, S dwords from word to word): site i, then axis +x, +y, +z.
+// A row is taken as its even and its odd sites (bit m: x = 2 m, 2 m + 1), which the strings hold side by side.
+// The rows next to row i + 1 are asked for before the bonds of row i, the couplings four rows ahead, and a
+// bond's sign and coupling are made kAhead bonds before they are used and kept there.
+template <int L, int S>
+__device__ __forceinline__ double cube_energy(const double* couplings, const uint32_t* E0, const uint32_t* E1)
+{
+    constexpr int H2 = L / 2, kAhead = 4, kRows = 4;
+    static_assert(L % 2 == 0, "whole rounds of kRows rows");
+    const __attribute__((address_space(1))) double* J = (const __attribute__((address_space(1))) double*)couplings;
+    struct Row {
+        uint32_t e0, e1, o0, o1;
+        int sh;
+        __device__ __forceinline__ uint32_t ev() const { return __builtin_amdgcn_alignbit(e1, e0, sh); }
+        __device__ __forceinline__ uint32_t od() const { return __builtin_amdgcn_alignbit(o1, o0, sh); }
+    };
+    auto load = [&](int y, int z) {  // colour 0 takes x = 2 m + (y + z) mod 2
+        const int b = H2 * (y + L * z), k = (b >> 5) * S, to1 = (int)(E1 - E0);
+        const int e = k + (((y + z) & 1) ? to1 : 0), o = k + (((y + z) & 1) ? 0 : to1);
+        return Row{E0[e], E0[e + S], E0[o], E0[o + S], b & 31};
+    };
+    const int lane = threadIdx.x & 63;
+    auto row_J = [&](int i) { return J[3 * L * (i < L * L ? i : L * L - 1) + (lane < 3 * L ? lane : 0)]; };
+    double Jq[kRows];
+#pragma unroll
+    for (int n = 0; n < kRows; ++n) Jq[n] = row_J(n);
+    const SignWords sw;
+    double E = 0.0;
+    Row ny = load(1, 0), nz = load(0, 1);
+    const Row r0 = load(0, 0);
+    uint32_t ev = r0.ev(), od = r0.od(), ev_z = 0, od_z = 0;  // this row, and the first row of the next plane
+    int y = 0, z = 0;
+#pragma unroll 1
+    for (int i = 0; i < L * L; i += kRows) {
+#pragma unroll
+        for (int n = 0; n < kRows; ++n) {
+            const uint32_t evy = ny.ev(), ody = ny.od(), evz = nz.ev(), odz = nz.od();
+            ev_z = y == 0 ? evz : ev_z;
+            od_z = y == 0 ? odz : od_z;
+            // bit m: the bond of x = 2 m (e) and of x = 2 m + 1 (o) along each axis
+            const uint32_t next = words::select_bits(1u << (H2 - 1), ev << (H2 - 1), ev >> 1);
+            const uint32_t e[3] = {ev ^ od, ev ^ evy, ev ^ evz};
+            const uint32_t o[3] = {od ^ next, od ^ ody, od ^ odz};
+            const bool wrap = y + 1 == L;
+            ev = wrap ? ev_z : evy;
+            od = wrap ? od_z : ody;
+            y = wrap ? 0 : y + 1;
+            z = wrap ? z + 1 : z;
+            ny = load(y + 1 < L ? y + 1 : 0, z < L ? z : 0);
+            nz = load(y, z + 1 < L ? z + 1 : 0);
+            double sg[3 * L], Jb[3 * L];
+#pragma unroll
+            for (int b = -kAhead; b < 3 * L; ++b) {
+                if (b >= 0) E = __builtin_fma(sg[b], Jb[b], E);
+                if (b + kAhead < 3 * L) {
+                    const int c = b + kAhead, x = c / 3;
+                    sg[c] = bond_sign(x & 1 ? o[c % 3] : e[c % 3], x >> 1, sw);
+                    Jb[c] = lane_of(Jq[n], c);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            Jq[n] = row_J(i + n + kRows);
+        }
+    }
+    return E;
+}
+
 struct GaussX { uint32_t w[6]; };
 
-// The attempts of a word that the bounds leave open, decided exactly: ties (bits with u = bound - 1)
-// and, where top is set, the sites with u = 0xFFFF (their calls are drawn again).  T64w: the word's rows
-// of the u64 table; sites is the mask of the word's sites, odd that of the sites 2 h + 1.  Returns the
-// accepted ones.
+// The attempts of a word that the bounds leave open, decided exactly: ties (bits with u = bound - 1) and the
+// sites with u = 0xFFFF of the calls in tops (bit i: call i, which is drawn again to find them).  Either way
+// u follows from the threshold, so no other call is drawn again but for the low bits of a true tie (one
+// word in 16 of a wave comes here; with every call of the word and of its ties drawn again, side 8 and 126
+// runs took 3% longer).  T64w: the word's rows of the u64 table; sites is the mask of the word's sites, odd
+// that of the sites 2 h + 1.  Returns the accepted ones.
 template <int NB>
-static __device__ __noinline__ uint32_t gauss_resolve(const uint64_t* __restrict__ T64w, GaussX X, uint32_t ties, bool top,
+static __device__ __noinline__ uint32_t gauss_resolve(const uint64_t* __restrict__ T64w, GaussX X, uint32_t ties, uint32_t tops,
                                                       uint32_t sites, uint32_t odd, uint32_t k, uint32_t rr, uint32_t ctr2,
                                                       uint32_t k0, uint32_t k1)
 {
-    if (top) {
-        for (int i = 0; i < 4; ++i) {
-            const uint4v v = philox10(4 * k + i, rr, ctr2, kTagMet, k0, k1);
-            for (int f = 0; f < 8; ++f) ties |= (uint32_t)(field16(v, f) == 0xFFFFu) << (8 * i + f);
-        }
+    uint32_t high = 0;  // sites with u = 0xFFFF
+    while (tops) {
+        const int i = __builtin_ctz(tops);
+        tops &= tops - 1;
+        const uint4v v = philox10(4 * k + i, rr, ctr2, kTagMet, k0, k1);
+        for (int f = 0; f < 8; ++f) high |= (uint32_t)(field16(v, f) == 0xFFFFu) << (8 * i + f);
     }
-    ties &= sites;
+    uint32_t open = (ties | high) & sites;
     uint32_t F = 0;
-    while (ties) {
-        const int j = __builtin_ctz(ties);
-        ties &= ties - 1;
+    while (open) {
+        const int j = __builtin_ctz(open);
+        open &= open - 1;
         int b = 0;
         for (int a = 0; a < NB; ++a) b |= (int)((X.w[a] >> j) & 1u) << a;
         const uint64_t T = T64w[((((j >> 3) << NB) + b) << 3) + (j & 7)];
         const uint32_t T16 = (uint32_t)(T >> 48);
-        const uint32_t u = (field16(philox10(4 * k + (j >> 3), rr, ctr2, kTagMet, k0, k1), j & 7));
+        const uint32_t u = (high >> j) & 1u ? 0xFFFFu : min(T16, 0xFFFEu);
         bool accept = T == ~0ull || u < T16;
         if (!accept && u == T16) accept = tie_accept(u, T, 2u * (32u * k + j) + ((odd >> j) & 1u), rr, ctr2, k0, k1);
         F |= (uint32_t)accept << j;
     }
     return F;
 }
+
+// whether either half of a word is 0xFFFF
+__device__ __forceinline__ bool any_top(uint32_t u) { return (u | 0xFFFFu) == 0xFFFFFFFFu || (u & 0xFFFFu) == 0xFFFFu; }
 
 // The attempts of word w of a colour (bits `sites` of it): X the neighbour words xor w in field order,
 // rows the table rows of the word's calls in this lane, T64w the word's rows of the u64 table.  Returns
@@ -426,7 +523,7 @@ __device__ __forceinline__ uint32_t gauss_word(uint32_t w, const uint32_t (&X)[N
             raw[i][t] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)pt.address(i, t), (int)rows[i][t >> 1]);
     }
     // outcomes and their places as in words::decide_word
-    uint32_t ra = 0, rb = 0, umax = 0;
+    uint32_t ra = 0, rb = 0, umax[4] = {0, 0, 0, 0};  // umax: of a call's draws
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         if (CALLS ? i >= CALLS : i >= nbytes) break;
@@ -438,7 +535,7 @@ __device__ __forceinline__ uint32_t gauss_word(uint32_t w, const uint32_t (&X)[N
             // site 2 t's entry is the low half of its word, site 2 t + 1's the high half
             const uint32_t bound = __builtin_amdgcn_perm(raw[i][2 * t + 1], raw[i][2 * t], 0x07060100u);
             e[t] = words::first_look(bound, vw[t]);
-            umax = (i | t) == 0 ? vw[t] : pk_max_u16(umax, vw[t]);
+            umax[i] = t == 0 ? vw[t] : pk_max_u16(umax[i], vw[t]);
         }
         const int o = 8 * (i & 1);
         uint32_t r = i < 2 ? ra : rb;
@@ -450,7 +547,13 @@ __device__ __forceinline__ uint32_t gauss_word(uint32_t w, const uint32_t (&X)[N
         else rb = r;
     }
     uint32_t acc = select_bits(0x0000FFFFu, select_bits(0x5555u, ra >> 1, ra >> 16), select_bits(0x55550000u, rb << 15, rb));
-    const bool top = (umax | 0xFFFFu) == 0xFFFFFFFFu || (umax & 0xFFFFu) == 0xFFFFu;
+    uint32_t all = umax[0];
+#pragma unroll
+    for (int i = 1; i < 4; ++i) {
+        if (CALLS ? i >= CALLS : i >= nbytes) break;
+        all = pk_max_u16(all, umax[i]);
+    }
+    const bool top = any_top(all);
     if (((ra | rb) & 0x55555555u) != 0 || top) {
         const uint32_t ties = select_bits(0x0000FFFFu, select_bits(0x5555u, ra, ra >> 15),
                                           select_bits(0x55550000u, rb << 16, rb << 1));
@@ -458,7 +561,9 @@ __device__ __forceinline__ uint32_t gauss_word(uint32_t w, const uint32_t (&X)[N
             GaussX gx = {};
 #pragma unroll
             for (int a = 0; a < NB; ++a) gx.w[a] = X[a];
-            acc |= gauss_resolve<NB>(T64w, gx, ties, top, sites, odd, k, c.rr, c.ctr2, c.k0, c.k1);
+            const uint32_t tops = (uint32_t)any_top(umax[0]) | (uint32_t)any_top(umax[1]) << 1 | (uint32_t)any_top(umax[2]) << 2 |
+                                  (uint32_t)any_top(umax[3]) << 3;
+            acc |= gauss_resolve<NB>(T64w, gx, ties, tops, sites, odd, k, c.rr, c.ctr2, c.k0, c.k1);
         }
     }
     return w ^ (acc & sites);
@@ -597,29 +702,7 @@ __global__ void __launch_bounds__(kGaussWaves * 64) k_sweep_gauss_cube(pa_state*
             strings::store_word_u8(row, Gm::STRIDE, k, words::select_bits(sig0, a, b) & in, words::select_bits(sig0, b, a) & in);
     }
     if (wave != 0) return;
-    const double* __restrict__ J = reinterpret_cast<const double*>(st->J);
-    constexpr uint32_t LM = (1u << L) - 1u;
-    double E = 0.0;
-#pragma unroll 1
-    for (int z = 0; z < L; ++z) {
-        uint32_t own = strings::string_row<L, 64>(0, z, E0 + G * 64, E1 + G * 64);
-        const uint32_t first = own;
-#pragma unroll 1
-        for (int y = 0; y < L; ++y) {
-            const uint32_t yp = y + 1 < L ? strings::string_row<L, 64>(y + 1, z, E0 + G * 64, E1 + G * 64) : first;
-            const uint32_t zp = strings::string_row<L, 64>(y, z + 1 < L ? z + 1 : 0, E0 + G * 64, E1 + G * 64);
-            const uint32_t bx = own ^ (((own >> 1) | (own << (L - 1))) & LM), by = own ^ yp, bz = own ^ zp;
-            const double* Jr = J + 3 * L * (y + L * z);
-            // unrolled by 2 only: unrolled fully, the couplings of a whole row would be held in VGPRs
-#pragma unroll 2
-            for (int x = 0; x < L; ++x) {
-                E = E + (((bx >> x) & 1u) ? -Jr[3 * x] : Jr[3 * x]);
-                E = E + (((by >> x) & 1u) ? -Jr[3 * x + 1] : Jr[3 * x + 1]);
-                E = E + (((bz >> x) & 1u) ? -Jr[3 * x + 2] : Jr[3 * x + 2]);
-            }
-            own = yp;
-        }
-    }
+    const double E = cube_energy<L, 64>(reinterpret_cast<const double*>(st->J), E0 + G * 64, E1 + G * 64);
     if (valid) reinterpret_cast<double*>(st->energy[st->cur])[r] = E;
 }
 
