@@ -7,6 +7,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "pa_common.h"
@@ -569,6 +571,44 @@ __device__ __forceinline__ uint32_t gauss_word(uint32_t w, const uint32_t (&X)[N
     return w ^ (acc & sites);
 }
 
+// The attempts of call i of word k alone, in place in the word's byte i; row: the call's row in this lane
+template <int NB>
+__device__ __forceinline__ uint32_t gauss_byte(uint32_t w, const uint32_t (&X)[NB], gu32x4 row, uint32_t sites, uint32_t odd,
+                                               const uint64_t* __restrict__ T64w, uint32_t k, int i, const words::Lane& c)
+{
+    using words::select_bits;
+    const int sh = 8 * i;
+    uint32_t XI[NB];  // the byte's neighbour patterns as a word's first byte
+#pragma unroll
+    for (int a = 0; a < NB; ++a) XI[a] = (X[a] >> sh) & 0xFFu;
+    Patterns<NB> pt;
+    pt.make(XI);
+    uint32_t raw[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) raw[t] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)pt.address(0, t), (int)row[t >> 1]);
+    const uint4v v = words::philox10_lane(4 * k + i, c.rr, c.ctr2, kTagMet, c.k0, c.k1);
+    const uint32_t vw[4] = {v.x, v.y, v.z, v.w};
+    uint32_t ra = 0, umax = vw[0];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        ra = words::lshl_or(words::first_look(__builtin_amdgcn_perm(raw[2 * t + 1], raw[2 * t], 0x07060100u), vw[t]), 2 * t, ra);
+        if (t > 0) umax = pk_max_u16(umax, vw[t]);
+    }
+    sites &= 0xFFu << sh;
+    uint32_t acc = (select_bits(0x5555u, ra >> 1, ra >> 16) & 0xFFu) << sh;
+    const bool top = any_top(umax);
+    if ((ra & 0x55555555u) != 0 || top) {
+        const uint32_t ties = (select_bits(0x5555u, ra, ra >> 15) & 0xFFu) << sh;
+        if ((ties & sites) || top) {
+            GaussX gx = {};
+#pragma unroll
+            for (int a = 0; a < NB; ++a) gx.w[a] = X[a];
+            acc |= gauss_resolve<NB>(T64w, gx, ties, (uint32_t)top << i, sites, odd, k, c.rr, c.ctr2, c.k0, c.k1);
+        }
+    }
+    return (w ^ (acc & sites)) >> sh;  // (the byte: the rest of the word arbitrary)
+}
+
 // A block takes four waves: 4 / NWV groups of 64 replicas, the words of each split by NWV waves.  1-D
 // grid; block -> (run, block of the run): with 8 or more runs, the (run, block) items are split into 8
 // contiguous ranges and the blocks of range x are those with id = x mod 8 (blocks go round-robin to the
@@ -576,6 +616,7 @@ __device__ __forceinline__ uint32_t gauss_word(uint32_t w, const uint32_t (&X)[N
 // wave takes part in the lane reads of the table (lanes past R compute and store nothing), so no
 // branch may split a wave around them.
 constexpr int kGaussWaves = 4;
+constexpr int kGaussCallWaves = 16;  // most waves of a block whose waves take calls instead of words
 
 __device__ __forceinline__ bool gauss_place(int n_runs, int blocks, int* run, int* block)
 {
@@ -706,15 +747,198 @@ __global__ void __launch_bounds__(kGaussWaves * 64) k_sweep_gauss_cube(pa_state*
     if (valid) reinterpret_cast<double*>(st->energy[st->cur])[r] = E;
 }
 
+// Small populations of sides 8 and 10: 16 replicas per block and a thread per (replica, call), so that a
+// population is four times as many blocks and a phase is one call long.  The lanes of a wave then work on
+// four calls, so the table lies in LDS (read there instead of from lane to lane), [colour][call][k][pattern]:
+// a site's 64 bounds take 32 banks, and a call's stride puts neighbouring calls on alternate halves.
+constexpr int kSplitReplicas = 16;
+constexpr int kSplitCall = 8 * 64 + 64;  // u16 of a call (128 bytes of padding)
+
+template <int L>
+struct GaussSplitSmem {
+    static constexpr int M = (strings::Geo<L>::NH + 7) / 8;
+    static constexpr int UNITS = (M + 3) / 4 * 4;  // calls at once: whole waves
+    uint32_t E[2 * strings::Geo<L>::EW * kSplitReplicas];
+    uint32_t tab[2 * strings::Geo<L>::NW * strings::Geo<L>::TW];
+    uint16_t bound[2 * M * kSplitCall];
+};
+
+// base plus byte B of v, an LDS address of this lane (one SDWA op)
+template <int B>
+__device__ __forceinline__ uint32_t add_byte(uint32_t base, uint32_t v)
+{
+    uint32_t r;
+    if constexpr (B == 0)
+        asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0" : "=v"(r) : "v"(base), "v"(v));
+    else if constexpr (B == 1)
+        asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1" : "=v"(r) : "v"(base), "v"(v));
+    else if constexpr (B == 2)
+        asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2" : "=v"(r) : "v"(base), "v"(v));
+    else
+        asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3" : "=v"(r) : "v"(base), "v"(v));
+    return r;
+}
+
+template <int L>
+__global__ void __launch_bounds__(kSplitReplicas * GaussSplitSmem<L>::UNITS)
+k_sweep_gauss_split(pa_state* __restrict__ states, int n_runs, int blocks, int64_t t0, int ns)
+{
+    using Gm = strings::Geo<L>;
+    using words::select_bits;
+    using words::xor3;
+    constexpr int Q = kSplitReplicas, G = Gm::G, EW = Gm::EW, NW = Gm::NW, TW = Gm::TW, M = GaussSplitSmem<L>::M;
+    constexpr int UNITS = GaussSplitSmem<L>::UNITS, THREADS = Q * UNITS;
+    constexpr bool WHOLE = Gm::NH % 32 == 0;
+    __shared__ GaussSplitSmem<L> sm;
+    int run, block;
+    if (!gauss_place(n_runs, blocks, &run, &block)) return;
+    const pa_state* st = states + run;
+    const int64_t R = st->R, r0 = (int64_t)block * Q;
+    if (st->status || r0 >= R) return;  // the same for the whole block
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int q = threadIdx.x % Q, unit = threadIdx.x / Q;
+    const int64_t r = r0 + q;
+    const bool valid = r < R;
+    strings::build_tables<L, false>(nullptr, sm.tab, lane, wave, THREADS / 64);
+    const uint16_t* __restrict__ Tab = gauss_table(st);
+    const uint64_t* __restrict__ Tab64 = gauss_table64<6>(st);
+    for (int e = ns > 0 ? (int)threadIdx.x : 2 * M * 64; e < 2 * M * 64; e += THREADS) {
+        const gu32x4 v = ((grow_ptr)Tab)[e];  // call e / 64, pattern e mod 64
+        uint16_t* t = sm.bound + (e >> 6) * kSplitCall + (e & 63);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) t[64 * k] = (uint16_t)(v[k >> 1] >> (16 * (k & 1)));
+    }
+    uint32_t* E0 = sm.E + q;
+    uint32_t* E1 = E0 + EW * Q;
+    uint8_t* row = (uint8_t*)st->spins[st->cur] + (valid ? r : R - 1) * Gm::STRIDE;
+    __syncthreads();
+    for (int k = unit; k < NW; k += UNITS) {
+        uint32_t ev, od;
+        strings::load_word_u8(row, Gm::STRIDE, k, &ev, &od);
+        const uint32_t sig0 = sm.tab[k * TW + 6], in = sm.tab[k * TW + 11];  // colour 0: x even, sites
+        const uint32_t v[2] = {select_bits(sig0, ev, od) & in, select_bits(sig0, od, ev) & in};
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            uint32_t* S = c ? E1 : E0;
+            S[(G + k) * Q] = v[c];
+            if constexpr (WHOLE) {
+                if (k < G) S[(G + NW + k) * Q] = v[c];
+                if (k >= NW - G) S[(k - (NW - G)) * Q] = v[c];
+            }
+        }
+    }
+    __syncthreads();
+    if constexpr (!WHOLE) {
+        strings::refresh_ghosts<L, Q>(E0, unit, UNITS);
+        strings::refresh_ghosts<L, Q>(E1, unit, UNITS);
+        __syncthreads();
+    }
+
+    words::Lane c;
+    c.rr = (uint32_t)r;
+    c.k0 = (uint32_t)st->seed;
+    c.k1 = (uint32_t)(st->seed >> 32);
+    // this thread's call: byte i of word k
+    const int m = unit, k = m >> 2, i = m & 3;
+    // bytes i of two words to bytes 1, 2 and, after them, byte i of a third to byte 3
+    const uint32_t two = 0x0C04000Cu + (uint32_t)i * 0x010100u, three = 0x04020100u + ((uint32_t)i << 24);
+    for (int64_t t = t0; t < t0 + ns; ++t) {
+        for (int col = 0; col < 2; ++col) {
+            c.ctr2 = (uint32_t)(2 * t + col);
+            uint32_t* W = col ? E1 : E0;
+            const uint32_t* O = col ? E0 : E1;
+            if (m < M) {
+                const uint4v v = philox10((uint32_t)m, c.rr, c.ctr2, kTagMet, c.k0, c.k1);
+                const uint32_t* T = sm.tab + (col * NW + k) * TW;
+                const uint32_t w = W[(G + k) * Q];
+                uint32_t nb[6];
+                strings::neighbours<L, Q>(O + (G + k) * Q, T, nb);
+                const uint32_t X[6] = {w ^ nb[0], w ^ nb[2], w ^ nb[4], w ^ nb[1], w ^ nb[3], w ^ nb[5]};
+                // rows 1..6 of an 8 x 8 bit matrix, transposed: byte s of (x, y) is twice site s's pattern
+                uint32_t x = __builtin_amdgcn_perm(X[2], __builtin_amdgcn_perm(X[1], X[0], two), three);
+                uint32_t y = __builtin_amdgcn_perm(X[5], __builtin_amdgcn_perm(X[4], X[3], two), three) >> 8;
+                uint32_t d;
+                d = (x ^ (x >> 7)) & 0x00AA00AAu;
+                x = xor3(x, d, d << 7);
+                d = (y ^ (y >> 7)) & 0x00AA00AAu;
+                y = xor3(y, d, d << 7);
+                d = (x ^ (x >> 14)) & 0x0000CCCCu;
+                x = xor3(x, d, d << 14);
+                d = (y ^ (y >> 14)) & 0x0000CCCCu;
+                y = xor3(y, d, d << 14);
+                d = (x ^ __builtin_amdgcn_alignbit(y, x, 28)) & 0xF0F0F0F0u;
+                x ^= d;
+                y ^= d >> 4;
+                const char* tb = reinterpret_cast<const char*>(sm.bound + (col * M + m) * kSplitCall);
+                auto bound = [&](auto B, uint32_t z, int s) -> uint32_t {
+                    constexpr int b = decltype(B)::value;
+                    const uint32_t a = add_byte<b>((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)tb, z);
+                    return *(const __attribute__((address_space(3))) uint16_t*)(uintptr_t)(a + 128 * s);
+                };
+                const uint32_t bd[8] = {bound(std::integral_constant<int, 0>{}, x, 0), bound(std::integral_constant<int, 1>{}, x, 1),
+                                        bound(std::integral_constant<int, 2>{}, x, 2), bound(std::integral_constant<int, 3>{}, x, 3),
+                                        bound(std::integral_constant<int, 0>{}, y, 4), bound(std::integral_constant<int, 1>{}, y, 5),
+                                        bound(std::integral_constant<int, 2>{}, y, 6), bound(std::integral_constant<int, 3>{}, y, 7)};
+                const uint32_t vw[4] = {v.x, v.y, v.z, v.w};
+                uint32_t ra = 0, umax = vw[0];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    ra = words::lshl_or(words::first_look(bd[2 * s] | bd[2 * s + 1] << 16, vw[s]), 2 * s, ra);
+                    if (s > 0) umax = pk_max_u16(umax, vw[s]);
+                }
+                const int sh = 8 * i;
+                const uint32_t sites = (WHOLE ? 0xFFFFFFFFu : T[11]) & (0xFFu << sh);
+                uint32_t acc = (select_bits(0x5555u, ra >> 1, ra >> 16) & 0xFFu) << sh;
+                const bool top = any_top(umax);
+                if ((ra & 0x55555555u) != 0 || top) {
+                    const uint32_t ties = (select_bits(0x5555u, ra, ra >> 15) & 0xFFu) << sh;
+                    if ((ties & sites) || top) {
+                        GaussX gx = {};
+#pragma unroll
+                        for (int a = 0; a < 6; ++a) gx.w[a] = X[a];
+                        acc |= gauss_resolve<6>(Tab64 + ((size_t)(col * M + 4 * k) << 9), gx, ties, (uint32_t)top << i, sites, ~T[6], (uint32_t)k,
+                                                c.rr, c.ctr2, c.k0, c.k1);
+                    }
+                }
+                // only this thread's byte of the word, whose other readers in this phase use their own bytes alone
+                const uint8_t out = (uint8_t)((w ^ (acc & sites)) >> sh);
+                auto byte = [&](int e) -> uint8_t& { return reinterpret_cast<uint8_t*>(W + e * Q)[i]; };
+                byte(G + k) = out;
+                if constexpr (WHOLE) {
+                    if (k < G) byte(G + NW + k) = out;
+                    if (k >= NW - G) byte(k - (NW - G)) = out;
+                }
+            }
+            __syncthreads();
+            if constexpr (!WHOLE) {
+                strings::refresh_ghosts<L, Q>(W, unit, UNITS);
+                __syncthreads();
+            }
+        }
+    }
+
+    // spins back, and (16 lanes of a wave) E
+    for (int w = unit; w < NW; w += UNITS) {
+        const uint32_t sig0 = sm.tab[w * TW + 6], in = sm.tab[w * TW + 11];
+        const uint32_t a = E0[(G + w) * Q], b = E1[(G + w) * Q];
+        if (valid) strings::store_word_u8(row, Gm::STRIDE, w, select_bits(sig0, a, b) & in, select_bits(sig0, b, a) & in);
+    }
+    // the blocks of a CU, one of every 256, leave E to different waves, which lie on different SIMDs
+    if (wave != (int)(blockIdx.x >> 8) % (THREADS / 64)) return;
+    const double E = cube_energy<L, Q>(reinterpret_cast<const double*>(st->J), E0 + G * Q, E1 + G * Q);
+    if (valid && lane < Q) reinterpret_cast<double*>(st->energy[st->cur])[r] = E;
+}
+
 // Chains: the two strings of a 64-replica group in dynamic LDS ([colour][word][64]), its words split by
 // the block's waves.  No ghost words: the bits of a word past its ends come from the words on both
 // sides, periodically.
-// WHOLE: N is a multiple of 64, every word has 32 sites.
-template <bool WHOLE>
-__global__ void __launch_bounds__(kGaussWaves * 64) k_sweep_gauss_chain(pa_state* __restrict__ states, int n_runs,
-                                                                        int blocks, int64_t t0, int ns)
+// WHOLE: N is a multiple of 64, every word has 32 sites.  CALLS: a wave takes a call of eight sites at a time
+// instead of a word, for small populations, where it is the wave's own chain that takes the time.
+template <bool WHOLE, bool CALLS>
+__global__ void __launch_bounds__((CALLS ? kGaussCallWaves : kGaussWaves) * 64)
+k_sweep_gauss_chain(pa_state* __restrict__ states, int n_runs, int blocks, int64_t t0, int ns)
 {
-    constexpr int NWV = kGaussWaves;
+    const int NWV = CALLS ? (int)(blockDim.x >> 6) : kGaussWaves;
     extern __shared__ uint32_t lds[];
     int run, block;
     if (!gauss_place(n_runs, blocks, &run, &block)) return;
@@ -740,7 +964,7 @@ __global__ void __launch_bounds__(kGaussWaves * 64) k_sweep_gauss_chain(pa_state
         E0[k * 64] = ev & in;
         E1[k * 64] = od & in;
     }
-    gauss_sync<NWV>();
+    __syncthreads();
     // the string's word k shifted by one site: bit b holds bit b + 1 or b - 1, periodically
     auto up = [&](const uint32_t* S, int k, uint32_t a) {
         return k + 1 < NW ? __builtin_amdgcn_alignbit(S[(k + 1) * 64], a, 1) : (a >> 1) | (S[0] << end);
@@ -761,30 +985,51 @@ __global__ void __launch_bounds__(kGaussWaves * 64) k_sweep_gauss_chain(pa_state
             rows[i] = ((grow_ptr)Tab)[((col * M + m) << 2) + (lane & 3)];
         }
     };
+    auto call_row = [&](int col, int m) { return ((grow_ptr)Tab)[((col * M + m) << 2) + (lane & 3)]; };
     gu32x4 rows[4];
-    if (wave < NW) load_rows(0, wave, rows);
+    if constexpr (CALLS) {
+        if (wave < M) rows[0] = call_row(0, wave);
+    } else {
+        if (wave < NW) load_rows(0, wave, rows);
+    }
     for (int64_t t = t0; t < t0 + ns; ++t) {
         for (int col = 0; col < 2; ++col) {
             c.ctr2 = (uint32_t)(2 * t + col);
             uint32_t* W = col ? E1 : E0;
             const uint32_t* O = col ? E0 : E1;
+            if constexpr (CALLS) {
 #pragma unroll 1
-            for (int k = wave; k < NW; k += NWV) {
-                gu32x4 next[4];
-                const bool last = k + NWV >= NW;
-                load_rows(last ? col ^ 1 : col, last ? wave : k + NWV, next);
-                const uint32_t w = W[k * 64], a = O[k * 64];
-                // neighbours +1 and -1 of site 2 b + col
-                const uint32_t X[2] = {w ^ (col ? up(O, k, a) : a), w ^ (col ? a : down(O, k, a))};
-                const uint64_t* T64w = Tab64 + ((size_t)(col * M + 4 * k) << 5);
-                const uint32_t odd = col ? 0xFFFFFFFFu : 0u;
-                const bool full = WHOLE || k + 1 < NW;
-                W[k * 64] = gauss_word<2, WHOLE ? 4 : 0>(w, X, rows, full ? 0xFFFFFFFFu : last_sites, odd, full ? 4 : last_bytes,
-                                                 T64w, k, c);
+                for (int m = wave; m < M; m += NWV) {
+                    const bool last = m + NWV >= M;
+                    const gu32x4 next = call_row(last ? col ^ 1 : col, last ? wave : m + NWV);
+                    const int k = m >> 2, i = m & 3;
+                    const uint32_t w = W[k * 64], a = O[k * 64];
+                    const uint32_t X[2] = {w ^ (col ? up(O, k, a) : a), w ^ (col ? a : down(O, k, a))};
+                    const uint32_t sites = WHOLE || k + 1 < NW ? 0xFFFFFFFFu : last_sites;
+                    reinterpret_cast<uint8_t*>(W + k * 64)[i] =
+                        (uint8_t)gauss_byte<2>(w, X, rows[0], sites, col ? 0xFFFFFFFFu : 0u,
+                                               Tab64 + ((size_t)(col * M + 4 * k) << 5), (uint32_t)k, i, c);
+                    rows[0] = next;
+                }
+            } else {
+#pragma unroll 1
+                for (int k = wave; k < NW; k += NWV) {
+                    gu32x4 next[4];
+                    const bool last = k + NWV >= NW;
+                    load_rows(last ? col ^ 1 : col, last ? wave : k + NWV, next);
+                    const uint32_t w = W[k * 64], a = O[k * 64];
+                    // neighbours +1 and -1 of site 2 b + col
+                    const uint32_t X[2] = {w ^ (col ? up(O, k, a) : a), w ^ (col ? a : down(O, k, a))};
+                    const uint64_t* T64w = Tab64 + ((size_t)(col * M + 4 * k) << 5);
+                    const uint32_t odd = col ? 0xFFFFFFFFu : 0u;
+                    const bool full = WHOLE || k + 1 < NW;
+                    W[k * 64] = gauss_word<2, WHOLE ? 4 : 0>(w, X, rows, full ? 0xFFFFFFFFu : last_sites, odd, full ? 4 : last_bytes,
+                                                     T64w, k, c);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) rows[i] = next[i];
+                    for (int i = 0; i < 4; ++i) rows[i] = next[i];
+                }
             }
-            gauss_sync<NWV>();
+            __syncthreads();
         }
     }
 #pragma unroll 1
@@ -939,14 +1184,25 @@ struct GaussLaunch {
     hipStream_t s;
 };
 
-template <int NWV, class K>
-static int launch_gauss_sweep(K kernel, size_t lds, const GaussLaunch& a, const pa_step& step)
+// Where the population (its capacity, in groups of 64, over the runs of the launch) leaves most of the chip
+// idle with a wave per word, its blocks are made of calls.  Chains of more than two calls, 20 sweeps: 64 sites,
+// 2 runs of 1000 (42 groups) 47.7 and 39.4 us, 16 runs (336) 49.4 and 43.7, 32 runs 50.2 and 54.1; 128 sites 86.4
+// and 48.5, 16 runs 87.3 and 61.7; 512 sites 142 and 108, 16 runs 184 and 118, 24 runs 189 and 205; 32 sites have
+// two calls and lose (32.1 and 35.9).  Cubes of side 8, 2 runs of 2000 (82 groups) 160 and 96 us, 4 runs 161
+// and 102, 8 runs 166 and 181; side 10, whose block fills a CU's LDS, 2 runs 288 and 115, 6 runs 297 and 321,
+// and a whole step with 4 runs of 1500 is 1.2 times as long.  Sides 4 and 6 would sweep faster too, but a step of
+// theirs is bound by its launches and gained nothing.
+constexpr int64_t kCallGroupsChain = 336;
+constexpr int64_t call_groups_cube(int L) { return L == 8 ? 168 : (L == 10 ? 96 : 0); }
+
+// per_block: replicas of a block of `waves` waves
+template <class K>
+static int launch_gauss_sweep(K kernel, int64_t per_block, int waves, size_t lds, const GaussLaunch& a, const pa_step& step)
 {
-    const int64_t per_block = 64 * (kGaussWaves / NWV);
     const int64_t blocks = (a.cap + per_block - 1) / per_block;
     const int64_t grid = a.n >= 8 ? (a.n * blocks + 7) / 8 * 8 : a.n * blocks;
     if (grid > INT32_MAX) return PA_ERR_ARG;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kGaussWaves * 64), lds, a.s, a.base, a.n, (int)blocks, step.t0,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3((unsigned)waves * 64), lds, a.s, a.base, a.n, (int)blocks, step.t0,
                        step.n_sweeps);
     return hip_status(hipGetLastError());
 }
@@ -963,26 +1219,34 @@ static int launch_gauss_cube(const GaussLaunch& a, const pa_step& step)
 {
     if (step.n_sweeps > 0) launch_gauss_table<6, L>(L * L * L, a, step.beta_to);
     constexpr int NWV = L == 4 ? 1 : 4;  // (side 4: one word per colour)
-    return launch_gauss_sweep<NWV>(k_sweep_gauss_cube<L, NWV>, 0, a, step);
+    if constexpr (call_groups_cube(L) > 0)
+        if (a.n * (a.cap / 64) <= call_groups_cube(L))
+            return launch_gauss_sweep(k_sweep_gauss_split<L>, kSplitReplicas, kSplitReplicas * GaussSplitSmem<L>::UNITS / 64, 0, a, step);
+    return launch_gauss_sweep(k_sweep_gauss_cube<L, NWV>, 64 * (kGaussWaves / NWV), kGaussWaves, 0, a, step);
 }
 
 static int launch_gauss_chain(int N, const GaussLaunch& a, const pa_step& step)
 {
     if (step.n_sweeps > 0) launch_gauss_table<2, 0>(N, a, step.beta_to);
+    const size_t lds = (size_t)2 * ((N / 2 + 31) / 32) * 64 * 4;
+    if (gauss_calls(N) > 2 && a.n * (a.cap / 64) <= kCallGroupsChain) {
+        const int waves = std::min(kGaussCallWaves, (gauss_calls(N) + 3) / 4 * 4);
+        return N % 64 == 0 ? launch_gauss_sweep(k_sweep_gauss_chain<true, true>, 64, waves, lds, a, step)
+                           : launch_gauss_sweep(k_sweep_gauss_chain<false, true>, 64, waves, lds, a, step);
+    }
     switch (gauss_calls(N)) {
-        case 1: return launch_gauss_sweep<1>(k_sweep_gauss_short<1>, 0, a, step);
-        case 2: return launch_gauss_sweep<1>(k_sweep_gauss_short<2>, 0, a, step);
-        case 3: return launch_gauss_sweep<1>(k_sweep_gauss_short<3>, 0, a, step);
-        case 4: return launch_gauss_sweep<1>(k_sweep_gauss_short<4>, 0, a, step);
-        case 5: return launch_gauss_sweep<1>(k_sweep_gauss_short<5>, 0, a, step);
-        case 6: return launch_gauss_sweep<1>(k_sweep_gauss_short<6>, 0, a, step);
-        case 7: return launch_gauss_sweep<1>(k_sweep_gauss_short<7>, 0, a, step);
-        case 8: return launch_gauss_sweep<1>(k_sweep_gauss_short<8>, 0, a, step);
+        case 1: return launch_gauss_sweep(k_sweep_gauss_short<1>, 64 * kGaussWaves, kGaussWaves, 0, a, step);
+        case 2: return launch_gauss_sweep(k_sweep_gauss_short<2>, 64 * kGaussWaves, kGaussWaves, 0, a, step);
+        case 3: return launch_gauss_sweep(k_sweep_gauss_short<3>, 64 * kGaussWaves, kGaussWaves, 0, a, step);
+        case 4: return launch_gauss_sweep(k_sweep_gauss_short<4>, 64 * kGaussWaves, kGaussWaves, 0, a, step);
+        case 5: return launch_gauss_sweep(k_sweep_gauss_short<5>, 64 * kGaussWaves, kGaussWaves, 0, a, step);
+        case 6: return launch_gauss_sweep(k_sweep_gauss_short<6>, 64 * kGaussWaves, kGaussWaves, 0, a, step);
+        case 7: return launch_gauss_sweep(k_sweep_gauss_short<7>, 64 * kGaussWaves, kGaussWaves, 0, a, step);
+        case 8: return launch_gauss_sweep(k_sweep_gauss_short<8>, 64 * kGaussWaves, kGaussWaves, 0, a, step);
         default: break;
     }
-    const size_t lds = (size_t)2 * ((N / 2 + 31) / 32) * 64 * 4;
-    return N % 64 == 0 ? launch_gauss_sweep<kGaussWaves>(k_sweep_gauss_chain<true>, lds, a, step)
-                       : launch_gauss_sweep<kGaussWaves>(k_sweep_gauss_chain<false>, lds, a, step);
+    return N % 64 == 0 ? launch_gauss_sweep(k_sweep_gauss_chain<true, false>, 64, kGaussWaves, lds, a, step)
+                       : launch_gauss_sweep(k_sweep_gauss_chain<false, false>, 64, kGaussWaves, lds, a, step);
 }
 
 int launch_sweep_gauss(const pa_run* runs, int n_runs, bool consecutive, const pa_step& step, hipStream_t s)
