@@ -13,6 +13,7 @@
 #include <type_traits>
 
 #include "pa_common.h"
+#include "pa_hist.h"
 #include "pa_host.h"
 
 namespace pa {
@@ -421,15 +422,23 @@ int launch_features(const pa_run* runs, int n, float* x, hipStream_t s)
     return hip_status(hipGetLastError());
 }
 
+// rho is read by a block per value, so the histogram is put back to zero by a launch of its own
+__global__ void __launch_bounds__(256) k_hist_clear(pa_state* base)
+{
+    pa_state* st = base + blockIdx.y;
+    if (st->status) return;
+    hist::clear(st, blockIdx.x, gridDim.x);
+}
+
 int launch_rho(const pa_run* runs, int n, const double* args, int n_args, int mode, double cap, int64_t ld,
                double* out, hipStream_t s)
 {
     RhoArgs a;
     for (int j = 0; j < kMaxRho; ++j) a.v[j] = j < n_args ? args[j] : 0.0;
-    int rc = launch_hist(runs, n, s);
-    if (rc != PA_OK) return rc;
+    launch_hist(runs, n, s);
     hipLaunchKernelGGL(k_rho, dim3((unsigned)n_args, (unsigned)n), dim3(256), 0, s, runs[0].state, a, n_args, mode,
                        cap, ld, out);
+    hipLaunchKernelGGL(k_hist_clear, dim3(32, (unsigned)n), dim3(256), 0, s, runs[0].state);
     return hip_status(hipGetLastError());
 }
 

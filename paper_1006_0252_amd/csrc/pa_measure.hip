@@ -7,13 +7,12 @@
 #include <algorithm>
 
 #include "pa_common.h"
+#include "pa_hist.h"
 #include "pa_host.h"
 
 #pragma clang fp contract(off)
 
 namespace pa {
-
-constexpr int kMiscEmin = 0, kMiscEmax = 1;
 
 // energy mean (exact integer sum), variance and skewness into record[k], by one wave from the histogram's
 // bins ilo .. ihi
@@ -47,15 +46,18 @@ __device__ __forceinline__ void energy_moments(pa_state* st, int64_t R, int ilo,
     rec->E_skew = m2 > 0.0 ? m3 / (m2 * sqrt(m2)) : 0.0;
 }
 
+// the moments from the histogram, which is put back to zero
 __global__ void __launch_bounds__(64) k_moments(pa_state* base)
 {
     pa_state* st = base + blockIdx.y;
     if (st->status) return;
     const WorkLayout wl = work_layout(st->N, st->n_bins, st->capacity);
-    const int64_t* hist = work_ptr<int64_t>(st, wl.hist);
-    const int64_t* misc = work_ptr<int64_t>(st, wl.misc);
-    const int ilo = ((int)misc[kMiscEmin] - st->E_base) >> 2, ihi = ((int)misc[kMiscEmax] - st->E_base) >> 2;
-    energy_moments(st, st->R, ilo, ihi, [&](int i) { return hist[i]; });
+    int64_t* h = work_ptr<int64_t>(st, wl.hist);
+    int64_t* misc = work_ptr<int64_t>(st, wl.misc);
+    const int ilo = ((int)misc[hist::kMiscEmin] - st->E_base) >> 2, ihi = ((int)misc[hist::kMiscEmax] - st->E_base) >> 2;
+    energy_moments(st, st->R, ilo, ihi, [&](int i) { return h[i]; });
+    for (int i = ilo + threadIdx.x; i <= ihi; i += 64) h[i] = 0;  // the bins that this lane has read
+    if (threadIdx.x == 0) hist::reset_range(misc);
 }
 
 // The same for populations of up to kSmallMoments replicas and kSmallMomentBins bins, a block per run with
@@ -299,8 +301,7 @@ int launch_measure(const pa_run* runs, int n, const pa_run* partner, int pair_xo
     if (cap <= kSmallMoments && bins <= kSmallMomentBins) {
         hipLaunchKernelGGL(k_moments_block, dim3((unsigned)n), dim3(kMomentThreads), (size_t)bins * 4, s, base);
     } else {
-        int rc = launch_hist(runs, n, s);
-        if (rc != PA_OK) return rc;
+        launch_hist(runs, n, s);
         hipLaunchKernelGGL(k_moments, dim3(1, n), dim3(64), 0, s, base);
     }
     if (partner || pair_xor) {

@@ -20,19 +20,17 @@
 #include <algorithm>
 
 #include "pa_common.h"
+#include "pa_hist.h"
 #include "pa_host.h"
 
 #pragma clang fp contract(off)
 
 namespace pa {
 
+using namespace hist;
+
 // Poisson(2^m) inversion tables, m = kLadderMin .. kLadderMax (host-built, uploaded once)
 __device__ uint64_t g_ladder[kLadderLevels][kLadderCap];
-
-// int64 slots of the misc area: E_lo and E_hi of the population being resampled (FP64 bits of E_lo
-// with Gaussian couplings), then ln Q and S of the step (FP64 bits), kept there until k_finish
-// commits the step to the run's state and record
-constexpr int kMiscEmin = 0, kMiscEmax = 1, kMiscLnQ = 2, kMiscS = 3;
 
 // ------------------------------------------------------------------ host tables
 // C[n] = floor(CDF_{2^m}(n) 2^32) with pmf recursion p_0 = exp(-Lambda), p_n = p_{n-1} Lambda / n;
@@ -87,19 +85,6 @@ int upload_ladder(hipStream_t s)
 }
 
 // ------------------------------------------------------------------ kernels
-__global__ void k_hist_clear(pa_state* base)
-{
-    pa_state* st = base + blockIdx.y;
-    if (st->status) return;
-    int64_t* hist = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).hist);
-    int64_t* misc = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).misc);
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < st->n_bins; i += gridDim.x * blockDim.x) hist[i] = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        misc[kMiscEmin] = INT32_MAX;
-        misc[kMiscEmax] = INT32_MIN;
-    }
-}
-
 constexpr int kHistLoads = 8;
 
 // histogram of the current population's energies, counted in an LDS copy of cap_bins entries
@@ -190,16 +175,18 @@ __device__ inline int ladder_level(double x)
     return m < kLadderMin ? kLadderMin : m;
 }
 
-// one block: S in ascending energy order, ln Q, per-bin Poisson parameters (the step's record is
-// written by k_finish, once the new population is known to fit)
+// one block: S in ascending energy order, ln Q, per-bin Poisson parameters, the histogram put back to zero
+// (the step's record is written by k_finish, once the new population is known to fit)
+constexpr int kNormBins = 1024;
+
 __global__ void __launch_bounds__(256) k_normalise(pa_state* base, ResampleParams p)
 {
     pa_state* st = base + blockIdx.y;
     if (st->status) return;
-    __shared__ double prod[1024];
+    __shared__ double prod[kNormBins];
     __shared__ double S_sh;
     const WorkLayout wl = work_layout(st->N, st->n_bins, st->capacity);
-    const int64_t* hist = work_ptr<int64_t>(st, wl.hist);
+    int64_t* hist = work_ptr<int64_t>(st, wl.hist);
     int64_t* misc = work_ptr<int64_t>(st, wl.misc);
     int64_t* bin_q = work_ptr<int64_t>(st, wl.bin_q);
     uint64_t* bin_keep = work_ptr<uint64_t>(st, wl.bin_keep);
@@ -210,9 +197,12 @@ __global__ void __launch_bounds__(256) k_normalise(pa_state* base, ResampleParam
     const double dbeta = p.beta_to - p.beta_from;
     // S = sum_i h_i w_i, i ascending; products in parallel (each rounded once), sum by one thread
     double S = 0.0;
-    for (int b0 = 0; b0 < n; b0 += 1024) {
-        const int cnt = min(1024, n - b0);
-        for (int t = threadIdx.x; t < cnt; t += blockDim.x) prod[t] = (double)hist[ilo + b0 + t] * p.w[b0 + t];
+    for (int b0 = 0; b0 < n; b0 += kNormBins) {
+        const int cnt = min(kNormBins, n - b0);
+        for (int t = threadIdx.x; t < cnt; t += blockDim.x) {
+            prod[t] = (double)hist[ilo + b0 + t] * p.w[b0 + t];
+            hist[ilo + b0 + t] = 0;
+        }
         __syncthreads();
         if (threadIdx.x == 0) S = add_in_order(S, prod, cnt);
         __syncthreads();
@@ -225,6 +215,8 @@ __global__ void __launch_bounds__(256) k_normalise(pa_state* base, ResampleParam
     const bool bad = !isfinite(S) || !(S > 0.0);
     if (threadIdx.x == 0) {
         const double lnQ = -dbeta * (double)E_lo + log(S) - log(R);
+        reset_range(misc);
+        *reinterpret_cast<double*>(&misc[kMiscElo]) = (double)E_lo;
         if (bad) {
             st->status |= PA_FLAG_NONFINITE;
         } else {
@@ -543,9 +535,8 @@ __global__ void k_finish(pa_state* base, ResampleParams p)
     pa_state* st = base + blockIdx.y;
     if (st->status) return;
     const int64_t* misc = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).misc);
-    const double E_lo = st->couplings == PA_GAUSS ? *reinterpret_cast<const double*>(&misc[kMiscEmin])
-                                                  : (double)misc[kMiscEmin];
-    commit_step(st, p, *reinterpret_cast<const double*>(&misc[kMiscLnQ]), *reinterpret_cast<const double*>(&misc[kMiscS]), E_lo);
+    const double* kept = reinterpret_cast<const double*>(misc);
+    commit_step(st, p, kept[kMiscLnQ], kept[kMiscS], kept[kMiscElo]);
 }
 
 // Launch shapes cover the largest run of the call; grid.y indexes the runs, whose states
@@ -567,7 +558,8 @@ static BatchShape batch_shape(const pa_run* runs, int n)
     return b;
 }
 
-int launch_hist(const pa_run* runs, int n, hipStream_t s)
+// the histograms of n runs, which must be zero, as they are between calls
+void launch_hist(const pa_run* runs, int n, hipStream_t s)
 {
     const BatchShape b = batch_shape(runs, n);
     // an LDS histogram of up to 16384 bins, sized for the largest run of the call that fits (runs
@@ -578,15 +570,12 @@ int launch_hist(const pa_run* runs, int n, hipStream_t s)
         pa_buffer_sizes(runs[r].dim, runs[r].L, runs[r].layout, runs[r].couplings, runs[r].capacity, runs[r].n_records, &sz);
         if (sz.n_bins <= 16384) cap_bins = std::max(cap_bins, sz.n_bins);
     }
-    const size_t hist_lds = (size_t)cap_bins * 4;
     // few blocks: each block zeroes and scans all bins of its LDS histogram and merges the occupied
     // ones with global atomics that land on the same few bins (L = 16, 1e6 replicas: 1024 blocks
     // 98 us, 256 blocks 29 us, 128 blocks 21 us; with eight loads in flight per thread, 128 blocks
     // 17.5 us, 256 blocks 28 us, and 64, 32, 16 blocks were slower already before)
     const unsigned hist_blocks = (unsigned)std::min<int64_t>(128, (b.cap_max + 255) / 256);
-    hipLaunchKernelGGL(k_hist_clear, dim3(32, n), dim3(256), 0, s, runs[0].state);
-    hipLaunchKernelGGL(k_hist, dim3(hist_blocks, n), dim3(256), hist_lds, s, runs[0].state, (int)cap_bins);
-    return PA_OK;
+    hipLaunchKernelGGL(k_hist, dim3(hist_blocks, n), dim3(256), (size_t)cap_bins * 4, s, runs[0].state, (int)cap_bins);
 }
 
 // Bit-packed gather, a block of kStageThreads consecutive destination replicas at a time.  The
@@ -931,7 +920,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_resample_small(pa_state* base
         if (tid == kCommit) {
             set_lnQ();
             int64_t* misc = work_ptr<int64_t>(st, wl.misc);
-            misc[kMiscEmin] = lo;
+            *reinterpret_cast<double*>(&misc[kMiscElo]) = E_lo;
             *reinterpret_cast<double*>(&misc[kMiscLnQ]) = lnQ;
             *reinterpret_cast<double*>(&misc[kMiscS]) = S;
         }
@@ -1032,7 +1021,7 @@ __global__ void __launch_bounds__(256) k_gauss_min(pa_state* base)
     }
     if (threadIdx.x == 0) {
         int64_t* misc = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).misc);
-        *reinterpret_cast<double*>(&misc[kMiscEmin]) = red[0];
+        *reinterpret_cast<double*>(&misc[kMiscElo]) = red[0];
     }
 }
 
@@ -1044,7 +1033,7 @@ __global__ void __launch_bounds__(256) k_gauss_weights(pa_state* base, double db
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= st->R) return;
     const int64_t* misc = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).misc);
-    const double E_lo = *reinterpret_cast<const double*>(&misc[kMiscEmin]);
+    const double E_lo = *reinterpret_cast<const double*>(&misc[kMiscElo]);
     const double* E = reinterpret_cast<const double*>(st->energy[st->cur]);
     double* w = reinterpret_cast<double*>(st->energy[st->cur ^ 1]);
     w[j] = expd(-(dbeta * (E[j] - E_lo)));
@@ -1073,7 +1062,7 @@ __global__ void __launch_bounds__(256) k_gauss_normalise(pa_state* base, Resampl
     }
     if (threadIdx.x != 0) return;
     const double dbeta = p.beta_to - p.beta_from;
-    const double E_lo = *reinterpret_cast<const double*>(&misc[kMiscEmin]);
+    const double E_lo = *reinterpret_cast<const double*>(&misc[kMiscElo]);
     if (!isfinite(S) || !(S > 0.0)) {
         st->status |= PA_FLAG_NONFINITE;
         return;
