@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "pa_common.h"
+#include "pa_hist.h"
 #include "pa_host.h"
 #include "pa_lattice.h"
 #include "pa_sweep_strings.h"
@@ -1136,11 +1137,13 @@ __global__ void __launch_bounds__(kGaussWaves * 64) k_sweep_gauss_short(pa_state
 // the tabled kernels cover cubes of even side 4 to 16 and chains of up to 4096 sites
 static bool gauss_tab_shape(int dim, int L) { return dim == 3 ? L >= 4 && L <= 16 : L <= 4096; }
 
-// energy mean, variance, skewness of the population (one block; any summation order: these are
+// energy mean, variance, skewness of the population, the overlap histogram cleared where one will be counted
+// (one block; any summation order: these are
 // compared to 1e-12, not bit for bit)
-__global__ void __launch_bounds__(256) k_moments_gauss(pa_state* base)
+__global__ void __launch_bounds__(256) k_moments_gauss(pa_state* base, bool overlap)
 {
     pa_state* st = base + blockIdx.y;
+    if (overlap) hist::clear_overlaps(st);
     if (st->status) return;
     __shared__ double red[256];
     const int64_t R = st->R;
@@ -1304,9 +1307,9 @@ int launch_energy_gauss(const pa_run* runs, int n, hipStream_t s)
     return hip_status(hipGetLastError());
 }
 
-int launch_moments_gauss(const pa_run* runs, int n, hipStream_t s)
+int launch_moments_gauss(const pa_run* runs, int n, bool overlap, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_moments_gauss, dim3(1, (unsigned)n), dim3(256), 0, s, runs[0].state);
+    hipLaunchKernelGGL(k_moments_gauss, dim3(1, (unsigned)n), dim3(256), 0, s, runs[0].state, overlap);
     return hip_status(hipGetLastError());
 }
 

@@ -32,5 +32,12 @@ __device__ __forceinline__ void clear(const pa_state* st, int block, int blocks)
     if (block == 0 && threadIdx.x == 0) reset_range(work_ptr<int64_t>(st, wl.misc));
 }
 
+// the histogram of the run's overlaps with a partner, cleared by one block before they are counted
+__device__ __forceinline__ void clear_overlaps(const pa_state* st)
+{
+    int64_t* qh = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).qhist);
+    for (int i = threadIdx.x; i <= st->N; i += blockDim.x) qh[i] = 0;
+}
+
 }  // namespace hist
 }  // namespace pa

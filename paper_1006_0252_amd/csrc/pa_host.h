@@ -50,6 +50,6 @@ int launch_energy_gauss(const pa_run* runs, int n, hipStream_t s);
 int launch_sweep_gauss(const pa_run* runs, int n_runs, bool consecutive, const pa_step& step, hipStream_t s);
 int launch_resample_gauss(const pa_run* runs, int n, const pa_step& step, hipStream_t s);
 int launch_measure_gauss(const pa_run* runs, int n, const pa_run* partner, int pair_xor, hipStream_t s);
-int launch_moments_gauss(const pa_run* runs, int n, hipStream_t s);
+int launch_moments_gauss(const pa_run* runs, int n, bool overlap, hipStream_t s);
 
 }  // namespace pa

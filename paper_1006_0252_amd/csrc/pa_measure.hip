@@ -46,10 +46,12 @@ __device__ __forceinline__ void energy_moments(pa_state* st, int64_t R, int ilo,
     rec->E_skew = m2 > 0.0 ? m3 / (m2 * sqrt(m2)) : 0.0;
 }
 
-// the moments from the histogram, which is put back to zero
-__global__ void __launch_bounds__(64) k_moments(pa_state* base)
+// the moments from the histogram, which is put back to zero; overlap: overlaps will be counted next (as a launch
+// of its own, clearing their histogram took 2 us of every measurement)
+__global__ void __launch_bounds__(64) k_moments(pa_state* base, bool overlap)
 {
     pa_state* st = base + blockIdx.y;
+    if (overlap) hist::clear_overlaps(st);
     if (st->status) return;
     const WorkLayout wl = work_layout(st->N, st->n_bins, st->capacity);
     int64_t* h = work_ptr<int64_t>(st, wl.hist);
@@ -64,9 +66,10 @@ __global__ void __launch_bounds__(64) k_moments(pa_state* base)
 // the histogram in LDS: one launch instead of three (clear, histogram, moments), 4 us a step instead of 10.
 constexpr int kSmallMoments = 8192, kSmallMomentBins = 8192, kMomentThreads = 1024;
 
-__global__ void __launch_bounds__(kMomentThreads) k_moments_block(pa_state* base)
+__global__ void __launch_bounds__(kMomentThreads) k_moments_block(pa_state* base, bool overlap)
 {
     pa_state* st = base + blockIdx.x;
+    if (overlap) hist::clear_overlaps(st);
     if (st->status) return;
     extern __shared__ uint32_t hloc[];
     const int R = (int)st->R, Eb = st->E_base, nb = st->n_bins;
@@ -87,13 +90,6 @@ __global__ void __launch_bounds__(kMomentThreads) k_moments_block(pa_state* base
         hi = max(hi, __shfl_xor(hi, off, 64));
     }
     energy_moments(st, R, lo, hi, [&](int i) { return (int64_t)hloc[i]; });
-}
-
-__global__ void k_qhist_clear(pa_state* base)
-{
-    pa_state* st = base + blockIdx.y;
-    int64_t* qh = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).qhist);
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i <= st->N; i += gridDim.x * blockDim.x) qh[i] = 0;
 }
 
 // Hamming distances, one byte per spin: a wave per replica pair (its lanes over 16-byte pieces of the
@@ -291,6 +287,7 @@ __global__ void k_free_energy(const pa_state* __restrict__ base, int n, double* 
 int launch_measure(const pa_run* runs, int n, const pa_run* partner, int pair_xor, hipStream_t s)
 {
     pa_state* base = runs[0].state;
+    const bool overlap = partner || pair_xor;
     int64_t cap = 0, bins = 0;
     for (int r = 0; r < n; ++r) {
         pa_sizes sz;
@@ -299,19 +296,18 @@ int launch_measure(const pa_run* runs, int n, const pa_run* partner, int pair_xo
         bins = std::max(bins, sz.n_bins);
     }
     if (cap <= kSmallMoments && bins <= kSmallMomentBins) {
-        hipLaunchKernelGGL(k_moments_block, dim3((unsigned)n), dim3(kMomentThreads), (size_t)bins * 4, s, base);
+        hipLaunchKernelGGL(k_moments_block, dim3((unsigned)n), dim3(kMomentThreads), (size_t)bins * 4, s, base, overlap);
     } else {
         launch_hist(runs, n, s);
-        hipLaunchKernelGGL(k_moments, dim3(1, n), dim3(64), 0, s, base);
+        hipLaunchKernelGGL(k_moments, dim3(1, n), dim3(64), 0, s, base, overlap);
     }
-    if (partner || pair_xor) {
+    if (overlap) {
         int64_t N = 0, P = 0;
         for (int r = 0; r < n; ++r) {
             N = std::max<int64_t>(N, runs[r].dim == 1 ? runs[r].L : (int64_t)runs[r].L * runs[r].L * runs[r].L);
             P = std::max<int64_t>(P, runs[r].capacity);
         }
         const pa_state* bg = partner ? partner->state : nullptr;
-        hipLaunchKernelGGL(k_qhist_clear, dim3((unsigned)((N + 256) / 256), n), dim3(256), 0, s, base);
         // the partner's population must be final before it is read: both runs on the same stream,
         // or the partner's stream joined by the caller
         // LDS histogram of up to 8192 bins (every cube; longer chains count in global memory)
@@ -334,8 +330,9 @@ int launch_measure(const pa_run* runs, int n, const pa_run* partner, int pair_xo
 // runs as for launch_measure (consecutive states when n > 1)
 int launch_measure_gauss(const pa_run* runs, int n, const pa_run* partner, int pair_xor, hipStream_t s)
 {
-    int rc = launch_moments_gauss(runs, n, s);
-    if (rc != PA_OK || !(partner || pair_xor)) return rc;
+    const bool overlap = partner || pair_xor;
+    const int rc = launch_moments_gauss(runs, n, overlap, s);
+    if (rc != PA_OK || !overlap) return rc;
     int64_t N = 0, P = 0;
     for (int r = 0; r < n; ++r) {
         N = std::max<int64_t>(N, runs[r].dim == 1 ? runs[r].L : (int64_t)runs[r].L * runs[r].L * runs[r].L);
@@ -343,7 +340,6 @@ int launch_measure_gauss(const pa_run* runs, int n, const pa_run* partner, int p
     }
     pa_state* base = runs[0].state;
     const pa_state* bg = partner ? partner->state : nullptr;
-    hipLaunchKernelGGL(k_qhist_clear, dim3((unsigned)((N + 256) / 256), n), dim3(256), 0, s, base);
     const int cap = N + 1 <= 8192 ? (int)(N + 1) : 0;
     const int64_t per_block = 4 * kOverlapU8Items;
     hipLaunchKernelGGL(k_overlap_u8, dim3((unsigned)((P + per_block - 1) / per_block), n), dim3(256),

@@ -1039,6 +1039,17 @@ __global__ void __launch_bounds__(256) k_gauss_weights(pa_state* base, double db
     w[j] = expd(-(dbeta * (E[j] - E_lo)));
 }
 
+// ln Q and S of a step, kept for k_finish (one thread)
+__device__ inline void gauss_keep(pa_state* st, const ResampleParams& p, int64_t* misc, double S, double E_lo)
+{
+    if (!isfinite(S) || !(S > 0.0)) {
+        st->status |= PA_FLAG_NONFINITE;
+        return;
+    }
+    *reinterpret_cast<double*>(&misc[kMiscLnQ]) = -(p.beta_to - p.beta_from) * E_lo + log(S) - log((double)st->R);
+    *reinterpret_cast<double*>(&misc[kMiscGaussS]) = S;
+}
+
 // a block per run: S in replica order, ln Q (the step's record is written by k_finish).  The block
 // loads the weights a chunk at a time into LDS with coalesced loads, and one thread adds them in order
 constexpr int kNormChunk = 4096;
@@ -1060,15 +1071,47 @@ __global__ void __launch_bounds__(256) k_gauss_normalise(pa_state* base, Resampl
         if (threadIdx.x == 0) S = add_in_order(S, chunk, n);
         __syncthreads();
     }
-    if (threadIdx.x != 0) return;
-    const double dbeta = p.beta_to - p.beta_from;
-    const double E_lo = *reinterpret_cast<const double*>(&misc[kMiscElo]);
-    if (!isfinite(S) || !(S > 0.0)) {
-        st->status |= PA_FLAG_NONFINITE;
-        return;
+    if (threadIdx.x == 0) gauss_keep(st, p, misc, S, *reinterpret_cast<const double*>(&misc[kMiscElo]));
+}
+
+// The three above for populations of up to kWeighCap replicas, a block per run with the weights in LDS: one
+// launch instead of three (8 runs of 2000: 24 us as three, 21 as one, and two gaps between launches fewer).  With
+// 512 threads it takes 15 us, but such blocks wait for room beside the other stream's sweeps where runs go
+// in halves: a step of 200 chains is then 1.2% longer.
+constexpr int kWeighCap = 8192, kWeighThreads = 256, kWeighLoads = 8;
+
+__global__ void __launch_bounds__(kWeighThreads) k_gauss_weigh(pa_state* base, ResampleParams p)
+{
+    pa_state* st = base + blockIdx.y;
+    if (st->status) return;
+    extern __shared__ double w_sh[];  // [capacity]
+    __shared__ double red[kWeighThreads / 64];
+    int64_t* misc = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).misc);
+    const int R = (int)st->R;
+    const glob<double> E = (glob<double>)st->energy[st->cur], w = (glob<double>)st->energy[st->cur ^ 1];
+    double E_lo = INFINITY;
+    for (int j0 = threadIdx.x; j0 < R; j0 += kWeighLoads * kWeighThreads) {
+        double e[kWeighLoads];
+#pragma unroll
+        for (int u = 0; u < kWeighLoads; ++u) e[u] = E[min(j0 + u * kWeighThreads, R - 1)];
+#pragma unroll
+        for (int u = 0; u < kWeighLoads; ++u) {
+            if (j0 + u * kWeighThreads < R) w_sh[j0 + u * kWeighThreads] = e[u];
+            E_lo = fmin(E_lo, e[u]);
+        }
     }
-    *reinterpret_cast<double*>(&misc[kMiscLnQ]) = -dbeta * E_lo + log(S) - log((double)R);
-    *reinterpret_cast<double*>(&misc[kMiscGaussS]) = S;
+    for (int o = 32; o > 0; o >>= 1) E_lo = fmin(E_lo, __shfl_xor(E_lo, o, 64));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = E_lo;
+    __syncthreads();
+    E_lo = red[0];
+    for (int i = 1; i < kWeighThreads / 64; ++i) E_lo = fmin(E_lo, red[i]);
+    const double dbeta = p.beta_to - p.beta_from;
+#pragma unroll 4
+    for (int j = threadIdx.x; j < R; j += kWeighThreads) w[j] = w_sh[j] = expd(-(dbeta * (w_sh[j] - E_lo)));
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    *reinterpret_cast<double*>(&misc[kMiscElo]) = E_lo;
+    gauss_keep(st, p, misc, add_in_order(0.0, w_sh, R), E_lo);
 }
 
 // copy numbers from the replica weights, drawn as in k_copies
@@ -1115,9 +1158,13 @@ int launch_resample_gauss(const pa_run* runs, int n, const pa_step& step, hipStr
     const unsigned cap_blocks = (unsigned)((cap + 255) / 256);
     const unsigned tiles = (unsigned)((cap + kScanTile - 1) / kScanTile);
     const unsigned ny = (unsigned)n;
-    hipLaunchKernelGGL(k_gauss_min, dim3(1, ny), dim3(256), 0, s, base);
-    hipLaunchKernelGGL(k_gauss_weights, dim3(cap_blocks, ny), dim3(256), 0, s, base, step.beta_to - step.beta_from);
-    hipLaunchKernelGGL(k_gauss_normalise, dim3(1, ny), dim3(256), 0, s, base, p);
+    if (cap <= kWeighCap) {
+        hipLaunchKernelGGL(k_gauss_weigh, dim3(1, ny), dim3(kWeighThreads), (size_t)cap * 8, s, base, p);
+    } else {
+        hipLaunchKernelGGL(k_gauss_min, dim3(1, ny), dim3(256), 0, s, base);
+        hipLaunchKernelGGL(k_gauss_weights, dim3(cap_blocks, ny), dim3(256), 0, s, base, step.beta_to - step.beta_from);
+        hipLaunchKernelGGL(k_gauss_normalise, dim3(1, ny), dim3(256), 0, s, base, p);
+    }
     hipLaunchKernelGGL(k_gauss_copies, dim3(tiles, ny), dim3(kScanTile), 0, s, base, p);
     hipLaunchKernelGGL(k_offsets, dim3(tiles, ny), dim3(kScanTile), 0, s, base);
     launch_gather(runs, n, s);
