@@ -356,12 +356,34 @@ int launch_free_energy(const pa_run* runs, int n, double* out, hipStream_t s)
 }
 
 // Averages over runs: a wave per average.  One thread per average added a few hundred dependent FP64 terms,
-// each behind an exp, in turn (18 sets of 200 runs 190 us, their 200 bootstrap replicates 305 us; now 8 and
-// 20 us): here each lane takes every 64th run and the wave adds the lanes' sums in a fixed tree.
+// each behind an exp, in turn (18 sets of 200 runs 190 us, their 200 bootstrap replicates 305 us; now 9 and
+// 22 us): here each lane takes every 64th run and the wave adds the lanes' sums in a fixed tree.
 __device__ __forceinline__ double wave_sum(double x)
 {
     for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
     return x;
+}
+
+// A sum with what its additions have rounded off (Knuth's two-sum): the sums whose error the spread of the
+// bootstrap replicates magnifies (weights, observables, plain means)
+struct Sum {
+    double s = 0.0, off = 0.0;
+    __device__ __forceinline__ void operator+=(double x)
+    {
+        const double t = s + x, z = t - s;
+        off += (s - (t - z)) + (x - z);
+        s = t;
+    }
+};
+
+__device__ __forceinline__ double wave_sum(Sum a)
+{
+    for (int o = 32; o > 0; o >>= 1) {
+        const double x = __shfl_xor(a.s, o, 64), off = __shfl_xor(a.off, o, 64);
+        a += x;
+        a.off += off;
+    }
+    return a.off == a.off ? a.s + a.off : a.s;  // (an infinite sum rounds off NaN)
 }
 
 __device__ __forceinline__ double wave_max(double x)
@@ -391,19 +413,17 @@ __device__ void weighted_one(int M, const double* __restrict__ xs, const double*
         if (xr > xmax) xmax = xr;
     }
     xmax = wave_max(xmax);
-    double Z = 0.0, Rsum = 0.0, m = 0.0;
+    Sum z_sum, x_sum;
+    double r_sum = 0.0, v = 0.0;
     for (int i = lane; i < M; i += 64) {
         const int r = run(i);
-        Z += exp(weight(r) - xmax);
-        Rsum += Rs ? Rs[r] : 1.0;
-        m += xs[r];
+        z_sum += exp(weight(r) - xmax);
+        r_sum += Rs ? Rs[r] : 1.0;
+        x_sum += xs[r];
     }
-    Z = wave_sum(Z);
-    Rsum = wave_sum(Rsum);
-    m = wave_sum(m) / (double)M;
-    double v = 0.0;
+    const double Z = wave_sum(z_sum), Rsum = wave_sum(r_sum), m = wave_sum(x_sum) / (double)M;
     for (int k0 = 0; k0 == 0 || k0 < n_obs; k0 += kObsAtOnce) {
-        double a[kObsAtOnce] = {};
+        Sum a[kObsAtOnce];
         for (int i = lane; i < M; i += 64) {
             const int r = run(i);
             if (n_obs > 0) {
@@ -482,15 +502,15 @@ __global__ void __launch_bounds__(64 * kAverageWaves) k_overlap_average(int n_se
     double xmax = -INFINITY;
     for (int p = lane; p < n_pairs; p += 64) xmax = fmax(xmax, xpair(p));
     xmax = wave_max(xmax);
-    double Z = 0.0;
-    for (int p = lane; p < n_pairs; p += 64) Z += exp(xpair(p) - xmax);
-    Z = wave_sum(Z);
-    double o[3] = {0.0, 0.0, 0.0};
+    Sum z_sum, q_sum[3];
+    for (int p = lane; p < n_pairs; p += 64) z_sum += exp(xpair(p) - xmax);
+    const double Z = wave_sum(z_sum);
+    double o[3];
     for (int p = lane; p < n_pairs; p += 64) {
         const double w = exp(xpair(p) - xmax) / Z;
-        for (int k = 0; k < 3; ++k) o[k] += w * Qs[3 * p + k];
+        for (int k = 0; k < 3; ++k) q_sum[k] += w * Qs[3 * p + k];
     }
-    for (int k = 0; k < 3; ++k) o[k] = wave_sum(o[k]);
+    for (int k = 0; k < 3; ++k) o[k] = wave_sum(q_sum[k]);
     if (lane != 0) return;
     double* os = out + set * 4;
     os[0] = o[0];
@@ -538,10 +558,9 @@ __global__ void __launch_bounds__(64 * kAverageWaves) k_bootstrap_err(int n_sets
     if (t >= (int64_t)n_sets * nq) return;
     const int64_t set = t / nq, q = t % nq;
     const double* r = rep + set * n_boot * nq + q;
-    double m = 0.0;
+    double m = 0.0, v = 0.0;
     for (int b = lane; b < n_boot; b += 64) m += r[(int64_t)b * nq];
     m = wave_sum(m) / (double)n_boot;
-    double v = 0.0;
     for (int b = lane; b < n_boot; b += 64) {
         const double d = r[(int64_t)b * nq] - m;
         v += d * d;
