@@ -380,7 +380,7 @@ def bench_gauss(args):
                    "n_sweeps": 100, "runs": 126, "disorder_seed": 1, "layout": "u8"},
         "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_LANE_OPS / 1e12,
                      "unit": "T lane-ops/s", "frac": achieved / PEAK_LANE_OPS, "traffic": None,
-                     "kernel": "k_gauss_table + k_sweep_gauss_tab (HIP events around pa_sweep)",
+                     "kernel": "k_gauss_table + k_sweep_gauss_cube (HIP events around pa_sweep)",
                      "ops_per_attempt": OPS_PER_ATTEMPT_GAUSS, "sweep_attempts_per_s": rate},
         "physics": {"free_energy_reference": "T=2", "minus_betaF_bar": r["minus_betaF_bar"], "var_betaF": r["var_betaF"],
                     "mean_minus_betaF": r["mean_minus_betaF"], "E_bar": r["E_bar"], "gamma_bar": r["gamma_bar"]},

@@ -1,7 +1,7 @@
 """Ensembles of independent runs and their weighted averages (Sec. III; Sec. IV eq. omegaprime).
 
-run_batched(): all runs of a batch annealed together (one launch per kernel, persistent
-sweep, the whole schedule captured as one HIP graph), then per realisation the run weights
+run_batched(): all runs of a batch annealed together (one launch per kernel, one
+per lattice size for the sweep, the whole schedule captured as one HIP graph), then per realisation the run weights
 R^(r) exp(-beta F~_r) (runs with unequal target sizes, Sec. III) give the weighted energy
 and free energy, and the pair weights R^(1) R^(2) exp(-beta (F~^(1) + F~^(2))) of the overlap
 pairs give the weighted <q^2>, <q^4>, Gamma and the Binder ratio, computed on the device by

@@ -402,7 +402,7 @@ class Run:
 
 class Batch:
     """Many runs whose device states are consecutive: every pa_* call covers all of them with
-    one launch per kernel (the sweep as one persistent launch over (run, tile) work items)."""
+    one launch per kernel (the sweep one launch per lattice size over (run, tile) work items)."""
 
     def __init__(self, specs, n_records, layout="bits64", device="cuda", stream=None, capacity_factor=1.25):
         """specs: list of dicts with dim, L, R0, seed, disorder_seed."""
