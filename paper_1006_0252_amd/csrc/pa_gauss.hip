@@ -475,9 +475,9 @@ struct GaussX { uint32_t w[6]; };
 // runs took 3% longer).  T64w: the word's rows of the u64 table; sites is the mask of the word's sites, odd
 // that of the sites 2 h + 1.  Returns the accepted ones.
 template <int NB>
-static __device__ __noinline__ uint32_t gauss_resolve(const uint64_t* __restrict__ T64w, GaussX X, uint32_t ties, uint32_t tops,
-                                                      uint32_t sites, uint32_t odd, uint32_t k, uint32_t rr, uint32_t ctr2,
-                                                      uint32_t k0, uint32_t k1)
+__device__ __forceinline__ uint32_t gauss_resolve(const uint64_t* __restrict__ T64w, const GaussX& X, uint32_t ties, uint32_t tops,
+                                                  uint32_t sites, uint32_t odd, uint32_t k, uint32_t rr, uint32_t ctr2,
+                                                  uint32_t k0, uint32_t k1)
 {
     uint32_t high = 0;  // sites with u = 0xFFFF
     while (tops) {
@@ -501,6 +501,17 @@ static __device__ __noinline__ uint32_t gauss_resolve(const uint64_t* __restrict
         F |= (uint32_t)accept << j;
     }
     return F;
+}
+
+// The same out of line, for the kernels of small populations: shorter code matters more there than registers
+// (in line, two runs of side 8 took 1.3% longer; in the others the values kept over a call took the registers
+// past what six waves per SIMD leave: 200 chains of 256 sites 0.90 ms a call, 0.86 in line).
+template <int NB>
+static __device__ __noinline__ uint32_t gauss_resolve_call(const uint64_t* __restrict__ T64w, GaussX X, uint32_t ties, uint32_t tops,
+                                                           uint32_t sites, uint32_t odd, uint32_t k, uint32_t rr, uint32_t ctr2,
+                                                           uint32_t k0, uint32_t k1)
+{
+    return gauss_resolve<NB>(T64w, X, ties, tops, sites, odd, k, rr, ctr2, k0, k1);
 }
 
 // whether either half of a word is 0xFFFF
@@ -604,7 +615,7 @@ __device__ __forceinline__ uint32_t gauss_byte(uint32_t w, const uint32_t (&X)[N
             GaussX gx = {};
 #pragma unroll
             for (int a = 0; a < NB; ++a) gx.w[a] = X[a];
-            acc |= gauss_resolve<NB>(T64w, gx, ties, (uint32_t)top << i, sites, odd, k, c.rr, c.ctr2, c.k0, c.k1);
+            acc |= gauss_resolve_call<NB>(T64w, gx, ties, (uint32_t)top << i, sites, odd, k, c.rr, c.ctr2, c.k0, c.k1);
         }
     }
     return (w ^ (acc & sites)) >> sh;  // (the byte: the rest of the word arbitrary)
@@ -644,8 +655,13 @@ struct GaussCubeSmem {
     uint32_t tab[2 * strings::Geo<L>::NW * strings::Geo<L>::TW];         // geometry masks
 };
 
+// Waves per SIMD that the registers must leave room for: six at sides 6 and 8 (126 runs, 20 sweeps of side 6 598
+// -> 582 us, 100 of side 8 4.19 -> 4.11 ms); the others are faster with the five they happen to get (side 4 162 and
+// 181 us, side 10, 40 runs, 795 and 891).
+constexpr int gauss_cube_waves(int L) { return L == 6 || L == 8 ? 6 : 1; }
+
 template <int L, int NWV>
-__global__ void __launch_bounds__(kGaussWaves * 64) k_sweep_gauss_cube(pa_state* __restrict__ states, int n_runs,
+__global__ void __launch_bounds__(kGaussWaves * 64, gauss_cube_waves(L)) k_sweep_gauss_cube(pa_state* __restrict__ states, int n_runs,
                                                                        int blocks, int64_t t0, int ns)
 {
     using Gm = strings::Geo<L>;
@@ -897,7 +913,7 @@ k_sweep_gauss_split(pa_state* __restrict__ states, int n_runs, int blocks, int64
                         GaussX gx = {};
 #pragma unroll
                         for (int a = 0; a < 6; ++a) gx.w[a] = X[a];
-                        acc |= gauss_resolve<6>(Tab64 + ((size_t)(col * M + 4 * k) << 9), gx, ties, (uint32_t)top << i, sites, ~T[6], (uint32_t)k,
+                        acc |= gauss_resolve_call<6>(Tab64 + ((size_t)(col * M + 4 * k) << 9), gx, ties, (uint32_t)top << i, sites, ~T[6], (uint32_t)k,
                                                 c.rr, c.ctr2, c.k0, c.k1);
                     }
                 }
