@@ -76,12 +76,12 @@ __device__ __forceinline__ void bond_masks(const int8_t* J, int N, int k, int la
 }
 
 // one colour's attempts in a word: X the bond words of +1 and -1 (set: J s s = -1)
-template <int MODE, int NBYTES>
+template <int MODE, int NBYTES, bool TIES_IN_LINE = true>
 __device__ __forceinline__ uint32_t update(uint32_t w, uint32_t b0, uint32_t b1, uint32_t sites, uint32_t k, int col,
                                            const Lane& c, const Thr& th)
 {
     const uint32_t cand = b0 & b1 & sites;
-    const uint32_t nw = decide_word<MODE, true, NBYTES>(w, 0u, 0u, cand, 4u * k, 1u, nullptr, c, th, [&]() {
+    const uint32_t nw = decide_word<MODE, true, NBYTES, TIES_IN_LINE>(w, 0u, 0u, cand, 4u * k, 1u, nullptr, c, th, [&]() {
         return WordSites{4u * k, 1u, 64u * k, 16u, col ? 0xFFFFFFFFu : 0u};
     });
     return select_bits(sites, nw, w);
@@ -199,7 +199,7 @@ __global__ void __launch_bounds__(64 * kWaves) k_sweep_chain(const pa_state* __r
                 const uint32_t* j = masks + 4 * k;
                 const uint32_t b0 = col ? xor3(w, up(O, k, a), j[1]) : xor3(w, a, j[0]);
                 const uint32_t b1 = col ? xor3(w, a, j[0]) : xor3(w, down(O, k, a), j[2]);
-                W[k * 64] = update<MODE, 4>(w, b0, b1, k + 1 < NW ? 0xFFFFFFFFu : last_sites, (uint32_t)k, col, c, th);
+                W[k * 64] = update<MODE, 4, false>(w, b0, b1, k + 1 < NW ? 0xFFFFFFFFu : last_sites, (uint32_t)k, col, c, th);
             }
             __syncthreads();
         }

@@ -61,12 +61,6 @@ __host__ __device__ constexpr int waves_of(int L, int LPR)
 constexpr int64_t kSplitGroups = 1024;
 __host__ __device__ constexpr bool always_split(int L) { return L >= 20; }
 
-// The second kernel template takes 91 registers there, which leave a CU room for two blocks of eight waves.
-// Held to 80, with some kept in memory over its rare out-of-line ties, it has room for three: ten sweeps at beta 3
-// of L = 20, 2 10^4 replicas (1250 blocks) 400 -> 388 us, 10^5 1840 -> 1726; L = 24, 10^4 388 -> 378; but L = 20,
-// 2000 replicas (125 blocks) 102 -> 108.  So from more than two blocks per CU on.
-constexpr unsigned kThirdBlock = 512;
-
 // groups of a block (a one-wave group needs no barrier: four share a bound table)
 __host__ __device__ constexpr int groups_of(int L, int LPR) { return waves_of(L, LPR) == 1 ? 4 : 1; }
 __host__ __device__ constexpr int threads_of(int L, int LPR) { return 64 * waves_of(L, LPR) * groups_of(L, LPR); }
@@ -292,9 +286,8 @@ __device__ __forceinline__ void place(int* group, int* wave)
 }
 
 // one run: group i of the grid takes replicas 64 / LPR i ..
-// EU: waves per SIMD that the registers must leave room for (1: as many as they happen to)
-template <int L, int MODE, int LAYOUT, int LPR, int EU = 1>
-__global__ void __launch_bounds__(threads_of(L, LPR), EU) k_sweep_group(const pa_state* __restrict__ st, SweepParams p, Thr th)
+template <int L, int MODE, int LAYOUT, int LPR>
+__global__ void __launch_bounds__(threads_of(L, LPR)) k_sweep_group(const pa_state* __restrict__ st, SweepParams p, Thr th)
 {
     __shared__ BlockSmem<L, LPR> sm;
     constexpr int GPB = groups_of(L, LPR);
@@ -379,12 +372,6 @@ static void launch(const Launch& a, const SweepParams& p, const Thr& th, hipStre
     const dim3 g((unsigned)((a.items * LPR + GPB - 1) / GPB)), b(threads_of(L, LPR));
     const bool z = all_tops_zero(th);
     if (a.run) {
-        if constexpr (always_split(L) && LPR == 4) {
-            if (z && g.x > kThirdBlock) {
-                hipLaunchKernelGGL((k_sweep_group<L, 2, LAYOUT, LPR, 6>), g, b, 0, s, a.run->state, p, th);
-                return;
-            }
-        }
         if (z) hipLaunchKernelGGL((k_sweep_group<L, 2, LAYOUT, LPR>), g, b, 0, s, a.run->state, p, th);
         else hipLaunchKernelGGL((k_sweep_group<L, 0, LAYOUT, LPR>), g, b, 0, s, a.run->state, p, th);
     } else {

@@ -201,8 +201,8 @@ __device__ __forceinline__ uint32_t site_of(const WordSites& ws, int b)
 //
 // General thresholds: bits = candidate sites whose field equals the top of their class, so u is
 // that top and only the low bits need drawing.  Returns the accepted ones.  Arguments come as
-// scalars: a structure passed by value to this out-of-line call would go through private memory.
-static __device__ __noinline__ uint32_t resolve_ties(uint32_t bits, uint32_t c0, uint32_t c1, uint32_t base,
+// scalars: a structure passed by value to the out-of-line form would go through private memory.
+__device__ __forceinline__ uint32_t resolve_ties(uint32_t bits, uint32_t c0, uint32_t c1, uint32_t base,
                                                      uint32_t byte_step, uint32_t odd, uint32_t rr, uint32_t ctr2,
                                                      uint32_t k0, uint32_t k1, uint32_t thi4, uint32_t thi5,
                                                      uint32_t thi6, uint64_t T4, uint64_t T5, uint64_t T6)
@@ -222,7 +222,7 @@ static __device__ __noinline__ uint32_t resolve_ties(uint32_t bits, uint32_t c0,
 
 // Every top zero: a candidate accepts only if u = 0 and its low bits fall below the threshold.
 // bytes: the bytes (bit i) whose fields hold a zero; their Philox calls are drawn again.
-static __device__ __noinline__ uint32_t resolve_zero_bytes(uint32_t bytes, uint32_t cand, uint32_t c0, uint32_t c1,
+__device__ __forceinline__ uint32_t resolve_zero_bytes(uint32_t bytes, uint32_t cand, uint32_t c0, uint32_t c1,
                                                            uint32_t call0, uint32_t call_step, uint32_t base,
                                                            uint32_t byte_step, uint32_t odd, uint32_t rr,
                                                            uint32_t ctr2, uint32_t k0, uint32_t k1, uint64_t T4,
@@ -249,6 +249,27 @@ static __device__ __noinline__ uint32_t resolve_zero_bytes(uint32_t bytes, uint3
     return racc;
 }
 
+// The same out of line.  A call keeps the values that live over it in high registers (sides from 20 on with
+// four lanes per replica: 91 registers, 50 in line, and 2 10^4 replicas of L = 20 at beta 3 400 us in line 360), and
+// its arguments cost the wave more than the few tied sites; but in line, the second kernel template with one lane
+// per replica is 0.6% slower (L = 16 at beta 4, 6.38 and 6.42 ms) and a chain of 256 sites in LDS 3% (41.7 and 43 us).
+static __device__ __noinline__ uint32_t resolve_ties_call(uint32_t bits, uint32_t c0, uint32_t c1, uint32_t base,
+                                                          uint32_t byte_step, uint32_t odd, uint32_t rr, uint32_t ctr2,
+                                                          uint32_t k0, uint32_t k1, uint32_t thi4, uint32_t thi5,
+                                                          uint32_t thi6, uint64_t T4, uint64_t T5, uint64_t T6)
+{
+    return resolve_ties(bits, c0, c1, base, byte_step, odd, rr, ctr2, k0, k1, thi4, thi5, thi6, T4, T5, T6);
+}
+
+static __device__ __noinline__ uint32_t resolve_zero_bytes_call(uint32_t bytes, uint32_t cand, uint32_t c0, uint32_t c1,
+                                                                uint32_t call0, uint32_t call_step, uint32_t base,
+                                                                uint32_t byte_step, uint32_t odd, uint32_t rr,
+                                                                uint32_t ctr2, uint32_t k0, uint32_t k1, uint64_t T4,
+                                                                uint64_t T5, uint64_t T6)
+{
+    return resolve_zero_bytes(bytes, cand, c0, c1, call0, call_step, base, byte_step, odd, rr, ctr2, k0, k1, T4, T5, T6);
+}
+
 // The Metropolis decision for the 32 sites of word w with bond classes c0, c1, c2 (c2 set: a
 // candidate, c >= 4; clear: flips outright); returns the new word.  MODE 0: bounds from the
 // 256-entry table tt; MODE 1: one bound, that of c = 4, for every candidate (chains); MODE 2: every top
@@ -256,8 +277,8 @@ static __device__ __noinline__ uint32_t resolve_zero_bytes(uint32_t bytes, uint3
 // (philox10_lane keeps the uniform rounds on the scalar unit).  ws_fn() gives the word's WordSites
 // (only the rare tie paths need them).  NBYTES < 4: only bytes 0 .. NBYTES - 1 hold sites (the last
 // word of a string); the other bytes' calls are not drawn and their bits come out as non-candidates
-// would (flipped), for the caller to ignore.
-template <int MODE, bool UNIFORM_CALLS, int NBYTES = 4, class WS>
+// would (flipped), for the caller to ignore.  TIES_IN_LINE: whether ties are decided in line (MODE 0, 1).
+template <int MODE, bool UNIFORM_CALLS, int NBYTES = 4, bool TIES_IN_LINE = true, class WS>
 __device__ __forceinline__ uint32_t decide_word(uint32_t w, uint32_t c0, uint32_t c1, uint32_t c2, uint32_t call0,
                                                 uint32_t call_step, const uint2* tt, const Lane& c, const Thr& th,
                                                 WS ws_fn)
@@ -287,8 +308,12 @@ __device__ __forceinline__ uint32_t decide_word(uint32_t w, uint32_t c0, uint32_
 #pragma unroll
             for (int i = 0; i < NBYTES; ++i) bytes |= (uint32_t)(m[i].x == 0 || m[i].y == 0) << i;
             const WordSites ws = ws_fn();
-            nw = w ^ (~c2 | resolve_zero_bytes(bytes, c2, c0, c1, call0, call_step, ws.base, ws.byte_step, ws.odd,
-                                               c.rr, c.ctr2, c.k0, c.k1, th.T4, th.T5, th.T6));
+            const uint32_t acc =
+                UNIFORM_CALLS ? resolve_zero_bytes_call(bytes, c2, c0, c1, call0, call_step, ws.base, ws.byte_step, ws.odd,
+                                                        c.rr, c.ctr2, c.k0, c.k1, th.T4, th.T5, th.T6)
+                              : resolve_zero_bytes(bytes, c2, c0, c1, call0, call_step, ws.base, ws.byte_step, ws.odd, c.rr,
+                                                   c.ctr2, c.k0, c.k1, th.T4, th.T5, th.T6);
+            nw = w ^ (~c2 | acc);
         }
         return nw;
     } else {
@@ -332,8 +357,10 @@ __device__ __forceinline__ uint32_t decide_word(uint32_t w, uint32_t c0, uint32_
                                               select_bits(0x55550000u, rb << 16, rb << 1)) & c2;
             if (ties) {
                 const WordSites ws = ws_fn();
-                acc |= resolve_ties(ties, c0, c1, ws.base, ws.byte_step, ws.odd, c.rr, c.ctr2, c.k0, c.k1, th.thi4,
-                                    th.thi5, th.thi6, th.T4, th.T5, th.T6);
+                acc |= TIES_IN_LINE ? resolve_ties(ties, c0, c1, ws.base, ws.byte_step, ws.odd, c.rr, c.ctr2, c.k0, c.k1,
+                                                   th.thi4, th.thi5, th.thi6, th.T4, th.T5, th.T6)
+                                    : resolve_ties_call(ties, c0, c1, ws.base, ws.byte_step, ws.odd, c.rr, c.ctr2, c.k0, c.k1,
+                                                        th.thi4, th.thi5, th.thi6, th.T4, th.T5, th.T6);
             }
         }
         return w ^ (~c2 | acc);

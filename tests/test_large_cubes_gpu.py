@@ -1,5 +1,5 @@
-"""Cold sweeps of cubes past side 18 with two and with three blocks per CU (chosen by the launch's blocks, so
-by the capacity alone) against the oracle, bit for bit, with enough attempts for dozens of zero draws."""
+"""Cold sweeps of cubes past side 18 in small and large launches (by the capacity) against the oracle, bit for
+bit, with enough attempts for dozens of zero draws."""
 import numpy as np
 import pytest
 
