@@ -232,9 +232,9 @@ __global__ void __launch_bounds__(64) k_sweep_gauss(const pa_state* __restrict__
 // words puts the patterns of sites k, 8 + k, 16 + k, 24 + k into bits 2..7 of the four bytes of one
 // word, so an address is one shift.  The u64 table of T64 follows in the same order.
 //
-// Bound by the vector ALU and the latency of a wave's own chain: 11.3 VALU and 1.27 LDS instructions per
-// attempt at side 8, of which Philox 4.7; the 94 registers leave five waves per SIMD.  126 runs of side
-// 8, R = 2000, 100 sweeps: 4.11 ms, 3.1e12 attempts/s; with one wave per group (as the kernel before, on
+// Bound by the vector ALU and the latency of a wave's own chain: 10.7 VALU and 1.27 LDS instructions per
+// attempt at side 8, of which Philox 4.7; the 73 registers leave six waves per SIMD.  126 runs of side
+// 8, R = 2000, 100 sweeps: 4.05 ms, 3.1e12 attempts/s; with one wave per group (as the kernel before, on
 // 16-site segments of both colours: 13.9 VALU) 5.23 ms, and a second round of blocks as soon as some
 // runs have more than 32 groups (R = 2060: 4.30 ms against 6.62 ms).  50 runs: 4.12 -> 2.08 ms.  The
 // sides other than 4 and 8 took one thread per replica: side 6, 8 runs, 20 sweeps 40 ms -> 0.09 ms.
