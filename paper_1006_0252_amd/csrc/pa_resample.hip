@@ -9,11 +9,13 @@
 //             Poisson(64) blocks q, ladder level m and thinning threshold
 //   copies    Poisson(lambda) per replica from its Philox stream (integer compares only), and the sum
 //             of each tile of kScanTile replicas
-//   offsets   exclusive scan of the copy numbers -> offsets, R~', capacity/extinction flags; source
-//             replica of every new replica
+//   offsets   exclusive scan of the copy numbers -> offsets, R~'; source replica of every new replica
 //   gather    copy spins and energies into the other buffer
-//   finish    swap buffers, R~ = R~', accumulate ln Q, record
-// Every kernel is a no-op once the run's sticky status is set.
+//   finish    swap buffers, R~ = R~', accumulate ln Q, record; or, where R~' does not fit, the
+//             capacity / extinction flag
+// Every kernel is a no-op once the run's sticky status is set.  The status is written only by launches of
+// one block per run, after every wave of it has read it: the blocks of a launch that change it under each
+// other could leave some waves of a block at its first line and take the rest on.
 #include <math.h>
 #include <string.h>
 
@@ -388,8 +390,8 @@ __global__ void __launch_bounds__(kScanTile) k_copies(pa_state* base, int32_t k)
 }
 
 // Offsets and sources, a block per tile of kScanTile consecutive sources.  The block adds the sums of the
-// tiles before it (and all of them, for R~' and the capacity and extinction checks, which every block
-// makes alike and block 0 records), scans its own copy numbers into offsets[j] (offsets[R] = R~'), and its
+// tiles before it (and all of them, for R~', which block 0 records, and for the capacity and extinction
+// checks, which every block makes alike and k_finish turns into the flag), scans its own copy numbers into offsets[j] (offsets[R] = R~'), and its
 // new replicas offsets[j0] .. offsets[j0 + 256] - 1 each find their source in the block's offsets in LDS
 // (largest j with offsets[j] <= r', 8 LDS steps) and are written in order.  Per new replica over the whole
 // array, the same search took ~20 dependent global loads; per source, the writes of uneven copy numbers
@@ -429,13 +431,8 @@ __global__ void __launch_bounds__(kScanTile) k_offsets(pa_state* base)
         total += red[0][w];
         before += red[1][w];
     }
-    const bool over = total > st->capacity;
-    if (mine == 0 && tid == 0) {
-        st->R_new = total;
-        if (over) st->status |= PA_FLAG_CAPACITY;
-        else if (total == 0) st->status |= PA_FLAG_EXTINCT;
-    }
-    if (over || total == 0) return;  // the same for every block
+    if (mine == 0 && tid == 0) st->R_new = total;
+    if (total > st->capacity || total == 0) return;  // the same for every block
     const int64_t j = j0 + tid;
     const int64_t v = j < R ? st->counts[j] : 0;
     int64_t x = v;  // inclusive wave scan
@@ -466,11 +463,17 @@ __global__ void __launch_bounds__(kScanTile) k_offsets(pa_state* base)
     }
 }
 
+// whether the step's new population is to be formed (offsets has run, finish has not)
+__device__ __forceinline__ bool accepted(const pa_state* st)
+{
+    return !st->status && st->R_new > 0 && st->R_new <= st->capacity;
+}
+
 // u8 gather: one thread per 16 bytes of a destination row
 __global__ void __launch_bounds__(256) k_gather_u8(pa_state* base)
 {
     pa_state* st = base + blockIdx.y;
-    if (st->status) return;
+    if (!accepted(st)) return;
     const int per_row = st->row_stride / 16;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t rn = t / per_row;
@@ -534,6 +537,10 @@ __global__ void k_finish(pa_state* base, ResampleParams p)
 {
     pa_state* st = base + blockIdx.y;
     if (st->status) return;
+    if (!accepted(st)) {
+        st->status |= st->R_new > 0 ? PA_FLAG_CAPACITY : PA_FLAG_EXTINCT;
+        return;
+    }
     const int64_t* misc = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).misc);
     const double* kept = reinterpret_cast<const double*>(misc);
     commit_step(st, p, kept[kMiscLnQ], kept[kMiscS], kept[kMiscElo]);
@@ -648,7 +655,7 @@ __global__ void __launch_bounds__(kStageThreads, 8) k_gather_bits_staged(pa_stat
 {
     __shared__ uint4 stage[kStageGroups * kStageRows * 16];
     pa_state* st = base + blockIdx.y;
-    if (st->status) return;
+    if (!accepted(st)) return;
     const int WB = st->dim == 1 ? 4 : (st->L <= 8 ? 1 : (st->L <= 16 ? 2 : 4));
     if (WB == 1) gather_staged<uint8_t>(st, rows_per, stage);
     else if (WB == 2) gather_staged<uint16_t>(st, rows_per, stage);
