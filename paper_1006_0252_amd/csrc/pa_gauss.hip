@@ -1159,7 +1159,7 @@ static bool gauss_tab_shape(int dim, int L) { return dim == 3 ? L >= 4 && L <= 1
 __global__ void __launch_bounds__(256) k_moments_gauss(pa_state* base, bool overlap)
 {
     pa_state* st = base + blockIdx.y;
-    if (overlap) hist::clear_overlaps(st);
+    if (overlap) hist::clear_overlaps(st, 0, 1);
     if (st->status) return;
     __shared__ double red[256];
     const int64_t R = st->R;

@@ -21,7 +21,7 @@ int launch_sweep_group_batch(int L, int layout, pa_state* base, int pos0, int po
                              const SweepParams& p, int64_t items, int64_t groups, hipStream_t s);
 // batched launchers: n runs whose device states are contiguous (runs[r].state == runs[0].state + r)
 int launch_resample(const pa_run* runs, int n, const pa_step& step, hipStream_t s);
-void launch_hist(const pa_run* runs, int n, hipStream_t s);
+void launch_hist(const pa_run* runs, int n, bool overlap, hipStream_t s);
 int launch_measure(const pa_run* runs, int n, const pa_run* partner, int pair_xor, hipStream_t s);
 int launch_free_energy(const pa_run* runs, int n, double* out, hipStream_t s);
 int launch_sweep_batch(const pa_run* runs, int n, const SweepParams& p, hipStream_t s);

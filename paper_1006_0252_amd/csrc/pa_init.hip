@@ -7,7 +7,6 @@
 #include <algorithm>
 
 #include "pa_common.h"
-#include "pa_hist.h"
 #include "pa_host.h"
 #include "pa_lattice.h"
 
@@ -208,7 +207,6 @@ __global__ void __launch_bounds__(256) k_init_finish(pa_state* base)
         if (i == offsetof(pa_record, R) / sizeof(double)) v = (double)st->R;
         d[i] = v;
     }
-    if (st->couplings != PA_GAUSS) hist::clear(st, 0, 1);
     if (threadIdx.x != 0) return;
     const int B = st->n_bonds;
     if (st->couplings != PA_GAUSS) {

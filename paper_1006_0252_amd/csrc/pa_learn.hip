@@ -391,19 +391,19 @@ __global__ void __launch_bounds__(256) k_rho(pa_state* base, RhoArgs args, int n
         result = NAN;
     } else {
         const WorkLayout wl = work_layout(st->N, st->n_bins, st->capacity);
-        const int64_t* hist = work_ptr<int64_t>(st, wl.hist);
+        const int64_t* h = work_ptr<int64_t>(st, wl.hist);
         const int64_t* misc = work_ptr<int64_t>(st, wl.misc);
-        const int ilo = (int)((misc[0] - st->E_base) >> 2), ihi = (int)((misc[1] - st->E_base) >> 2);
+        const int ilo = (int)((misc[hist::kMiscEmin] - st->E_base) >> 2), ihi = (int)((misc[hist::kMiscEmax] - st->E_base) >> 2);
         const double R = (double)st->R;
         if (mode == 0) {
-            result = rho_of(hist, ilo, ihi, R, args.v[j], red);
-        } else if (rho_of(hist, ilo, ihi, R, cap, red) <= args.v[j]) {
+            result = rho_of(h, ilo, ihi, R, args.v[j], red);
+        } else if (rho_of(h, ilo, ihi, R, cap, red) <= args.v[j]) {
             result = cap;
         } else {
             double lo = 0.0, hi = cap;
             for (int it = 0; it < 64; ++it) {
                 const double mid = 0.5 * (lo + hi);
-                if (rho_of(hist, ilo, ihi, R, mid, red) < args.v[j]) lo = mid;
+                if (rho_of(h, ilo, ihi, R, mid, red) < args.v[j]) lo = mid;
                 else hi = mid;
             }
             result = 0.5 * (lo + hi);
@@ -422,23 +422,14 @@ int launch_features(const pa_run* runs, int n, float* x, hipStream_t s)
     return hip_status(hipGetLastError());
 }
 
-// rho is read by a block per value, so the histogram is put back to zero by a launch of its own
-__global__ void __launch_bounds__(256) k_hist_clear(pa_state* base)
-{
-    pa_state* st = base + blockIdx.y;
-    if (st->status) return;
-    hist::clear(st, blockIdx.x, gridDim.x);
-}
-
 int launch_rho(const pa_run* runs, int n, const double* args, int n_args, int mode, double cap, int64_t ld,
                double* out, hipStream_t s)
 {
     RhoArgs a;
     for (int j = 0; j < kMaxRho; ++j) a.v[j] = j < n_args ? args[j] : 0.0;
-    launch_hist(runs, n, s);
+    launch_hist(runs, n, false, s);
     hipLaunchKernelGGL(k_rho, dim3((unsigned)n_args, (unsigned)n), dim3(256), 0, s, runs[0].state, a, n_args, mode,
                        cap, ld, out);
-    hipLaunchKernelGGL(k_hist_clear, dim3(32, (unsigned)n), dim3(256), 0, s, runs[0].state);
     return hip_status(hipGetLastError());
 }
 

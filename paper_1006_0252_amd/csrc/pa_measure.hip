@@ -46,30 +46,26 @@ __device__ __forceinline__ void energy_moments(pa_state* st, int64_t R, int ilo,
     rec->E_skew = m2 > 0.0 ? m3 / (m2 * sqrt(m2)) : 0.0;
 }
 
-// the moments from the histogram, which is put back to zero; overlap: overlaps will be counted next (as a launch
-// of its own, clearing their histogram took 2 us of every measurement)
-__global__ void __launch_bounds__(64) k_moments(pa_state* base, bool overlap)
+__global__ void __launch_bounds__(64) k_moments(pa_state* base)
 {
     pa_state* st = base + blockIdx.y;
-    if (overlap) hist::clear_overlaps(st);
     if (st->status) return;
     const WorkLayout wl = work_layout(st->N, st->n_bins, st->capacity);
-    int64_t* h = work_ptr<int64_t>(st, wl.hist);
-    int64_t* misc = work_ptr<int64_t>(st, wl.misc);
+    const int64_t* h = work_ptr<int64_t>(st, wl.hist);
+    const int64_t* misc = work_ptr<int64_t>(st, wl.misc);
     const int ilo = ((int)misc[hist::kMiscEmin] - st->E_base) >> 2, ihi = ((int)misc[hist::kMiscEmax] - st->E_base) >> 2;
     energy_moments(st, st->R, ilo, ihi, [&](int i) { return h[i]; });
-    for (int i = ilo + threadIdx.x; i <= ihi; i += 64) h[i] = 0;  // the bins that this lane has read
-    if (threadIdx.x == 0) hist::reset_range(misc);
 }
 
 // The same for populations of up to kSmallMoments replicas and kSmallMomentBins bins, a block per run with
 // the histogram in LDS: one launch instead of three (clear, histogram, moments), 4 us a step instead of 10.
+// overlap: overlaps will be counted next, and their histogram is cleared here.
 constexpr int kSmallMoments = 8192, kSmallMomentBins = 8192, kMomentThreads = 1024;
 
 __global__ void __launch_bounds__(kMomentThreads) k_moments_block(pa_state* base, bool overlap)
 {
     pa_state* st = base + blockIdx.x;
-    if (overlap) hist::clear_overlaps(st);
+    if (overlap) hist::clear_overlaps(st, 0, 1);
     if (st->status) return;
     extern __shared__ uint32_t hloc[];
     const int R = (int)st->R, Eb = st->E_base, nb = st->n_bins;
@@ -298,8 +294,8 @@ int launch_measure(const pa_run* runs, int n, const pa_run* partner, int pair_xo
     if (cap <= kSmallMoments && bins <= kSmallMomentBins) {
         hipLaunchKernelGGL(k_moments_block, dim3((unsigned)n), dim3(kMomentThreads), (size_t)bins * 4, s, base, overlap);
     } else {
-        launch_hist(runs, n, s);
-        hipLaunchKernelGGL(k_moments, dim3(1, n), dim3(64), 0, s, base, overlap);
+        launch_hist(runs, n, overlap, s);
+        hipLaunchKernelGGL(k_moments, dim3(1, n), dim3(64), 0, s, base);
     }
     if (overlap) {
         int64_t N = 0, P = 0;

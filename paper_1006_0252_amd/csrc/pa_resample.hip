@@ -3,7 +3,7 @@
 //
 // Chain of kernels on the run's stream, all sized by capacity and reading the population size
 // from the device, with no host synchronisation:
-//   hist      energy histogram h (width-4 bins from E_base), E_lo, E_hi      (integer atomics)
+//   hist      energy histogram h (width-4 bins from E_base), E_lo, E_hi      (cleared, integer atomics)
 //   normalise S = sum_E h(E) w(E - E_lo) in ascending E (FP64, one thread, fixed order),
 //             ln Q, and per bin the mean copy number lambda = R_target w / S split into
 //             Poisson(64) blocks q, ladder level m and thinning threshold
@@ -87,6 +87,15 @@ int upload_ladder(hipStream_t s)
 }
 
 // ------------------------------------------------------------------ kernels
+// the histograms before the count; overlap: those of the overlaps too
+__global__ void __launch_bounds__(256) k_hist_clear(pa_state* base, bool overlap)
+{
+    pa_state* st = base + blockIdx.y;
+    if (overlap) clear_overlaps(st, blockIdx.x, gridDim.x);
+    if (st->status) return;
+    clear(st, blockIdx.x, gridDim.x);
+}
+
 constexpr int kHistLoads = 8;
 
 // histogram of the current population's energies, counted in an LDS copy of cap_bins entries
@@ -177,8 +186,8 @@ __device__ inline int ladder_level(double x)
     return m < kLadderMin ? kLadderMin : m;
 }
 
-// one block: S in ascending energy order, ln Q, per-bin Poisson parameters, the histogram put back to zero
-// (the step's record is written by k_finish, once the new population is known to fit)
+// one block: S in ascending energy order, ln Q, per-bin Poisson parameters (the step's record is
+// written by k_finish, once the new population is known to fit)
 constexpr int kNormBins = 1024;
 
 __global__ void __launch_bounds__(256) k_normalise(pa_state* base, ResampleParams p)
@@ -188,7 +197,7 @@ __global__ void __launch_bounds__(256) k_normalise(pa_state* base, ResampleParam
     __shared__ double prod[kNormBins];
     __shared__ double S_sh;
     const WorkLayout wl = work_layout(st->N, st->n_bins, st->capacity);
-    int64_t* hist = work_ptr<int64_t>(st, wl.hist);
+    const int64_t* hist = work_ptr<int64_t>(st, wl.hist);
     int64_t* misc = work_ptr<int64_t>(st, wl.misc);
     int64_t* bin_q = work_ptr<int64_t>(st, wl.bin_q);
     uint64_t* bin_keep = work_ptr<uint64_t>(st, wl.bin_keep);
@@ -201,10 +210,7 @@ __global__ void __launch_bounds__(256) k_normalise(pa_state* base, ResampleParam
     double S = 0.0;
     for (int b0 = 0; b0 < n; b0 += kNormBins) {
         const int cnt = min(kNormBins, n - b0);
-        for (int t = threadIdx.x; t < cnt; t += blockDim.x) {
-            prod[t] = (double)hist[ilo + b0 + t] * p.w[b0 + t];
-            hist[ilo + b0 + t] = 0;
-        }
+        for (int t = threadIdx.x; t < cnt; t += blockDim.x) prod[t] = (double)hist[ilo + b0 + t] * p.w[b0 + t];
         __syncthreads();
         if (threadIdx.x == 0) S = add_in_order(S, prod, cnt);
         __syncthreads();
@@ -217,7 +223,6 @@ __global__ void __launch_bounds__(256) k_normalise(pa_state* base, ResampleParam
     const bool bad = !isfinite(S) || !(S > 0.0);
     if (threadIdx.x == 0) {
         const double lnQ = -dbeta * (double)E_lo + log(S) - log(R);
-        reset_range(misc);
         *reinterpret_cast<double*>(&misc[kMiscElo]) = (double)E_lo;
         if (bad) {
             st->status |= PA_FLAG_NONFINITE;
@@ -565,8 +570,8 @@ static BatchShape batch_shape(const pa_run* runs, int n)
     return b;
 }
 
-// the histograms of n runs, which must be zero, as they are between calls
-void launch_hist(const pa_run* runs, int n, hipStream_t s)
+// the energy histograms of n runs (overlap: those of their overlaps are cleared as well)
+void launch_hist(const pa_run* runs, int n, bool overlap, hipStream_t s)
 {
     const BatchShape b = batch_shape(runs, n);
     // an LDS histogram of up to 16384 bins, sized for the largest run of the call that fits (runs
@@ -582,6 +587,7 @@ void launch_hist(const pa_run* runs, int n, hipStream_t s)
     // 98 us, 256 blocks 29 us, 128 blocks 21 us; with eight loads in flight per thread, 128 blocks
     // 17.5 us, 256 blocks 28 us, and 64, 32, 16 blocks were slower already before)
     const unsigned hist_blocks = (unsigned)std::min<int64_t>(128, (b.cap_max + 255) / 256);
+    hipLaunchKernelGGL(k_hist_clear, dim3(32, n), dim3(256), 0, s, runs[0].state, overlap);
     hipLaunchKernelGGL(k_hist, dim3(hist_blocks, n), dim3(256), (size_t)cap_bins * 4, s, runs[0].state, (int)cap_bins);
 }
 
@@ -995,7 +1001,7 @@ int launch_resample(const pa_run* runs, int n, const pa_step& step, hipStream_t 
     if (launch_resample_small(runs, n, p, s)) return hip_status(hipGetLastError());
     pa_state* base = runs[0].state;
     const unsigned tiles = (unsigned)((b.cap_max + kScanTile - 1) / kScanTile);
-    launch_hist(runs, n, s);
+    launch_hist(runs, n, false, s);
     hipLaunchKernelGGL(k_normalise, dim3(1, n), dim3(256), 0, s, base, p);
     hipLaunchKernelGGL(k_copies, dim3(tiles, n), dim3(kScanTile), 0, s, base, (int32_t)step.k);
     hipLaunchKernelGGL(k_offsets, dim3(tiles, n), dim3(kScanTile), 0, s, base);
