@@ -441,31 +441,38 @@ __device__ void weighted_one(int M, const double* __restrict__ xs, const double*
         }
     }
     v = wave_sum(v);
-    if (lane != 0) return;
-    o[n_obs] = xmax + log(Z) - log(Rsum);
-    o[n_obs + 1] = M > 1 ? v / (double)(M - 1) : 0.0;
-    o[n_obs + 2] = m;
+    if (lane == 0) {
+        o[n_obs] = xmax + log(Z) - log(Rsum);
+        o[n_obs + 1] = M > 1 ? v / (double)(M - 1) : 0.0;
+        o[n_obs + 2] = m;
+    }
 }
 
 constexpr int kAverageWaves = 4;  // averages per block
 
-// the average a wave takes
+// the averages a wave takes: wave_item, wave_item + wave_items, ..
 __device__ __forceinline__ int64_t wave_item()
 {
     return (int64_t)blockIdx.x * kAverageWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
+__device__ __forceinline__ int64_t wave_items() { return (int64_t)gridDim.x * kAverageWaves; }
 
 __global__ void __launch_bounds__(64 * kAverageWaves) k_weighted_average(int n_sets, int M, const double* __restrict__ x,
                                                                          const double* __restrict__ R,
                                                                          const double* __restrict__ A, int n_obs,
                                                                          double* __restrict__ out)
 {
-    const int64_t set = wave_item();
-    if (set >= n_sets) return;
-    weighted_one(M, x + set * M, R ? R + set * M : nullptr, A + set * M * n_obs, n_obs, nullptr, out + set * (n_obs + 3));
+    for (int64_t set = wave_item(); set < n_sets; set += wave_items())
+        weighted_one(M, x + set * M, R ? R + set * M : nullptr, A + set * M * n_obs, n_obs, nullptr, out + set * (n_obs + 3));
 }
 
-static unsigned average_blocks(int64_t n) { return (unsigned)((n + kAverageWaves - 1) / kAverageWaves); }
+// enough blocks to fill the chip many times over, and few enough for any number of averages (a launch has
+// fewer than 2^32 threads: a wave per average is 2^26 averages)
+constexpr int64_t kAverageBlocks = 1 << 20;
+static unsigned average_blocks(int64_t n)
+{
+    return (unsigned)std::min((n + kAverageWaves - 1) / kAverageWaves, kAverageBlocks);
+}
 
 int launch_weighted_average_dev(int n_sets, int M, const double* x, const double* R, const double* A, int n_obs,
                                 double* out, hipStream_t s)
@@ -484,35 +491,36 @@ __global__ void __launch_bounds__(64 * kAverageWaves) k_overlap_average(int n_se
                                                                         const double* __restrict__ Q,
                                                                         double* __restrict__ out)
 {
-    const int64_t set = wave_item();
-    if (set >= n_sets) return;
     const int lane = threadIdx.x & 63;
-    const double* xs = x + set * 2 * n_pairs;
-    const double* Rs = R ? R + set * 2 * n_pairs : nullptr;
-    const double* Qs = Q + set * n_pairs * 3;
-    // exponent of pair p: x^(1) + x^(2) (+ ln(R^(1) R^(2)))
-    auto xpair = [&](int p) {
-        const double xp = xs[2 * p] + xs[2 * p + 1];
-        return xp + (Rs ? log(Rs[2 * p] * Rs[2 * p + 1]) : 0.0);
-    };
-    double xmax = -INFINITY;
-    for (int p = lane; p < n_pairs; p += 64) xmax = fmax(xmax, xpair(p));
-    xmax = wave_max(xmax);
-    Sum z_sum, q_sum[3];
-    for (int p = lane; p < n_pairs; p += 64) z_sum += exp(xpair(p) - xmax);
-    const double Z = wave_sum(z_sum);
-    double o[3];
-    for (int p = lane; p < n_pairs; p += 64) {
-        const double w = exp(xpair(p) - xmax) / Z;
-        for (int k = 0; k < 3; ++k) q_sum[k] += w * Qs[3 * p + k];
+    for (int64_t set = wave_item(); set < n_sets; set += wave_items()) {
+        const double* xs = x + set * 2 * n_pairs;
+        const double* Rs = R ? R + set * 2 * n_pairs : nullptr;
+        const double* Qs = Q + set * n_pairs * 3;
+        // exponent of pair p: x^(1) + x^(2) (+ ln(R^(1) R^(2)))
+        auto xpair = [&](int p) {
+            const double xp = xs[2 * p] + xs[2 * p + 1];
+            return xp + (Rs ? log(Rs[2 * p] * Rs[2 * p + 1]) : 0.0);
+        };
+        double xmax = -INFINITY;
+        for (int p = lane; p < n_pairs; p += 64) xmax = fmax(xmax, xpair(p));
+        xmax = wave_max(xmax);
+        Sum z_sum, q_sum[3];
+        for (int p = lane; p < n_pairs; p += 64) z_sum += exp(xpair(p) - xmax);
+        const double Z = wave_sum(z_sum);
+        double o[3];
+        for (int p = lane; p < n_pairs; p += 64) {
+            const double w = exp(xpair(p) - xmax) / Z;
+            for (int k = 0; k < 3; ++k) q_sum[k] += w * Qs[3 * p + k];
+        }
+        for (int k = 0; k < 3; ++k) o[k] = wave_sum(q_sum[k]);
+        if (lane == 0) {
+            double* os = out + set * 4;
+            os[0] = o[0];
+            os[1] = o[1];
+            os[2] = o[2];
+            os[3] = 0.5 * (3.0 - o[1] / (o[0] * o[0]));
+        }
     }
-    for (int k = 0; k < 3; ++k) o[k] = wave_sum(q_sum[k]);
-    if (lane != 0) return;
-    double* os = out + set * 4;
-    os[0] = o[0];
-    os[1] = o[1];
-    os[2] = o[2];
-    os[3] = 0.5 * (3.0 - o[1] / (o[0] * o[0]));
 }
 
 int launch_overlap_average_dev(int n_sets, int n_pairs, const double* x, const double* R, const double* Q,
@@ -529,18 +537,18 @@ __global__ void __launch_bounds__(64 * kAverageWaves) k_bootstrap(int n_sets, in
                                                                   const double* __restrict__ A, int n_obs, int n_boot,
                                                                   const int32_t* __restrict__ idx, double* __restrict__ rep)
 {
-    const int64_t t = wave_item();
-    if (t >= (int64_t)n_sets * n_boot) return;
-    const int64_t set = t / n_boot, b = t % n_boot;
-    const int32_t* pick = idx + b * M;
     const int lane = threadIdx.x & 63;
-    bool bad = false;
-    for (int i = lane; i < M; i += 64) bad = bad || (uint32_t)pick[i] >= (uint32_t)M;
-    if (__ballot(bad)) {  // an index outside the set: no read through it, NaN results
-        for (int q = lane; q < n_obs + 3; q += 64) rep[t * (n_obs + 3) + q] = NAN;
-        return;
+    for (int64_t t = wave_item(); t < (int64_t)n_sets * n_boot; t += wave_items()) {
+        const int64_t set = t / n_boot, b = t % n_boot;
+        const int32_t* pick = idx + b * M;
+        bool bad = false;
+        for (int i = lane; i < M; i += 64) bad = bad || (uint32_t)pick[i] >= (uint32_t)M;
+        if (__ballot(bad)) {  // an index outside the set: no read through it, NaN results
+            for (int q = lane; q < n_obs + 3; q += 64) rep[t * (n_obs + 3) + q] = NAN;
+            continue;
+        }
+        weighted_one(M, x + set * M, R ? R + set * M : nullptr, A + set * M * n_obs, n_obs, pick, rep + t * (n_obs + 3));
     }
-    weighted_one(M, x + set * M, R ? R + set * M : nullptr, A + set * M * n_obs, n_obs, pick, rep + t * (n_obs + 3));
 }
 
 // error of each quantity: standard deviation over the replicates (1 / (n_boot - 1)), a wave per (set,
@@ -549,20 +557,20 @@ __global__ void __launch_bounds__(64 * kAverageWaves) k_bootstrap_err(int n_sets
                                                                       const double* __restrict__ rep,
                                                                       double* __restrict__ err)
 {
-    const int64_t t = wave_item();
     const int nq = n_obs + 3, lane = threadIdx.x & 63;
-    if (t >= (int64_t)n_sets * nq) return;
-    const int64_t set = t / nq, q = t % nq;
-    const double* r = rep + set * n_boot * nq + q;
-    double m = 0.0, v = 0.0;
-    for (int b = lane; b < n_boot; b += 64) m += r[(int64_t)b * nq];
-    m = wave_sum(m) / (double)n_boot;
-    for (int b = lane; b < n_boot; b += 64) {
-        const double d = r[(int64_t)b * nq] - m;
-        v += d * d;
+    for (int64_t t = wave_item(); t < (int64_t)n_sets * nq; t += wave_items()) {
+        const int64_t set = t / nq, q = t % nq;
+        const double* r = rep + set * n_boot * nq + q;
+        double m = 0.0, v = 0.0;
+        for (int b = lane; b < n_boot; b += 64) m += r[(int64_t)b * nq];
+        m = wave_sum(m) / (double)n_boot;
+        for (int b = lane; b < n_boot; b += 64) {
+            const double d = r[(int64_t)b * nq] - m;
+            v += d * d;
+        }
+        v = wave_sum(v);
+        if (lane == 0) err[t] = n_boot > 1 ? sqrt(v / (double)(n_boot - 1)) : 0.0;
     }
-    v = wave_sum(v);
-    if (lane == 0) err[t] = n_boot > 1 ? sqrt(v / (double)(n_boot - 1)) : 0.0;
 }
 
 int launch_bootstrap_dev(int n_sets, int M, const double* x, const double* R, const double* A, int n_obs, int n_boot,
