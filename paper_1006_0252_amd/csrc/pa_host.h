@@ -5,6 +5,18 @@
 
 namespace pa {
 
+// A launch of 2^32 threads or more along x is cut short without an error.  blocks of threads each go in parts:
+// go(first block, blocks of the part).
+constexpr int64_t kLaunchThreads = (int64_t)1 << 31;
+
+template <class F>
+void launch_parts(int64_t blocks, int threads, F go)
+{
+    const int64_t most = kLaunchThreads / threads;
+    for (int64_t first = 0; first < blocks; first += most)
+        go((uint32_t)first, (unsigned)(blocks - first < most ? blocks - first : most));
+}
+
 // host launch helpers (defined in the .hip files)
 // initialise n runs with consecutive states on one stream, of one dim, layout and coupling kind (any sizes)
 int launch_init(const pa_run* runs, int n, const int8_t* const* J_host, hipStream_t s);

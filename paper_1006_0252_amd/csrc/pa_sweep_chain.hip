@@ -147,14 +147,16 @@ __global__ void __launch_bounds__(64 * kWaves) k_sweep_chain_short(const pa_stat
 }
 
 // Longer chains: the strings of a block's 64 replicas in LDS ([colour][word][replica]) and the masks of
-// every word ([word][4]), the words split by four waves that meet after each colour.
+// every word ([word][4]), the words split by four waves that meet after each colour.  first: the first block
+// of this part of the grid.
 template <int MODE, int LAYOUT>
-__global__ void __launch_bounds__(64 * kWaves) k_sweep_chain(const pa_state* __restrict__ base, SweepParams p, Thr th)
+__global__ void __launch_bounds__(64 * kWaves) k_sweep_chain(const pa_state* __restrict__ base, uint32_t first, SweepParams p,
+                                                             Thr th)
 {
     extern __shared__ uint32_t lds[];
     const pa_state* __restrict__ st = base + blockIdx.y;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t R = st->R, r = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t R = st->R, r = (int64_t)(first + blockIdx.x) * 64 + lane;
     if (st->status || r - lane >= R) return;  // the same for the whole block
     const bool valid = r < R;
     const int N = st->N, n_rows = (N + 31) / 32, stride = st->row_stride, NW = (N / 2 + 31) / 32;
@@ -457,7 +459,9 @@ static void launch(int N, const pa_state* base, int n, int64_t cap, const SweepP
         default: break;
     }
     const size_t lds = ((size_t)2 * NW * 64 + 4 * NW + 64) * 4;
-    hipLaunchKernelGGL((k_sweep_chain<MODE, LAYOUT>), dim3((unsigned)(cap / 64), (unsigned)n), b, lds, s, base, p, th);
+    launch_parts(cap / 64, (int)b.x, [&](uint32_t first, unsigned blocks) {
+        hipLaunchKernelGGL((k_sweep_chain<MODE, LAYOUT>), dim3(blocks, (unsigned)n), b, lds, s, base, first, p, th);
+    });
 }
 
 }  // namespace chain

@@ -285,16 +285,17 @@ __device__ __forceinline__ void place(int* group, int* wave)
     *wave = w % waves_of(L, LPR);
 }
 
-// one run: group i of the grid takes replicas 64 / LPR i ..
+// one run: group i of the grid takes replicas 64 / LPR i ..; first: the first block of this part of the grid
 template <int L, int MODE, int LAYOUT, int LPR>
-__global__ void __launch_bounds__(threads_of(L, LPR)) k_sweep_group(const pa_state* __restrict__ st, SweepParams p, Thr th)
+__global__ void __launch_bounds__(threads_of(L, LPR)) k_sweep_group(const pa_state* __restrict__ st, uint32_t first, SweepParams p,
+                                                                    Thr th)
 {
     __shared__ BlockSmem<L, LPR> sm;
     constexpr int GPB = groups_of(L, LPR);
     if (st->status) return;  // sticky error: the population stays as it is
     int gi, wave;
     place<L, LPR>(&gi, &wave);
-    const int64_t r0 = ((int64_t)blockIdx.x * GPB + gi) * (64 / LPR);
+    const int64_t r0 = ((int64_t)(first + blockIdx.x) * GPB + gi) * (64 / LPR);
     if (GPB == 1 && r0 >= st->R) return;
     if (MODE != 2) build_bounds(sm.tt, th, threadIdx.x, threads_of(L, LPR));
     if constexpr (GPB > 1) {
@@ -307,15 +308,16 @@ __global__ void __launch_bounds__(threads_of(L, LPR)) k_sweep_group(const pa_sta
 // a group of equal-L runs of a batch: the LPR groups from LPR b on take item b of the work list
 // (k_batch_tiles: 64 replicas each)
 template <int L, int MODE, int LAYOUT, int LPR>
-__global__ void __launch_bounds__(threads_of(L, LPR)) k_sweep_group_batch(pa_state* base, int pos0, int pos1,
-                                                                          BatchOrder order, SweepParams p, Thr th)
+__global__ void __launch_bounds__(threads_of(L, LPR)) k_sweep_group_batch(pa_state* base, uint32_t first, int pos0,
+                                                                          int pos1, BatchOrder order, SweepParams p,
+                                                                          Thr th)
 {
     __shared__ BlockSmem<L, LPR> sm;
     constexpr int GPB = groups_of(L, LPR);
     int gi, wave;
     place<L, LPR>(&gi, &wave);
     const int64_t* tb = work_ptr<int64_t>(base, work_layout(base->N, base->n_bins, base->capacity).batch);
-    const int64_t sub = (int64_t)blockIdx.x * GPB + gi;
+    const int64_t sub = (int64_t)(first + blockIdx.x) * GPB + gi;
     const int64_t item = tb[pos0] + sub / LPR;
     if (GPB == 1 && item >= tb[pos1]) return;
     if (MODE != 2) build_bounds(sm.tt, th, threadIdx.x, threads_of(L, LPR));
@@ -333,14 +335,15 @@ __global__ void __launch_bounds__(threads_of(L, LPR)) k_sweep_group_batch(pa_sta
 // Initial population and energies of runs of one side (grid.y: position in order), written once: drawing
 // the rows and then reading them back per bond took 1.3 ms at L = 16, 10^6 replicas, this 0.4 ms.
 template <int L, int LAYOUT>
-__global__ void __launch_bounds__(threads_of(L, always_split(L) ? 4 : 1)) k_init_group(pa_state* base, BatchOrder order)
+__global__ void __launch_bounds__(threads_of(L, always_split(L) ? 4 : 1)) k_init_group(pa_state* base, uint32_t first,
+                                                                                      BatchOrder order)
 {
     constexpr int LPR = always_split(L) ? 4 : 1;
     __shared__ BlockSmem<L, LPR> sm;
     const pa_state* st = base + order.run[blockIdx.y];
     int gi, wave;
     place<L, LPR>(&gi, &wave);
-    const int64_t r0 = ((int64_t)blockIdx.x * groups_of(L, LPR) + gi) * (64 / LPR);
+    const int64_t r0 = ((int64_t)(first + blockIdx.x) * groups_of(L, LPR) + gi) * (64 / LPR);
     // (a wave that leaves alone is a whole group and meets no barrier)
     if (r0 >= (LAYOUT == PA_U8 ? st->R : st->capacity)) return;
     sweep_shared<L, 2, LAYOUT, LPR, true>(st, r0, wave, sm.g[gi], sm.tt, SweepParams{}, Thr{});
@@ -351,9 +354,12 @@ static void launch_init(pa_state* base, const BatchOrder& order, int n, int64_t 
 {
     constexpr int LPR = always_split(L) ? 4 : 1;
     const int64_t per_block = 64 / LPR * groups_of(L, LPR);
-    const dim3 g((unsigned)((cap + per_block - 1) / per_block), (unsigned)n), b(threads_of(L, LPR));
-    if (layout == PA_U8) hipLaunchKernelGGL((k_init_group<L, PA_U8>), g, b, 0, s, base, order);
-    else hipLaunchKernelGGL((k_init_group<L, PA_BITS64>), g, b, 0, s, base, order);
+    const dim3 b(threads_of(L, LPR));
+    launch_parts((cap + per_block - 1) / per_block, (int)b.x, [&](uint32_t first, unsigned blocks) {
+        const dim3 g(blocks, (unsigned)n);
+        if (layout == PA_U8) hipLaunchKernelGGL((k_init_group<L, PA_U8>), g, b, 0, s, base, first, order);
+        else hipLaunchKernelGGL((k_init_group<L, PA_BITS64>), g, b, 0, s, base, first, order);
+    });
 }
 
 struct Launch {
@@ -369,15 +375,22 @@ template <int L, int LAYOUT, int LPR>
 static void launch(const Launch& a, const SweepParams& p, const Thr& th, hipStream_t s)
 {
     constexpr int GPB = groups_of(L, LPR);
-    const dim3 g((unsigned)((a.items * LPR + GPB - 1) / GPB)), b(threads_of(L, LPR));
+    const dim3 b(threads_of(L, LPR));
     const bool z = all_tops_zero(th);
-    if (a.run) {
-        if (z) hipLaunchKernelGGL((k_sweep_group<L, 2, LAYOUT, LPR>), g, b, 0, s, a.run->state, p, th);
-        else hipLaunchKernelGGL((k_sweep_group<L, 0, LAYOUT, LPR>), g, b, 0, s, a.run->state, p, th);
-    } else {
-        if (z) hipLaunchKernelGGL((k_sweep_group_batch<L, 2, LAYOUT, LPR>), g, b, 0, s, a.base, a.pos0, a.pos1, *a.order, p, th);
-        else hipLaunchKernelGGL((k_sweep_group_batch<L, 0, LAYOUT, LPR>), g, b, 0, s, a.base, a.pos0, a.pos1, *a.order, p, th);
-    }
+    launch_parts((a.items * LPR + GPB - 1) / GPB, (int)b.x, [&](uint32_t first, unsigned blocks) {
+        const dim3 g(blocks);
+        if (a.run) {
+            if (z) hipLaunchKernelGGL((k_sweep_group<L, 2, LAYOUT, LPR>), g, b, 0, s, a.run->state, first, p, th);
+            else hipLaunchKernelGGL((k_sweep_group<L, 0, LAYOUT, LPR>), g, b, 0, s, a.run->state, first, p, th);
+        } else {
+            if (z)
+                hipLaunchKernelGGL((k_sweep_group_batch<L, 2, LAYOUT, LPR>), g, b, 0, s, a.base, first, a.pos0, a.pos1, *a.order,
+                                   p, th);
+            else
+                hipLaunchKernelGGL((k_sweep_group_batch<L, 0, LAYOUT, LPR>), g, b, 0, s, a.base, first, a.pos0, a.pos1, *a.order,
+                                   p, th);
+        }
+    });
 }
 
 template <int L, int LAYOUT>
