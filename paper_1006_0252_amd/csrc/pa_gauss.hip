@@ -1221,6 +1221,14 @@ static int launch_gauss_sweep(K kernel, int64_t per_block, int waves, size_t lds
     const int64_t blocks = (a.cap + per_block - 1) / per_block;
     const int64_t grid = a.n >= 8 ? (a.n * blocks + 7) / 8 * 8 : a.n * blocks;
     if (grid > INT32_MAX) return PA_ERR_ARG;
+    if (grid * waves * 64 > kLaunchThreads && a.n > 1) {  // (the runs of a launch all take the largest one's blocks)
+        GaussLaunch lo = a, hi = a;
+        lo.n = a.n / 2;
+        hi.n = a.n - lo.n;
+        hi.base += lo.n;
+        const int st = launch_gauss_sweep(kernel, per_block, waves, lds, lo, step);
+        return st != PA_OK ? st : launch_gauss_sweep(kernel, per_block, waves, lds, hi, step);
+    }
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3((unsigned)waves * 64), lds, a.s, a.base, a.n, (int)blocks, step.t0,
                        step.n_sweeps);
     return hip_status(hipGetLastError());

@@ -59,3 +59,19 @@ def first_replicas(run, R):
     raw = run.spins[info.cur][: (R + 63) // 64 * 64 * row].cpu().numpy()
     return (pa.unpack_spins(raw, run.dim, run.L, run.layout, R, int(run.sizes.row_stride)),
             run.energy[info.cur][: 4 * R].cpu().numpy().view(np.int32))
+
+
+def test_uneven_gaussian_batch():
+    """1100 runs take the blocks of the largest one each"""
+    print("[case] uneven Gaussian batch", flush=True)
+    specs = [dict(dim=3, L=6, R0=1_000_000 if r == 700 else 40, seed=r + 1, disorder_seed=3, couplings="gauss")
+             for r in range(1100)]
+    batch = pa.Batch(specs, 2, layout="u8", device=DEV).init()
+    st = pa.Schedule([0.4, 0.5], 1, batch.runs[0].n_bins, device=DEV).step(1)
+    J = o.couplings_gauss(3, 6, 3)
+    batch.sweep(st)
+    for r in (0, 1, 699, 700, 701, 1099):
+        s, E = o.init_replicas_gauss(3, 6, J, r + 1, 0, 40)
+        o.sweep_replicas_gauss(3, 6, J, r + 1, 0.5, 0, s, E, st.t0, st.n_sweeps)
+        got = batch.runs[r].population()
+        assert np.array_equal(got[0][:40], s) and np.array_equal(got[1][:40], E)
