@@ -255,7 +255,7 @@ int launch_init(const pa_run* runs, int n, const int8_t* const* J_host, hipStrea
     const bool gauss = runs[0].couplings == PA_GAUSS;
     const int layout = runs[0].layout;
     // one launch covers the largest run of the call
-    int64_t cap = 0, R0 = 0, bonds = 0, stride = 0;
+    int64_t cap = 0, R0 = 0, bonds = 0, pieces = 0;  // pieces: 16 bytes of a run's byte rows
     bool all_given = J_host != nullptr;
     for (int r = 0; r < n; ++r) {
         pa_sizes sz;
@@ -264,7 +264,7 @@ int launch_init(const pa_run* runs, int n, const int8_t* const* J_host, hipStrea
         cap = std::max(cap, runs[r].capacity);
         R0 = std::max(R0, runs[r].R0);
         bonds = std::max(bonds, sz.n_bonds);
-        stride = std::max(stride, sz.row_stride);
+        pieces = std::max(pieces, runs[r].R0 * (sz.row_stride / 16));
         const int8_t* J = J_host ? J_host[r] : nullptr;
         all_given = all_given && J;
         if (J) {
@@ -286,7 +286,7 @@ int launch_init(const pa_run* runs, int n, const int8_t* const* J_host, hipStrea
         hipLaunchKernelGGL(k_write_states, dim3((unsigned)m), dim3(64), 0, s, base + r0, c);
     }
     const unsigned ny = (unsigned)n;
-    const dim3 g_u8((unsigned)((R0 * (stride / 16) + 255) / 256), ny);
+    const dim3 g_u8((unsigned)((pieces + 255) / 256), ny);
     if (gauss) {
         // couplings from the host (libm), then spins as for +-1 couplings and FP64 energies
         int rc = gauss_couplings_upload(runs, n, s);

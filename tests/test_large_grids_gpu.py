@@ -75,3 +75,21 @@ def test_uneven_gaussian_batch():
         o.sweep_replicas_gauss(3, 6, J, r + 1, 0.5, 0, s, E, st.t0, st.n_sweeps)
         got = batch.runs[r].population()
         assert np.array_equal(got[0][:40], s) and np.array_equal(got[1][:40], E)
+
+
+def test_mixed_chains_initialised():
+    """a run of many short chains beside one of few long ones: the most replicas times the longest rows are 2^32
+    pieces of 16 bytes and 1.6 10^6 more"""
+    print("[case] mixed chains", flush=True)
+    sizes = [(16, (1 << 24) + 6400), (4096, 70)]
+    specs = [dict(dim=1, L=N, R0=R, seed=i + 1, disorder_seed=3) for i, (N, R) in enumerate(sizes)]
+    batch = pa.Batch(specs, 2, layout="u8", device=DEV).init()
+    for i, (N, R) in enumerate(sizes):
+        J = o.couplings(1, N, 3)
+        run = batch.runs[i]
+        E = run.energies()
+        for first in (0, R // 2 // 64 * 64, R - 64):
+            n = min(64, R - first)
+            s_o, E_o = o.init_replicas(1, N, J, i + 1, first, n)
+            raw = run.spins[0][first * N: (first + n) * N].cpu().numpy().reshape(n, N)
+            assert np.array_equal(raw, s_o) and np.array_equal(E[first: first + n], E_o)
