@@ -396,12 +396,14 @@ __global__ void __launch_bounds__(kScanTile) k_copies(pa_state* base, int32_t k)
 
 // Offsets and sources, a block per tile of kScanTile consecutive sources.  The block adds the sums of the
 // tiles before it (and all of them, for R~', which block 0 records, and for the capacity and extinction
-// checks, which every block makes alike and k_finish turns into the flag), scans its own copy numbers into offsets[j] (offsets[R] = R~'), and its
-// new replicas offsets[j0] .. offsets[j0 + 256] - 1 each find their source in the block's offsets in LDS
-// (largest j with offsets[j] <= r', 8 LDS steps) and are written in order.  Per new replica over the whole
-// array, the same search took ~20 dependent global loads; per source, the writes of uneven copy numbers
-// were scattered and slower still.  As separate launches (sums, their scan, offsets, sources) 27 us at
-// 10^6 replicas and four launches of 4 us at 5 10^4; this 18 and 5.
+// checks, which every block makes alike and k_finish turns into the flag), scans its own copy numbers into
+// offsets[j] (offsets[R] = R~'), and its new replicas offsets[j0] .. offsets[j0 + 256] - 1 each find their
+// source in the block's offsets in LDS (largest j with offsets[j] <= r', 8 LDS steps) and are written in
+// order.  Per new replica over the whole array, the same search took ~20 dependent global loads; per
+// source, the writes of uneven copy numbers were scattered and slower still.  As four launches (sums,
+// their scan, offsets, sources) 27 us at 10^6 replicas and 16 at 5 10^4; this 15 (with the scan) and 5.
+// SCANNED: k_scan_tiles has turned the sums into the copies before each tile, and the total after the last.
+template <bool SCANNED>
 __global__ void __launch_bounds__(kScanTile) k_offsets(pa_state* base)
 {
     pa_state* st = base + blockIdx.y;
@@ -416,25 +418,30 @@ __global__ void __launch_bounds__(kScanTile) k_offsets(pa_state* base)
     const int64_t* sums = work_ptr<int64_t>(st, wl.scan);
     const int tiles = (int)((R + kScanTile - 1) / kScanTile), mine = (int)blockIdx.x;
     int64_t before = 0, total = 0;
+    if constexpr (SCANNED) {
+        before = sums[mine];
+        total = sums[tiles];
+    } else {
 #pragma unroll 4
-    for (int i = tid; i < tiles; i += kScanTile) {
-        const int64_t v = sums[i];
-        total += v;
-        before += i < mine ? v : 0;
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        total += __shfl_xor(total, o, 64);
-        before += __shfl_xor(before, o, 64);
-    }
-    if (lane == 0) {
-        red[0][wv] = total;
-        red[1][wv] = before;
-    }
-    __syncthreads();
-    total = before = 0;
-    for (int w = 0; w < kScanTile / 64; ++w) {
-        total += red[0][w];
-        before += red[1][w];
+        for (int i = tid; i < tiles; i += kScanTile) {
+            const int64_t v = sums[i];
+            total += v;
+            before += i < mine ? v : 0;
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            total += __shfl_xor(total, o, 64);
+            before += __shfl_xor(before, o, 64);
+        }
+        if (lane == 0) {
+            red[0][wv] = total;
+            red[1][wv] = before;
+        }
+        __syncthreads();
+        total = before = 0;
+        for (int w = 0; w < kScanTile / 64; ++w) {
+            total += red[0][w];
+            before += red[1][w];
+        }
     }
     if (mine == 0 && tid == 0) st->R_new = total;
     if (total > st->capacity || total == 0) return;  // the same for every block
@@ -466,6 +473,63 @@ __global__ void __launch_bounds__(kScanTile) k_offsets(pa_state* base)
         }
         src[d] = (int32_t)(j0 + lo);
     }
+}
+
+// The exclusive scan of a run's tile sums in place, their total after them, by one block.
+constexpr int kScanThreads = 1024, kScanLoads = 8;
+
+__global__ void __launch_bounds__(kScanThreads) k_scan_tiles(pa_state* base)
+{
+    pa_state* st = base + blockIdx.y;
+    if (st->status) return;
+    __shared__ int64_t red[kScanThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tiles = (int)((st->R + kScanTile - 1) / kScanTile);
+    int64_t* sums = work_ptr<int64_t>(st, work_layout(st->N, st->n_bins, st->capacity).scan);
+    int64_t carry = 0;
+    for (int i0 = 0; i0 < tiles; i0 += kScanThreads * kScanLoads) {
+        const int first = i0 + tid * kScanLoads;
+        int64_t v[kScanLoads], own = 0;
+#pragma unroll
+        for (int u = 0; u < kScanLoads; ++u) v[u] = first + u < tiles ? sums[first + u] : 0;
+#pragma unroll
+        for (int u = 0; u < kScanLoads; ++u) own += v[u];
+        int64_t x = own;  // inclusive wave scan
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) red[wv] = x;
+        __syncthreads();
+        int64_t before = carry + x - own;
+        for (int w = 0; w < kScanThreads / 64; ++w) {
+            before += w < wv ? red[w] : 0;
+            carry += red[w];
+        }
+#pragma unroll
+        for (int u = 0; u < kScanLoads; ++u) {
+            if (first + u < tiles) sums[first + u] = before;
+            before += v[u];
+        }
+        __syncthreads();  // red has been read
+    }
+    if (tid == 0) sums[tiles] = carry;
+}
+
+// Every block adding all the sums grows with the square of the population, so from kDirectTiles tiles of the
+// largest capacity on they are scanned first.  A whole resampling of L = 4, bit-packed, with the sums added
+// and scanned: 2 10^5 replicas 39.0 and 39.9 us, 5 10^5 51.2 and 51.3, 10^6 70.7 and 67.1, 2 10^6 108 and 95,
+// 10^7 926 and 378, 10^8 65.7 and 3.72 ms.
+constexpr int64_t kDirectTiles = 2048;
+
+static void launch_offsets(pa_state* base, int n, unsigned tiles, hipStream_t s)
+{
+    if (tiles <= kDirectTiles) {
+        hipLaunchKernelGGL(k_offsets<false>, dim3(tiles, n), dim3(kScanTile), 0, s, base);
+        return;
+    }
+    hipLaunchKernelGGL(k_scan_tiles, dim3(1, n), dim3(kScanThreads), 0, s, base);
+    hipLaunchKernelGGL(k_offsets<true>, dim3(tiles, n), dim3(kScanTile), 0, s, base);
 }
 
 // whether the step's new population is to be formed (offsets has run, finish has not)
@@ -1004,7 +1068,7 @@ int launch_resample(const pa_run* runs, int n, const pa_step& step, hipStream_t 
     launch_hist(runs, n, false, s);
     hipLaunchKernelGGL(k_normalise, dim3(1, n), dim3(256), 0, s, base, p);
     hipLaunchKernelGGL(k_copies, dim3(tiles, n), dim3(kScanTile), 0, s, base, (int32_t)step.k);
-    hipLaunchKernelGGL(k_offsets, dim3(tiles, n), dim3(kScanTile), 0, s, base);
+    launch_offsets(base, n, tiles, s);
     launch_gather(runs, n, s);
     hipLaunchKernelGGL(k_finish, dim3(1, n), dim3(1), 0, s, base, p);
     return hip_status(hipGetLastError());
@@ -1179,7 +1243,7 @@ int launch_resample_gauss(const pa_run* runs, int n, const pa_step& step, hipStr
         hipLaunchKernelGGL(k_gauss_normalise, dim3(1, ny), dim3(256), 0, s, base, p);
     }
     hipLaunchKernelGGL(k_gauss_copies, dim3(tiles, ny), dim3(kScanTile), 0, s, base, p);
-    hipLaunchKernelGGL(k_offsets, dim3(tiles, ny), dim3(kScanTile), 0, s, base);
+    launch_offsets(base, n, tiles, s);
     launch_gather(runs, n, s);
     hipLaunchKernelGGL(k_finish, dim3(1, ny), dim3(1), 0, s, base, p);
     return hip_status(hipGetLastError());
