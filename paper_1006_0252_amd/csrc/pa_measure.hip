@@ -5,6 +5,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "pa_common.h"
 #include "pa_hist.h"
@@ -353,10 +354,12 @@ int launch_free_energy(const pa_run* runs, int n, double* out, hipStream_t s)
 
 // Averages over runs: a wave per average.  One thread per average added a few hundred dependent FP64 terms,
 // each behind an exp, in turn (18 sets of 200 runs 190 us, their 200 bootstrap replicates 305 us; now 9 and
-// 22 us): here each lane takes every 64th run and the wave adds the lanes' sums in a fixed tree.
-__device__ __forceinline__ double wave_sum(double x)
+// 22 us): here each lane takes every 64th run and the wave adds the lanes' sums in a fixed tree.  Many
+// averages of few runs take W = 16, 4 or 1 lanes each (launch_averages).
+template <int W>
+__device__ __forceinline__ double lanes_sum(double x)
 {
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+    for (int off = W / 2; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
     return x;
 }
 
@@ -372,9 +375,10 @@ struct Sum {
     }
 };
 
-__device__ __forceinline__ double wave_sum(Sum a)
+template <int W>
+__device__ __forceinline__ double lanes_sum(Sum a)
 {
-    for (int o = 32; o > 0; o >>= 1) {
+    for (int o = W / 2; o > 0; o >>= 1) {
         const double x = __shfl_xor(a.s, o, 64), off = __shfl_xor(a.off, o, 64);
         a += x;
         a.off += off;
@@ -382,9 +386,14 @@ __device__ __forceinline__ double wave_sum(Sum a)
     return a.off == a.off ? a.s + a.off : a.s;  // (an infinite sum rounds off NaN)
 }
 
-__device__ __forceinline__ double wave_max(double x)
+// The other sums: a wave's lanes add few terms each; fewer lanes keep what their longer chains round off.
+template <int W>
+using LaneSum = std::conditional_t<W == 64, double, Sum>;
+
+template <int W>
+__device__ __forceinline__ double lanes_max(double x)
 {
-    for (int off = 32; off > 0; off >>= 1) {
+    for (int off = W / 2; off > 0; off >>= 1) {
         const double y = __shfl_xor(x, off, 64);
         x = y > x ? y : x;
     }
@@ -392,35 +401,36 @@ __device__ __forceinline__ double wave_max(double x)
 }
 
 // weighted average of one set of M runs (Sec. III), optionally through a row of resampled run
-// indices, by one wave.  o[0..n_obs-1] = A_bar, o[n_obs] = -beta F_bar, o[n_obs+1] = Var, o[n_obs+2] =
+// indices, by W lanes.  o[0..n_obs-1] = A_bar, o[n_obs] = -beta F_bar, o[n_obs+1] = Var, o[n_obs+2] =
 // mean.
 constexpr int kObsAtOnce = 4;
 
-__device__ void weighted_one(int M, const double* __restrict__ xs, const double* __restrict__ Rs,
+template <int W>
+__device__ __forceinline__ void weighted_one(int M, const double* __restrict__ xs, const double* __restrict__ Rs,
                              const double* __restrict__ As, int n_obs, const int32_t* __restrict__ pick,
                              double* __restrict__ o)
 {
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x % W;
     auto run = [&](int i) { return pick ? pick[i] : i; };
     auto weight = [&](int r) { return xs[r] + (Rs ? log(Rs[r]) : 0.0); };
     double xmax = -INFINITY;
-    for (int i = lane; i < M; i += 64) {
+    for (int i = lane; i < M; i += W) {
         const double xr = weight(run(i));
         if (xr > xmax) xmax = xr;
     }
-    xmax = wave_max(xmax);
+    xmax = lanes_max<W>(xmax);
     Sum z_sum, x_sum;
-    double r_sum = 0.0, v = 0.0;
-    for (int i = lane; i < M; i += 64) {
+    LaneSum<W> r_sum = {}, v_sum = {};
+    for (int i = lane; i < M; i += W) {
         const int r = run(i);
         z_sum += exp(weight(r) - xmax);
         r_sum += Rs ? Rs[r] : 1.0;
         x_sum += xs[r];
     }
-    const double Z = wave_sum(z_sum), Rsum = wave_sum(r_sum), m = wave_sum(x_sum) / (double)M;
+    const double Z = lanes_sum<W>(z_sum), Rsum = lanes_sum<W>(r_sum), m = lanes_sum<W>(x_sum) / (double)M;
     for (int k0 = 0; k0 == 0 || k0 < n_obs; k0 += kObsAtOnce) {
         Sum a[kObsAtOnce];
-        for (int i = lane; i < M; i += 64) {
+        for (int i = lane; i < M; i += W) {
             const int r = run(i);
             if (n_obs > 0) {
                 const double w = exp(weight(r) - xmax) / Z;
@@ -430,17 +440,17 @@ __device__ void weighted_one(int M, const double* __restrict__ xs, const double*
             }
             if (k0 == 0) {
                 const double d = xs[r] - m;
-                v += d * d;
+                v_sum += d * d;
             }
         }
 #pragma unroll
         for (int k = 0; k < kObsAtOnce; ++k) {
             if (k0 + k >= n_obs) break;
-            const double s = wave_sum(a[k]);
+            const double s = lanes_sum<W>(a[k]);
             if (lane == 0) o[k0 + k] = s;
         }
     }
-    v = wave_sum(v);
+    const double v = lanes_sum<W>(v_sum);
     if (lane == 0) {
         o[n_obs] = xmax + log(Z) - log(Rsum);
         o[n_obs + 1] = M > 1 ? v / (double)(M - 1) : 0.0;
@@ -448,51 +458,75 @@ __device__ void weighted_one(int M, const double* __restrict__ xs, const double*
     }
 }
 
-constexpr int kAverageWaves = 4;  // averages per block
+constexpr int kAverageThreads = 256;
 
-// the averages a wave takes: wave_item, wave_item + wave_items, ..
-__device__ __forceinline__ int64_t wave_item()
+// the averages of a thread's W lanes: lanes_item, lanes_item + lanes_items, ..
+template <int W>
+__device__ __forceinline__ int64_t lanes_item()
 {
-    return (int64_t)blockIdx.x * kAverageWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t i = (int64_t)blockIdx.x * (kAverageThreads / W);
+    return W == 64 ? i + __builtin_amdgcn_readfirstlane(threadIdx.x / 64) : i + threadIdx.x / W;
 }
-__device__ __forceinline__ int64_t wave_items() { return (int64_t)gridDim.x * kAverageWaves; }
+template <int W>
+__device__ __forceinline__ int64_t lanes_items()
+{
+    return (int64_t)gridDim.x * (kAverageThreads / W);
+}
 
-__global__ void __launch_bounds__(64 * kAverageWaves) k_weighted_average(int n_sets, int M, const double* __restrict__ x,
+template <int W>
+__global__ void __launch_bounds__(kAverageThreads) k_weighted_average(int n_sets, int M, const double* __restrict__ x,
                                                                          const double* __restrict__ R,
                                                                          const double* __restrict__ A, int n_obs,
                                                                          double* __restrict__ out)
 {
-    for (int64_t set = wave_item(); set < n_sets; set += wave_items())
-        weighted_one(M, x + set * M, R ? R + set * M : nullptr, A + set * M * n_obs, n_obs, nullptr, out + set * (n_obs + 3));
+    for (int64_t set = lanes_item<W>(); set < n_sets; set += lanes_items<W>())
+        weighted_one<W>(M, x + set * M, R ? R + set * M : nullptr, A + set * M * n_obs, n_obs, nullptr, out + set * (n_obs + 3));
 }
 
-// enough blocks to fill the chip many times over, and few enough for any number of averages (a launch has
-// fewer than 2^32 threads: a wave per average is 2^26 averages)
-constexpr int64_t kAverageBlocks = 1 << 20;
-static unsigned average_blocks(int64_t n)
+// Lanes of an average of M terms, n of them in the call.  A wave's fixed cost (the tree of its sums) is spread
+// over M / 64 terms a lane, so few terms take fewer lanes, down to one where the lanes fill the chip all the
+// same; the terms of M <= one share cache lines.  Weighted averages with 64, 16, 4 and 1 lanes, us: 500 of 4 runs
+// 6.7, 6.4, 4.9 and 6.0; 500 of 64 runs 6.5, 8.5, 16 and 68; 8000 of 20 runs 18, 7.8, 8.0 and 24; 30 000 of 32
+// runs 58, 18, 14 and 40; 10^5 of 4 runs 176, 41, 12 and 9; 10^6 of 8 runs 1655, 362, 106 and 203.  10^5 replicates
+// of 100 runs 240, 113, 102 and 171, 4 10^6 of 8 runs 8.9, 2.0, 0.63 and 0.38 ms.
+constexpr int64_t kFillLanes1 = 1 << 16, kFillLanes4 = 1 << 15, kFillLanes16 = 1 << 12;
+
+// go(lanes as a constant, blocks): enough blocks to fill the chip many times over, and few enough for any
+// number of averages (a launch has fewer than 2^32 threads: a wave per average is 2^26 averages)
+template <class F>
+static void launch_averages(int64_t n, int64_t M, int64_t one, F go)
 {
-    return (unsigned)std::min((n + kAverageWaves - 1) / kAverageWaves, kAverageBlocks);
+    auto with = [&](auto W) {
+        const int64_t per = kAverageThreads / decltype(W)::value;
+        go(W, dim3((unsigned)std::min((n + per - 1) / per, (int64_t)1 << 20)));
+    };
+    if (M <= one && n >= kFillLanes1) with(std::integral_constant<int, 1>{});
+    else if (M <= 8 || (M <= 16 && n >= kFillLanes16) || (M <= 64 && n >= kFillLanes4)) with(std::integral_constant<int, 4>{});
+    else if (M <= 128 && n >= kFillLanes16) with(std::integral_constant<int, 16>{});
+    else with(std::integral_constant<int, 64>{});
 }
 
 int launch_weighted_average_dev(int n_sets, int M, const double* x, const double* R, const double* A, int n_obs,
                                 double* out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_weighted_average, dim3(average_blocks(n_sets)), dim3(64 * kAverageWaves), 0, s, n_sets, M, x, R, A,
-                       n_obs, out);
+    launch_averages(n_sets, M, 4, [&](auto W, dim3 g) {
+        hipLaunchKernelGGL(k_weighted_average<decltype(W)::value>, g, dim3(kAverageThreads), 0, s, n_sets, M, x, R, A, n_obs, out);
+    });
     return hip_status(hipGetLastError());
 }
 
-// Overlap observables over pairs of runs (Sec. IV, eqs. pqs and omegaprime), one wave per set:
+// Overlap observables over pairs of runs (Sec. IV, eqs. pqs and omegaprime), W lanes per set:
 // pair p joins runs 2p and 2p + 1 and weighs exp(x^(1) + x^(2)) (times R^(1) R^(2) when R is
 // given, Sec. III); Q holds each pair's (<q^2>, <q^4>, Gamma).  The weighted moments give the
 // Binder ratio g = (3 - [q^4] / [q^2]^2) / 2.  o = ([q^2], [q^4], [Gamma], g).
-__global__ void __launch_bounds__(64 * kAverageWaves) k_overlap_average(int n_sets, int n_pairs, const double* __restrict__ x,
+template <int W>
+__global__ void __launch_bounds__(kAverageThreads) k_overlap_average(int n_sets, int n_pairs, const double* __restrict__ x,
                                                                         const double* __restrict__ R,
                                                                         const double* __restrict__ Q,
                                                                         double* __restrict__ out)
 {
-    const int lane = threadIdx.x & 63;
-    for (int64_t set = wave_item(); set < n_sets; set += wave_items()) {
+    const int lane = threadIdx.x % W;
+    for (int64_t set = lanes_item<W>(); set < n_sets; set += lanes_items<W>()) {
         const double* xs = x + set * 2 * n_pairs;
         const double* Rs = R ? R + set * 2 * n_pairs : nullptr;
         const double* Qs = Q + set * n_pairs * 3;
@@ -502,17 +536,17 @@ __global__ void __launch_bounds__(64 * kAverageWaves) k_overlap_average(int n_se
             return xp + (Rs ? log(Rs[2 * p] * Rs[2 * p + 1]) : 0.0);
         };
         double xmax = -INFINITY;
-        for (int p = lane; p < n_pairs; p += 64) xmax = fmax(xmax, xpair(p));
-        xmax = wave_max(xmax);
+        for (int p = lane; p < n_pairs; p += W) xmax = fmax(xmax, xpair(p));
+        xmax = lanes_max<W>(xmax);
         Sum z_sum, q_sum[3];
-        for (int p = lane; p < n_pairs; p += 64) z_sum += exp(xpair(p) - xmax);
-        const double Z = wave_sum(z_sum);
+        for (int p = lane; p < n_pairs; p += W) z_sum += exp(xpair(p) - xmax);
+        const double Z = lanes_sum<W>(z_sum);
         double o[3];
-        for (int p = lane; p < n_pairs; p += 64) {
+        for (int p = lane; p < n_pairs; p += W) {
             const double w = exp(xpair(p) - xmax) / Z;
             for (int k = 0; k < 3; ++k) q_sum[k] += w * Qs[3 * p + k];
         }
-        for (int k = 0; k < 3; ++k) o[k] = wave_sum(q_sum[k]);
+        for (int k = 0; k < 3; ++k) o[k] = lanes_sum<W>(q_sum[k]);
         if (lane == 0) {
             double* os = out + set * 4;
             os[0] = o[0];
@@ -526,49 +560,52 @@ __global__ void __launch_bounds__(64 * kAverageWaves) k_overlap_average(int n_se
 int launch_overlap_average_dev(int n_sets, int n_pairs, const double* x, const double* R, const double* Q,
                                double* out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_overlap_average, dim3(average_blocks(n_sets)), dim3(64 * kAverageWaves), 0, s, n_sets, n_pairs, x, R,
-                       Q, out);
+    launch_averages(n_sets, n_pairs, 4, [&](auto W, dim3 g) {
+        hipLaunchKernelGGL(k_overlap_average<decltype(W)::value>, g, dim3(kAverageThreads), 0, s, n_sets, n_pairs, x, R, Q, out);
+    });
     return hip_status(hipGetLastError());
 }
 
-// bootstrap replicates: wave per (set, replicate b), the weighted average of the runs idx[b][.]
-__global__ void __launch_bounds__(64 * kAverageWaves) k_bootstrap(int n_sets, int M, const double* __restrict__ x,
+// bootstrap replicates: W lanes per (set, replicate b), the weighted average of the runs idx[b][.]
+template <int W>
+__global__ void __launch_bounds__(kAverageThreads) k_bootstrap(int n_sets, int M, const double* __restrict__ x,
                                                                   const double* __restrict__ R,
                                                                   const double* __restrict__ A, int n_obs, int n_boot,
                                                                   const int32_t* __restrict__ idx, double* __restrict__ rep)
 {
-    const int lane = threadIdx.x & 63;
-    for (int64_t t = wave_item(); t < (int64_t)n_sets * n_boot; t += wave_items()) {
+    const int lane = threadIdx.x % W;
+    for (int64_t t = lanes_item<W>(); t < (int64_t)n_sets * n_boot; t += lanes_items<W>()) {
         const int64_t set = t / n_boot, b = t % n_boot;
         const int32_t* pick = idx + b * M;
-        bool bad = false;
-        for (int i = lane; i < M; i += 64) bad = bad || (uint32_t)pick[i] >= (uint32_t)M;
-        if (__ballot(bad)) {  // an index outside the set: no read through it, NaN results
-            for (int q = lane; q < n_obs + 3; q += 64) rep[t * (n_obs + 3) + q] = NAN;
+        double bad = 0.0;
+        for (int i = lane; i < M; i += W) bad = (uint32_t)pick[i] >= (uint32_t)M ? 1.0 : bad;
+        if (lanes_max<W>(bad) > 0.0) {  // an index outside the set: no read through it, NaN results
+            for (int q = lane; q < n_obs + 3; q += W) rep[t * (n_obs + 3) + q] = NAN;
             continue;
         }
-        weighted_one(M, x + set * M, R ? R + set * M : nullptr, A + set * M * n_obs, n_obs, pick, rep + t * (n_obs + 3));
+        weighted_one<W>(M, x + set * M, R ? R + set * M : nullptr, A + set * M * n_obs, n_obs, pick, rep + t * (n_obs + 3));
     }
 }
 
-// error of each quantity: standard deviation over the replicates (1 / (n_boot - 1)), a wave per (set,
+// error of each quantity: standard deviation over the replicates (1 / (n_boot - 1)), W lanes per (set,
 // quantity)
-__global__ void __launch_bounds__(64 * kAverageWaves) k_bootstrap_err(int n_sets, int n_obs, int n_boot,
+template <int W>
+__global__ void __launch_bounds__(kAverageThreads) k_bootstrap_err(int n_sets, int n_obs, int n_boot,
                                                                       const double* __restrict__ rep,
                                                                       double* __restrict__ err)
 {
-    const int nq = n_obs + 3, lane = threadIdx.x & 63;
-    for (int64_t t = wave_item(); t < (int64_t)n_sets * nq; t += wave_items()) {
+    const int nq = n_obs + 3, lane = threadIdx.x % W;
+    for (int64_t t = lanes_item<W>(); t < (int64_t)n_sets * nq; t += lanes_items<W>()) {
         const int64_t set = t / nq, q = t % nq;
         const double* r = rep + set * n_boot * nq + q;
-        double m = 0.0, v = 0.0;
-        for (int b = lane; b < n_boot; b += 64) m += r[(int64_t)b * nq];
-        m = wave_sum(m) / (double)n_boot;
-        for (int b = lane; b < n_boot; b += 64) {
+        LaneSum<W> m_sum = {}, v_sum = {};
+        for (int b = lane; b < n_boot; b += W) m_sum += r[(int64_t)b * nq];
+        const double m = lanes_sum<W>(m_sum) / (double)n_boot;
+        for (int b = lane; b < n_boot; b += W) {
             const double d = r[(int64_t)b * nq] - m;
-            v += d * d;
+            v_sum += d * d;
         }
-        v = wave_sum(v);
+        const double v = lanes_sum<W>(v_sum);
         if (lane == 0) err[t] = n_boot > 1 ? sqrt(v / (double)(n_boot - 1)) : 0.0;
     }
 }
@@ -576,11 +613,14 @@ __global__ void __launch_bounds__(64 * kAverageWaves) k_bootstrap_err(int n_sets
 int launch_bootstrap_dev(int n_sets, int M, const double* x, const double* R, const double* A, int n_obs, int n_boot,
                          const int32_t* idx, double* rep, double* err, hipStream_t s)
 {
-    const int64_t nr = (int64_t)n_sets * n_boot, ne = (int64_t)n_sets * (n_obs + 3);
-    hipLaunchKernelGGL(k_bootstrap, dim3(average_blocks(nr)), dim3(64 * kAverageWaves), 0, s, n_sets, M, x, R, A, n_obs, n_boot,
-                       idx, rep);
-    hipLaunchKernelGGL(k_bootstrap_err, dim3(average_blocks(ne)), dim3(64 * kAverageWaves), 0, s, n_sets, n_obs, n_boot,
-                       (const double*)rep, err);
+    launch_averages((int64_t)n_sets * n_boot, M, 8, [&](auto W, dim3 g) {
+        hipLaunchKernelGGL(k_bootstrap<decltype(W)::value>, g, dim3(kAverageThreads), 0, s, n_sets, M, x, R, A, n_obs, n_boot, idx,
+                           rep);
+    });
+    launch_averages((int64_t)n_sets * (n_obs + 3), n_boot, 4, [&](auto W, dim3 g) {
+        hipLaunchKernelGGL(k_bootstrap_err<decltype(W)::value>, g, dim3(kAverageThreads), 0, s, n_sets, n_obs, n_boot,
+                           (const double*)rep, err);
+    });
     return hip_status(hipGetLastError());
 }
 
