@@ -400,6 +400,13 @@ __device__ __forceinline__ double lanes_max(double x)
     return x;
 }
 
+template <int W>
+__device__ __forceinline__ bool lanes_any(bool b)
+{
+    const uint64_t v = __ballot(b);
+    return W == 64 ? v != 0 : (v >> (threadIdx.x % 64 / W * W) & ((1u << (W % 64)) - 1u)) != 0;
+}
+
 // weighted average of one set of M runs (Sec. III), optionally through a row of resampled run
 // indices, by W lanes.  o[0..n_obs-1] = A_bar, o[n_obs] = -beta F_bar, o[n_obs+1] = Var, o[n_obs+2] =
 // mean.
@@ -577,9 +584,9 @@ __global__ void __launch_bounds__(kAverageThreads) k_bootstrap(int n_sets, int M
     for (int64_t t = lanes_item<W>(); t < (int64_t)n_sets * n_boot; t += lanes_items<W>()) {
         const int64_t set = t / n_boot, b = t % n_boot;
         const int32_t* pick = idx + b * M;
-        double bad = 0.0;
-        for (int i = lane; i < M; i += W) bad = (uint32_t)pick[i] >= (uint32_t)M ? 1.0 : bad;
-        if (lanes_max<W>(bad) > 0.0) {  // an index outside the set: no read through it, NaN results
+        bool bad = false;
+        for (int i = lane; i < M; i += W) bad = bad || (uint32_t)pick[i] >= (uint32_t)M;
+        if (lanes_any<W>(bad)) {  // an index outside the set: no read through it, NaN results
             for (int q = lane; q < n_obs + 3; q += W) rep[t * (n_obs + 3) + q] = NAN;
             continue;
         }
