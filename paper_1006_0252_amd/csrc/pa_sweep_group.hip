@@ -58,7 +58,12 @@ __host__ __device__ constexpr int waves_of(int L, int LPR)
 // 1563 groups 449 and 488; L = 16, 782 groups 553 and 514, 1563 groups 925 and 960), and from L = 20
 // on for every size: a CU's LDS holds one block of 64 replicas there, whose waves all wait at its
 // barriers (L = 20, 6250 groups 7.9 and 7.6 ms; L = 24, 625 groups 1.58 and 1.34 ms).
-constexpr int64_t kSplitGroups = 1024;
+// Up to three sweeps it is the blocks' tables and transfers that count, which four lanes per replica repeat four
+// times as often: there fewer than 384 groups (one and four lanes, L = 16, 313 groups, one sweep 45 and 41 us,
+// three 101 and 77; 469 groups, one 46 and 57, three 101 and 113; L = 8, 469 groups, one 11.0 and 13.5, three
+// 20.7 and 21.3; L = 6 is faster with four).
+constexpr int64_t kSplitGroups = 1024, kShortGroups = 384;
+constexpr int kShortSweeps = 3;
 __host__ __device__ constexpr bool always_split(int L) { return L >= 20; }
 
 // groups of a block (a one-wave group needs no barrier: four share a bound table)
@@ -79,6 +84,15 @@ struct BlockSmem {
     uint2 tt[256];  // first-look bounds
 };
 
+// Rows that fill their words (sides 8 and 16): the half-sites of word k are the site bits 64 k .. of the
+// replica, whole rows whose even and odd sites are taken a dword at a time (one sweep, row by row and so: L = 16,
+// 3 10^5 replicas 363 and 332 us; L = 8, 10^7 1605 and 1304).
+template <int L>
+constexpr bool whole_rows()
+{
+    return 8 * Geo<L>::WB == L;
+}
+
 // Sites 2 h (ev) and 2 h + 1 (od) of the 32 half-sites h of word k from the bit-packed rows of the
 // group (base: the lane's word of row 0): half-sites 32 k ..
 // lie in the rows 32 k / (L/2) ..
@@ -86,7 +100,7 @@ template <int L>
 __device__ __forceinline__ void load_word_bits(const uint8_t* base, int k, uint32_t* ev, uint32_t* od)
 {
     using Gm = Geo<L>;
-    constexpr int H2 = Gm::H2, MAXR = (31 + H2 - 1) / H2 + 1;
+    constexpr int H2 = Gm::H2, MAXR = whole_rows<L>() ? 64 / L : (31 + H2 - 1) / H2 + 1;
     const int r0 = 32 * k / H2;
     uint32_t v[MAXR];
 #pragma unroll
@@ -94,6 +108,15 @@ __device__ __forceinline__ void load_word_bits(const uint8_t* base, int k, uint3
         const int r = r0 + i < Gm::NR ? r0 + i : Gm::NR - 1;
         const uint8_t* a = base + (int64_t)r * 64 * Gm::WB;
         v[i] = Gm::WB == 1 ? (uint32_t)*a : (Gm::WB == 2 ? (uint32_t)*(const uint16_t*)a : *(const uint32_t*)a);
+    }
+    if constexpr (whole_rows<L>()) {
+        uint32_t d[2] = {0, 0}, o_lo, o_hi;
+#pragma unroll
+        for (int i = 0; i < MAXR; ++i) d[L * i / 32] |= v[i] << (L * i % 32);
+        const uint32_t e_lo = split_row(d[0], &o_lo), e_hi = split_row(d[1], &o_hi);
+        *ev = e_lo | (e_hi << 16);
+        *od = o_lo | (o_hi << 16);
+        return;
     }
     uint32_t e = 0, o = 0;
 #pragma unroll
@@ -125,6 +148,73 @@ __device__ __forceinline__ void store_row_bits(uint8_t* base, int r, const uint3
     if (Gm::WB == 1) *a = (uint8_t)v;
     else if (Gm::WB == 2) *(uint16_t*)a = (uint16_t)v;
     else *(uint32_t*)a = v;
+}
+
+// the rows of word k's sites 2 h (ev) and 2 h + 1 (od), where they are whole
+template <int L>
+__device__ __forceinline__ void store_word_bits(uint8_t* base, int k, uint32_t ev, uint32_t od)
+{
+    using Gm = Geo<L>;
+    static_assert(whole_rows<L>() && Gm::WB <= 2, "sides 8 and 16");
+    const uint32_t d[2] = {merge_row(ev & 0xFFFFu, od & 0xFFFFu), merge_row(ev >> 16, od >> 16)};
+    uint8_t* a = base + (int64_t)k * (64 / L) * 64 * Gm::WB;
+#pragma unroll
+    for (int i = 0; i < 64 / L; ++i) {
+        const uint32_t v = d[L * i / 32] >> (L * i % 32);
+        if (Gm::WB == 1) a[64 * i] = (uint8_t)v;
+        else reinterpret_cast<uint16_t*>(a)[64 * i] = (uint16_t)v;
+    }
+}
+
+// The rows of a lane's replica between memory (base: its word of row 0) and its two strings, each row once and
+// the strings in registers, for a wave that has the whole replica.  By words, the rows that lie in two of
+// them are read twice and a word's loads wait for the last word's: 10^5 replicas of L = 6, one sweep 23.6 us,
+// ten 90.4; so 18.2 and 85.0; 10^7 of L = 4, one 267, so 227.
+template <int L>
+__device__ __forceinline__ void load_replica_bits(const uint8_t* base, uint32_t (&s0)[Geo<L>::NW], uint32_t (&s1)[Geo<L>::NW])
+{
+    using Gm = Geo<L>;
+    constexpr int H2 = Gm::H2;
+    constexpr uint32_t HM = (1u << H2) - 1u;
+    static_assert(Gm::WB == 1, "rows of a byte");
+    uint32_t v[Gm::NR];
+#pragma unroll
+    for (int r = 0; r < Gm::NR; ++r) v[r] = base[64 * r];
+#pragma unroll
+    for (int k = 0; k < Gm::NW; ++k) s0[k] = s1[k] = 0;
+#pragma unroll
+    for (int r = 0; r < Gm::NR; ++r) {
+        uint32_t odd;
+        const uint32_t even = split_colours(v[r], &odd) & HM;
+        const bool flip = (r % L + r / L) & 1;  // colour 0 takes x = 2 m + (y + z) mod 2
+        const uint32_t c0 = flip ? odd & HM : even, c1 = flip ? even : odd & HM;
+        const int k = H2 * r / 32, sh = H2 * r % 32;
+        s0[k] |= c0 << sh;
+        s1[k] |= c1 << sh;
+        if (sh + H2 > 32) {
+            s0[k + 1] |= c0 >> (32 - sh);
+            s1[k + 1] |= c1 >> (32 - sh);
+        }
+    }
+}
+
+template <int L>
+__device__ __forceinline__ void store_replica_bits(uint8_t* base, const uint32_t (&s0)[Geo<L>::NW], const uint32_t (&s1)[Geo<L>::NW])
+{
+    using Gm = Geo<L>;
+    constexpr int H2 = Gm::H2;
+    constexpr uint32_t HM = (1u << H2) - 1u;
+#pragma unroll
+    for (int r = 0; r < Gm::NR; ++r) {
+        const int k = H2 * r / 32, sh = H2 * r % 32;
+        uint32_t c0 = s0[k] >> sh, c1 = s1[k] >> sh;
+        if (sh + H2 > 32) {
+            c0 |= s0[k + 1] << (32 - sh);
+            c1 |= s1[k + 1] << (32 - sh);
+        }
+        const bool flip = (r % L + r / L) & 1;
+        base[64 * r] = (uint8_t)merge_colours((flip ? c1 : c0) & HM, (flip ? c0 : c1) & HM);
+    }
 }
 
 // the initial spins of word k's sites 2 h (ev) and 2 h + 1 (od): 64 consecutive bits of the replica's
@@ -185,9 +275,20 @@ __device__ __forceinline__ void sweep_shared(const pa_state* st, int64_t r0, int
             if (k >= NW - G) S[(k - (NW - G)) * Q] = v;
         }
     };
+    // a wave with the whole bit-packed replica moves it at once
+    constexpr bool AT_ONCE = LAYOUT == PA_BITS64 && UNITS == 1;
     sync();  // the tables
+    if constexpr (AT_ONCE && !INIT) {
+        uint32_t s0[NW], s1[NW];
+        load_replica_bits<L>(rows, s0, s1);
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            put(E0, k, s0[k]);
+            put(E1, k, s1[k]);
+        }
+    }
 #pragma unroll 1
-    for (int k = unit; k < NW; k += UNITS) {
+    for (int k = AT_ONCE && !INIT ? NW : unit; k < NW; k += UNITS) {
         uint32_t ev, od;
         if constexpr (INIT) init_word(k, (uint32_t)r, valid, (uint32_t)st->seed, (uint32_t)(st->seed >> 32), &ev, &od);
         else if constexpr (LAYOUT == PA_U8) load_word_u8(rows, Gm::STRIDE, k, &ev, &od);
@@ -260,13 +361,27 @@ __device__ __forceinline__ void sweep_shared(const pa_state* st, int64_t r0, int
         for (int d = 0; d < 6; ++d) neg += __popc(xor3(w, nb[d], T[d]) & T[11]);
     }
     atomicAdd(&sm.neg[q], (uint32_t)neg);
-    if constexpr (LAYOUT == PA_U8) {
+    constexpr bool WORDS = LAYOUT == PA_U8 || (whole_rows<L>() && !AT_ONCE);
+    if constexpr (WORDS) {
 #pragma unroll 1
         for (int k = unit; k < NW; k += UNITS) {
             const uint32_t sig0 = sm.tab[k * TW + 6], in = sm.tab[k * TW + 11];
             const uint32_t a = E0[(G + k) * Q], b = E1[(G + k) * Q];
-            if (valid) store_word_u8(rows, Gm::STRIDE, k, select_bits(sig0, a, b) & in, select_bits(sig0, b, a) & in);
+            const uint32_t ev = select_bits(sig0, a, b) & in, od = select_bits(sig0, b, a) & in;
+            if constexpr (LAYOUT == PA_U8) {
+                if (valid) store_word_u8(rows, Gm::STRIDE, k, ev, od);
+            } else {
+                if (valid || INIT) store_word_bits<L>(rows, k, ev, od);
+            }
         }
+    } else if constexpr (AT_ONCE) {
+        uint32_t s0[NW], s1[NW];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            s0[k] = E0[(G + k) * Q];
+            s1[k] = E1[(G + k) * Q];
+        }
+        if (valid || INIT) store_replica_bits<L>(rows, s0, s1);
     } else {
 #pragma unroll 1
         for (int i = unit; i < Gm::NR; i += UNITS)
@@ -398,7 +513,7 @@ static void launch(const Launch& a, const SweepParams& p, const Thr& th, hipStre
 {
     // (L = 4: one word per colour, nothing to split)
     if constexpr (L > 4) {
-        if (always_split(L) || a.groups < kSplitGroups) {
+        if (always_split(L) || a.groups < (L > 6 && p.n_sweeps <= kShortSweeps ? kShortGroups : kSplitGroups)) {
             launch<L, LAYOUT, 4>(a, p, th, s);
             return;
         }

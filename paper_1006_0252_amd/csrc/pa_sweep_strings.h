@@ -79,43 +79,67 @@ __device__ __forceinline__ uint32_t funnel(const uint32_t* Ok)
     }
 }
 
-// The per-word tables of words first, first + step, .., built by the calling wave: lanes 0..31 take
-// bit t of word k of colour 0, lanes 32..63 the same bit of colour 1, and a ballot of each flag gives
-// the two words at once.  Entries: 0..5
-// the coupling masks (bit set where J = -1) of the +x, -x, +y, -y, +z, -z bonds, 6 the sites with
-// x even (sigma = 0), 7 and 8 the first and last site of a row (m = 0, m = L/2 - 1), 9 and 10 the
-// first and last row of a plane (y = 0, y = L - 1), 11 the bits that are sites (b < L^3 / 2).  Without
-// COUPLINGS (J unused) 0..5 are zero.
+// The geometry masks of a side's words, known when it is compiled: per (colour, word) 0 the sites with x even
+// (sigma = 0), 1 and 2 the first and last site of a row (m = 0, m = L/2 - 1), 3 and 4 the first and last row of a
+// plane (y = 0, y = L - 1), 5 the bits that are sites (b < L^3 / 2).
+template <int L>
+struct Masks {
+    uint32_t w[2 * Geo<L>::NW][6];
+};
+
+template <int L>
+constexpr Masks<L> make_masks()
+{
+    using Gm = Geo<L>;
+    Masks<L> t = {};
+    for (int b = 0; b < Gm::NH; ++b) {
+        const int m = b % Gm::H2, r = b / Gm::H2, y = r % L, z = r / L;
+        const uint32_t bit = 1u << (b & 31);
+        for (int c = 0; c < 2; ++c) {
+            uint32_t* w = t.w[c * Gm::NW + (b >> 5)];
+            w[0] |= (c + y + z) & 1 ? 0u : bit;
+            w[1] |= m == 0 ? bit : 0u;
+            w[2] |= m == Gm::H2 - 1 ? bit : 0u;
+            w[3] |= y == 0 ? bit : 0u;
+            w[4] |= y == L - 1 ? bit : 0u;
+            w[5] |= bit;
+        }
+    }
+    return t;
+}
+
+template <int L>
+__device__ constexpr Masks<L> g_masks = make_masks<L>();
+
+// The per-word tables, by waves first, first + step, .. of step.  Entries: 0..5
+// the coupling masks (bit set where J = -1) of the +x, -x, +y, -y, +z, -z bonds (without COUPLINGS, J unused,
+// left as they are), 6..11 the geometry masks.  Lanes 0..31 take bit t of word k of colour 0, lanes 32..63 the
+// same bit of colour 1, and a ballot of each bond's sign gives the two words at once.  (The geometry masks
+// by ballots too: one sweep of L = 16, 3 10^5 replicas 332 us, so 325; 5 10^4, whose blocks have 16 replicas, 94 and 86.)
 template <int L, bool COUPLINGS = true>
 __device__ void build_tables(const int8_t* J, uint32_t* tab, int lane, int first = 0, int step = 1)
 {
     using Gm = Geo<L>;
+    for (int e = 64 * first + lane; e < 12 * Gm::NW; e += 64 * step) tab[e / 6 * Gm::TW + 6 + e % 6] = (&g_masks<L>.w[0][0])[e];
+    if constexpr (!COUPLINGS) return;
     const int c = lane >> 5, t = lane & 31;
     for (int k = first; k < Gm::NW; k += step) {
         const int b = 32 * k + t;
-        bool f[12] = {false, false, false, false, false, false, false, false, false, false, false, false};
+        bool f[6] = {false, false, false, false, false, false};
         if (b < Gm::NH) {
             const int m = b % Gm::H2, r = b / Gm::H2, y = r % L, z = r / L;
-            const int sg = (c + y + z) & 1, x = 2 * m + sg;
+            const int x = 2 * m + ((c + y + z) & 1);
             const int xm = (x + L - 1) % L, ym = (y + L - 1) % L, zm = (z + L - 1) % L;
             const int i = x + L * (y + L * z);
-            if (COUPLINGS) {
-                f[0] = J[3 * i + 0] < 0;
-                f[1] = J[3 * (xm + L * (y + L * z)) + 0] < 0;
-                f[2] = J[3 * i + 1] < 0;
-                f[3] = J[3 * (x + L * (ym + L * z)) + 1] < 0;
-                f[4] = J[3 * i + 2] < 0;
-                f[5] = J[3 * (x + L * (y + L * zm)) + 2] < 0;
-            }
-            f[6] = sg == 0;
-            f[7] = m == 0;
-            f[8] = m == Gm::H2 - 1;
-            f[9] = y == 0;
-            f[10] = y == L - 1;
-            f[11] = true;
+            f[0] = J[3 * i + 0] < 0;
+            f[1] = J[3 * (xm + L * (y + L * z)) + 0] < 0;
+            f[2] = J[3 * i + 1] < 0;
+            f[3] = J[3 * (x + L * (ym + L * z)) + 1] < 0;
+            f[4] = J[3 * i + 2] < 0;
+            f[5] = J[3 * (x + L * (y + L * zm)) + 2] < 0;
         }
 #pragma unroll
-        for (int e = 0; e < 12; ++e) {
+        for (int e = 0; e < 6; ++e) {
             const uint64_t v = __ballot(f[e]);
             if (lane == 0) {
                 tab[(0 * Gm::NW + k) * Gm::TW + e] = (uint32_t)v;
