@@ -41,14 +41,14 @@ __global__ void __launch_bounds__(256) k_couplings(const pa_state* __restrict__ 
 }
 
 // u8: thread per (replica, 16 consecutive sites); spin i of replica r is bit (i mod 128)
-// of Philox(ctr (i/128, r, 0, 1), key seed)
-__global__ void __launch_bounds__(256) k_init_u8(const pa_state* __restrict__ base)
+// of Philox(ctr (i/128, r, 0, 1), key seed); first: the first block of this part of the grid
+__global__ void __launch_bounds__(256) k_init_u8(const pa_state* __restrict__ base, uint32_t first)
 {
     const pa_state* st = base + blockIdx.y;
     const uint32_t k0 = (uint32_t)st->seed, k1 = (uint32_t)(st->seed >> 32);
     const int N = st->N, stride = st->row_stride;
     const int per_row = stride / 16;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = (int64_t)(first + blockIdx.x) * blockDim.x + threadIdx.x;
     const int64_t r = t / per_row;
     const int q = (int)(t - r * per_row);
     if (r >= st->R0) return;
@@ -117,11 +117,11 @@ __global__ void __launch_bounds__(256) k_init_bits64(const pa_state* __restrict_
 }
 
 // u8 energies: one wave per replica, lanes over sites, each site owns its + bonds
-__global__ void __launch_bounds__(256) k_energy_u8(const pa_state* __restrict__ base, int buf)
+__global__ void __launch_bounds__(256) k_energy_u8(const pa_state* __restrict__ base, uint32_t first, int buf)
 {
     const pa_state* st = base + blockIdx.y;
     const int N = st->N, L = st->L, dim = st->dim, stride = st->row_stride;
-    const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t r = (int64_t)(first + blockIdx.x) * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (r >= st->R) return;
     const uint8_t* s = (const uint8_t*)st->spins[buf] + r * stride;
@@ -286,12 +286,16 @@ int launch_init(const pa_run* runs, int n, const int8_t* const* J_host, hipStrea
         hipLaunchKernelGGL(k_write_states, dim3((unsigned)m), dim3(64), 0, s, base + r0, c);
     }
     const unsigned ny = (unsigned)n;
-    const dim3 g_u8((unsigned)((pieces + 255) / 256), ny);
+    auto init_u8 = [&] {
+        launch_parts((pieces + 255) / 256, 256, [&](uint32_t first, unsigned blocks) {
+            hipLaunchKernelGGL(k_init_u8, dim3(blocks, ny), dim3(256), 0, s, base, first);
+        });
+    };
     if (gauss) {
         // couplings from the host (libm), then spins as for +-1 couplings and FP64 energies
         int rc = gauss_couplings_upload(runs, n, s);
         if (rc != PA_OK) return rc;
-        hipLaunchKernelGGL(k_init_u8, g_u8, dim3(256), 0, s, base);
+        init_u8();
         rc = launch_energy_gauss(runs, n, s);
         if (rc != PA_OK) return rc;
         hipLaunchKernelGGL(k_init_finish, dim3(1, ny), dim3(256), 0, s, base);
@@ -325,8 +329,10 @@ int launch_init(const pa_run* runs, int n, const int8_t* const* J_host, hipStrea
             if (rc != PA_OK) return rc;
         }
     } else if (layout == PA_U8) {
-        hipLaunchKernelGGL(k_init_u8, g_u8, dim3(256), 0, s, base);
-        hipLaunchKernelGGL(k_energy_u8, dim3((unsigned)((R0 + 3) / 4), ny), dim3(256), 0, s, base, 0);
+        init_u8();
+        launch_parts((R0 + 3) / 4, 256, [&](uint32_t first, unsigned blocks) {
+            hipLaunchKernelGGL(k_energy_u8, dim3(blocks, ny), dim3(256), 0, s, base, first, 0);
+        });
     } else {
         const dim3 g((unsigned)((cap + 255) / 256), ny);
         hipLaunchKernelGGL(k_init_bits64, g, dim3(256), 0, s, base);

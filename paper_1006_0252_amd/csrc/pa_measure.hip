@@ -92,10 +92,12 @@ __global__ void __launch_bounds__(kMomentThreads) k_moments_block(pa_state* base
 // Hamming distances, one byte per spin: a wave per replica pair (its lanes over 16-byte pieces of the
 // rows, then a wave sum), kOverlapU8Items pairs per wave in turn; the block counts its distances in
 // an LDS histogram (cap entries, when N + 1 fits) and adds the non-zero bins to the run's
-// histogram (one global atomic per pair serialised on the few bins a population's distances take)
+// histogram (one global atomic per pair serialised on the few bins a population's distances take);
+// first: the first block of this part of the grid
 constexpr int kOverlapU8Items = 8;
 
-__global__ void __launch_bounds__(256) k_overlap_u8(pa_state* base, const pa_state* b_given, int pair_xor, int cap)
+__global__ void __launch_bounds__(256) k_overlap_u8(pa_state* base, uint32_t first, const pa_state* b_given,
+                                                    int pair_xor, int cap)
 {
     extern __shared__ uint32_t hloc[];
     if (pair_xor && (blockIdx.y & 1)) return;  // a pair's distances are counted once, by its first run
@@ -103,7 +105,7 @@ __global__ void __launch_bounds__(256) k_overlap_u8(pa_state* base, const pa_sta
     const pa_state* b = pair_xor ? base + (blockIdx.y ^ 1) : b_given;
     if (a->status || b->status) return;
     const int64_t P = min(a->R, b->R);
-    const int64_t j0 = (int64_t)blockIdx.x * 4 * kOverlapU8Items;
+    const int64_t j0 = (int64_t)(first + blockIdx.x) * 4 * kOverlapU8Items;
     if (j0 >= P) return;  // the same for the whole block
     const int stride = a->row_stride, N = a->N;
     const bool local = N + 1 <= cap;
@@ -144,6 +146,15 @@ __global__ void __launch_bounds__(256) k_overlap_u8(pa_state* base, const pa_sta
             if (c) atomicAdd((unsigned long long*)&qh[d], (unsigned long long)c);
         }
     }
+}
+
+// P: the most pairs of a run
+static void launch_overlap_u8(pa_state* base, int n, int64_t P, const pa_state* b, int pair_xor, int cap, hipStream_t s)
+{
+    const int64_t per_block = 4 * kOverlapU8Items;
+    launch_parts((P + per_block - 1) / per_block, 256, [&](uint32_t first, unsigned blocks) {
+        hipLaunchKernelGGL(k_overlap_u8, dim3(blocks, n), dim3(256), (size_t)cap * 4, s, base, first, b, pair_xor, cap);
+    });
 }
 
 // Hamming distances of a 64-replica group g of runs A and B, bit-packed layout, one wave: each lane
@@ -310,9 +321,7 @@ int launch_measure(const pa_run* runs, int n, const pa_run* partner, int pair_xo
         // LDS histogram of up to 8192 bins (every cube; longer chains count in global memory)
         const int cap = N + 1 <= 8192 ? (int)(N + 1) : 0;
         if (runs[0].layout == PA_U8) {
-            const int64_t per_block = 4 * kOverlapU8Items;
-            hipLaunchKernelGGL(k_overlap_u8, dim3((unsigned)((P + per_block - 1) / per_block), n), dim3(256),
-                               (size_t)cap * 4, s, base, bg, pair_xor, cap);
+            launch_overlap_u8(base, n, P, bg, pair_xor, cap, s);
         } else {
             const int64_t per_block = 64 * kOverlapGroups;
             hipLaunchKernelGGL(k_overlap_bits, dim3((unsigned)((P + per_block - 1) / per_block), n), dim3(256),
@@ -338,9 +347,7 @@ int launch_measure_gauss(const pa_run* runs, int n, const pa_run* partner, int p
     pa_state* base = runs[0].state;
     const pa_state* bg = partner ? partner->state : nullptr;
     const int cap = N + 1 <= 8192 ? (int)(N + 1) : 0;
-    const int64_t per_block = 4 * kOverlapU8Items;
-    hipLaunchKernelGGL(k_overlap_u8, dim3((unsigned)((P + per_block - 1) / per_block), n), dim3(256),
-                       (size_t)cap * 4, s, base, bg, pair_xor, cap);
+    launch_overlap_u8(base, n, P, bg, pair_xor, cap, s);
     hipLaunchKernelGGL(k_overlap_stats, dim3(1, n), dim3(256), 0, s, base, bg, pair_xor);
     return hip_status(hipGetLastError());
 }

@@ -538,13 +538,13 @@ __device__ __forceinline__ bool accepted(const pa_state* st)
     return !st->status && st->R_new > 0 && st->R_new <= st->capacity;
 }
 
-// u8 gather: one thread per 16 bytes of a destination row
-__global__ void __launch_bounds__(256) k_gather_u8(pa_state* base)
+// u8 gather: one thread per 16 bytes of a destination row; first: the first block of this part of the grid
+__global__ void __launch_bounds__(256) k_gather_u8(pa_state* base, uint32_t first)
 {
     pa_state* st = base + blockIdx.y;
     if (!accepted(st)) return;
     const int per_row = st->row_stride / 16;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = (int64_t)(first + blockIdx.x) * blockDim.x + threadIdx.x;
     const int64_t rn = t / per_row;
     const int c = (int)(t - rn * per_row);
     if (rn >= st->R_new) return;
@@ -618,7 +618,7 @@ __global__ void k_finish(pa_state* base, ResampleParams p)
 // Launch shapes cover the largest run of the call; grid.y indexes the runs, whose states
 // are contiguous (state r at runs[0].state + r).  A single run is n = 1.
 struct BatchShape {
-    int64_t cap_max = 0, stride_max = 0, rows_max = 0;
+    int64_t cap_max = 0, pieces_max = 0, rows_max = 0;  // pieces: 16 bytes of a run's byte rows
 };
 
 static BatchShape batch_shape(const pa_run* runs, int n)
@@ -628,7 +628,7 @@ static BatchShape batch_shape(const pa_run* runs, int n)
         pa_sizes sz;
         pa_buffer_sizes(runs[r].dim, runs[r].L, runs[r].layout, runs[r].couplings, runs[r].capacity, runs[r].n_records, &sz);
         b.cap_max = std::max(b.cap_max, runs[r].capacity);
-        b.stride_max = std::max(b.stride_max, sz.row_stride);
+        b.pieces_max = std::max(b.pieces_max, runs[r].capacity * (sz.row_stride / 16));
         b.rows_max = std::max<int64_t>(b.rows_max, runs[r].dim == 1 ? (runs[r].L + 31) / 32 : runs[r].L * runs[r].L);
     }
     return b;
@@ -737,8 +737,9 @@ static void launch_gather(const pa_run* runs, int n, hipStream_t s)
     const BatchShape b = batch_shape(runs, n);
     pa_state* base = runs[0].state;
     if (runs[0].layout == PA_U8) {
-        const int64_t threads = b.cap_max * (b.stride_max / 16);
-        hipLaunchKernelGGL(k_gather_u8, dim3((unsigned)((threads + 255) / 256), n), dim3(256), 0, s, base);
+        launch_parts((b.pieces_max + 255) / 256, 256, [&](uint32_t first, unsigned blocks) {
+            hipLaunchKernelGGL(k_gather_u8, dim3(blocks, n), dim3(256), 0, s, base, first);
+        });
     } else {
         const int64_t blocks = (b.cap_max + kStageThreads - 1) / kStageThreads;
         const int64_t passes = (b.rows_max + kStageRows - 1) / kStageRows;
