@@ -92,7 +92,10 @@ int gauss_couplings_upload(const pa_run* runs, int n, hipStream_t s)
             }
             J.emplace_back((size_t)B);
             couplings_host(q[r].disorder_seed, J.back());
-            if (hipMemcpyAsync(q[r].J, J.back().data(), (size_t)B * 8, hipMemcpyHostToDevice, s) != hipSuccess) return PA_ERR_HIP;
+            if (hipMemcpyAsync(q[r].J, J.back().data(), (size_t)B * 8, hipMemcpyHostToDevice, s) != hipSuccess) {
+                (void)hipStreamSynchronize(s);  // the copies before it read the host vectors
+                return PA_ERR_HIP;
+            }
         }
         if (copies)
             hipLaunchKernelGGL(k_copy_couplings, dim3((unsigned)((most + 255) / 256), (unsigned)m), dim3(256), 0, s,
