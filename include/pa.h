@@ -425,7 +425,7 @@ int pa_mlp_grad(const uint16_t* w, const float* x, const double* target, int64_t
 
 /* pa_mlp_grad for callers that cannot allocate device memory (code under HIP graph capture,
  * serving loops, harnesses that forbid hipMalloc): the same kernels and the same result, bit for
- * bit, with the work matrix and partial gradients in a fixed device array of the library
+ * bit, with the partial gradients in a fixed device array of the library
  * (PA_MLP_STATIC_MAX_B samples, 6.6 MB, held on each device from the first call until the process
  * ends) instead of caller memory.  Allocates nothing.  B > PA_MLP_STATIC_MAX_B returns PA_ERR_SIZE
  * before any device work.  Every call on a device shares that device's array: calls that overlap

@@ -29,6 +29,7 @@ static_assert(kOffB4 + 1 == kParams && kParams == PA_MLP_PARAMS, "parameter layo
 // kMaxBlocks).
 constexpr int kRows = 396;
 constexpr int kChunk = 1024;
+constexpr int64_t kMaxSamples = (int64_t)65535 * kChunk;  // samples of a gradient (more are refused)
 constexpr int kTile = 32;
 constexpr int kMaxBlocks = 512;
 
@@ -433,8 +434,8 @@ int launch_rho(const pa_run* runs, int n, const double* args, int n_args, int mo
     return hip_status(hipGetLastError());
 }
 
-// The loss gradient of a batch of at most kStaticMaxB samples with its work matrix and partial
-// gradients in a fixed device array instead of caller memory, for callers that cannot allocate.
+// The loss gradient of a batch of at most kStaticMaxB samples with its partial gradients in a fixed device
+// array (of pa_mlp_work_bytes' size) instead of caller memory, for callers that cannot allocate.
 // Every call on a device shares that device's array: calls that overlap on one GPU race.  Nothing
 // in it needs clearing between calls (every element a call reads, it has written first).
 constexpr int64_t kStaticMaxB = 4096;
@@ -464,7 +465,7 @@ static int scratch_address(float** out)
 static int mlp_grad_launch(const uint16_t* w, const float* x, const double* target, int64_t B, float* wk, float* grad,
                            float* loss, hipStream_t s)
 {
-    if (mlp_chunks(B) > 65535) return PA_ERR_ARG;
+    if (B > kMaxSamples) return PA_ERR_ARG;
     const int64_t tiles = mlp_tiles(B);
     const int blocks = (int)(tiles < kMaxBlocks ? tiles : kMaxBlocks);
     hipLaunchKernelGGL(k_mlp<true>, dim3((unsigned)blocks), dim3(256), 0, s, w, x, B, 0.0f, 0.0f, (float*)nullptr, target,

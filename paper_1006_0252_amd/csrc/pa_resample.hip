@@ -401,7 +401,7 @@ __global__ void __launch_bounds__(kScanTile) k_copies(pa_state* base, int32_t k)
 // source in the block's offsets in LDS (largest j with offsets[j] <= r', 8 LDS steps) and are written in
 // order.  Per new replica over the whole array, the same search took ~20 dependent global loads; per
 // source, the writes of uneven copy numbers were scattered and slower still.  As four launches (sums,
-// their scan, offsets, sources) 27 us at 10^6 replicas and 16 at 5 10^4; this 15 (with the scan) and 5.
+// their scan, offsets, sources) 27 us at 10^6 replicas and 16 at 5 10^4; this 16 (with the scan) and 5.
 // SCANNED: k_scan_tiles has turned the sums into the copies before each tile, and the total after the last.
 template <bool SCANNED>
 __global__ void __launch_bounds__(kScanTile) k_offsets(pa_state* base)

@@ -12,7 +12,7 @@
 // and by a wave's own chain of instructions where it does not (hence the second pair of kernels, with a
 // lane per call).  The generic kernel takes a site at a
 // time and moves byte rows a byte at a time: N = 64, 5 sweeps, 1000 replicas 29 us (here
-// 5 us), 200 runs of them 80 (here 24).
+// 4.6), 200 runs of them 80 (here 24).
 #include "pa_common.h"
 #include "pa_host.h"
 #include "pa_sweep_strings.h"
@@ -418,12 +418,12 @@ __global__ void __launch_bounds__(64 * kWaves) k_sweep_chain_split(const pa_stat
 }
 
 // Where the population (its capacity, in groups of 64, over the runs of the call) is too small for a lane
-// per replica to fill the chip, a lane per call (five sweeps at beta 0.5, capacities 1.5 times 1000 replicas
-// a run, lane per replica and per call).  Chains of up to 128 sites, more than one call: N = 64, 1 run 10.4
-// and 7.4 us, 32 runs (800 groups) 11.6 and 10.0, 64 runs (1600) 15.3 and 12.9, 100 runs 15.9 and 16.6; N = 128,
-// 1 run 16.1 and 7.8, 64 runs 25.4 and 18.6; N = 16 has one call and gains nothing (7.1 and 7.4).  Longer
-// ones: N = 200, 1 run 14.2 and 10.3, 8 runs (200 groups) 15.0 and 13.0, 16 runs 17.5 and 17.6; N = 1024, 1 run 39
-// and 11.7, 8 runs 40.8 and 25.2.
+// per replica to fill the chip, a lane per call (five sweeps at beta 0.5 after one another, capacities 1.6 times
+// 1000 replicas a run, lane per replica and per call).  Chains of up to 128 sites, more than one call: N = 64,
+// 1 run 7.7 and 4.6 us, 32 runs (800 groups) 8.5 and 7.0, 64 runs (1600) 11.6 and 10.7, 100 runs 12.5 and 13.5;
+// N = 128, 1 run 13.4 and 4.7, 64 runs 21.7 and 15.8; N = 16 has one call and gains nothing (4.4 and 4.6).  Longer
+// ones: N = 200, 1 run 11.3 and 7.3, 8 runs (200 groups) 12.0 and 9.6, 16 runs 14.7 and 12.8; N = 1024, 1 run 35.2
+// and 8.4, 8 runs 37.1 and 20.0.
 constexpr int64_t kSplitShort = 1536, kSplitLong = 256;
 
 template <int MODE, int LAYOUT>

@@ -12,11 +12,11 @@
 // the waves meet at one barrier per phase (and one more where the string's length is not a whole
 // number of words and its ghost words are funnels of other waves' words).
 //
-// Bound by the vector ALU (VALUBusy 100%; 7.6 instructions per attempt at L = 16, of which Philox 4.7).
+// Bound by the vector ALU (VALUBusy 100%; 7.5 instructions per attempt at L = 16, of which Philox 4.7).
 // Measured, ten sweeps at beta 0.5 or 1, against the kernels it replaced (one wave per group, four lanes
-// per replica with rows or colour words, and the generic kernel): L = 16, 10^6 replicas 8.08 -> 7.70 ms
-// (5.3e12 attempts/s); L = 12, 2 10^5 replicas 1.11 -> 0.76 ms; L = 10, 3 10^4 0.25 -> 0.097 ms; L = 8 in
-// bytes, 5 10^4 157 -> 84 us; L = 14, 10^5 5.6 -> 0.66 ms; L = 20, 2 10^4 6.8 -> 0.42 ms.
+// per replica with rows or colour words, and the generic kernel): L = 16, 10^6 replicas 8.10 -> 7.55 ms
+// (5.4e12 attempts/s); L = 12, 2 10^5 replicas 1.10 -> 0.75 ms; L = 10, 3 10^4 0.25 -> 0.089 ms; L = 8 in
+// bytes, 5 10^4 152 -> 71 us; L = 14, 10^5 5.6 -> 0.65 ms; L = 20, 2 10^4 6.8 -> 0.41 ms.
 #include <algorithm>
 #include <type_traits>
 
@@ -53,11 +53,11 @@ __host__ __device__ constexpr int waves_of(int L, int LPR)
 }
 
 // Four lanes per replica instead of one: where the population has fewer 64-replica groups than four
-// per CU (ten sweeps at beta 0.5 or 1, one lane and four lanes: L = 6, 157 groups 45 and 26 us; L = 8, 782
-// groups 92 and 84 us, 3125 groups 251 and 256 us; L = 12, 157 groups 134 and 74 us, 782 groups 284 and 265,
-// 1563 groups 449 and 488; L = 16, 782 groups 553 and 514, 1563 groups 925 and 960), and from L = 20
+// per CU (ten sweeps at beta 0.5 or 1, one lane and four lanes: L = 6, 157 groups 62 and 22 us; L = 8, 782
+// groups 80 and 71 us, 3125 groups 216 and 219 us; L = 12, 157 groups 130 and 66 us, 782 groups 272 and 243,
+// 1563 groups 432 and 456; L = 16, 782 groups 536 and 484, 1563 groups 899 and 911), and from L = 20
 // on for every size: a CU's LDS holds one block of 64 replicas there, whose waves all wait at its
-// barriers (L = 20, 6250 groups 7.9 and 7.6 ms; L = 24, 625 groups 1.58 and 1.34 ms).
+// barriers (L = 20, 6250 groups 7.9 and 7.5 ms; L = 24, 625 groups 1.58 and 1.33 ms).
 // Up to three sweeps it is the blocks' tables and transfers that count, which four lanes per replica repeat four
 // times as often: there fewer than 384 groups (one and four lanes, L = 16, 313 groups, one sweep 45 and 41 us,
 // three 101 and 77; 469 groups, one 46 and 57, three 101 and 113; L = 8, 469 groups, one 11.0 and 13.5, three
@@ -448,7 +448,7 @@ __global__ void __launch_bounds__(threads_of(L, LPR)) k_sweep_group_batch(pa_sta
 }
 
 // Initial population and energies of runs of one side (grid.y: position in order), written once: drawing
-// the rows and then reading them back per bond took 1.3 ms at L = 16, 10^6 replicas, this 0.4 ms.
+// the rows and then reading them back per bond took 1.3 ms at L = 16, 10^6 replicas, this 0.37 ms.
 template <int L, int LAYOUT>
 __global__ void __launch_bounds__(threads_of(L, always_split(L) ? 4 : 1)) k_init_group(pa_state* base, uint32_t first,
                                                                                       BatchOrder order)
